@@ -595,6 +595,21 @@ __device__ __forceinline__ float row16_sum(float x) {
   return x;
 }
 
+// sum over the wave (every lane gets it) and inclusive prefix sum over its lanes
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int32_t dpp_add(int32_t x) {
+  return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ int32_t wave_scan(int32_t x) {
+  x = dpp_add<0x111, 0xf>(x);        // row_shr:1
+  x = dpp_add<0x112, 0xf>(x);        // row_shr:2
+  x = dpp_add<0x114, 0xf>(x);        // row_shr:4
+  x = dpp_add<0x118, 0xf>(x);        // row_shr:8
+  x = dpp_add<0x142, 0xa>(x);        // row_bcast:15 into rows 1 and 3
+  return dpp_add<0x143, 0xc>(x);     // row_bcast:31 into rows 2 and 3
+}
+__device__ __forceinline__ int32_t wave_sum(int32_t x) { return __builtin_amdgcn_readlane(wave_scan(x), 63); }
+
 __device__ __forceinline__ uint4 nt_load16(const char* p) {
   const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
   return make_uint4(v.x, v.y, v.z, v.w);
@@ -621,23 +636,30 @@ __host__ __device__ constexpr int32_t auto_part(int i) {
 // here; every kernel that follows reads it from there.  Also zeroes the ticket
 // counters of all layers and, if a clock table is given, resets its rows and notes the time in the row
 // after the last.
-__global__ __launch_bounds__(256) void k_attn_plan(const int32_t* __restrict__ ctx, int32_t batch, int32_t part_tokens,
-                                                   int32_t min_units, int32_t n_kv_heads,
-                                                   int32_t max_blocks, int32_t minus, uint2* __restrict__ items,
-                                                   int32_t* __restrict__ hdr, uint32_t* __restrict__ counters,
-                                                   int32_t n_counters, uint32_t* __restrict__ err,
-                                                   unsigned long long* __restrict__ clock) {
-  __shared__ int32_t s_off[kMaxPlanBatch];   // first full item of the sequence
-  __shared__ int32_t s_nf[kMaxPlanBatch];
-  __shared__ int32_t s_ctx[kMaxPlanBatch];  // context length, clamped to [0, what the table can name]
-  __shared__ int32_t s_rem[kMaxPlanBatch];   // size of the short item, -1 if none
-  __shared__ int32_t s_total_full;
+//
+// One workgroup, so its time is latency: nothing in it may walk the batch one element at a time.  The offsets of the
+// full items come from a scan of the workgroup, and the rank of a short item from a count over unique keys (size,
+// then sequence) that reads four of them per LDS access; with a serial scan and a scalar rank loop the launch took
+// 5.1 / 13.3 / 1 689 us at 64 / 256 / 4 096 sequences, now 3.4 / 5.5 / 280.
+constexpr int kPlanThreads = 1024;       // at most; 256 do for up to 256 sequences (launch_attn_plan)
+static_assert(kMaxPlanBatch == 4096, "the rank keys hold a sequence index in 12 bits");
+
+__global__ __launch_bounds__(kPlanThreads) void k_attn_plan(const int32_t* __restrict__ ctx, int32_t batch,
+                                                            int32_t part_tokens, int32_t min_units, int32_t n_kv_heads,
+                                                            int32_t max_blocks, int32_t minus,
+                                                            uint2* __restrict__ items, int32_t* __restrict__ hdr,
+                                                            uint32_t* __restrict__ counters, int32_t n_counters,
+                                                            uint32_t* __restrict__ err,
+                                                            unsigned long long* __restrict__ clock) {
+  __shared__ int32_t s_ctx[kMaxPlanBatch];   // context length, clamped to [0, what the table can name]
+  __shared__ __align__(16) int32_t s_key[kMaxPlanBatch];   // short items: size << 12 | (4095 - sequence), else -1
+  __shared__ int32_t s_full[kPlanThreads / 64], s_short[kPlanThreads / 64];   // per wave, of one round of the scan
   __shared__ int32_t s_units[kAutoParts];    // items per candidate item size
-  __shared__ int32_t s_part;
-  if (threadIdx.x < kAutoParts) s_units[threadIdx.x] = 0;
+  const int32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nt = blockDim.x;
+  if (tid < kAutoParts) s_units[tid] = 0;
   __syncthreads();
   int32_t my_units[kAutoParts] = {};
-  for (int32_t b = threadIdx.x; b < batch; b += blockDim.x) {
+  for (int32_t b = tid; b < batch; b += nt) {
     const int32_t raw = ctx[b];
     const int32_t full = clamp_ctx(raw, max_blocks);
     if (raw > full) atomicOr(err, PIE_DEVERR_BAD_HANDLE);   // the table cannot name that many blocks
@@ -651,64 +673,70 @@ __global__ __launch_bounds__(256) void k_attn_plan(const int32_t* __restrict__ c
   // (items x kv heads) for the decode kernel's workgroups to share, the smallest candidate if none does.
   if (min_units > 0) {
 #pragma unroll
-    for (int i = 0; i < kAutoParts; ++i)
-      if (my_units[i]) atomicAdd(&s_units[i], my_units[i]);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int32_t pick = auto_part(0);
-      for (int i = 1; i < kAutoParts; ++i)
-        if ((long long)s_units[i] * n_kv_heads > min_units) pick = auto_part(i);
-      s_part = pick;
+    for (int i = 0; i < kAutoParts; ++i) {
+      const int32_t n = wave_sum(my_units[i]);
+      if (lane == 0 && n) atomicAdd(&s_units[i], n);
     }
-  } else if (threadIdx.x == 0) {
-    s_part = part_tokens;
   }
-  __syncthreads();
-  part_tokens = s_part;
-  if (threadIdx.x == 0) hdr[1] = part_tokens;
-  for (int32_t b = threadIdx.x; b < batch; b += blockDim.x) {
-    const int32_t c = s_ctx[b];
-    const int32_t nf = c > 0 ? c / part_tokens : 0;
-    const int32_t rem = c > 0 ? c % part_tokens : 0;
-    s_nf[b] = nf;
-    s_rem[b] = (rem > 0 || c <= 0) ? rem : -1;
-  }
-  for (int32_t i = threadIdx.x; i < n_counters; i += blockDim.x) counters[i] = 0;
+  for (int32_t i = tid; i < n_counters; i += nt) counters[i] = 0;
   if (clock) {                                   // one row per launch: min / max slots to their neutral values
-    for (int32_t i = threadIdx.x; i < n_counters; i += blockDim.x) {
+    for (int32_t i = tid; i < n_counters; i += nt) {
       clock[(size_t)i * kClockRow + kClockKernelStart] = ~0ull;
       clock[(size_t)i * kClockRow + kClockKernelEnd] = 0ull;
       clock[(size_t)i * kClockRow + kClockLayerEnd] = 0ull;
       clock[(size_t)i * kClockRow + kClockGrid] = 0ull;
     }
-    if (threadIdx.x == 0) clock[(size_t)n_counters * kClockRow] = wall_clock64();   // the step begins
+    if (tid == 0) clock[(size_t)n_counters * kClockRow] = wall_clock64();   // the step begins
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int32_t off = 0, n_short = 0;
-    for (int32_t b = 0; b < batch; ++b) {
-      s_off[b] = off;
-      off += s_nf[b];
-      if (s_rem[b] >= 0) ++n_short;
+  if (min_units > 0) {
+    part_tokens = auto_part(0);
+    for (int i = 1; i < kAutoParts; ++i)
+      if ((long long)s_units[i] * n_kv_heads > min_units) part_tokens = auto_part(i);
+  }
+  // full items in sequence order, a round of one per thread at a time
+  int32_t n_full = 0, n_short = 0;
+  for (int32_t b0 = 0; b0 < batch; b0 += nt) {
+    const int32_t b = b0 + tid;
+    const bool live = b < batch;
+    const int32_t c = live ? s_ctx[b] : 0;
+    const int32_t nf = c / part_tokens, rem = c - nf * part_tokens;
+    const bool has_short = live && (rem > 0 || c <= 0);
+    const int32_t incl = wave_scan(nf);
+    const unsigned long long shorts = __builtin_amdgcn_ballot_w64(has_short);
+    if (lane == 63) {
+      s_full[wave] = incl;
+      s_short[wave] = __popcll(shorts);
     }
-    s_total_full = off;
-    hdr[0] = off + n_short;
+    __syncthreads();
+    int32_t off = n_full + incl - nf;
+    for (int w = 0; w < nt / 64; ++w) {
+      if (w < wave) off += s_full[w];
+      n_full += s_full[w];
+      n_short += s_short[w];
+    }
+    if (live) {
+      for (int32_t p = 0; p < nf; ++p) items[off + p] = make_uint2((uint32_t)b | ((uint32_t)p << 16), (uint32_t)c);
+      s_key[b] = has_short ? (rem << 12) | (kMaxPlanBatch - 1 - b) : -1;
+    }
+    __syncthreads();                             // the round's sums are read before the next round's are written
+  }
+  if (tid < 4 && ((batch + 3) & ~3) - 4 + tid >= batch) s_key[((batch + 3) & ~3) - 4 + tid] = -1;   // to a whole vector
+  if (tid == 0) {
+    hdr[0] = n_full + n_short;
+    hdr[1] = part_tokens;
   }
   __syncthreads();
-  const int32_t total_full = s_total_full;
-  for (int32_t b = threadIdx.x; b < batch; b += blockDim.x) {
-    const int32_t nf = s_nf[b];
-    for (int32_t p = 0; p < nf; ++p)
-      items[s_off[b] + p] = make_uint2((uint32_t)b | ((uint32_t)p << 16), (uint32_t)s_ctx[b]);
-    const int32_t key = s_rem[b];
-    if (key >= 0) {
-      int32_t rank = 0;                                  // longest first, ties by sequence index
-      for (int32_t o = 0; o < batch; ++o) {
-        const int32_t k2 = s_rem[o];
-        rank += (k2 > key || (k2 == key && o < b)) ? 1 : 0;
-      }
-      items[total_full + rank] = make_uint2((uint32_t)b | ((uint32_t)nf << 16), (uint32_t)s_ctx[b]);
+  for (int32_t b = tid; b < batch; b += nt) {
+    const int32_t key = s_key[b];
+    if (key < 0) continue;
+    int32_t rank = 0;                            // longest first, ties by sequence index
+    for (int32_t o = 0; o < batch; o += 4) {
+      const int4 k = *reinterpret_cast<const int4*>(&s_key[o]);
+      rank += (k.x > key ? 1 : 0) + (k.y > key ? 1 : 0) + (k.z > key ? 1 : 0) + (k.w > key ? 1 : 0);
     }
+    const int32_t c = s_ctx[b];
+    items[n_full + rank] = make_uint2((uint32_t)b | ((uint32_t)(c / part_tokens) << 16), (uint32_t)c);
   }
 }
 
@@ -1562,7 +1590,7 @@ int launch_attn_plan(const pie_pool* p, const int32_t* d_ctx, int32_t batch, int
   if (batch > kMaxPlanBatch || batch > w.lay_batch || max_blocks > w.lay_max_blocks) return PIE_EINVAL;
   // automatic item size: keep more than about eight and a half units per workgroup of the persistent decode grid
   const int32_t min_units = p->attn_partition <= 0 ? p->n_cu * 17 : 0;
-  hipLaunchKernelGGL(k_attn_plan, dim3(1), dim3(256), 0, s, d_ctx, batch, part_tokens_of(p), min_units,
+  hipLaunchKernelGGL(k_attn_plan, dim3(1), dim3(batch > 256 ? kPlanThreads : 256), 0, s, d_ctx, batch, part_tokens_of(p), min_units,
                      p->cfg.n_kv_heads, max_blocks, without_last ? 1 : 0, plan_items(w),
                      plan_hdr(w), plan_counters(w), w.n_counters, p->d_err, reset_clock ? p->d_clock : nullptr);
   PIE_HIP(hipGetLastError());

@@ -107,6 +107,28 @@ def test_partition_size_does_not_change_the_result_beyond_rounding():
     lib.close()
 
 
+@pytest.mark.parametrize("batch", [1, 63, 64, 257, 1023, 1029])
+def test_planning_of_batches_around_its_rounds(batch):
+    """The planning kernel scans the batch in rounds of one sequence per thread (256 or 1024 threads) and ranks the
+    short items four keys at a time: batches of one, of a wave, of a round and of a round and a ragged rest, with
+    empty sequences, equal lengths and lengths that are whole items among them."""
+    w = I.Workload("plan_rounds", 1, batch, 2, 1, 64, I.DTYPE_F16, ctx_lo=0, ctx_hi=300, value_scale=1.0, seed=35)
+    ctx = I.draw_ctx_lens(w)
+    ctx[::7] = 256
+    ctx[5::11] = 0
+    case = I.make_case(w, ctx_lens=ctx)
+    lib, mod, table = GH.make_pools(case, int(case.n_blocks.sum()) + 3, 2, 2, fill=H.nan_fill(w.dtype), max_blocks=19)
+    lib.set_attn_partition(256)
+    got = run_attn(lib, case, table)
+    live = np.nonzero(ctx)[0]
+    q, K, V = H.dense_f64(case, 0)
+    ref = np.zeros_like(got)
+    ref[live] = A.dense_attention(q[live], [K[b] for b in live], [V[b] for b in live], ctx[live])
+    check(got[live], ref[live], w.dtype)
+    assert (np.delete(got, live, axis=0) == 0).all()
+    lib.close()
+
+
 def test_ctx_one_is_bit_exact_and_ctx_zero_gives_zeros():
     w = I.Workload("one", 1, 4, 8, 2, 128, I.DTYPE_BF16, ctx_lo=1, ctx_hi=1, value_scale=1.0, seed=35)
     case = I.make_case(w)
