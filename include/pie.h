@@ -194,10 +194,12 @@ int pie_set_swap_path(pie_pool* pool, int32_t path);
  * [256, 4096]); longer contexts are split and reduced.  0, the default: chosen on the device for every batch,
  * from 512 / 768 / 1024 / 1536 / 2048 / 3072 / 4096, as the largest size that still leaves the persistent decode
  * grid more than about eight and a half (partition, kv head) units per workgroup (small units even out the
- * workgroups' different streaming rates, every unit has a fixed cost). */
+ * workgroups' different streaming rates, every unit has a fixed cost).  With 0, calls of up to 256 sequences and the
+ * layers of small steps run as one launch with a split of its own, as fine as it takes to fill the GPU. */
 int pie_set_attn_partition(pie_pool* pool, int32_t tokens);
 
-/* The size the last attention planning launch used (the one set, or the one chosen).  Waits for the pool. */
+/* The size the last attention call planned with (the one set, or the one chosen by the rule above, also where a
+ * one-launch call split the contexts differently).  Waits for the pool. */
 int pie_get_attn_partition_sync(pie_pool* pool, int32_t* out_tokens);
 
 /* 16-bit caches with one query head per kv head (MHA): on != 0 computes the attention's two products on the
@@ -278,7 +280,8 @@ int pie_attn_stream_probe_sync(pie_pool* pool, int32_t layer, const int32_t* d_b
  * prefetched on swap_in_stream into the other staging region meanwhile.  With a new token (d_k_new), the
  * attention reads the context without it from the cache and takes the token itself from d_k_new / d_v_new, so
  * no layer waits for the rows to be stored: those of the GPU-homed tail blocks of all layers are written by one
- * launch on swap_out_stream beside the first layers (compute_stream is ordered after it when the step ends),
+ * launch on swap_out_stream beside the first layers (compute_stream is ordered after it when the step ends), or, in a
+ * small step, by each layer's own launch,
  * those of host-homed tails into their staged copies on swap_out_stream once the copy has arrived, and from
  * there layer l's dirty blocks go home at once (the layer only reads them, so append and write-back run beside
  * it; swap_in_stream carries nothing but the copies, back to back).  Behind the last layer, layer 0's blocks

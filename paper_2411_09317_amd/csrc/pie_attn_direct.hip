@@ -1,0 +1,638 @@
+// Paged-attention decode in one launch, for calls too small to fill the GPU for long.
+//
+// The planned path (pie_kernels.hip) costs four launches a call - plan, resolve, decode, reduce - or two a layer inside
+// a step, and cuts contexts into items of at least 512 tokens.  Below a few hundred MB of keys and values per layer its
+// time is launches, the gaps between them and a grid that mostly idles, not bytes.  Here every workgroup works out the
+// whole split for itself from the context lengths (at most four per lane, one scan), looks its blocks up through table
+// and map, streams them, and the workgroup that finishes a (sequence, kv head) last merges the partial states, adds the
+// newest token and writes the result; with new rows it also stores them.
+//
+// What bounds it: for small calls a chain of dependent accesses, about 7 us from the first workgroup's start (context
+// lengths and split 1.4 us, table and map 0.7, a block 0.9, the part's state stored 1.0 and counted 0.4 to 1.3, the
+// merge 1.4); for large ones HBM.  us a call, planned before and in one launch now: one sequence of 700 tokens, 32
+// heads over 8: 24.4 and 14.0; one of 32 749, 64 over 8: 48.5 and 34.6 (134 MB); 30 of 500 to 2 500, 32 over 32: 123 and
+// 116 (650 MB); 12 of 32 768, 64 over 8: 290 and 255 (1.6 GB, 6.3 TB/s).  A layer of a step of 8 sequences of 128 to
+// 4 096 tokens, 32 over 8: 16.8 and 12.0.
+
+#include <hip/hip_ext.h>
+
+#include <atomic>
+
+#include "pie_attn_device.h"
+
+namespace pie {
+
+struct DirectArgs {
+  const char* kv_layer;
+  const int32_t* table;      // [B][max_blocks] handles
+  const int32_t* map;        // handle -> slot
+  const int32_t* ctx;
+  uint32_t* err;
+  const char* q;             // [B][Hq][d]
+  char* out;                 // [B][Hq][d]
+  const char* new_k;         // newest token's rows [B][Hkv][d] (see AttnArgs), or NULL
+  const char* new_v;
+  float* ws;                 // partial states: [unit][group][d + 4]
+  uint32_t* arrive;          // per (sequence, head unit): workgroups that have stored their part; zero between launches
+  uint32_t* arrive_other;    // the other launches' words, cleared here
+  int32_t* hdr;              // plan header, to note the nominal item size in, or NULL
+  unsigned long long* clock;    // as in AttnArgs
+  unsigned long long* clock_wg;
+  size_t block_bytes;
+  int32_t ws_bytes;
+  float scale_log2e;
+  int32_t batch, max_blocks, n_kv_heads, group, n_q_heads;
+  int32_t n_handles, n_gpu_blocks, n_slots, stage_valid;
+  int32_t min_units;         // as in k_attn_plan; 0: the size is the smallest whatever the lengths
+  int32_t max_items;         // items (all sequences' parts) the split may make
+  int32_t append;            // kAppend*: store the new rows into the tail blocks this says, or -1
+};
+
+// ---- one wave's share of a unit ------------------------------------------------------------------------
+
+template <typename E_, int HD_, bool SPLIT>
+struct Wave16 {              // 16-bit caches: all query heads of a kv head, on the matrix cores
+  using E = E_;
+  static constexpr int HD = HD_, NL = HD / 32, EB = 2, kWavesPerEu = HD == 128 ? 3 : 4;
+  uint4 q[NL];
+  float m, l;
+  f32x4 o[HD / 16];
+  __device__ __forceinline__ void load_q(const char* base, size_t row0, int G, int lane, float) {
+    const int col = lane & 15, quad = lane >> 4;
+#pragma unroll
+    for (int kc = 0; kc < NL; ++kc) {
+      q[kc] = make_uint4(0, 0, 0, 0);
+      if (col < G) q[kc] = *reinterpret_cast<const uint4*>(base + ((row0 + col) * HD + 32 * kc + 8 * quad) * 2);
+    }
+  }
+  __device__ __forceinline__ void reset() {
+    m = kNegBig;
+    l = 0.f;
+#pragma unroll
+    for (int n = 0; n < HD / 16; ++n) o[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ __forceinline__ void block(uint4 (&kr)[NL], uint4 (&vr)[NL], int32_t t_first, int32_t limit, int lane, float scale) {
+    mfma_block<E, HD, SPLIT>(kr, vr, q, t_first, limit, lane >> 4, scale, m, l, o);
+  }
+  __device__ __forceinline__ void to_lds(float* s_m, float* s_l, float* s_acc, int row_floats, int wave, int G, int lane) {
+    const int col = lane & 15, quad = lane >> 4;
+    l = quad16_sum(l);
+    if (col < G) {
+      if (quad == 0) {
+        s_m[wave * kMaxGroup + col] = m;
+        s_l[wave * kMaxGroup + col] = l;
+      }
+      float* row = s_acc + ((size_t)wave * G + col) * row_floats + 4 * quad;
+#pragma unroll
+      for (int n = 0; n < HD / 16; ++n) *reinterpret_cast<f32x4*>(row + 16 * n) = o[n];
+    }
+  }
+};
+
+template <int HD_>
+struct Wave32 {              // fp32 caches: one query head, on the vector ALU
+  using E = F32;
+  static constexpr int HD = HD_, NL = HD / 16, EB = 4, kWavesPerEu = 2;
+  float q[NL][4];
+  float m, l, acc[NL];
+  __device__ __forceinline__ void load_q(const char* base, size_t row0, int, int lane, float scale) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const float4 t = *reinterpret_cast<const float4*>(base + (row0 * HD + 4 * (4 * i + (lane >> 4))) * 4);
+      q[i][0] = t.x * scale; q[i][1] = t.y * scale; q[i][2] = t.z * scale; q[i][3] = t.w * scale;
+    }
+  }
+  __device__ __forceinline__ void reset() {
+    m = kNegBig;
+    l = 0.f;
+#pragma unroll
+    for (int n = 0; n < NL; ++n) acc[n] = 0.f;
+  }
+  __device__ __forceinline__ void block(uint4 (&kr)[NL], uint4 (&vr)[NL], int32_t t_first, int32_t limit, int lane, float) {
+    f32_block<HD>(kr, vr, q, t_first, limit, lane, m, l, acc);
+  }
+  __device__ __forceinline__ void to_lds(float* s_m, float* s_l, float* s_acc, int row_floats, int wave, int, int lane) {
+    l = row16_sum(l);
+#pragma unroll
+    for (int n = 0; n < NL; ++n) acc[n] = quad16_sum(acc[n]);
+    if (lane == 0) {
+      s_m[wave * kMaxGroup] = m;
+      s_l[wave * kMaxGroup] = l;
+    }
+    if (lane < 16) {
+#pragma unroll
+      for (int n = 0; n < NL; ++n) s_acc[wave * row_floats + 16 * n + lane] = acc[n];
+    }
+  }
+};
+
+// ---- partial states between workgroups -------------------------------------------------------------------
+// They may run on different XCDs, whose L2 caches do not see each other's lines.  So a part is written through and
+// read past them (the sc1 accesses an agent-scope atomic uses, sixteen bytes at a time): a part is complete when the
+// writer's stores have been counted down, which every writing wave waits for before its workgroup is counted in, and
+// the reader starts when all are in.  No cache is written back or invalidated for it: a release and an acquire fence
+// at agent scope instead cost 20 to 100 us here, since each makes a whole L2 do so.
+constexpr int kAuxAgent = 16;                    // sc1
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t parts_rsrc(float* base, int32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00027000);
+}
+__device__ __forceinline__ void put4(__amdgpu_buffer_rsrc_t r, int32_t off, const float4& x) {
+  __builtin_amdgcn_raw_buffer_store_b128(bits_as<u32x4>(x), r, off, 0, kAuxAgent);
+}
+__device__ __forceinline__ float4 get4(__amdgpu_buffer_rsrc_t r, int32_t off, int32_t wave_off) {
+  return bits_as<float4>(__builtin_amdgcn_raw_buffer_load_b128(r, off, wave_off, kAuxAgent));
+}
+__device__ __forceinline__ void put2(__amdgpu_buffer_rsrc_t r, int32_t off, float x, float y) {
+  __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(x), __float_as_uint(y)}, r, off, 0, kAuxAgent);
+}
+__device__ __forceinline__ float2 get2(__amdgpu_buffer_rsrc_t r, int32_t off) {
+  return bits_as<float2>(__builtin_amdgcn_raw_buffer_load_b64(r, off, 0, kAuxAgent));
+}
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// four consecutive elements
+template <typename E>
+__device__ __forceinline__ float4 load_elem4(const char* base, size_t idx) {
+  const float2 a = load_elem2<E>(base, idx), b = load_elem2<E>(base, idx + 2);
+  return make_float4(a.x, a.y, b.x, b.y);
+}
+__device__ __forceinline__ void axpy(float4& y, float w, const float4& x) {
+  y.x = fmaf(w, x.x, y.x); y.y = fmaf(w, x.y, y.y); y.z = fmaf(w, x.z, y.z); y.w = fmaf(w, x.w, y.w);
+}
+
+// max / sum over a head's threads, one or two rows of sixteen lanes; every one of them gets it
+template <int TPH>
+__device__ __forceinline__ float head_max(float x) {
+  x = row16_max(x);
+  if constexpr (TPH == 32) x = fmaxf(x, __shfl_xor(x, 16, 64));
+  return x;
+}
+template <int TPH>
+__device__ __forceinline__ float head_sum(float x) {
+  x = row16_sum(x);
+  if constexpr (TPH == 32) x += __shfl_xor(x, 16, 64);
+  return x;
+}
+
+// ceil(x / y) for 0 <= x, 1 <= y, x + y < 2^20, exactly: half a unit keeps the quotient off the integers by more than
+// the reciprocal's error.
+__device__ __forceinline__ int32_t div_up(int32_t x, int32_t y) {
+  return (int32_t)(((float)(x + y - 1) + 0.5f) * __builtin_amdgcn_rcpf((float)y));
+}
+
+constexpr int kDirectLaneSeqs = 4;               // sequences per lane in the split
+constexpr int kDirectSeqs = 64 * kDirectLaneSeqs;
+constexpr int kDirectRows = 16384;               // partial states (unit, head of the group) there is room for
+constexpr int kDirectMaxUnits = 4096;
+static_assert(kDirectMaxUnits <= kArriveWords && kDirectMaxUnits <= kClockWgs, "a word per (sequence, head), a pair per workgroup");
+constexpr int kDirectMaxQuanta = 64;             // blocks per wave and unit: the slot list has a lane each
+
+template <typename W, int NW>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(W::kWavesPerEu, 8)))
+void k_attn_direct(const DirectArgs a) {
+  using E = typename W::E;
+  constexpr int HD = W::HD, NL = W::NL, EB = W::EB;
+  constexpr int NT = NW * 64, QUANTUM = NW * kBlockTokens;
+  constexpr int TILE_BYTES = kBlockTokens * HD * EB;
+  constexpr int ROW = HD + 4;                     // padded LDS row of one head's accumulator
+  constexpr int TPH = HD / 4;                     // threads per head when states are merged, four dims each
+  constexpr int PART = (HD + 4) * 4;              // bytes of a head's partial state: accumulator, max, sum, padding
+
+  extern __shared__ __align__(16) float s_dyn[];
+  __shared__ uint32_t s_arrived;
+  __shared__ __align__(16) float s_w[NT];         // weights of the parts being merged, a thread each
+  float* s_m = s_dyn;                             // [NW][16]
+  float* s_l = s_dyn + NW * kMaxGroup;            // [NW][16]
+  float* s_acc = s_dyn + 2 * NW * kMaxGroup;      // [NW][G][ROW]
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int32_t G = a.group, H = a.n_kv_heads;
+  if (a.clock && tid == 0) {
+    const unsigned long long t = wall_clock64();
+    if (a.clock_wg) {
+      a.clock_wg[2 * blockIdx.x] = t;
+      if (blockIdx.x == 0) a.clock[kClockGrid] = gridDim.x;
+    } else {
+      atomicMin(&a.clock[kClockKernelStart], t);
+    }
+  }
+  // Launches take turns with two sets of arrival words.  The last arrival at a word leaves it zero; each launch also
+  // clears the set it does not use, so that whatever calls that must not overlap did to a set is gone one launch later.
+  if (const uint32_t i = blockIdx.x + (uint32_t)tid * gridDim.x; i < (uint32_t)kArriveWords)
+    a.arrive_other[i * kArriveStride] = 0u;
+
+  // ---- the split: every wave computes the same one.  Lane i has the sequences i, i + 64, ...
+  const int32_t minus = a.new_k ? 1 : 0;          // the newest token is not read from the cache
+  int32_t c4[kDirectLaneSeqs], q4[kDirectLaneSeqs], n4[kDirectLaneSeqs], k4[kDirectLaneSeqs], end4[kDirectLaneSeqs];
+  int32_t total = 0;
+#pragma unroll
+  for (int i = 0; i < kDirectLaneSeqs; ++i) {
+    c4[i] = q4[i] = 0;
+    if (64 * i < a.batch) {
+      const int32_t b = 64 * i + lane;
+      if (b < a.batch) {
+        const int32_t raw = a.ctx[b];
+        const int32_t full = clamp_ctx(raw, a.max_blocks);
+        if (raw > full && blockIdx.x == 0) atomicOr(a.err, PIE_DEVERR_BAD_HANDLE);
+        c4[i] = full > minus ? full - minus : 0;
+        q4[i] = c4[i] > 0 ? (c4[i] + QUANTUM - 1) / QUANTUM : 1;
+      }
+      total += wave_sum(q4[i]);
+    }
+  }
+  if (a.hdr && blockIdx.x == 0) {                 // the item size the planning kernel would have chosen, as asked for by
+    int32_t size = auto_part(0);                  // pie_get_attn_partition_sync
+    if (a.min_units > 0) {
+#pragma unroll 1
+      for (int t = 1; t < kAutoParts; ++t) {
+        int32_t n = 0;
+#pragma unroll
+        for (int i = 0; i < kDirectLaneSeqs; ++i)
+          if (64 * i + lane < a.batch) n += c4[i] > 0 ? (c4[i] + auto_part(t) - 1) / auto_part(t) : 1;
+        if ((long long)wave_sum(n) * H > a.min_units) size = auto_part(t);
+      }
+    }
+    if (tid == 0) a.hdr[1] = size;
+  }
+  // quanta per part: the smallest that keeps the parts of all sequences within max_items
+  auto items_of = [&](int32_t k) {
+    int32_t n = 0;
+#pragma unroll
+    for (int i = 0; i < kDirectLaneSeqs; ++i)
+      if (64 * i < a.batch) n += div_up(q4[i], k);   // (0 beyond the batch)
+    return wave_sum(n);
+  };
+  int32_t k = (total + a.max_items - 1) / a.max_items;
+  while (k < kDirectMaxQuanta && items_of(k) > a.max_items) k += 1 + k / 8;
+  if (k > kDirectMaxQuanta) k = kDirectMaxQuanta;
+  int32_t n_items = 0;
+#pragma unroll
+  for (int i = 0; i < kDirectLaneSeqs; ++i) {
+    n4[i] = k4[i] = end4[i] = 0;
+    if (64 * i < a.batch) {
+      if (q4[i] > 0) {                            // parts of a sequence as equal as whole quanta allow
+        const int32_t n = div_up(q4[i], k);
+        k4[i] = div_up(q4[i], n);
+        n4[i] = div_up(q4[i], k4[i]);
+      }
+      end4[i] = n_items + wave_scan(n4[i]);       // items up to and including the lane's sequence
+      n_items = __builtin_amdgcn_readlane(end4[i], 63);
+    }
+  }
+  // one unit a workgroup: the launch has at least as many workgroups as the split can make units
+  const int32_t unit = blockIdx.x;
+  if (unit < n_items * H) {
+    const int32_t item = unit / H, g = unit - item * H;
+    int32_t b = 0;                                // sequences whose items all come before this one
+#pragma unroll
+    for (int i = 0; i < kDirectLaneSeqs; ++i)
+      if (64 * i < a.batch) b += __popcll(__builtin_amdgcn_ballot_w64(64 * i + lane < a.batch && end4[i] <= item));
+    int32_t ctx_b = 0, kq = 1, np = 1, end = 1;
+#pragma unroll
+    for (int i = 0; i < kDirectLaneSeqs; ++i)
+      if (b >> 6 == i) {
+        ctx_b = __builtin_amdgcn_readlane(c4[i], b & 63);
+        kq = __builtin_amdgcn_readlane(k4[i], b & 63);
+        np = __builtin_amdgcn_readlane(n4[i], b & 63);
+        end = __builtin_amdgcn_readlane(end4[i], b & 63);
+      }
+    const int32_t part = item - (end - np);
+    const int32_t tok0 = part * kq * QUANTUM;
+    const int32_t tok1 = min(ctx_b, tok0 + kq * QUANTUM);   // <= tok0 only for an empty sequence
+    const int32_t jb0 = tok0 / kBlockTokens;
+    const int32_t jb1 = tok1 > 0 ? (tok1 + kBlockTokens - 1) / kBlockTokens : 0;
+    const int32_t n_it = (jb1 - jb0 - wave + NW - 1) / NW;  // blocks of this wave: jb0 + wave + NW * it; <= 64
+    const size_t row0 = (size_t)b * a.n_q_heads + (size_t)g * G;
+
+    // The block this sequence's newest token goes to, if this workgroup is the one that stores it: the last part's.
+    const bool stores = a.append >= 0 && part == np - 1;
+    int32_t tail = -1, tail_pos = 0;
+    uint4 k_row;
+    uint32_t v_el = 0;
+    if (stores) {
+      const int32_t raw = a.ctx[b];
+      tail_pos = raw - 1;
+      if (raw > 0) {
+        const int32_t j = tail_pos / kBlockTokens;
+        const int32_t handle = j < a.max_blocks ? a.table[(size_t)b * a.max_blocks + j] : -1;
+        tail = append_slot(handle, a.map, a.n_handles, a.n_gpu_blocks, a.n_slots, a.append, tid == 0, a.err);
+        const size_t row = ((size_t)b * H + g) * HD * EB;
+        if (tid < HD * EB / 16) k_row = *reinterpret_cast<const uint4*>(a.new_k + row + (size_t)tid * 16);
+        if (tid < HD) v_el = EB == 2 ? *reinterpret_cast<const uint16_t*>(a.new_v + row + (size_t)tid * 2)
+                                     : *reinterpret_cast<const uint32_t*>(a.new_v + row + (size_t)tid * 4);
+      }
+    }
+
+    int32_t slots = -1;
+    if (lane < n_it)
+      slots = resolve_slot(a.table[(size_t)b * a.max_blocks + jb0 + wave + NW * lane], a.map, a.n_handles, a.n_gpu_blocks,
+                           a.n_slots, a.stage_valid != 0, a.err);
+    W w;
+    w.load_q(a.q, row0, G, lane, a.scale_log2e);
+    w.reset();
+    uint4 kA[NL], vA[NL], kB[NL], vB[NL];
+    auto load_tile = [&](uint4 (&kr)[NL], uint4 (&vr)[NL], int32_t it) {
+      int32_t slot = __builtin_amdgcn_readlane(slots, it);
+      slot = slot < 0 ? 0 : slot;                 // flagged blocks are masked when consumed
+      const char* kp = a.kv_layer + (size_t)slot * a.block_bytes + (size_t)g * TILE_BYTES + (size_t)lane * 16;
+#pragma unroll
+      for (int i = 0; i < NL; ++i) kr[i] = nt_load16(kp + (size_t)i * 1024);
+#pragma unroll
+      for (int i = 0; i < NL; ++i) vr[i] = nt_load16(kp + a.block_bytes / 2 + (size_t)i * 1024);
+    };
+    auto consume = [&](uint4 (&kr)[NL], uint4 (&vr)[NL], int32_t it) {
+      const bool present = __builtin_amdgcn_readlane(slots, it) >= 0;
+      w.block(kr, vr, (jb0 + wave + NW * it) * kBlockTokens, present ? tok1 : 0, lane, a.scale_log2e);
+    };
+    if (n_it > 0) load_tile(kA, vA, 0);
+    for (int32_t it = 0; it < n_it; it += 2) {
+      if (it + 1 < n_it) load_tile(kB, vB, it + 1);
+      consume(kA, vA, it);
+      if (it + 1 < n_it) {
+        if (it + 2 < n_it) load_tile(kA, vA, it + 2);
+        consume(kB, vB, it + 1);
+      }
+    }
+    w.to_lds(s_m, s_l, s_acc, ROW, wave, G, lane);
+    if (stores && tail >= 0) {                    // rows at or beyond tok1 are masked by index wherever they are read
+      char* blk = const_cast<char*>(a.kv_layer) + (size_t)tail * a.block_bytes + (size_t)g * TILE_BYTES;
+      const int32_t t = tail_pos % kBlockTokens, v = 16 / EB;
+      if (tid < HD * EB / 16) *reinterpret_cast<uint4*>(blk + (size_t)k_tile_index(t, tid * v, v) * EB) = k_row;
+      if (tid < HD) {
+        char* dst = blk + a.block_bytes / 2 + (size_t)v_tile_index(t, tid, v) * EB;
+        if (EB == 2) *reinterpret_cast<uint16_t*>(dst) = (uint16_t)v_el;
+        else *reinterpret_cast<uint32_t*>(dst) = v_el;
+      }
+    }
+    __syncthreads();
+
+    // thread t has head t / TPH, dims 4 (t % TPH) ..
+    const int32_t cols = G * TPH;
+    // The newest token's part is (q . k, 1, v).  Its rows are read here, for the thread's first column, so that they
+    // have arrived when the last step needs them.
+    const bool add_new = a.new_k && clamp_ctx(a.ctx[b], a.max_blocks) > 0;
+    const size_t kv_row = ((size_t)b * H + g) * HD;
+    float4 qd, kd, vd;
+    auto read_new = [&](int c) {
+      const int d0 = 4 * (c % TPH);
+      qd = load_elem4<E>(a.q, (row0 + c / TPH) * HD + d0);
+      kd = load_elem4<E>(a.new_k, kv_row + d0);
+      vd = load_elem4<E>(a.new_v, kv_row + d0);
+    };
+    if (add_new && tid < cols) read_new(tid);
+    auto finish = [&](int c, float M, float L, float4 A) {
+      const int d0 = 4 * (c % TPH);
+      const size_t row = row0 + c / TPH;
+      if (add_new) {
+        if (c >= NT) read_new(c);
+        const float dot = fmaf(qd.x, kd.x, qd.y * kd.y) + fmaf(qd.z, kd.z, qd.w * kd.w);
+        const float s_new = head_sum<TPH>(dot) * a.scale_log2e;
+        const float m2 = fmaxf(M, s_new);
+        const float w_old = __builtin_amdgcn_exp2f(M - m2), w_new = __builtin_amdgcn_exp2f(s_new - m2);
+        L = fmaf(L, w_old, w_new);
+        A = make_float4(A.x * w_old, A.y * w_old, A.z * w_old, A.w * w_old);
+        axpy(A, w_new, vd);
+      }
+      const bool some = L > 0.f;
+      store_elem2<E>(a.out, row * HD + d0, make_float2(some ? A.x / L : 0.f, some ? A.y / L : 0.f));
+      store_elem2<E>(a.out, row * HD + d0 + 2, make_float2(some ? A.z / L : 0.f, some ? A.w / L : 0.f));
+    };
+    // n states in LDS (the waves', or the merging groups') into one
+    auto merge_lds = [&](int n, int h, int d0, float& M, float& L, float4& A) {
+      M = s_m[h];
+      for (int i = 1; i < n; ++i) M = fmaxf(M, s_m[i * kMaxGroup + h]);
+      L = 0.f;
+      A = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int i = 0; i < n; ++i) {
+        const float wt = __builtin_amdgcn_exp2f(s_m[i * kMaxGroup + h] - M);
+        L = fmaf(wt, s_l[i * kMaxGroup + h], L);
+        axpy(A, wt, *reinterpret_cast<const float4*>(&s_acc[((size_t)i * G + h) * ROW + d0]));
+      }
+    };
+    const __amdgpu_buffer_rsrc_t parts = parts_rsrc(a.ws, a.ws_bytes);
+    for (int c = tid; c < cols; c += NT) {
+      const int h = c / TPH, d0 = 4 * (c % TPH);
+      float M, L;
+      float4 A;
+      merge_lds(NW, h, d0, M, L, A);
+      if (np == 1) {
+        finish(c, M, L, A);
+      } else {
+        const int32_t off = (unit * G + h) * PART;
+        put4(parts, off + d0 * 4, A);
+        if (d0 == 0) put2(parts, off + HD * 4, M, L);
+      }
+    }
+    if (np > 1) {
+      wait_stores();
+      __syncthreads();
+      uint32_t* word = a.arrive + ((size_t)b * H + g) * kArriveStride;
+      if (tid == 0)
+        s_arrived = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+      __syncthreads();
+      if (s_arrived == (uint32_t)np) {            // every part is stored: merge them, in order
+        if (tid == 0) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // A head's threads take TPH parts at a time: thread i reads part i's (M, L) and works out its weight, then
+        // every thread sums its four dims over the parts, sixteen loads in flight, the weights fetched from LDS.
+        // With few heads and many parts, groups of threads take a share of the parts each and meet in LDS.
+        const int pitch = (cols + 63) & ~63;      // threads of a group: whole waves
+        const int nsub = np > 16 ? max(1, NT / pitch) : 1;
+        const int sub = nsub > 1 ? wave * 64 / pitch : 0;
+        constexpr int UNR = 16;
+        const int32_t step = H * G * PART;
+        for (int c = tid - sub * pitch; c < cols && sub < nsub; c += NT) {
+          const int h = c / TPH, t = c % TPH, d0 = 4 * t;
+          const int32_t first = (((end - np) * H + g) * G + h) * PART;
+          const int32_t s_end = np * (sub + 1) / nsub;
+          float M = kNegBig, L = 0.f;
+          float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
+          for (int32_t s0 = np * sub / nsub; s0 < s_end; s0 += TPH) {
+            const int32_t n = min(s_end - s0, TPH);
+            float2 ml = make_float2(kNegBig, 0.f);
+            if (t < n) ml = get2(parts, first + (s0 + t) * step + HD * 4);
+            for (int32_t u0 = 0; u0 < n; u0 += UNR) {
+              float4 ai[UNR];
+#pragma unroll
+              for (int u = 0; u < UNR; ++u) ai[u] = get4(parts, first + d0 * 4, (s0 + min(u0 + u, n - 1)) * step);
+              if (u0 == 0) {
+                const float m_new = fmaxf(M, head_max<TPH>(ml.x));
+                const float corr = __builtin_amdgcn_exp2f(M - m_new);
+                const float wt = t < n ? __builtin_amdgcn_exp2f(ml.x - m_new) : 0.f;
+                L = fmaf(L, corr, head_sum<TPH>(wt * ml.y));
+                A = make_float4(A.x * corr, A.y * corr, A.z * corr, A.w * corr);
+                M = m_new;
+                s_w[tid] = wt;                    // read by this wave only
+                __builtin_amdgcn_wave_barrier();
+              }
+#pragma unroll
+              for (int u = 0; u < UNR; u += 4) {  // (threads beyond n hold weight 0; TPH is a multiple of UNR)
+                const float4 wu = *reinterpret_cast<const float4*>(&s_w[(tid & ~(TPH - 1)) + u0 + u]);
+                axpy(A, wu.x, ai[u]);
+                axpy(A, wu.y, ai[u + 1]);
+                axpy(A, wu.z, ai[u + 2]);
+                axpy(A, wu.w, ai[u + 3]);
+              }
+            }
+          }
+          if (nsub == 1) {
+            finish(c, M, L, A);
+          } else {
+            if (d0 == 0) {
+              s_m[sub * kMaxGroup + h] = M;
+              s_l[sub * kMaxGroup + h] = L;
+            }
+            *reinterpret_cast<float4*>(&s_acc[((size_t)sub * G + h) * ROW + d0]) = A;
+          }
+        }
+        if (nsub > 1) {
+          __syncthreads();
+          if (tid < cols) {
+            const int h = tid / TPH, d0 = 4 * (tid % TPH);
+            float M, L;
+            float4 A;
+            merge_lds(nsub, h, d0, M, L, A);
+            finish(tid, M, L, A);
+          }
+        }
+      }
+    }
+  }
+  if (a.clock && tid == 0) {
+    const unsigned long long t = wall_clock64();
+    if (a.clock_wg) a.clock_wg[2 * blockIdx.x + 1] = t;
+    else { atomicMax(&a.clock[kClockKernelEnd], t); atomicMax(&a.clock[kClockLayerEnd], t); }
+  }
+}
+
+// ---- dispatch --------------------------------------------------------------------------------------------
+
+size_t attn_direct_floats(const pie_config& c) { return (size_t)kDirectRows * (c.head_dim + 4); }
+
+// How many units the split of a call may make; 0: the call is left to the planned path, which has what this one lacks -
+// an item size set by the caller, the vector-ALU variant, fp32 with grouped queries (every query head reads the keys
+// and values again: many small items share them in the caches, 80 us against 95 to 104 for six sequences of 100 to
+// 4 000 tokens, 32 heads over 8), more sequences than the in-kernel split covers - or for which the units do not fit.
+// Otherwise: as few units as hold every (sequence, kv head) pair and the longest context the table can name, in steps
+// of the compute units.  One workgroup a compute unit streams as fast as two or three, and every part more has to be
+// stored, counted and merged: one sequence of 32 749 tokens, 64 heads over 8, takes 33.0 us at one unit per compute
+// unit, 37.6 at three, 44.1 at six.  Beyond one, three workgroups are resident per compute unit, so multiples of three
+// (64 sequences of 500 to 2 500 tokens, 32 heads over 8: 77.6 / 72.8 / 74.9 us at two / three / six); short contexts
+// want few (60 of 60 to 300 tokens, 32 heads, a step of 8 layers: 325 us at nine, 379 at fifteen).
+static int32_t direct_max_units(const pie_pool* p, int32_t batch, int32_t max_blocks) {
+  if (p->attn_partition > 0 || p->attn_valu) return 0;
+  if (batch < 1 || batch > kDirectSeqs || max_blocks < 1) return 0;
+  const pie_config& c = p->cfg;
+  const int64_t group = c.n_q_heads / c.n_kv_heads, tokens = (int64_t)max_blocks * kBlockTokens;
+  if (c.dtype == PIE_DTYPE_F32 && group > 1) return 0;
+  const int64_t longest = (int64_t)kDirectMaxQuanta * kWaves * kBlockTokens;
+  const int64_t least = batch * ((tokens + longest - 1) / longest) * c.n_kv_heads;
+  int64_t room = kDirectRows / group;
+  if (room > kDirectMaxUnits) room = kDirectMaxUnits;
+  if (least > room) return 0;
+  for (const int per_cu : {1, 3, 6, 9, 15}) {
+    const int64_t units = (int64_t)per_cu * p->n_cu;
+    if (units >= least && units <= room) return (int32_t)units;
+  }
+  return (int32_t)room;
+}
+
+bool attn_direct(const pie_pool* p, int32_t batch, int32_t max_blocks) { return direct_max_units(p, batch, max_blocks) > 0; }
+
+// Within a step the planned path plans once for all layers and stores the new rows in one launch beside the first, so
+// it catches up sooner: from about 2 M tokens x kv heads in the table (1 045 us against 1 045 for 8 layers of 120
+// sequences of 500 to 2 500 tokens at 8 kv heads, 1 086 against 1 111 for 190 of 300 to 1 700) unless there are too few
+// (sequence, kv head) pairs to fill the compute units (16 layers, 24 sequences of 100 to 1 100 tokens, 32 kv heads:
+// 667 us here, 716 planned; of 32 layers with 64 of 1 024 to 2 048: 8 410 here, 8 103 planned).
+bool attn_direct_step(const pie_pool* p, int32_t batch, int32_t max_blocks) {
+  const int64_t pairs = (int64_t)batch * p->cfg.n_kv_heads;
+  if (pairs > 3 * (int64_t)p->n_cu && pairs * max_blocks * kBlockTokens > (int64_t)8192 * p->n_cu) return false;
+  return attn_direct(p, batch, max_blocks);
+}
+
+template <typename W, int NW>
+static int launch_direct(const DirectArgs& a, int32_t grid, hipStream_t s, hipEvent_t done) {
+  const size_t lds = ((size_t)NW * 2 * kMaxGroup + (size_t)NW * a.group * (W::HD + 4)) * sizeof(float);
+  if (done) hipExtLaunchKernelGGL((k_attn_direct<W, NW>), dim3(grid), dim3(NW * 64), (uint32_t)lds, s, nullptr, done, 0, a);
+  else hipLaunchKernelGGL((k_attn_direct<W, NW>), dim3(grid), dim3(NW * 64), (uint32_t)lds, s, a);
+  PIE_HIP(hipGetLastError());
+  return PIE_OK;
+}
+
+int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const int32_t* d_table, int32_t max_blocks,
+                       const int32_t* d_ctx, int32_t batch, void* d_out, bool stage_valid, hipStream_t s,
+                       const void* d_k_new, const void* d_v_new, int32_t append, const LayerView* view,
+                       const AttnWork* work, hipEvent_t k_start, hipEvent_t k_end, unsigned long long* clock_row,
+                       hipEvent_t done) {
+  const pie_config& c = p->cfg;
+  if (((uintptr_t)d_q | (uintptr_t)d_out) % 16) return PIE_EINVAL;
+  if (c.n_gpu_blocks + 2 * c.n_stage_blocks <= 0) return PIE_EINVAL;
+  if ((d_k_new == nullptr) != (d_v_new == nullptr)) return PIE_EINVAL;
+  if (((uintptr_t)d_k_new | (uintptr_t)d_v_new) % 16) return PIE_EINVAL;
+  const int32_t group = c.n_q_heads / c.n_kv_heads, H = c.n_kv_heads, max_units = direct_max_units(p, batch, max_blocks);
+  if (max_units <= 0) return PIE_EINVAL;
+  DirectArgs a;
+  a.kv_layer = view ? view->kv_base : p->d_kv + (size_t)layer * p->d_layer_stride;
+  a.table = d_table;
+  a.map = view ? view->map : p->d_map[layer & 1];
+  a.ctx = d_ctx;
+  a.err = p->d_err;
+  a.q = (const char*)d_q;
+  a.out = (char*)d_out;
+  a.new_k = (const char*)d_k_new;
+  a.new_v = (const char*)d_v_new;
+  a.ws = work ? reinterpret_cast<float*>(work->plan) : p->d_ws;   // a call's own scratch from its start
+  uint32_t* words = work ? work->arrive : p->d_arrive;
+  const uint32_t turn = (work ? work->arrive_turn : &p->arrive_turn)->fetch_add(1, std::memory_order_relaxed) & 1u;
+  a.arrive = words + turn * kArriveSet;
+  a.arrive_other = words + (1u - turn) * kArriveSet;
+  a.hdr = work ? nullptr : p->d_plan;
+  a.block_bytes = p->block_bytes;
+  a.ws_bytes = (int32_t)(attn_direct_floats(c) * sizeof(float));
+  a.scale_log2e = p->scale_log2e;
+  a.batch = batch;
+  a.max_blocks = max_blocks;
+  a.n_kv_heads = H;
+  a.group = group;
+  a.n_q_heads = c.n_q_heads;
+  a.n_handles = view ? view->n_handles : p->n_handles;
+  a.n_gpu_blocks = view ? view->n_slots : c.n_gpu_blocks;
+  a.n_slots = view ? view->n_slots : c.n_gpu_blocks + 2 * c.n_stage_blocks;
+  a.stage_valid = stage_valid ? 1 : 0;
+  const int64_t second = ((int64_t)max_blocks * kBlockTokens + auto_part(1) - 1) / auto_part(1);
+  a.min_units = batch * second * H > attn_min_units(p) ? attn_min_units(p) : 0;
+  a.max_items = max_units / H;
+  a.append = append;
+  // no more workgroups than the widest context the table can hold makes units
+  const int32_t quanta = (max_blocks + kWaves - 1) / kWaves;
+  const int64_t most = (int64_t)batch * quanta * H;
+  const int32_t grid = most < max_units ? (int32_t)most : max_units;
+  a.clock = clock_row;
+  a.clock_wg = nullptr;
+  if (clock_row && grid <= kClockWgs) {
+    const size_t row = (size_t)(clock_row - p->d_clock) / kClockRow;
+    a.clock_wg = p->d_clock + ((size_t)c.n_layers + 1) * kClockRow + row * kClockWgs * 2;
+  }
+  if (k_start) PIE_HIP(hipEventRecord(k_start, s));
+  int rc = PIE_EINVAL;
+  const bool hd128 = c.head_dim == 128;
+  switch (c.dtype) {
+    case PIE_DTYPE_F32:
+      rc = hd128 ? launch_direct<Wave32<128>, kWaves>(a, grid, s, done) : launch_direct<Wave32<64>, kWaves>(a, grid, s, done);
+      break;
+    case PIE_DTYPE_F16:
+      rc = hd128 ? launch_direct<Wave16<F16, 128, false>, kWaves>(a, grid, s, done)
+                 : launch_direct<Wave16<F16, 64, false>, kWaves>(a, grid, s, done);
+      break;
+    case PIE_DTYPE_BF16:
+      rc = hd128 ? launch_direct<Wave16<BF16, 128, true>, kWaves>(a, grid, s, done)
+                 : launch_direct<Wave16<BF16, 64, true>, kWaves>(a, grid, s, done);
+      break;
+  }
+  if (rc) return rc;
+  if (k_end) PIE_HIP(hipEventRecord(k_end, s));
+  return PIE_OK;
+}
+
+}  // namespace pie

@@ -516,7 +516,10 @@ int pie_elastic_step(pie_elastic_pool* lp, const void* d_q_all, const void* d_k_
   pie::note_stream(p, os);
   int rc;
   // with a new token the attention takes it from the new rows, the rest of the context from the cache
-  if ((rc = pie::launch_attn_plan(p, d_ctx_lens, batch, max_blocks, cs, false, nullptr, d_k_new != nullptr))) return rc;
+  // (a small batch's layers are one launch each, appends included: pie_attn_direct.hip)
+  const bool direct = pie::attn_direct_step(p, batch, max_blocks);
+  if (!direct && (rc = pie::launch_attn_plan(p, d_ctx_lens, batch, max_blocks, cs, false, nullptr, d_k_new != nullptr)))
+    return rc;
   for (int32_t k = 0; k < lp->n; ++k) {
     // the presence check: wait until the layer is physically on the GPU
     if ((rc = poll_moves(lp, cs))) return rc;
@@ -540,19 +543,25 @@ int pie_elastic_step(pie_elastic_pool* lp, const void* d_q_all, const void* d_k_
       lp->stats.stall_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_wait0).count();
     // the layer's blocks through its own map: every slot of the GPU memory counts as resident
     pie::LayerView view{p->d_kv, lp->d_maps + (size_t)k * lp->H, lp->H, lp->N * lp->C};
-    if (d_k_new) {
-      if ((rc = pie::launch_kv_append(p, k, 1, (const char*)d_k_new + k * kv_stride, (const char*)d_v_new + k * kv_stride,
-                                      d_block_table, max_blocks, d_ctx_lens, batch, pie::kAppendGpuStrict, cs, &view)))
+    const char* q_k = (const char*)d_q_all + k * q_stride;
+    char* out_k = (char*)d_out_all + k * q_stride;
+    const char* k_k = d_k_new ? (const char*)d_k_new + k * kv_stride : nullptr;
+    const char* v_k = d_k_new ? (const char*)d_v_new + k * kv_stride : nullptr;
+    if (direct) {
+      if ((rc = pie::launch_attn_direct(p, k, q_k, d_block_table, max_blocks, d_ctx_lens, batch, out_k, false, cs, k_k, v_k,
+                                        d_k_new ? pie::kAppendGpuStrict : -1, &view)))
+        return rc;
+    } else {
+      if (d_k_new && (rc = pie::launch_kv_append(p, k, 1, k_k, v_k, d_block_table, max_blocks, d_ctx_lens, batch,
+                                                 pie::kAppendGpuStrict, cs, &view)))
+        return rc;
+      if ((rc = pie::launch_attn_resolve(p, d_block_table, d_ctx_lens, batch, max_blocks, true, false, false, false, cs,
+                                         &view)))
+        return rc;
+      if ((rc = pie::launch_attn_decode(p, k, q_k, max_blocks, d_ctx_lens, batch, out_k, cs, nullptr, nullptr, k, nullptr,
+                                        &view, nullptr, nullptr, k_k, v_k)))
         return rc;
     }
-    if ((rc = pie::launch_attn_resolve(p, d_block_table, d_ctx_lens, batch, max_blocks, true, false, false, false, cs,
-                                       &view)))
-      return rc;
-    if ((rc = pie::launch_attn_decode(p, k, (const char*)d_q_all + k * q_stride, max_blocks, d_ctx_lens, batch,
-                                      (char*)d_out_all + k * q_stride, cs, nullptr, nullptr, k, nullptr, &view, nullptr,
-                                      nullptr, d_k_new ? (const char*)d_k_new + k * kv_stride : nullptr,
-                                      d_v_new ? (const char*)d_v_new + k * kv_stride : nullptr)))
-      return rc;
     if (p->layer_compute_us > 0.f && (rc = pie::launch_busy(p->layer_compute_us, p->wall_clock_khz, cs))) return rc;
     PIE_HIP(hipEventRecord(lp->ev_layer[k], cs));
     lp->ev_layer_rec[k] = 1;

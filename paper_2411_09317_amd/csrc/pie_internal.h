@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <condition_variable>
 #include <cstdint>
 #include <deque>
@@ -43,7 +44,13 @@ constexpr int kClockInEnd = 4;        // the layer's swap-in: its copy has ended
 constexpr int kClockOutStart = 5;     // (not stamped)
 constexpr int kClockOutEnd = 6;       // the layer's write-back has ended
 constexpr int kClockGrid = 7;         // workgroups of the decode kernel that wrote per-workgroup words (0: none)
-constexpr int kClockWgs = 2048;       // per-workgroup (first, last moment) pairs per layer, after the rows
+constexpr int kClockWgs = 4096;       // per-workgroup (first, last moment) pairs per layer, after the rows
+
+// Arrival words of the one-launch attention path: two sets of as many (sequence, head) pairs as it may merge at once,
+// each word in a cache line of its own (atomics on one line are served one after another, about 10 ns each).
+constexpr int kArriveWords = 4096;
+constexpr int kArriveStride = 32;
+constexpr int kArriveSet = kArriveWords * kArriveStride;
 
 struct Home {
   int32_t where = -1;  // PIE_WHERE_* or -1 = unallocated
@@ -82,6 +89,8 @@ struct AttnWork {
   int32_t* plan;
   float* ws;
   size_t ws_floats;
+  uint32_t* arrive;         // 2 x kArriveSet words of the one-launch path, and whose turn it is
+  std::atomic<uint32_t>* arrive_turn;
   int32_t n_counters;       // ticket counters the planning kernel zeroes
   int32_t lay_batch, lay_max_blocks;
 };
@@ -123,6 +132,8 @@ struct pie_pool {
   float* d_ws = nullptr;        // split-context partials
   size_t ws_floats = 0;
   int32_t* d_plan = nullptr;    // attention planning state: header, ticket counters, items, resolved tables
+  uint32_t* d_arrive = nullptr; // arrival words of the one-launch attention path
+  mutable std::atomic<uint32_t> arrive_turn{0};   // the set of them the next launch uses (its low bit)
   int32_t n_cu = 256;           // compute units of the device
   uint32_t* d_err = nullptr;    // device error flags
   unsigned long long* d_clock = nullptr;   // clock table: (n_layers + 1) rows of kClockRow words
@@ -246,8 +257,19 @@ int launch_attn_decode(const pie_pool* p, int32_t layer, const void* d_q, int32_
                        unsigned long long* clock_row = nullptr, const LayerView* view = nullptr,
                        hipEvent_t done = nullptr, const AttnWork* work = nullptr, const void* d_k_new = nullptr,
                        const void* d_v_new = nullptr);
+inline int32_t attn_min_units(const pie_pool* p) { return p->n_cu * 17; }   // see k_attn_plan
+// The one-launch attention path (pie_attn_direct.hip): whether it takes a call on its own or a step's layers, and the
+// launch, which needs no planning before it.  append: kAppend* mode in which the new rows are stored as well, or -1.
+bool attn_direct_step(const pie_pool* p, int32_t batch, int32_t max_blocks);
+bool attn_direct(const pie_pool* p, int32_t batch, int32_t max_blocks);
+size_t attn_direct_floats(const pie_config& c);
+int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const int32_t* d_table, int32_t max_blocks,
+                       const int32_t* d_ctx, int32_t batch, void* d_out, bool stage_valid, hipStream_t s,
+                       const void* d_k_new = nullptr, const void* d_v_new = nullptr, int32_t append = -1,
+                       const LayerView* view = nullptr, const AttnWork* work = nullptr, hipEvent_t k_start = nullptr,
+                       hipEvent_t k_end = nullptr, unsigned long long* clock_row = nullptr, hipEvent_t done = nullptr);
 int launch_stream_probe(const pie_pool* p, int32_t layer, int32_t max_blocks, int32_t batch, hipStream_t s);
-int attn_static_scratch(char** out);
+int attn_static_scratch(char** out, std::atomic<uint32_t>** out_turn = nullptr);
 int attn_static_work(const pie_pool* p, int32_t batch, int32_t max_blocks, AttnWork* out);
 size_t attn_plan_ints(const pie_config& c);
 size_t attn_workspace_floats(const pie_config& c);

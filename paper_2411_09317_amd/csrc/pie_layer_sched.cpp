@@ -376,9 +376,11 @@ int pie_layer_step(pie_layer_pool* lp, const void* d_q_all, const void* d_k_new,
   pie::note_stream(p, os);
   int rc;
   if ((rc = pie::flush_map(p, cs))) return rc;
+  // a small batch's layers are one launch each, appends included (pie_attn_direct.hip)
+  const bool direct = pie::attn_direct_step(p, batch, max_blocks);
   for (int32_t k = 0; k < lp->n_layers; ++k) {
     // one ticket counter per launch since the last planning kernel; there are as many as GPU slots
-    if (k % n_slots == 0) {
+    if (!direct && k % n_slots == 0) {
       // with a new token the attention takes it from the new rows, the rest of the context from the cache
       if ((rc = pie::launch_attn_plan(p, d_ctx_lens, batch, max_blocks, cs, false, nullptr, d_k_new != nullptr))) return rc;
       if (k == 0 && (rc = pie::launch_attn_resolve(p, d_block_table, d_ctx_lens, batch, max_blocks, true, false, true,
@@ -406,17 +408,22 @@ int pie_layer_step(pie_layer_pool* lp, const void* d_q_all, const void* d_k_new,
     if (waited)
       lp->stats.stall_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_wait0).count();
     const int32_t slot = act.gpu_slot;
-    if (d_k_new) {
-      if ((rc = pie::launch_kv_append(p, slot, 1, (const char*)d_k_new + k * kv_stride, (const char*)d_v_new + k * kv_stride,
-                                      d_block_table, max_blocks, d_ctx_lens, batch, pie::kAppendGpuStrict, cs)))
+    const char* q_k = (const char*)d_q_all + k * q_stride;
+    char* out_k = (char*)d_out_all + k * q_stride;
+    const char* k_k = d_k_new ? (const char*)d_k_new + k * kv_stride : nullptr;
+    const char* v_k = d_k_new ? (const char*)d_v_new + k * kv_stride : nullptr;
+    if (direct) {
+      if ((rc = pie::launch_attn_direct(p, slot, q_k, d_block_table, max_blocks, d_ctx_lens, batch, out_k, false, cs, k_k,
+                                        v_k, d_k_new ? pie::kAppendGpuStrict : -1)))
+        return rc;
+    } else {
+      if (d_k_new && (rc = pie::launch_kv_append(p, slot, 1, k_k, v_k, d_block_table, max_blocks, d_ctx_lens, batch,
+                                                 pie::kAppendGpuStrict, cs)))
+        return rc;
+      if ((rc = pie::launch_attn_decode(p, slot, q_k, max_blocks, d_ctx_lens, batch, out_k, cs, nullptr, nullptr,
+                                        k % n_slots, nullptr, nullptr, nullptr, nullptr, k_k, v_k)))
         return rc;
     }
-    if ((rc = pie::launch_attn_decode(p, slot, (const char*)d_q_all + k * q_stride, max_blocks, d_ctx_lens, batch,
-                                      (char*)d_out_all + k * q_stride, cs, nullptr, nullptr, k % n_slots, nullptr,
-                                      nullptr, nullptr, nullptr,
-                                      d_k_new ? (const char*)d_k_new + k * kv_stride : nullptr,
-                                      d_v_new ? (const char*)d_v_new + k * kv_stride : nullptr)))
-      return rc;
     if (p->layer_compute_us > 0.f && (rc = pie::launch_busy(p->layer_compute_us, p->wall_clock_khz, cs))) return rc;
     PIE_HIP(hipEventRecord(lp->ev_slot[slot], cs));
     lp->ev_slot_rec[slot] = 1;

@@ -42,7 +42,7 @@ static bool config_ok(const pie_config* c) {
 
 struct Layout {
   size_t block_bytes, d_layer_stride, h_layer_stride;
-  size_t off_map0, off_map1, off_ws, off_plan, off_err, off_clock, d_total, h_total;
+  size_t off_map0, off_map1, off_ws, off_plan, off_err, off_clock, off_arrive, d_total, h_total;
   size_t ws_floats;
 };
 
@@ -62,6 +62,7 @@ static Layout layout_of(const pie_config& c) {
   l.off_err = off; off += kAlign;
   l.off_clock = off;
   off = align_up(off + (((size_t)c.n_layers + 1) * kClockRow + (size_t)c.n_layers * kClockWgs * 2) * 8, kAlign);
+  l.off_arrive = off; off = align_up(off + (size_t)2 * kArriveSet * 4, kAlign);
   l.d_total = off;
   l.h_total = l.h_layer_stride * c.n_layers;
   return l;
@@ -483,6 +484,7 @@ int pie_pool_init(const pie_config* cfg, void* d_base, size_t d_bytes, void* h_p
     p->d_plan = (int32_t*)(base + l.off_plan);
     p->d_err = (uint32_t*)(base + l.off_err);
     p->d_clock = (unsigned long long*)(base + l.off_clock);
+    p->d_arrive = (uint32_t*)(base + l.off_arrive);
     int rc = PIE_OK;
     {
       int dev = 0, n_cu = 0;
@@ -535,6 +537,7 @@ int pie_pool_init(const pie_config* cfg, void* d_base, size_t d_bytes, void* h_p
     if ((rc = launch_map_fill(p->d_map[0], p->n_handles, -1, nullptr))) return fail(rc);
     if ((rc = launch_map_fill(p->d_map[1], p->n_handles, -1, nullptr))) return fail(rc);
     if ((rc = launch_zero_u32(p->d_err, kAlign / 4, nullptr))) return fail(rc);
+    if ((rc = launch_zero_u32(p->d_arrive, 2 * kArriveSet, nullptr))) return fail(rc);
     if ((rc = launch_zero_u32((uint32_t*)p->d_clock, (cfg->n_layers + 1) * kClockRow * 2, nullptr))) return fail(rc);
     err = hipStreamSynchronize(nullptr);
     if (err != hipSuccess) { g_last_hip_error = (int)err; return fail(PIE_EHIP); }
@@ -835,6 +838,12 @@ static int attn_decode_impl(pie_pool* p, int32_t layer, const void* d_q, const i
   bool stage_valid = false;
   int rc;
   if ((rc = compute_prologue(p, layer, s, &stage_valid))) return rc;
+  if (attn_direct(p, batch, max_blocks)) {
+    if ((rc = launch_attn_direct(p, layer, d_q, d_block_table, max_blocks, d_ctx_lens, batch, d_out, stage_valid, s,
+                                 nullptr, nullptr, -1, nullptr, work)))
+      return rc;
+    return compute_epilogue(p, layer, s);
+  }
   const int r = layer & 1;
   if ((rc = launch_attn_plan(p, d_ctx_lens, batch, max_blocks, s, false, work))) return rc;
   if ((rc = launch_attn_resolve(p, d_block_table, d_ctx_lens, batch, max_blocks, r == 0, stage_valid, r == 1,
@@ -998,18 +1007,25 @@ static int step_body(pie_pool* p, const StepJob& j) {
   // arrived, just ahead of their write-back.
   const bool with_new = d_k_new != nullptr;
   const bool staged_tails = with_new && n_dirty > 0;
-  if (with_new) {                                // the appends read the maps sent above
+  const int32_t append_mode = staged_tails ? kAppendGpuHomed : kAppendGpuStrict;
+  // A small batch's layers are one launch each, which stores the GPU-homed tails' rows too (pie_attn_direct.hip).
+  const bool direct = attn_direct_step(p, batch, max_blocks);
+  const bool append_apart = with_new && !direct;
+  if (append_apart || staged_tails) {            // the appends read the maps sent above
     PIE_HIP(hipEventRecord(p->ev_map, cs));
     p->ev_map_rec = true;
   }
-  if ((rc = launch_attn_plan(p, d_ctx_lens, batch, max_blocks, cs, clocked, nullptr, with_new))) return rc;
-  if ((rc = launch_attn_resolve(p, d_block_table, d_ctx_lens, batch, max_blocks, true, true, L > 1, true, cs)))
+  // (with monitoring by device clock the planning kernel runs in any case: it resets the clock table)
+  if ((!direct || clocked) &&
+      (rc = launch_attn_plan(p, d_ctx_lens, batch, max_blocks, cs, clocked, nullptr, with_new)))
     return rc;
-  if (with_new) {
-    note_stream(p, os);
-    if (os != cs) PIE_HIP(hipStreamWaitEvent(os, p->ev_map, 0));
-    if ((rc = launch_kv_append(p, 0, L, d_k_new, d_v_new, d_block_table, max_blocks, d_ctx_lens, batch,
-                               staged_tails ? kAppendGpuHomed : kAppendGpuStrict, os)))
+  if (!direct &&
+      (rc = launch_attn_resolve(p, d_block_table, d_ctx_lens, batch, max_blocks, true, true, L > 1, true, cs)))
+    return rc;
+  if (with_new) note_stream(p, os);
+  if ((append_apart || staged_tails) && os != cs) PIE_HIP(hipStreamWaitEvent(os, p->ev_map, 0));
+  if (append_apart) {
+    if ((rc = launch_kv_append(p, 0, L, d_k_new, d_v_new, d_block_table, max_blocks, d_ctx_lens, batch, append_mode, os)))
       return rc;
     PIE_HIP(hipEventRecord(p->ev_append, os));
   }
@@ -1057,13 +1073,19 @@ static int step_body(pie_pool* p, const StepJob& j) {
     // for the event that completes with the layer's last kernel.
     const bool standin = p->layer_compute_us > 0.f;
     hipEvent_t read_done = n_prefetch > 0 ? p->ev_read[l & 1] : nullptr;
-    if ((rc = launch_attn_decode(p, l, (const char*)d_q_all + l * q_stride, max_blocks, d_ctx_lens, batch,
-                                 (char*)d_out_all + l * q_stride, cs, timed ? p->lev[l].k_start : nullptr,
-                                 timed ? p->lev[l].k_end : nullptr, -1, clock_row(l), nullptr,
-                                 standin ? nullptr : read_done, nullptr,
-                                 with_new ? (const char*)d_k_new + l * kv_stride : nullptr,
-                                 with_new ? (const char*)d_v_new + l * kv_stride : nullptr)))
-      return rc;
+    const char* q_l = (const char*)d_q_all + l * q_stride;
+    char* out_l = (char*)d_out_all + l * q_stride;
+    const char* k_l = with_new ? (const char*)d_k_new + l * kv_stride : nullptr;
+    const char* v_l = with_new ? (const char*)d_v_new + l * kv_stride : nullptr;
+    hipEvent_t k_start = timed ? p->lev[l].k_start : nullptr, k_end = timed ? p->lev[l].k_end : nullptr;
+    hipEvent_t done = standin ? nullptr : read_done;
+    if (direct)
+      rc = launch_attn_direct(p, l, q_l, d_block_table, max_blocks, d_ctx_lens, batch, out_l, true, cs, k_l, v_l,
+                              with_new ? append_mode : -1, nullptr, nullptr, k_start, k_end, clock_row(l), done);
+    else
+      rc = launch_attn_decode(p, l, q_l, max_blocks, d_ctx_lens, batch, out_l, cs, k_start, k_end, -1, clock_row(l),
+                              nullptr, done, nullptr, k_l, v_l);
+    if (rc) return rc;
     if (standin && (rc = launch_busy(p->layer_compute_us, p->wall_clock_khz, cs, clock_row(l), read_done)))
       return rc;
     if (timed) PIE_HIP(hipEventRecord(p->lev[l].attn_end, cs));
@@ -1110,7 +1132,7 @@ static int step_body(pie_pool* p, const StepJob& j) {
   if (clocked && (rc = launch_clock_fold(p->d_clock, L, cs))) return rc;
   // Whatever follows this step on the compute stream, or waits for the step's compute work, finds the new rows
   // in the GPU-homed tail blocks.  That launch ran beside the first layers: usually the host sees it finished.
-  if (with_new && os != cs) {
+  if (append_apart && os != cs) {
     const hipError_t e = hipEventQuery(p->ev_append);
     if (e != hipSuccess) {
       (void)hipGetLastError();

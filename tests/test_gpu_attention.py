@@ -107,6 +107,56 @@ def test_partition_size_does_not_change_the_result_beyond_rounding():
     lib.close()
 
 
+ONE_LAUNCH = [
+    # name, dtype, Hq, Hkv, d, context lengths: around a pass of the four waves (64 tokens), a block, a lane of
+    # sequences (64) and the batch the split covers (256); parts merged 16 at a time and over several groups of threads;
+    # one and two rows of lanes per head, 1 to 16 heads
+    ("pass_edges_bf16", I.DTYPE_BF16, 8, 2, 128, [1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 0]),
+    ("pass_edges_f16_d64", I.DTYPE_F16, 4, 4, 64, [65, 64, 63, 1, 0, 1040]),
+    ("pass_edges_f32", I.DTYPE_F32, 2, 2, 128, [65, 64, 63, 1, 0, 1040]),
+    ("many_parts_g1_d64", I.DTYPE_F16, 1, 1, 64, [4097]),
+    ("many_parts_g1_d128", I.DTYPE_BF16, 1, 1, 128, [4090, 33]),
+    ("many_parts_g8", I.DTYPE_BF16, 8, 1, 128, [9001]),
+    ("many_parts_g16_d64", I.DTYPE_F16, 16, 1, 64, [3000, 2999]),
+    ("g3", I.DTYPE_BF16, 6, 2, 64, [700, 1]),
+    ("many_parts_f32", I.DTYPE_F32, 1, 1, 64, [5000]),
+    ("longest_unit", I.DTYPE_F16, 300, 300, 64, [4096]),
+    ("batch_64", I.DTYPE_F16, 2, 1, 64, [5 + 3 * i for i in range(64)]),
+    ("batch_65", I.DTYPE_F16, 2, 1, 64, [199 - 3 * i for i in range(65)]),
+    ("batch_256", I.DTYPE_BF16, 2, 2, 64, [1 + (7 * i) % 130 for i in range(256)]),
+    ("pairs_beyond_three_per_cu", I.DTYPE_F16, 16, 16, 64, [20 + (11 * i) % 90 for i in range(60)]),
+]
+
+
+@pytest.mark.parametrize("name,dtype,hq,hkv,d,ctx", ONE_LAUNCH, ids=[s[0] for s in ONE_LAUNCH])
+def test_one_launch_path_at_its_edges(name, dtype, hq, hkv, d, ctx):
+    """The call of one launch (no item size set) against the oracle, with a table wider than the contexts, poisoned
+    unused rows and slots; again, again and from the static scratch to the same bits (the arrival words it merges
+    by take turns); and against the planned path."""
+    w = I.Workload(name, 1, len(ctx), hq, hkv, d, dtype, value_scale=1.0, seed=36)
+    ctx = np.asarray(ctx, np.int32)
+    case = I.make_case(w, ctx_lens=ctx)
+    lib, mod, table = GH.make_pools(case, int(case.n_blocks.sum()) + 3, 2, 2, fill=H.nan_fill(dtype),
+                                    max_blocks=int(case.n_blocks.max()) + 5)
+    q, K, V = H.dense_f64(case, 0)
+    live = np.nonzero(ctx)[0]
+    ref = np.zeros(q.shape)
+    ref[live] = A.dense_attention(q[live], [K[b] for b in live], [V[b] for b in live], ctx[live])
+    got = run_attn(lib, case, table)
+    check(got[live], ref[live], dtype)
+    assert (np.delete(got, live, axis=0) == 0).all()
+    for _ in range(3):
+        assert np.array_equal(run_attn(lib, case, table), got)
+    qd = GH.to_dev(case.q[0], dtype)
+    out = torch.full_like(qd, float("nan"))
+    lib.attn_decode_static(0, qd, torch.from_numpy(table).to(GH.DEV), torch.from_numpy(ctx).to(GH.DEV), out)
+    assert lib.check_errors() == 0
+    assert np.array_equal(GH.from_dev(out, dtype), got)
+    lib.set_attn_partition(512)
+    check(run_attn(lib, case, table)[live], ref[live], dtype)
+    lib.close()
+
+
 @pytest.mark.parametrize("batch", [1, 63, 64, 257, 1023, 1029])
 def test_planning_of_batches_around_its_rounds(batch):
     """The planning kernel scans the batch in rounds of one sequence per thread (256 or 1024 threads) and ranks the
