@@ -543,13 +543,16 @@ int pie_elastic_step(pie_elastic_pool* lp, const void* d_q_all, const void* d_k_
       lp->stats.stall_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_wait0).count();
     // the layer's blocks through its own map: every slot of the GPU memory counts as resident
     pie::LayerView view{p->d_kv, lp->d_maps + (size_t)k * lp->H, lp->H, lp->N * lp->C};
+    // the layer's event rides on its last kernel, unless something follows that
+    const hipEvent_t done = p->layer_compute_us > 0.f ? nullptr : lp->ev_layer[k];
     const char* q_k = (const char*)d_q_all + k * q_stride;
     char* out_k = (char*)d_out_all + k * q_stride;
     const char* k_k = d_k_new ? (const char*)d_k_new + k * kv_stride : nullptr;
     const char* v_k = d_k_new ? (const char*)d_v_new + k * kv_stride : nullptr;
     if (direct) {
       if ((rc = pie::launch_attn_direct(p, k, q_k, d_block_table, max_blocks, d_ctx_lens, batch, out_k, false, cs, k_k, v_k,
-                                        d_k_new ? pie::kAppendGpuStrict : -1, &view)))
+                                        d_k_new ? pie::kAppendGpuStrict : -1, &view, nullptr, nullptr, nullptr, nullptr,
+                                        done)))
         return rc;
     } else {
       if (d_k_new && (rc = pie::launch_kv_append(p, k, 1, k_k, v_k, d_block_table, max_blocks, d_ctx_lens, batch,
@@ -559,11 +562,11 @@ int pie_elastic_step(pie_elastic_pool* lp, const void* d_q_all, const void* d_k_
                                          &view)))
         return rc;
       if ((rc = pie::launch_attn_decode(p, k, q_k, max_blocks, d_ctx_lens, batch, out_k, cs, nullptr, nullptr, k, nullptr,
-                                        &view, nullptr, nullptr, k_k, v_k)))
+                                        &view, done, nullptr, k_k, v_k)))
         return rc;
     }
     if (p->layer_compute_us > 0.f && (rc = pie::launch_busy(p->layer_compute_us, p->wall_clock_khz, cs))) return rc;
-    PIE_HIP(hipEventRecord(lp->ev_layer[k], cs));
+    if (!done) PIE_HIP(hipEventRecord(lp->ev_layer[k], cs));
     lp->ev_layer_rec[k] = 1;
     // The protocol's two checks belong to the moment this layer starts computing, which is when the previous
     // one has ended: the host waits for that (this layer's work is already queued behind it), then looks.

@@ -408,24 +408,27 @@ int pie_layer_step(pie_layer_pool* lp, const void* d_q_all, const void* d_k_new,
     if (waited)
       lp->stats.stall_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_wait0).count();
     const int32_t slot = act.gpu_slot;
+    // the layer's event rides on its last kernel, unless something follows that
+    const hipEvent_t done = p->layer_compute_us > 0.f ? nullptr : lp->ev_slot[slot];
     const char* q_k = (const char*)d_q_all + k * q_stride;
     char* out_k = (char*)d_out_all + k * q_stride;
     const char* k_k = d_k_new ? (const char*)d_k_new + k * kv_stride : nullptr;
     const char* v_k = d_k_new ? (const char*)d_v_new + k * kv_stride : nullptr;
     if (direct) {
       if ((rc = pie::launch_attn_direct(p, slot, q_k, d_block_table, max_blocks, d_ctx_lens, batch, out_k, false, cs, k_k,
-                                        v_k, d_k_new ? pie::kAppendGpuStrict : -1)))
+                                        v_k, d_k_new ? pie::kAppendGpuStrict : -1, nullptr, nullptr, nullptr, nullptr,
+                                        nullptr, done)))
         return rc;
     } else {
       if (d_k_new && (rc = pie::launch_kv_append(p, slot, 1, k_k, v_k, d_block_table, max_blocks, d_ctx_lens, batch,
                                                  pie::kAppendGpuStrict, cs)))
         return rc;
       if ((rc = pie::launch_attn_decode(p, slot, q_k, max_blocks, d_ctx_lens, batch, out_k, cs, nullptr, nullptr,
-                                        k % n_slots, nullptr, nullptr, nullptr, nullptr, k_k, v_k)))
+                                        k % n_slots, nullptr, nullptr, done, nullptr, k_k, v_k)))
         return rc;
     }
     if (p->layer_compute_us > 0.f && (rc = pie::launch_busy(p->layer_compute_us, p->wall_clock_khz, cs))) return rc;
-    PIE_HIP(hipEventRecord(lp->ev_slot[slot], cs));
+    if (!done) PIE_HIP(hipEventRecord(lp->ev_slot[slot], cs));
     lp->ev_slot_rec[slot] = 1;
     // The protocol's two checks belong to the moment this layer starts computing, which is when the previous
     // one has ended: the host waits for that (this layer's work is already queued behind it), then looks.

@@ -401,10 +401,21 @@ static int compute_prologue(pie_pool* p, int32_t layer, hipStream_t s, bool* sta
   return flush_map(p, s);
 }
 
-static int compute_epilogue(pie_pool* p, int32_t layer, hipStream_t s) {
+// The event an attention call's last kernel completes, instead of two recorded behind it: a recorded event is a packet
+// of its own, about 4 us between this call's kernel and the next one's.  It marks the region's last reader; what waits
+// for all compute work waits for both regions' readers besides ev_compute.  NULL while the stream is being captured
+// into a graph (compute_epilogue then records both as nodes of the graph).
+static hipEvent_t reader_event(pie_pool* p, int32_t layer, hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (s && hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();
+  return st == hipStreamCaptureStatusNone ? p->ev_read[layer & 1] : nullptr;
+}
+
+static int compute_epilogue(pie_pool* p, int32_t layer, hipStream_t s, hipEvent_t completed = nullptr) {
   const int r = layer & 1;
-  PIE_HIP(hipEventRecord(p->ev_read[r], s));
   p->ev_read_rec[r] = true;
+  if (completed) return PIE_OK;
+  PIE_HIP(hipEventRecord(p->ev_read[r], s));
   PIE_HIP(hipEventRecord(p->ev_compute, s));
   p->ev_compute_rec = true;
   return PIE_OK;
@@ -731,6 +742,8 @@ int pie_migrate(pie_pool* p, int32_t n, const int32_t* handles, int32_t to_where
     const bool on_host = cp.path == PIE_SWAP_DMA && !p->dma_stream_order;
     note_stream(p, s);
     if ((rc = order_after(s, p->ev_compute, p->ev_compute_rec, on_host))) return rc;
+    for (int r = 0; r < 2; ++r)
+      if ((rc = order_after(s, p->ev_read[r], p->ev_read_rec[r], on_host))) return rc;
     // an earlier migration, possibly on another stream, may still be reading a slot this one is given
     if ((rc = order_after(s, p->ev_migrate, p->ev_migrate_rec, on_host))) return rc;
     for (int r = 0; r < 2; ++r) {
@@ -838,11 +851,12 @@ static int attn_decode_impl(pie_pool* p, int32_t layer, const void* d_q, const i
   bool stage_valid = false;
   int rc;
   if ((rc = compute_prologue(p, layer, s, &stage_valid))) return rc;
+  const hipEvent_t done = reader_event(p, layer, s);
   if (attn_direct(p, batch, max_blocks)) {
     if ((rc = launch_attn_direct(p, layer, d_q, d_block_table, max_blocks, d_ctx_lens, batch, d_out, stage_valid, s,
-                                 nullptr, nullptr, -1, nullptr, work)))
+                                 nullptr, nullptr, -1, nullptr, work, nullptr, nullptr, nullptr, done)))
       return rc;
-    return compute_epilogue(p, layer, s);
+    return compute_epilogue(p, layer, s, done);
   }
   const int r = layer & 1;
   if ((rc = launch_attn_plan(p, d_ctx_lens, batch, max_blocks, s, false, work))) return rc;
@@ -850,9 +864,9 @@ static int attn_decode_impl(pie_pool* p, int32_t layer, const void* d_q, const i
                                 stage_valid, s, nullptr, work)))
     return rc;
   if ((rc = launch_attn_decode(p, layer, d_q, max_blocks, d_ctx_lens, batch, d_out, s, nullptr, nullptr, ticket,
-                               nullptr, nullptr, nullptr, work)))
+                               nullptr, nullptr, done, work)))
     return rc;
-  return compute_epilogue(p, layer, s);
+  return compute_epilogue(p, layer, s, done);
 }
 
 int pie_attn_decode(pie_pool* p, int32_t layer, const void* d_q, const int32_t* d_block_table, int32_t max_blocks,

@@ -157,6 +157,65 @@ def test_one_launch_path_at_its_edges(name, dtype, hq, hkv, d, ctx):
     lib.close()
 
 
+@pytest.mark.parametrize("ctx,part", [([700, 33], 0), ([9000], 0), ([900, 1, 64], 512)])
+def test_the_allocation_free_call_replays_from_a_graph(ctx, part):
+    """pie_attn_decode_static captured into a graph, on the one-launch and on the planned path: every replay, with new
+    queries, eager calls in between and two replays back to back, gives the bits of the eager call."""
+    w = I.Workload("graph", 1, len(ctx), 8, 2, 128, I.DTYPE_BF16, value_scale=1.0, seed=37)
+    case = I.make_case(w, ctx_lens=np.asarray(ctx, np.int32))
+    lib, mod, table = GH.make_pools(case, int(case.n_blocks.sum()) + 1, 0, 0)
+    lib.set_attn_partition(part)
+    tb, cl = torch.from_numpy(table).to(GH.DEV), torch.from_numpy(case.ctx_lens).to(GH.DEV)
+    q = GH.to_dev(case.q[0], w.dtype)
+    out, eager = torch.zeros_like(q), torch.zeros_like(q)
+    s = torch.cuda.Stream()
+    lib.attn_decode_static(0, q, tb, cl, eager, s)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        lib.attn_decode_static(0, q, tb, cl, out, s)
+    gen = torch.Generator(device=GH.DEV).manual_seed(3)
+    for i in range(6):
+        q.copy_(torch.randn(q.shape, device=GH.DEV, generator=gen))
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        if i % 3 == 2:
+            graph.replay()
+        torch.cuda.synchronize()
+        (lib.attn_decode if i % 2 else lib.attn_decode_static)(0, q, tb, cl, eager, s)
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), eager.view(torch.int16)), i
+    assert lib.check_errors() == 0
+    del graph
+    lib.close()
+
+
+def test_a_migration_right_behind_attention_calls_waits_for_them():
+    """Blocks are moved to the host, and other blocks' bytes into their slots, on another stream right behind attention
+    calls of both regions' layers that read them: the calls' results are those of the cache before the move."""
+    w = I.Workload("behind", 2, 2, 8, 8, 128, I.DTYPE_F16, ctx_lo=2500, ctx_hi=3000, value_scale=1.0, seed=38)
+    case = I.make_case(w)
+    n = int(case.n_blocks.sum())
+    lib, mod, table = GH.make_pools(case, n, n, 2 * n)
+    spare = lib.block_alloc(B.HOST, n)
+    lib.host_image().fill_(0x7f)                     # what moves in behind them would turn every result into NaN
+    tb, cl = torch.from_numpy(table).to(GH.DEV), torch.from_numpy(case.ctx_lens).to(GH.DEV)
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    qs = [GH.to_dev(case.q[l], w.dtype) for l in range(2)]
+    outs = [torch.zeros_like(q) for q in qs]
+    torch.cuda.synchronize()
+    for l in range(2):
+        lib.attn_decode(l, qs[l], tb, cl, outs[l], s1)
+    handles = [int(h) for h in table.ravel() if h >= 0]
+    lib.migrate(handles, B.HOST, s2)
+    lib.migrate(spare, B.GPU, s2)
+    lib.sync()
+    for l in range(2):
+        check(GH.from_dev(outs[l], w.dtype), A.dense_attention(*H.dense_f64(case, l), case.ctx_lens), w.dtype)
+    lib.close()
+
+
 @pytest.mark.parametrize("batch", [1, 63, 64, 257, 1023, 1029])
 def test_planning_of_batches_around_its_rounds(batch):
     """The planning kernel scans the batch in rounds of one sequence per thread (256 or 1024 threads) and ranks the
