@@ -160,7 +160,7 @@ struct pie_pool {
   hipEvent_t ev_in[2] = {nullptr, nullptr};       // last swap-in into region r
   hipEvent_t ev_read[2] = {nullptr, nullptr};     // last compute work that may touch region r
   hipEvent_t ev_out[2] = {nullptr, nullptr};      // last write-back from region r
-  hipEvent_t ev_compute = nullptr;                // last compute work
+  hipEvent_t ev_compute = nullptr;                // the last step's compute work
   hipEvent_t ev_migrate = nullptr;                // last migration
   hipEvent_t ev_map = nullptr;                    // last map update sent on the compute stream
   hipEvent_t ev_append = nullptr;                 // a step's append into the GPU-homed tail blocks (write-back stream)

@@ -401,23 +401,16 @@ static int compute_prologue(pie_pool* p, int32_t layer, hipStream_t s, bool* sta
   return flush_map(p, s);
 }
 
-// The event an attention call's last kernel completes, instead of two recorded behind it: a recorded event is a packet
-// of its own, about 4 us between this call's kernel and the next one's.  It marks the region's last reader; what waits
-// for all compute work waits for both regions' readers besides ev_compute.  NULL while the stream is being captured
-// into a graph (compute_epilogue then records both as nodes of the graph).
-static hipEvent_t reader_event(pie_pool* p, int32_t layer, hipStream_t s) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (s && hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();
-  return st == hipStreamCaptureStatusNone ? p->ev_read[layer & 1] : nullptr;
-}
-
-static int compute_epilogue(pie_pool* p, int32_t layer, hipStream_t s, hipEvent_t completed = nullptr) {
+// Marks the end of a compute call's work for what may have to wait for it: the next user of the layer's staging region,
+// and migrations, which wait for both regions' marks.  A recorded event is a packet of its own, about 4 us between this
+// call's kernel and the next one's, so a pool without host blocks, where nothing can ever move, records none, and the
+// others this one.  (To complete the event with the kernel itself, as pie_step does, is free on the device, but after a
+// thousand calls in a row the runtime is busy retiring the events' signals and slows the host for milliseconds.)
+static int compute_epilogue(pie_pool* p, int32_t layer, hipStream_t s) {
+  if (p->cfg.n_host_blocks == 0) return PIE_OK;
   const int r = layer & 1;
-  p->ev_read_rec[r] = true;
-  if (completed) return PIE_OK;
   PIE_HIP(hipEventRecord(p->ev_read[r], s));
-  PIE_HIP(hipEventRecord(p->ev_compute, s));
-  p->ev_compute_rec = true;
+  p->ev_read_rec[r] = true;
   return PIE_OK;
 }
 
@@ -851,12 +844,11 @@ static int attn_decode_impl(pie_pool* p, int32_t layer, const void* d_q, const i
   bool stage_valid = false;
   int rc;
   if ((rc = compute_prologue(p, layer, s, &stage_valid))) return rc;
-  const hipEvent_t done = reader_event(p, layer, s);
   if (attn_direct(p, batch, max_blocks)) {
     if ((rc = launch_attn_direct(p, layer, d_q, d_block_table, max_blocks, d_ctx_lens, batch, d_out, stage_valid, s,
-                                 nullptr, nullptr, -1, nullptr, work, nullptr, nullptr, nullptr, done)))
+                                 nullptr, nullptr, -1, nullptr, work)))
       return rc;
-    return compute_epilogue(p, layer, s, done);
+    return compute_epilogue(p, layer, s);
   }
   const int r = layer & 1;
   if ((rc = launch_attn_plan(p, d_ctx_lens, batch, max_blocks, s, false, work))) return rc;
@@ -864,9 +856,9 @@ static int attn_decode_impl(pie_pool* p, int32_t layer, const void* d_q, const i
                                 stage_valid, s, nullptr, work)))
     return rc;
   if ((rc = launch_attn_decode(p, layer, d_q, max_blocks, d_ctx_lens, batch, d_out, s, nullptr, nullptr, ticket,
-                               nullptr, nullptr, done, work)))
+                               nullptr, nullptr, nullptr, work)))
     return rc;
-  return compute_epilogue(p, layer, s, done);
+  return compute_epilogue(p, layer, s);
 }
 
 int pie_attn_decode(pie_pool* p, int32_t layer, const void* d_q, const int32_t* d_block_table, int32_t max_blocks,
