@@ -36,6 +36,7 @@ struct DirectArgs {
   uint32_t* arrive;          // per (sequence, head unit): workgroups that have stored their part; zero between launches
   uint32_t* arrive_other;    // the other launches' words, cleared here
   int32_t* hdr;              // plan header, to note the nominal item size in, or NULL
+  int32_t* plan;             // records and slot lists of the items (kPlan*): written, or with REPLAY read; or NULL
   unsigned long long* clock;    // as in AttnArgs
   unsigned long long* clock_wg;
   size_t block_bytes;
@@ -188,7 +189,12 @@ constexpr int kDirectMaxUnits = 4096;
 static_assert(kDirectMaxUnits <= kArriveWords && kDirectMaxUnits <= kClockWgs, "a word per (sequence, head), a pair per workgroup");
 constexpr int kDirectMaxQuanta = 64;             // blocks per wave and unit: the slot list has a lane each
 
-template <typename W, int NW>
+// A step's layers share the split and, per staging region, the slots: the first layer of each region leaves what it
+// worked out for every item, and the others (REPLAY) start from that, one access deep instead of four.
+constexpr int kPlanRec = 8;                      // b, tok0, tok1, parts, first item, part, tail slot, raw context length
+constexpr int kPlanInts = kPlanRec + kDirectMaxQuanta * kWaves;   // a record, then the slots of each wave's blocks
+
+template <typename W, int NW, bool REPLAY>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(W::kWavesPerEu, 8)))
 void k_attn_direct(const DirectArgs a) {
   using E = typename W::E;
@@ -209,124 +215,123 @@ void k_attn_direct(const DirectArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int32_t G = a.group, H = a.n_kv_heads;
-  if (a.clock && tid == 0) {
-    const unsigned long long t = wall_clock64();
-    if (a.clock_wg) {
-      a.clock_wg[2 * blockIdx.x] = t;
-      if (blockIdx.x == 0) a.clock[kClockGrid] = gridDim.x;
-    } else {
-      atomicMin(&a.clock[kClockKernelStart], t);
-    }
-  }
-  // Launches take turns with two sets of arrival words.  The last arrival at a word leaves it zero; each launch also
-  // clears the set it does not use, so that whatever calls that must not overlap did to a set is gone one launch later.
-  if (const uint32_t i = blockIdx.x + (uint32_t)tid * gridDim.x; i < (uint32_t)kArriveWords)
-    a.arrive_other[i * kArriveStride] = 0u;
-
-  // ---- the split: every wave computes the same one.  Lane i has the sequences i, i + 64, ...
-  const int32_t minus = a.new_k ? 1 : 0;          // the newest token is not read from the cache
-  int32_t c4[kDirectLaneSeqs], q4[kDirectLaneSeqs], n4[kDirectLaneSeqs], k4[kDirectLaneSeqs], end4[kDirectLaneSeqs];
-  int32_t total = 0;
-#pragma unroll
-  for (int i = 0; i < kDirectLaneSeqs; ++i) {
-    c4[i] = q4[i] = 0;
-    if (64 * i < a.batch) {
-      const int32_t b = 64 * i + lane;
-      if (b < a.batch) {
-        const int32_t raw = a.ctx[b];
-        const int32_t full = clamp_ctx(raw, a.max_blocks);
-        if (raw > full && blockIdx.x == 0) atomicOr(a.err, PIE_DEVERR_BAD_HANDLE);
-        c4[i] = full > minus ? full - minus : 0;
-        q4[i] = c4[i] > 0 ? (c4[i] + QUANTUM - 1) / QUANTUM : 1;
-      }
-      total += wave_sum(q4[i]);
-    }
-  }
-  if (a.hdr && blockIdx.x == 0) {                 // the item size the planning kernel would have chosen, as asked for by
-    int32_t size = auto_part(0);                  // pie_get_attn_partition_sync
-    if (a.min_units > 0) {
-#pragma unroll 1
-      for (int t = 1; t < kAutoParts; ++t) {
-        int32_t n = 0;
-#pragma unroll
-        for (int i = 0; i < kDirectLaneSeqs; ++i)
-          if (64 * i + lane < a.batch) n += c4[i] > 0 ? (c4[i] + auto_part(t) - 1) / auto_part(t) : 1;
-        if ((long long)wave_sum(n) * H > a.min_units) size = auto_part(t);
-      }
-    }
-    if (tid == 0) a.hdr[1] = size;
-  }
-  // quanta per part: the smallest that keeps the parts of all sequences within max_items
-  auto items_of = [&](int32_t k) {
-    int32_t n = 0;
-#pragma unroll
-    for (int i = 0; i < kDirectLaneSeqs; ++i)
-      if (64 * i < a.batch) n += div_up(q4[i], k);   // (0 beyond the batch)
-    return wave_sum(n);
-  };
-  int32_t k = (total + a.max_items - 1) / a.max_items;
-  while (k < kDirectMaxQuanta && items_of(k) > a.max_items) k += 1 + k / 8;
-  if (k > kDirectMaxQuanta) k = kDirectMaxQuanta;
-  int32_t n_items = 0;
-#pragma unroll
-  for (int i = 0; i < kDirectLaneSeqs; ++i) {
-    n4[i] = k4[i] = end4[i] = 0;
-    if (64 * i < a.batch) {
-      if (q4[i] > 0) {                            // parts of a sequence as equal as whole quanta allow
-        const int32_t n = div_up(q4[i], k);
-        k4[i] = div_up(q4[i], n);
-        n4[i] = div_up(q4[i], k4[i]);
-      }
-      end4[i] = n_items + wave_scan(n4[i]);       // items up to and including the lane's sequence
-      n_items = __builtin_amdgcn_readlane(end4[i], 63);
-    }
-  }
-  // one unit a workgroup: the launch has at least as many workgroups as the split can make units
+  // (no store comes before the uniform loads below: they are then scalar loads)
+  const unsigned long long t_start = a.clock ? wall_clock64() : 0ull;
   const int32_t unit = blockIdx.x;
-  if (unit < n_items * H) {
-    const int32_t item = unit / H, g = unit - item * H;
-    int32_t b = 0;                                // sequences whose items all come before this one
+  const int32_t item = unit / H, g = unit - item * H;
+  int32_t b, ctx_raw, tok0, tok1, np, first, part, tail;   // this unit: one part of sequence b, of np from item `first`
+  if constexpr (REPLAY) {
+    const int32_t* rec = a.plan + (size_t)item * kPlanInts;
+    b = rec[0]; tok0 = rec[1]; tok1 = rec[2]; np = rec[3]; first = rec[4]; part = rec[5]; tail = rec[6]; ctx_raw = rec[7];
+  } else {
+    // ---- the split: every wave computes the same one.  Lane i has the sequences i, i + 64, ...
+    const int32_t minus = a.new_k ? 1 : 0;          // the newest token is not read from the cache
+    int32_t c4[kDirectLaneSeqs], q4[kDirectLaneSeqs], n4[kDirectLaneSeqs], k4[kDirectLaneSeqs], end4[kDirectLaneSeqs];
+    int32_t total = 0;
 #pragma unroll
-    for (int i = 0; i < kDirectLaneSeqs; ++i)
-      if (64 * i < a.batch) b += __popcll(__builtin_amdgcn_ballot_w64(64 * i + lane < a.batch && end4[i] <= item));
-    int32_t ctx_b = 0, kq = 1, np = 1, end = 1;
-#pragma unroll
-    for (int i = 0; i < kDirectLaneSeqs; ++i)
-      if (b >> 6 == i) {
-        ctx_b = __builtin_amdgcn_readlane(c4[i], b & 63);
-        kq = __builtin_amdgcn_readlane(k4[i], b & 63);
-        np = __builtin_amdgcn_readlane(n4[i], b & 63);
-        end = __builtin_amdgcn_readlane(end4[i], b & 63);
+    for (int i = 0; i < kDirectLaneSeqs; ++i) {
+      c4[i] = q4[i] = 0;
+      if (64 * i < a.batch) {
+        const int32_t b = 64 * i + lane;
+        if (b < a.batch) {
+          const int32_t raw = a.ctx[b];
+          const int32_t full = clamp_ctx(raw, a.max_blocks);
+          if (raw > full && blockIdx.x == 0) atomicOr(a.err, PIE_DEVERR_BAD_HANDLE);
+          c4[i] = full > minus ? full - minus : 0;
+          q4[i] = c4[i] > 0 ? (c4[i] + QUANTUM - 1) / QUANTUM : 1;
+        }
+        total += wave_sum(q4[i]);
       }
-    const int32_t part = item - (end - np);
-    const int32_t tok0 = part * kq * QUANTUM;
-    const int32_t tok1 = min(ctx_b, tok0 + kq * QUANTUM);   // <= tok0 only for an empty sequence
+    }
+    if (a.hdr && blockIdx.x == 0) {                 // the item size the planning kernel would have chosen, as asked for by
+      int32_t size = auto_part(0);                  // pie_get_attn_partition_sync
+      if (a.min_units > 0) {
+#pragma unroll 1
+        for (int t = 1; t < kAutoParts; ++t) {
+          int32_t n = 0;
+#pragma unroll
+          for (int i = 0; i < kDirectLaneSeqs; ++i)
+            if (64 * i + lane < a.batch) n += c4[i] > 0 ? (c4[i] + auto_part(t) - 1) / auto_part(t) : 1;
+          if ((long long)wave_sum(n) * H > a.min_units) size = auto_part(t);
+        }
+      }
+      if (tid == 0) a.hdr[1] = size;
+    }
+    // quanta per part: the smallest that keeps the parts of all sequences within max_items
+    auto items_of = [&](int32_t k) {
+      int32_t n = 0;
+#pragma unroll
+      for (int i = 0; i < kDirectLaneSeqs; ++i)
+        if (64 * i < a.batch) n += div_up(q4[i], k);   // (0 beyond the batch)
+      return wave_sum(n);
+    };
+    int32_t k = (total + a.max_items - 1) / a.max_items;
+    while (k < kDirectMaxQuanta && items_of(k) > a.max_items) k += 1 + k / 8;
+    if (k > kDirectMaxQuanta) k = kDirectMaxQuanta;
+    int32_t n_items = 0;
+#pragma unroll
+    for (int i = 0; i < kDirectLaneSeqs; ++i) {
+      n4[i] = k4[i] = end4[i] = 0;
+      if (64 * i < a.batch) {
+        if (q4[i] > 0) {                            // parts of a sequence as equal as whole quanta allow
+          const int32_t n = div_up(q4[i], k);
+          k4[i] = div_up(q4[i], n);
+          n4[i] = div_up(q4[i], k4[i]);
+        }
+        end4[i] = n_items + wave_scan(n4[i]);       // items up to and including the lane's sequence
+        n_items = __builtin_amdgcn_readlane(end4[i], 63);
+      }
+    }
+    // one unit a workgroup: the launch has at least as many workgroups as the split can make units
+    b = 0;                                          // sequences whose items all come before this one
+#pragma unroll
+      for (int i = 0; i < kDirectLaneSeqs; ++i)
+        if (64 * i < a.batch) b += __popcll(__builtin_amdgcn_ballot_w64(64 * i + lane < a.batch && end4[i] <= item));
+    int32_t ctx_b = 0, kq = 1, end = 1;
+    np = 1;
+#pragma unroll
+      for (int i = 0; i < kDirectLaneSeqs; ++i)
+        if (b >> 6 == i) {
+          ctx_b = __builtin_amdgcn_readlane(c4[i], b & 63);
+          kq = __builtin_amdgcn_readlane(k4[i], b & 63);
+          np = __builtin_amdgcn_readlane(n4[i], b & 63);
+          end = __builtin_amdgcn_readlane(end4[i], b & 63);
+        }
+    first = end - np;
+    part = item - first;
+    tok0 = part * kq * QUANTUM;
+    tok1 = min(ctx_b, tok0 + kq * QUANTUM);         // <= tok0 only for an empty sequence
+    if (item >= n_items) b = -1;
+    ctx_raw = b >= 0 ? a.ctx[b] : 0;
+    // where this sequence's newest token goes, if its last part's workgroups store it
+    tail = -1;
+    if (a.append >= 0 && b >= 0 && part == np - 1 && ctx_raw > 0) {
+      const int32_t j = (ctx_raw - 1) / kBlockTokens;
+      tail = append_slot(j < a.max_blocks ? a.table[(size_t)b * a.max_blocks + j] : -1, a.map, a.n_handles, a.n_gpu_blocks,
+                         a.n_slots, a.append, tid == 0, a.err);
+    }
+  }
+  if (b >= 0) {
     const int32_t jb0 = tok0 / kBlockTokens;
     const int32_t jb1 = tok1 > 0 ? (tok1 + kBlockTokens - 1) / kBlockTokens : 0;
     const int32_t n_it = (jb1 - jb0 - wave + NW - 1) / NW;  // blocks of this wave: jb0 + wave + NW * it; <= 64
     const size_t row0 = (size_t)b * a.n_q_heads + (size_t)g * G;
 
-    // The block this sequence's newest token goes to, if this workgroup is the one that stores it: the last part's.
-    const bool stores = a.append >= 0 && part == np - 1;
-    int32_t tail = -1, tail_pos = 0;
+    const bool stores = a.append >= 0 && tail >= 0;
     uint4 k_row;
     uint32_t v_el = 0;
     if (stores) {
-      const int32_t raw = a.ctx[b];
-      tail_pos = raw - 1;
-      if (raw > 0) {
-        const int32_t j = tail_pos / kBlockTokens;
-        const int32_t handle = j < a.max_blocks ? a.table[(size_t)b * a.max_blocks + j] : -1;
-        tail = append_slot(handle, a.map, a.n_handles, a.n_gpu_blocks, a.n_slots, a.append, tid == 0, a.err);
-        const size_t row = ((size_t)b * H + g) * HD * EB;
-        if (tid < HD * EB / 16) k_row = *reinterpret_cast<const uint4*>(a.new_k + row + (size_t)tid * 16);
-        if (tid < HD) v_el = EB == 2 ? *reinterpret_cast<const uint16_t*>(a.new_v + row + (size_t)tid * 2)
-                                     : *reinterpret_cast<const uint32_t*>(a.new_v + row + (size_t)tid * 4);
-      }
+      const size_t row = ((size_t)b * H + g) * HD * EB;
+      if (tid < HD * EB / 16) k_row = *reinterpret_cast<const uint4*>(a.new_k + row + (size_t)tid * 16);
+      if (tid < HD) v_el = EB == 2 ? *reinterpret_cast<const uint16_t*>(a.new_v + row + (size_t)tid * 2)
+                                   : *reinterpret_cast<const uint32_t*>(a.new_v + row + (size_t)tid * 4);
     }
 
     int32_t slots = -1;
-    if (lane < n_it)
+    int32_t* list = a.plan + (size_t)item * kPlanInts + kPlanRec + wave * kDirectMaxQuanta;
+    if (REPLAY)
+      slots = list[lane];                         // (the lanes beyond n_it read what nobody uses)
+    else if (lane < n_it)
       slots = resolve_slot(a.table[(size_t)b * a.max_blocks + jb0 + wave + NW * lane], a.map, a.n_handles, a.n_gpu_blocks,
                            a.n_slots, a.stage_valid != 0, a.err);
     W w;
@@ -347,6 +352,7 @@ void k_attn_direct(const DirectArgs a) {
       w.block(kr, vr, (jb0 + wave + NW * it) * kBlockTokens, present ? tok1 : 0, lane, a.scale_log2e);
     };
     if (n_it > 0) load_tile(kA, vA, 0);
+    if (!REPLAY && a.plan && g == 0) list[lane] = slots;
     for (int32_t it = 0; it < n_it; it += 2) {
       if (it + 1 < n_it) load_tile(kB, vB, it + 1);
       consume(kA, vA, it);
@@ -356,9 +362,9 @@ void k_attn_direct(const DirectArgs a) {
       }
     }
     w.to_lds(s_m, s_l, s_acc, ROW, wave, G, lane);
-    if (stores && tail >= 0) {                    // rows at or beyond tok1 are masked by index wherever they are read
+    if (stores) {                                 // rows at or beyond tok1 are masked by index wherever they are read
       char* blk = const_cast<char*>(a.kv_layer) + (size_t)tail * a.block_bytes + (size_t)g * TILE_BYTES;
-      const int32_t t = tail_pos % kBlockTokens, v = 16 / EB;
+      const int32_t t = (ctx_raw - 1) % kBlockTokens, v = 16 / EB;
       if (tid < HD * EB / 16) *reinterpret_cast<uint4*>(blk + (size_t)k_tile_index(t, tid * v, v) * EB) = k_row;
       if (tid < HD) {
         char* dst = blk + a.block_bytes / 2 + (size_t)v_tile_index(t, tid, v) * EB;
@@ -372,7 +378,7 @@ void k_attn_direct(const DirectArgs a) {
     const int32_t cols = G * TPH;
     // The newest token's part is (q . k, 1, v).  Its rows are read here, for the thread's first column, so that they
     // have arrived when the last step needs them.
-    const bool add_new = a.new_k && clamp_ctx(a.ctx[b], a.max_blocks) > 0;
+    const bool add_new = a.new_k && ctx_raw > 0;
     const size_t kv_row = ((size_t)b * H + g) * HD;
     float4 qd, kd, vd;
     auto read_new = [&](int c) {
@@ -444,18 +450,18 @@ void k_attn_direct(const DirectArgs a) {
         const int32_t step = H * G * PART;
         for (int c = tid - sub * pitch; c < cols && sub < nsub; c += NT) {
           const int h = c / TPH, t = c % TPH, d0 = 4 * t;
-          const int32_t first = (((end - np) * H + g) * G + h) * PART;
+          const int32_t part0 = ((first * H + g) * G + h) * PART;
           const int32_t s_end = np * (sub + 1) / nsub;
           float M = kNegBig, L = 0.f;
           float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
           for (int32_t s0 = np * sub / nsub; s0 < s_end; s0 += TPH) {
             const int32_t n = min(s_end - s0, TPH);
             float2 ml = make_float2(kNegBig, 0.f);
-            if (t < n) ml = get2(parts, first + (s0 + t) * step + HD * 4);
+            if (t < n) ml = get2(parts, part0 + (s0 + t) * step + HD * 4);
             for (int32_t u0 = 0; u0 < n; u0 += UNR) {
               float4 ai[UNR];
 #pragma unroll
-              for (int u = 0; u < UNR; ++u) ai[u] = get4(parts, first + d0 * 4, (s0 + min(u0 + u, n - 1)) * step);
+              for (int u = 0; u < UNR; ++u) ai[u] = get4(parts, part0 + d0 * 4, (s0 + min(u0 + u, n - 1)) * step);
               if (u0 == 0) {
                 const float m_new = fmaxf(M, head_max<TPH>(ml.x));
                 const float corr = __builtin_amdgcn_exp2f(M - m_new);
@@ -499,16 +505,37 @@ void k_attn_direct(const DirectArgs a) {
       }
     }
   }
+  if (!REPLAY && a.plan && g == 0 && tid < kPlanRec) {
+    const int32_t rec[kPlanRec] = {b, tok0, tok1, np, first, part, tail, ctx_raw};
+    int32_t x = rec[0];
+#pragma unroll
+    for (int i = 1; i < kPlanRec; ++i) x = tid == i ? rec[i] : x;
+    a.plan[(size_t)item * kPlanInts + tid] = x;
+  }
+  // Launches take turns with two sets of arrival words.  The last arrival at a word leaves it zero; each launch also
+  // clears the set it does not use, so that whatever calls that must not overlap did to a set is gone one launch later.
+  if (const uint32_t i = blockIdx.x + (uint32_t)tid * gridDim.x; i < (uint32_t)kArriveWords)
+    a.arrive_other[i * kArriveStride] = 0u;
   if (a.clock && tid == 0) {
     const unsigned long long t = wall_clock64();
-    if (a.clock_wg) a.clock_wg[2 * blockIdx.x + 1] = t;
-    else { atomicMax(&a.clock[kClockKernelEnd], t); atomicMax(&a.clock[kClockLayerEnd], t); }
+    if (a.clock_wg) {
+      a.clock_wg[2 * blockIdx.x] = t_start;
+      a.clock_wg[2 * blockIdx.x + 1] = t;
+      if (blockIdx.x == 0) a.clock[kClockGrid] = gridDim.x;
+    } else {
+      atomicMin(&a.clock[kClockKernelStart], t_start);
+      atomicMax(&a.clock[kClockKernelEnd], t);
+      atomicMax(&a.clock[kClockLayerEnd], t);
+    }
   }
 }
 
 // ---- dispatch --------------------------------------------------------------------------------------------
 
-size_t attn_direct_floats(const pie_config& c) { return (size_t)kDirectRows * (c.head_dim + 4); }
+// Its scratch: the parts, then the items' records and slot lists of the two staging regions.
+static size_t parts_floats(const pie_config& c) { return (size_t)kDirectRows * (c.head_dim + 4); }
+static size_t plan_region_ints(const pie_config& c) { return ((size_t)kDirectMaxUnits / c.n_kv_heads + 1) * kPlanInts; }
+size_t attn_direct_floats(const pie_config& c) { return parts_floats(c) + 2 * plan_region_ints(c); }
 
 // How many units the split of a call may make; 0: the call is left to the planned path, which has what this one lacks -
 // an item size set by the caller, the vector-ALU variant, fp32 with grouped queries (every query head reads the keys
@@ -551,20 +578,27 @@ bool attn_direct_step(const pie_pool* p, int32_t batch, int32_t max_blocks) {
   return attn_direct(p, batch, max_blocks);
 }
 
-template <typename W, int NW>
-static int launch_direct(const DirectArgs& a, int32_t grid, hipStream_t s, hipEvent_t done) {
+template <typename W, int NW, bool REPLAY>
+static int launch_direct_as(const DirectArgs& a, int32_t grid, hipStream_t s, hipEvent_t done) {
   const size_t lds = ((size_t)NW * 2 * kMaxGroup + (size_t)NW * a.group * (W::HD + 4)) * sizeof(float);
-  if (done) hipExtLaunchKernelGGL((k_attn_direct<W, NW>), dim3(grid), dim3(NW * 64), (uint32_t)lds, s, nullptr, done, 0, a);
-  else hipLaunchKernelGGL((k_attn_direct<W, NW>), dim3(grid), dim3(NW * 64), (uint32_t)lds, s, a);
+  if (done) hipExtLaunchKernelGGL((k_attn_direct<W, NW, REPLAY>), dim3(grid), dim3(NW * 64), (uint32_t)lds, s, nullptr, done, 0, a);
+  else hipLaunchKernelGGL((k_attn_direct<W, NW, REPLAY>), dim3(grid), dim3(NW * 64), (uint32_t)lds, s, a);
   PIE_HIP(hipGetLastError());
   return PIE_OK;
+}
+
+template <typename W, int NW>
+static int launch_direct(const DirectArgs& a, int32_t grid, hipStream_t s, hipEvent_t done, bool replay) {
+  return replay ? launch_direct_as<W, NW, true>(a, grid, s, done) : launch_direct_as<W, NW, false>(a, grid, s, done);
 }
 
 int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const int32_t* d_table, int32_t max_blocks,
                        const int32_t* d_ctx, int32_t batch, void* d_out, bool stage_valid, hipStream_t s,
                        const void* d_k_new, const void* d_v_new, int32_t append, const LayerView* view,
                        const AttnWork* work, hipEvent_t k_start, hipEvent_t k_end, unsigned long long* clock_row,
-                       hipEvent_t done) {
+                       hipEvent_t done, int32_t plan) {
+  const bool replay = plan == kDirectPlanReplay;
+  if (plan != kDirectPlanNone && (work || view)) return PIE_EINVAL;   // the plan lies in the pool's scratch, by layer & 1
   const pie_config& c = p->cfg;
   if (((uintptr_t)d_q | (uintptr_t)d_out) % 16) return PIE_EINVAL;
   if (c.n_gpu_blocks + 2 * c.n_stage_blocks <= 0) return PIE_EINVAL;
@@ -589,7 +623,9 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   a.arrive_other = words + (1u - turn) * kArriveSet;
   a.hdr = work ? nullptr : p->d_plan;
   a.block_bytes = p->block_bytes;
-  a.ws_bytes = (int32_t)(attn_direct_floats(c) * sizeof(float));
+  a.ws_bytes = (int32_t)(parts_floats(c) * sizeof(float));
+  a.plan = plan == kDirectPlanNone ? nullptr
+                                   : reinterpret_cast<int32_t*>(p->d_ws + parts_floats(c)) + (layer & 1) * plan_region_ints(c);
   a.scale_log2e = p->scale_log2e;
   a.batch = batch;
   a.max_blocks = max_blocks;
@@ -619,15 +655,16 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   const bool hd128 = c.head_dim == 128;
   switch (c.dtype) {
     case PIE_DTYPE_F32:
-      rc = hd128 ? launch_direct<Wave32<128>, kWaves>(a, grid, s, done) : launch_direct<Wave32<64>, kWaves>(a, grid, s, done);
+      rc = hd128 ? launch_direct<Wave32<128>, kWaves>(a, grid, s, done, replay)
+                 : launch_direct<Wave32<64>, kWaves>(a, grid, s, done, replay);
       break;
     case PIE_DTYPE_F16:
-      rc = hd128 ? launch_direct<Wave16<F16, 128, false>, kWaves>(a, grid, s, done)
-                 : launch_direct<Wave16<F16, 64, false>, kWaves>(a, grid, s, done);
+      rc = hd128 ? launch_direct<Wave16<F16, 128, false>, kWaves>(a, grid, s, done, replay)
+                 : launch_direct<Wave16<F16, 64, false>, kWaves>(a, grid, s, done, replay);
       break;
     case PIE_DTYPE_BF16:
-      rc = hd128 ? launch_direct<Wave16<BF16, 128, true>, kWaves>(a, grid, s, done)
-                 : launch_direct<Wave16<BF16, 64, true>, kWaves>(a, grid, s, done);
+      rc = hd128 ? launch_direct<Wave16<BF16, 128, true>, kWaves>(a, grid, s, done, replay)
+                 : launch_direct<Wave16<BF16, 64, true>, kWaves>(a, grid, s, done, replay);
       break;
   }
   if (rc) return rc;

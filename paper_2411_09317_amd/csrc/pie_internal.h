@@ -260,6 +260,9 @@ int launch_attn_decode(const pie_pool* p, int32_t layer, const void* d_q, int32_
 inline int32_t attn_min_units(const pie_pool* p) { return p->n_cu * 17; }   // see k_attn_plan
 // The one-launch attention path (pie_attn_direct.hip): whether it takes a call on its own or a step's layers, and the
 // launch, which needs no planning before it.  append: kAppend* mode in which the new rows are stored as well, or -1.
+// plan: whether the launch leaves its split and slots for the layers of the same region that follow with the same batch,
+// table, context lengths and maps (kDirectPlanWrite), or starts from what one left (kDirectPlanReplay).
+constexpr int32_t kDirectPlanNone = 0, kDirectPlanWrite = 1, kDirectPlanReplay = 2;
 bool attn_direct_step(const pie_pool* p, int32_t batch, int32_t max_blocks);
 bool attn_direct(const pie_pool* p, int32_t batch, int32_t max_blocks);
 size_t attn_direct_floats(const pie_config& c);
@@ -267,7 +270,8 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
                        const int32_t* d_ctx, int32_t batch, void* d_out, bool stage_valid, hipStream_t s,
                        const void* d_k_new = nullptr, const void* d_v_new = nullptr, int32_t append = -1,
                        const LayerView* view = nullptr, const AttnWork* work = nullptr, hipEvent_t k_start = nullptr,
-                       hipEvent_t k_end = nullptr, unsigned long long* clock_row = nullptr, hipEvent_t done = nullptr);
+                       hipEvent_t k_end = nullptr, unsigned long long* clock_row = nullptr, hipEvent_t done = nullptr,
+                       int32_t plan = 0);
 int launch_stream_probe(const pie_pool* p, int32_t layer, int32_t max_blocks, int32_t batch, hipStream_t s);
 int attn_static_scratch(char** out, std::atomic<uint32_t>** out_turn = nullptr);
 int attn_static_work(const pie_pool* p, int32_t batch, int32_t max_blocks, AttnWork* out);

@@ -1087,7 +1087,8 @@ static int step_body(pie_pool* p, const StepJob& j) {
     hipEvent_t done = standin ? nullptr : read_done;
     if (direct)
       rc = launch_attn_direct(p, l, q_l, d_block_table, max_blocks, d_ctx_lens, batch, out_l, true, cs, k_l, v_l,
-                              with_new ? append_mode : -1, nullptr, nullptr, k_start, k_end, clock_row(l), done);
+                              with_new ? append_mode : -1, nullptr, nullptr, k_start, k_end, clock_row(l), done,
+                              L <= 2 ? kDirectPlanNone : l < 2 ? kDirectPlanWrite : kDirectPlanReplay);
     else
       rc = launch_attn_decode(p, l, q_l, max_blocks, d_ctx_lens, batch, out_l, cs, k_start, k_end, -1, clock_row(l),
                               nullptr, done, nullptr, k_l, v_l);

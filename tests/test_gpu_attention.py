@@ -216,6 +216,52 @@ def test_a_migration_right_behind_attention_calls_waits_for_them():
     lib.close()
 
 
+@pytest.mark.parametrize("layers,hq,hkv,d,dtype,ctx,host", [
+    (3, 8, 2, 128, I.DTYPE_BF16, [700, 1, 16, 17, 0, 1000], 0.0),
+    (5, 4, 4, 64, I.DTYPE_F16, [65, 33, 129, 2], 0.25),
+    (4, 2, 2, 64, I.DTYPE_F32, [300, 64, 1], 0.3),
+])
+def test_the_layers_of_a_step_that_start_from_an_earlier_layers_split(layers, hq, hkv, d, dtype, ctx, host):
+    """From the third layer on a small step's launches take their split, slots and tail slots from the first layer of
+    their staging region: every layer's result against the oracle, twice in a row with other lengths in between, and
+    the stored rows against what a step of the planned path stores."""
+    w = I.Workload("replay", layers, len(ctx), hq, hkv, d, dtype, value_scale=1.0, seed=39)
+    ctx = np.asarray(ctx, np.int32)
+    case = I.make_case(w, ctx_lens=ctx, host_fraction=host)
+    n = int(case.n_blocks.sum()) + 2
+    images = []
+    for part in (0, 512):
+        lib, mod, table = GH.make_pools(case, n, n, n, upto_ctx=np.maximum(ctx - 1, 0), max_blocks=int(case.n_blocks.max()) + 3)
+        lib.set_attn_partition(part)
+        rows = [np.stack([np.stack([dense[b][l, max(ctx[b] - 1, 0)] if ctx[b] else np.zeros((hkv, d), dense[b].dtype)
+                                    for b in range(len(ctx))]) for l in range(layers)])
+                for dense in ([k if k.shape[1] else np.zeros((layers, 1, hkv, d), k.dtype) for k in case.k_dense],
+                              [v if v.shape[1] else np.zeros((layers, 1, hkv, d), v.dtype) for v in case.v_dense])]
+        q, k, v = (GH.to_dev(x, dtype) for x in (case.q, rows[0], rows[1]))
+        tb = torch.from_numpy(table).to(GH.DEV)
+        s = [torch.cuda.Stream() for _ in range(3)]
+        for lens in (ctx, np.minimum(ctx, 16), ctx):
+            out = torch.full_like(q, float("nan"))
+            pf, dirty = lib.prefetch_list(table, lens)
+            full = lens is ctx
+            lib.step(q, k if full else None, v if full else None, tb, torch.from_numpy(lens.copy()).to(GH.DEV), pf,
+                     dirty if full else [], out, *s)
+            lib.sync()
+            assert lib.check_errors() == 0
+            if not full:
+                continue
+            got = GH.from_dev(out, dtype)
+            live = np.nonzero(ctx)[0]
+            for l in range(layers):
+                qd, K, V = H.dense_f64(case, l)
+                check(got[l][live], A.dense_attention(qd[live], [K[b] for b in live], [V[b] for b in live], ctx[live]), dtype)
+                assert (np.delete(got[l], live, axis=0) == 0).all()
+        g, h = GH.images_of(lib)
+        images.append((g[:, :n].copy(), h.copy()))
+        lib.close()
+    assert np.array_equal(images[0][0], images[1][0]) and np.array_equal(images[0][1], images[1][1])
+
+
 @pytest.mark.parametrize("batch", [1, 63, 64, 257, 1023, 1029])
 def test_planning_of_batches_around_its_rounds(batch):
     """The planning kernel scans the batch in rounds of one sequence per thread (256 or 1024 threads) and ranks the
