@@ -218,10 +218,11 @@ void k_attn_direct(const DirectArgs a) {
   // (no store comes before the uniform loads below: they are then scalar loads)
   const unsigned long long t_start = a.clock ? wall_clock64() : 0ull;
   const int32_t unit = blockIdx.x;
-  const int32_t item = unit / H, g = unit - item * H;
+  const int32_t place = unit / H, g = unit - place * H;
+  int32_t at = place;                             // where in the plan this item's record stands
   int32_t b, ctx_raw, tok0, tok1, np, first, part, tail;   // this unit: one part of sequence b, of np from item `first`
   if constexpr (REPLAY) {
-    const int32_t* rec = a.plan + (size_t)item * kPlanInts;
+    const int32_t* rec = a.plan + (size_t)place * kPlanInts;
     b = rec[0]; tok0 = rec[1]; tok1 = rec[2]; np = rec[3]; first = rec[4]; part = rec[5]; tail = rec[6]; ctx_raw = rec[7];
   } else {
     // ---- the split: every wave computes the same one.  Lane i has the sequences i, i + 64, ...
@@ -282,6 +283,7 @@ void k_attn_direct(const DirectArgs a) {
         n_items = __builtin_amdgcn_readlane(end4[i], 63);
       }
     }
+    const int32_t item = place;
     // one unit a workgroup: the launch has at least as many workgroups as the split can make units
     b = 0;                                          // sequences whose items all come before this one
 #pragma unroll
@@ -302,6 +304,15 @@ void k_attn_direct(const DirectArgs a) {
     tok0 = part * kq * QUANTUM;
     tok1 = min(ctx_b, tok0 + kq * QUANTUM);         // <= tok0 only for an empty sequence
     if (item >= n_items) b = -1;
+    // The plan lists the items by size, largest first, so that the layers that start from it spread the large parts over
+    // the compute units and end on small ones: 639 -> 617 us for 16 layers of 24 sequences of 100 to 1 100 tokens.
+    if (a.plan && b >= 0) {
+      int32_t before = 0;
+#pragma unroll
+      for (int i = 0; i < kDirectLaneSeqs; ++i)
+        if (64 * i < a.batch) before += k4[i] > kq || (k4[i] == kq && 64 * i + lane < b) ? n4[i] : 0;
+      at = wave_sum(before) + part;
+    }
     ctx_raw = b >= 0 ? a.ctx[b] : 0;
     // where this sequence's newest token goes, if its last part's workgroups store it
     tail = -1;
@@ -328,7 +339,7 @@ void k_attn_direct(const DirectArgs a) {
     }
 
     int32_t slots = -1;
-    int32_t* list = a.plan + (size_t)item * kPlanInts + kPlanRec + wave * kDirectMaxQuanta;
+    int32_t* list = a.plan + (size_t)at * kPlanInts + kPlanRec + wave * kDirectMaxQuanta;
     if (REPLAY)
       slots = list[lane];                         // (the lanes beyond n_it read what nobody uses)
     else if (lane < n_it)
@@ -426,7 +437,7 @@ void k_attn_direct(const DirectArgs a) {
       if (np == 1) {
         finish(c, M, L, A);
       } else {
-        const int32_t off = (unit * G + h) * PART;
+        const int32_t off = (((first + part) * H + g) * G + h) * PART;
         put4(parts, off + d0 * 4, A);
         if (d0 == 0) put2(parts, off + HD * 4, M, L);
       }
@@ -510,7 +521,7 @@ void k_attn_direct(const DirectArgs a) {
     int32_t x = rec[0];
 #pragma unroll
     for (int i = 1; i < kPlanRec; ++i) x = tid == i ? rec[i] : x;
-    a.plan[(size_t)item * kPlanInts + tid] = x;
+    a.plan[(size_t)at * kPlanInts + tid] = x;
   }
   // Launches take turns with two sets of arrival words.  The last arrival at a word leaves it zero; each launch also
   // clears the set it does not use, so that whatever calls that must not overlap did to a set is gone one launch later.
