@@ -190,11 +190,13 @@ static_assert(kDirectMaxUnits <= kArriveWords && kDirectMaxUnits <= kClockWgs, "
 constexpr int kDirectMaxQuanta = 64;             // blocks per wave and unit: the slot list has a lane each
 
 // A step's layers share the split and, per staging region, the slots: the first layer of each region leaves what it
-// worked out for every item, and the others (REPLAY) start from that, one access deep instead of four.
+// worked out for every item, and the others start from that, one access deep instead of four.  Where every layer has a
+// map of its own (the growing caches) they share the split alone.  PLAN: kDirectPlanReplay, kDirectPlanReplaySplit, or
+// kDirectPlanNone, which also covers the launches that write the plan.
 constexpr int kPlanRec = 8;                      // b, tok0, tok1, parts, first item, part, tail slot, raw context length
 constexpr int kPlanInts = kPlanRec + kDirectMaxQuanta * kWaves;   // a record, then the slots of each wave's blocks
 
-template <typename W, int NW, bool REPLAY>
+template <typename W, int NW, int PLAN>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(W::kWavesPerEu, 8)))
 void k_attn_direct(const DirectArgs a) {
   using E = typename W::E;
@@ -204,6 +206,8 @@ void k_attn_direct(const DirectArgs a) {
   constexpr int ROW = HD + 4;                     // padded LDS row of one head's accumulator
   constexpr int TPH = HD / 4;                     // threads per head when states are merged, four dims each
   constexpr int PART = (HD + 4) * 4;              // bytes of a head's partial state: accumulator, max, sum, padding
+
+  constexpr bool REPLAY = PLAN != kDirectPlanNone, SLOTS = PLAN == kDirectPlanReplay;
 
   extern __shared__ __align__(16) float s_dyn[];
   __shared__ uint32_t s_arrived;
@@ -314,8 +318,9 @@ void k_attn_direct(const DirectArgs a) {
       at = wave_sum(before) + part;
     }
     ctx_raw = b >= 0 ? a.ctx[b] : 0;
-    // where this sequence's newest token goes, if its last part's workgroups store it
-    tail = -1;
+  }
+  if constexpr (!SLOTS) {                         // where this sequence's newest token goes, if its last part's
+    tail = -1;                                    // workgroups store it
     if (a.append >= 0 && b >= 0 && part == np - 1 && ctx_raw > 0) {
       const int32_t j = (ctx_raw - 1) / kBlockTokens;
       tail = append_slot(j < a.max_blocks ? a.table[(size_t)b * a.max_blocks + j] : -1, a.map, a.n_handles, a.n_gpu_blocks,
@@ -340,7 +345,7 @@ void k_attn_direct(const DirectArgs a) {
 
     int32_t slots = -1;
     int32_t* list = a.plan + (size_t)at * kPlanInts + kPlanRec + wave * kDirectMaxQuanta;
-    if (REPLAY)
+    if (SLOTS)
       slots = list[lane];                         // (the lanes beyond n_it read what nobody uses)
     else if (lane < n_it)
       slots = resolve_slot(a.table[(size_t)b * a.max_blocks + jb0 + wave + NW * lane], a.map, a.n_handles, a.n_gpu_blocks,
@@ -589,18 +594,22 @@ bool attn_direct_step(const pie_pool* p, int32_t batch, int32_t max_blocks) {
   return attn_direct(p, batch, max_blocks);
 }
 
-template <typename W, int NW, bool REPLAY>
+template <typename W, int NW, int PLAN>
 static int launch_direct_as(const DirectArgs& a, int32_t grid, hipStream_t s, hipEvent_t done) {
   const size_t lds = ((size_t)NW * 2 * kMaxGroup + (size_t)NW * a.group * (W::HD + 4)) * sizeof(float);
-  if (done) hipExtLaunchKernelGGL((k_attn_direct<W, NW, REPLAY>), dim3(grid), dim3(NW * 64), (uint32_t)lds, s, nullptr, done, 0, a);
-  else hipLaunchKernelGGL((k_attn_direct<W, NW, REPLAY>), dim3(grid), dim3(NW * 64), (uint32_t)lds, s, a);
+  if (done) hipExtLaunchKernelGGL((k_attn_direct<W, NW, PLAN>), dim3(grid), dim3(NW * 64), (uint32_t)lds, s, nullptr, done, 0, a);
+  else hipLaunchKernelGGL((k_attn_direct<W, NW, PLAN>), dim3(grid), dim3(NW * 64), (uint32_t)lds, s, a);
   PIE_HIP(hipGetLastError());
   return PIE_OK;
 }
 
 template <typename W, int NW>
-static int launch_direct(const DirectArgs& a, int32_t grid, hipStream_t s, hipEvent_t done, bool replay) {
-  return replay ? launch_direct_as<W, NW, true>(a, grid, s, done) : launch_direct_as<W, NW, false>(a, grid, s, done);
+static int launch_direct(const DirectArgs& a, int32_t grid, hipStream_t s, hipEvent_t done, int32_t plan) {
+  switch (plan) {
+    case kDirectPlanReplay: return launch_direct_as<W, NW, kDirectPlanReplay>(a, grid, s, done);
+    case kDirectPlanReplaySplit: return launch_direct_as<W, NW, kDirectPlanReplaySplit>(a, grid, s, done);
+    default: return launch_direct_as<W, NW, kDirectPlanNone>(a, grid, s, done);
+  }
 }
 
 int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const int32_t* d_table, int32_t max_blocks,
@@ -608,8 +617,7 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
                        const void* d_k_new, const void* d_v_new, int32_t append, const LayerView* view,
                        const AttnWork* work, hipEvent_t k_start, hipEvent_t k_end, unsigned long long* clock_row,
                        hipEvent_t done, int32_t plan) {
-  const bool replay = plan == kDirectPlanReplay;
-  if (plan != kDirectPlanNone && (work || view)) return PIE_EINVAL;   // the plan lies in the pool's scratch, by layer & 1
+  if (plan != kDirectPlanNone && work) return PIE_EINVAL;   // the plan lies in the pool's scratch, by layer & 1
   const pie_config& c = p->cfg;
   if (((uintptr_t)d_q | (uintptr_t)d_out) % 16) return PIE_EINVAL;
   if (c.n_gpu_blocks + 2 * c.n_stage_blocks <= 0) return PIE_EINVAL;
@@ -636,7 +644,7 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   a.block_bytes = p->block_bytes;
   a.ws_bytes = (int32_t)(parts_floats(c) * sizeof(float));
   a.plan = plan == kDirectPlanNone ? nullptr
-                                   : reinterpret_cast<int32_t*>(p->d_ws + parts_floats(c)) + (layer & 1) * plan_region_ints(c);
+                                   : reinterpret_cast<int32_t*>(p->d_ws + parts_floats(c)) + (view ? 0 : layer & 1) * plan_region_ints(c);
   a.scale_log2e = p->scale_log2e;
   a.batch = batch;
   a.max_blocks = max_blocks;
@@ -666,16 +674,16 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   const bool hd128 = c.head_dim == 128;
   switch (c.dtype) {
     case PIE_DTYPE_F32:
-      rc = hd128 ? launch_direct<Wave32<128>, kWaves>(a, grid, s, done, replay)
-                 : launch_direct<Wave32<64>, kWaves>(a, grid, s, done, replay);
+      rc = hd128 ? launch_direct<Wave32<128>, kWaves>(a, grid, s, done, plan)
+                 : launch_direct<Wave32<64>, kWaves>(a, grid, s, done, plan);
       break;
     case PIE_DTYPE_F16:
-      rc = hd128 ? launch_direct<Wave16<F16, 128, false>, kWaves>(a, grid, s, done, replay)
-                 : launch_direct<Wave16<F16, 64, false>, kWaves>(a, grid, s, done, replay);
+      rc = hd128 ? launch_direct<Wave16<F16, 128, false>, kWaves>(a, grid, s, done, plan)
+                 : launch_direct<Wave16<F16, 64, false>, kWaves>(a, grid, s, done, plan);
       break;
     case PIE_DTYPE_BF16:
-      rc = hd128 ? launch_direct<Wave16<BF16, 128, true>, kWaves>(a, grid, s, done, replay)
-                 : launch_direct<Wave16<BF16, 64, true>, kWaves>(a, grid, s, done, replay);
+      rc = hd128 ? launch_direct<Wave16<BF16, 128, true>, kWaves>(a, grid, s, done, plan)
+                 : launch_direct<Wave16<BF16, 64, true>, kWaves>(a, grid, s, done, plan);
       break;
   }
   if (rc) return rc;

@@ -552,7 +552,7 @@ int pie_elastic_step(pie_elastic_pool* lp, const void* d_q_all, const void* d_k_
     if (direct) {
       if ((rc = pie::launch_attn_direct(p, k, q_k, d_block_table, max_blocks, d_ctx_lens, batch, out_k, false, cs, k_k, v_k,
                                         d_k_new ? pie::kAppendGpuStrict : -1, &view, nullptr, nullptr, nullptr, nullptr,
-                                        done)))
+                                        done, k == 0 ? pie::kDirectPlanWrite : pie::kDirectPlanReplaySplit)))
         return rc;
     } else {
       if (d_k_new && (rc = pie::launch_kv_append(p, k, 1, k_k, v_k, d_block_table, max_blocks, d_ctx_lens, batch,

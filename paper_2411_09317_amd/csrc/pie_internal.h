@@ -261,8 +261,9 @@ inline int32_t attn_min_units(const pie_pool* p) { return p->n_cu * 17; }   // s
 // The one-launch attention path (pie_attn_direct.hip): whether it takes a call on its own or a step's layers, and the
 // launch, which needs no planning before it.  append: kAppend* mode in which the new rows are stored as well, or -1.
 // plan: whether the launch leaves its split and slots for the layers of the same region that follow with the same batch,
-// table, context lengths and maps (kDirectPlanWrite), or starts from what one left (kDirectPlanReplay).
-constexpr int32_t kDirectPlanNone = 0, kDirectPlanWrite = 1, kDirectPlanReplay = 2;
+// table, context lengths and maps (kDirectPlanWrite), or starts from what one left: all of it (kDirectPlanReplay), or
+// the split alone (kDirectPlanReplaySplit: the layer has a map of its own).
+constexpr int32_t kDirectPlanNone = 0, kDirectPlanWrite = 1, kDirectPlanReplay = 2, kDirectPlanReplaySplit = 3;
 bool attn_direct_step(const pie_pool* p, int32_t batch, int32_t max_blocks);
 bool attn_direct(const pie_pool* p, int32_t batch, int32_t max_blocks);
 size_t attn_direct_floats(const pie_config& c);
