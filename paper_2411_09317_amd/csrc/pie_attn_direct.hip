@@ -583,15 +583,21 @@ static int32_t direct_max_units(const pie_pool* p, int32_t batch, int32_t max_bl
 
 bool attn_direct(const pie_pool* p, int32_t batch, int32_t max_blocks) { return direct_max_units(p, batch, max_blocks) > 0; }
 
-// Within a step the planned path plans once for all layers and stores the new rows in one launch beside the first, so
-// it catches up sooner: from about 2 M tokens x kv heads in the table (1 045 us against 1 045 for 8 layers of 120
-// sequences of 500 to 2 500 tokens at 8 kv heads, 1 086 against 1 111 for 190 of 300 to 1 700) unless there are too few
-// (sequence, kv head) pairs to fill the compute units (16 layers, 24 sequences of 100 to 1 100 tokens, 32 kv heads:
-// 667 us here, 716 planned; of 32 layers with 64 of 1 024 to 2 048: 8 410 here, 8 103 planned).
-bool attn_direct_step(const pie_pool* p, int32_t batch, int32_t max_blocks) {
+// A step's layers.  Up to three (sequence, kv head) pairs per compute unit, or with short contexts, each layer's launch
+// stores its new rows as well: 16 layers of 24 sequences of 100 to 1 100 tokens, 32 kv heads: 606 us against 721
+// planned; 8 layers of 120 of 60 to 300, 8 kv heads: 213 against 260.  In bigger steps that would put partial-line writes
+// among every layer's reads (32 layers of 64 sequences of 1 024 to 2 048, 32 kv heads: 8 329 us against 8 056 planned),
+// so the rows of all layers are stored by one launch beside the first, as on the planned path.  There the one-launch path
+// saves the reduction, 3 to 10 us a layer, and loses about 40 us a step, because that launch finds less room beside its
+// workgroups than beside the persistent grid's: with grouped queries it gains from about 8 layers on (16 layers of 256
+// sequences of 128 to 4 096, 32 heads over 8: 3 465 us against 3 615; with host blocks 8 layers 1 782 / 1 794, 4 layers
+// 987 / 983), without from about 32 (32 layers as above: 7 994 / 8 107; with host blocks 8 164 / 8 176, 12 layers
+// 3 147 / 3 123).
+int attn_step_path(const pie_pool* p, int32_t n_layers, int32_t batch, int32_t max_blocks) {
+  if (!attn_direct(p, batch, max_blocks)) return kStepPlanned;
   const int64_t pairs = (int64_t)batch * p->cfg.n_kv_heads;
-  if (pairs > 3 * (int64_t)p->n_cu && pairs * max_blocks * kBlockTokens > (int64_t)8192 * p->n_cu) return false;
-  return attn_direct(p, batch, max_blocks);
+  if (pairs <= 3 * (int64_t)p->n_cu || pairs * max_blocks * kBlockTokens <= (int64_t)8192 * p->n_cu) return kStepDirect;
+  return n_layers >= (p->cfg.n_q_heads > p->cfg.n_kv_heads ? 8 : 32) ? kStepDirectAppendApart : kStepPlanned;
 }
 
 template <typename W, int NW, int PLAN>

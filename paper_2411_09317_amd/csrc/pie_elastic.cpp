@@ -516,8 +516,9 @@ int pie_elastic_step(pie_elastic_pool* lp, const void* d_q_all, const void* d_k_
   pie::note_stream(p, os);
   int rc;
   // with a new token the attention takes it from the new rows, the rest of the context from the cache
-  // (a small batch's layers are one launch each, appends included: pie_attn_direct.hip)
-  const bool direct = pie::attn_direct_step(p, batch, max_blocks);
+  // (the layers may be one launch each, in small steps appends included: pie_attn_direct.hip)
+  const int path = pie::attn_step_path(p, lp->n, batch, max_blocks);
+  const bool direct = path != pie::kStepPlanned, append_apart = d_k_new && path != pie::kStepDirect;
   if (!direct && (rc = pie::launch_attn_plan(p, d_ctx_lens, batch, max_blocks, cs, false, nullptr, d_k_new != nullptr)))
     return rc;
   for (int32_t k = 0; k < lp->n; ++k) {
@@ -549,15 +550,15 @@ int pie_elastic_step(pie_elastic_pool* lp, const void* d_q_all, const void* d_k_
     char* out_k = (char*)d_out_all + k * q_stride;
     const char* k_k = d_k_new ? (const char*)d_k_new + k * kv_stride : nullptr;
     const char* v_k = d_k_new ? (const char*)d_v_new + k * kv_stride : nullptr;
+    if (append_apart && (rc = pie::launch_kv_append(p, k, 1, k_k, v_k, d_block_table, max_blocks, d_ctx_lens, batch,
+                                                    pie::kAppendGpuStrict, cs, &view)))
+      return rc;
     if (direct) {
       if ((rc = pie::launch_attn_direct(p, k, q_k, d_block_table, max_blocks, d_ctx_lens, batch, out_k, false, cs, k_k, v_k,
-                                        d_k_new ? pie::kAppendGpuStrict : -1, &view, nullptr, nullptr, nullptr, nullptr,
+                                        d_k_new && !append_apart ? pie::kAppendGpuStrict : -1, &view, nullptr, nullptr, nullptr, nullptr,
                                         done, k == 0 ? pie::kDirectPlanWrite : pie::kDirectPlanReplaySplit)))
         return rc;
     } else {
-      if (d_k_new && (rc = pie::launch_kv_append(p, k, 1, k_k, v_k, d_block_table, max_blocks, d_ctx_lens, batch,
-                                                 pie::kAppendGpuStrict, cs, &view)))
-        return rc;
       if ((rc = pie::launch_attn_resolve(p, d_block_table, d_ctx_lens, batch, max_blocks, true, false, false, false, cs,
                                          &view)))
         return rc;

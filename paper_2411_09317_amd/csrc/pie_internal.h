@@ -258,13 +258,16 @@ int launch_attn_decode(const pie_pool* p, int32_t layer, const void* d_q, int32_
                        hipEvent_t done = nullptr, const AttnWork* work = nullptr, const void* d_k_new = nullptr,
                        const void* d_v_new = nullptr);
 inline int32_t attn_min_units(const pie_pool* p) { return p->n_cu * 17; }   // see k_attn_plan
-// The one-launch attention path (pie_attn_direct.hip): whether it takes a call on its own or a step's layers, and the
-// launch, which needs no planning before it.  append: kAppend* mode in which the new rows are stored as well, or -1.
+// The one-launch attention path (pie_attn_direct.hip): whether it takes a call, and the launch,
+// which needs no planning before it.  append: kAppend* mode in which the new rows are stored as well, or -1.
 // plan: whether the launch leaves its split and slots for the layers of the same region that follow with the same batch,
 // table, context lengths and maps (kDirectPlanWrite), or starts from what one left: all of it (kDirectPlanReplay), or
 // the split alone (kDirectPlanReplaySplit: the layer has a map of its own).
 constexpr int32_t kDirectPlanNone = 0, kDirectPlanWrite = 1, kDirectPlanReplay = 2, kDirectPlanReplaySplit = 3;
-bool attn_direct_step(const pie_pool* p, int32_t batch, int32_t max_blocks);
+// How the layers of a step of n_layers run: planned, or in a launch each, which stores the new rows or leaves that to
+// k_kv_append.  The same for every kind of step, so that their results are the same bits.
+constexpr int kStepPlanned = 0, kStepDirect = 1, kStepDirectAppendApart = 2;
+int attn_step_path(const pie_pool* p, int32_t n_layers, int32_t batch, int32_t max_blocks);
 bool attn_direct(const pie_pool* p, int32_t batch, int32_t max_blocks);
 size_t attn_direct_floats(const pie_config& c);
 int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const int32_t* d_table, int32_t max_blocks,

@@ -376,8 +376,9 @@ int pie_layer_step(pie_layer_pool* lp, const void* d_q_all, const void* d_k_new,
   pie::note_stream(p, os);
   int rc;
   if ((rc = pie::flush_map(p, cs))) return rc;
-  // a small batch's layers are one launch each, appends included (pie_attn_direct.hip)
-  const bool direct = pie::attn_direct_step(p, batch, max_blocks);
+  // the layers may be one launch each, in small steps appends included (pie_attn_direct.hip)
+  const int path = pie::attn_step_path(p, lp->n_layers, batch, max_blocks);
+  const bool direct = path != pie::kStepPlanned, append_apart = d_k_new && path != pie::kStepDirect;
   for (int32_t k = 0; k < lp->n_layers; ++k) {
     // one ticket counter per launch since the last planning kernel; there are as many as GPU slots
     if (!direct && k % n_slots == 0) {
@@ -414,15 +415,15 @@ int pie_layer_step(pie_layer_pool* lp, const void* d_q_all, const void* d_k_new,
     char* out_k = (char*)d_out_all + k * q_stride;
     const char* k_k = d_k_new ? (const char*)d_k_new + k * kv_stride : nullptr;
     const char* v_k = d_k_new ? (const char*)d_v_new + k * kv_stride : nullptr;
+    if (append_apart && (rc = pie::launch_kv_append(p, slot, 1, k_k, v_k, d_block_table, max_blocks, d_ctx_lens, batch,
+                                                    pie::kAppendGpuStrict, cs)))
+      return rc;
     if (direct) {
       if ((rc = pie::launch_attn_direct(p, slot, q_k, d_block_table, max_blocks, d_ctx_lens, batch, out_k, false, cs, k_k,
-                                        v_k, d_k_new ? pie::kAppendGpuStrict : -1, nullptr, nullptr, nullptr, nullptr,
+                                        v_k, d_k_new && !append_apart ? pie::kAppendGpuStrict : -1, nullptr, nullptr, nullptr, nullptr,
                                         nullptr, done)))
         return rc;
     } else {
-      if (d_k_new && (rc = pie::launch_kv_append(p, slot, 1, k_k, v_k, d_block_table, max_blocks, d_ctx_lens, batch,
-                                                 pie::kAppendGpuStrict, cs)))
-        return rc;
       if ((rc = pie::launch_attn_decode(p, slot, q_k, max_blocks, d_ctx_lens, batch, out_k, cs, nullptr, nullptr,
                                         k % n_slots, nullptr, nullptr, done, nullptr, k_k, v_k)))
         return rc;

@@ -1014,9 +1014,10 @@ static int step_body(pie_pool* p, const StepJob& j) {
   const bool with_new = d_k_new != nullptr;
   const bool staged_tails = with_new && n_dirty > 0;
   const int32_t append_mode = staged_tails ? kAppendGpuHomed : kAppendGpuStrict;
-  // A small batch's layers are one launch each, which stores the GPU-homed tails' rows too (pie_attn_direct.hip).
-  const bool direct = attn_direct_step(p, batch, max_blocks);
-  const bool append_apart = with_new && !direct;
+  // The layers may be one launch each, which in small steps stores the GPU-homed tails' rows too (pie_attn_direct.hip).
+  const int path = attn_step_path(p, L, batch, max_blocks);
+  const bool direct = path != kStepPlanned;
+  const bool append_apart = with_new && path != kStepDirect;
   if (append_apart || staged_tails) {            // the appends read the maps sent above
     PIE_HIP(hipEventRecord(p->ev_map, cs));
     p->ev_map_rec = true;
@@ -1087,7 +1088,7 @@ static int step_body(pie_pool* p, const StepJob& j) {
     hipEvent_t done = standin ? nullptr : read_done;
     if (direct)
       rc = launch_attn_direct(p, l, q_l, d_block_table, max_blocks, d_ctx_lens, batch, out_l, true, cs, k_l, v_l,
-                              with_new ? append_mode : -1, nullptr, nullptr, k_start, k_end, clock_row(l), done,
+                              with_new && !append_apart ? append_mode : -1, nullptr, nullptr, k_start, k_end, clock_row(l), done,
                               L <= 2 ? kDirectPlanNone : l < 2 ? kDirectPlanWrite : kDirectPlanReplay);
     else
       rc = launch_attn_decode(p, l, q_l, max_blocks, d_ctx_lens, batch, out_l, cs, k_start, k_end, -1, clock_row(l),
