@@ -288,7 +288,7 @@ def roofline_of(w, dw, streams, steps, warmup):
     traffic, source = traffic_from_profile(f"attn_decode_{w.name}_pmc.txt")
     res = {"tokens_per_s": w.batch / s, "ms_per_step": s * 1e3, "layers": w.n_layers,
            "attn_partition_tokens": dw.pool.attn_partition(),
-           "roofline": {"bound": "hbm", "kernel": "k_attn_decode_mfma", "achieved": achieved, "peak": HBM_PEAK_GBS,
+           "roofline": {"bound": "hbm", "kernel": "k_attn_direct", "achieved": achieved, "peak": HBM_PEAK_GBS,
                         "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": source,
                         "kernel_ms": k_ms, "algorithmic_bytes_per_launch": dw.kv_bytes_per_layer,
                         "stream_probe_ms": probe_ms, "frac_of_stream_probe": probe_ms / k_ms}}
@@ -890,7 +890,8 @@ def main():
                                                                    "slowdown) and inflation_e2e (step time, waits "
                                                                    "included) in swap, swap_below_knee, swap_kernel.*, "
                                                                    "cfg4.fixed_fraction[], cfg5.overflow_on_host"}},
-        "roofline": {"bound": "hbm", "kernel": "k_attn_decode_mfma", "achieved": achieved, "peak": HBM_PEAK_GBS,
+        "roofline": {"bound": "hbm", "kernel": "k_attn_decode_mfma" if args.partition or args.attn_vector_alu else
+                     "k_attn_direct", "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": traffic_from_profile(f"attn_decode_{w.name}_pmc.txt")[0],
                      "traffic_source": traffic_from_profile(f"attn_decode_{w.name}_pmc.txt")[1],

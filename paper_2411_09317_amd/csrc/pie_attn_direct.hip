@@ -35,6 +35,7 @@ struct DirectArgs {
   float* ws;                 // partial states: [unit][group][d + 4]
   uint32_t* arrive;          // per (sequence, head unit): workgroups that have stored their part; zero between launches
   uint32_t* arrive_other;    // the other launches' words, cleared here
+  uint32_t arrive_words;     // of each
   int32_t* hdr;              // plan header, to note the nominal item size in, or NULL
   int32_t* plan;             // records and slot lists of the items (kPlan*): written, or with REPLAY read; or NULL
   unsigned long long* clock;    // as in AttnArgs
@@ -530,7 +531,7 @@ void k_attn_direct(const DirectArgs a) {
   }
   // Launches take turns with two sets of arrival words.  The last arrival at a word leaves it zero; each launch also
   // clears the set it does not use, so that whatever calls that must not overlap did to a set is gone one launch later.
-  if (const uint32_t i = blockIdx.x + (uint32_t)tid * gridDim.x; i < (uint32_t)kArriveWords)
+  if (const uint32_t i = blockIdx.x + (uint32_t)tid * gridDim.x; i < a.arrive_words)
     a.arrive_other[i * kArriveStride] = 0u;
   if (a.clock && tid == 0) {
     const unsigned long long t = wall_clock64();
@@ -548,9 +549,22 @@ void k_attn_direct(const DirectArgs a) {
 
 // ---- dispatch --------------------------------------------------------------------------------------------
 
-// Its scratch: the parts, then the items' records and slot lists of the two staging regions.
-static size_t parts_floats(const pie_config& c) { return (size_t)kDirectRows * (c.head_dim + 4); }
-static size_t plan_region_ints(const pie_config& c) { return ((size_t)kDirectMaxUnits / c.n_kv_heads + 1) * kPlanInts; }
+// Its scratch in a pool: the parts, then the items' records and slot lists of the two staging regions, for as many units
+// as the pool's largest batch and widest table can make (a call's own scratch has room for any).
+static size_t pool_items(const pie_config& c) {
+  const size_t most = (size_t)kDirectMaxUnits / c.n_kv_heads + 1;
+  const size_t pool = (size_t)c.max_batch * (((size_t)c.max_blocks_per_seq + kWaves - 1) / kWaves) + 1;
+  return pool < most ? pool : most;
+}
+static size_t parts_floats(const pie_config& c) {
+  const size_t rows = pool_items(c) * c.n_q_heads;
+  return (rows < (size_t)kDirectRows ? rows : (size_t)kDirectRows) * (c.head_dim + 4);
+}
+static size_t plan_region_ints(const pie_config& c) { return pool_items(c) * kPlanInts; }
+size_t attn_arrive_words(const pie_config& c) {
+  const size_t pairs = (size_t)c.max_batch * c.n_kv_heads;
+  return pairs < (size_t)kArriveWords ? pairs : (size_t)kArriveWords;
+}
 size_t attn_direct_floats(const pie_config& c) { return parts_floats(c) + 2 * plan_region_ints(c); }
 
 // How many units the split of a call may make; 0: the call is left to the planned path, which has what this one lacks -
@@ -644,11 +658,13 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   a.ws = work ? reinterpret_cast<float*>(work->plan) : p->d_ws;   // a call's own scratch from its start
   uint32_t* words = work ? work->arrive : p->d_arrive;
   const uint32_t turn = (work ? work->arrive_turn : &p->arrive_turn)->fetch_add(1, std::memory_order_relaxed) & 1u;
-  a.arrive = words + turn * kArriveSet;
-  a.arrive_other = words + (1u - turn) * kArriveSet;
+  a.arrive_words = (uint32_t)(work ? kArriveWords : attn_arrive_words(c));
+  const size_t set = (size_t)a.arrive_words * kArriveStride;
+  a.arrive = words + turn * set;
+  a.arrive_other = words + (1u - turn) * set;
   a.hdr = work ? nullptr : p->d_plan;
   a.block_bytes = p->block_bytes;
-  a.ws_bytes = (int32_t)(parts_floats(c) * sizeof(float));
+  a.ws_bytes = (int32_t)((work ? (size_t)kDirectRows * (c.head_dim + 4) : parts_floats(c)) * sizeof(float));
   a.plan = plan == kDirectPlanNone ? nullptr
                                    : reinterpret_cast<int32_t*>(p->d_ws + parts_floats(c)) + (view ? 0 : layer & 1) * plan_region_ints(c);
   a.scale_log2e = p->scale_log2e;

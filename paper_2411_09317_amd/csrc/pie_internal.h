@@ -47,10 +47,10 @@ constexpr int kClockGrid = 7;         // workgroups of the decode kernel that wr
 constexpr int kClockWgs = 4096;       // per-workgroup (first, last moment) pairs per layer, after the rows
 
 // Arrival words of the one-launch attention path: two sets of as many (sequence, head) pairs as it may merge at once,
+// at most kArriveWords,
 // each word in a cache line of its own (atomics on one line are served one after another, about 10 ns each).
 constexpr int kArriveWords = 4096;
 constexpr int kArriveStride = 32;
-constexpr int kArriveSet = kArriveWords * kArriveStride;
 
 struct Home {
   int32_t where = -1;  // PIE_WHERE_* or -1 = unallocated
@@ -89,7 +89,7 @@ struct AttnWork {
   int32_t* plan;
   float* ws;
   size_t ws_floats;
-  uint32_t* arrive;         // 2 x kArriveSet words of the one-launch path, and whose turn it is
+  uint32_t* arrive;         // two sets of words of the one-launch path, and whose turn it is
   std::atomic<uint32_t>* arrive_turn;
   int32_t n_counters;       // ticket counters the planning kernel zeroes
   int32_t lay_batch, lay_max_blocks;
@@ -270,6 +270,7 @@ constexpr int kStepPlanned = 0, kStepDirect = 1, kStepDirectAppendApart = 2;
 int attn_step_path(const pie_pool* p, int32_t n_layers, int32_t batch, int32_t max_blocks);
 bool attn_direct(const pie_pool* p, int32_t batch, int32_t max_blocks);
 size_t attn_direct_floats(const pie_config& c);
+size_t attn_arrive_words(const pie_config& c);   // arrival words in a pool, each set
 int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const int32_t* d_table, int32_t max_blocks,
                        const int32_t* d_ctx, int32_t batch, void* d_out, bool stage_valid, hipStream_t s,
                        const void* d_k_new = nullptr, const void* d_v_new = nullptr, int32_t append = -1,

@@ -1475,7 +1475,7 @@ int launch_stream_probe(const pie_pool* p, int32_t layer, int32_t max_blocks, in
 // address is ever handed to kernels (the array's name in host code is a host-side stand-in).
 
 constexpr size_t kStaticScratchBytes = (size_t)40 << 20;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + 2 * kArriveSet * 4];   // arrival words last
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + 2 * kArriveWords * kArriveStride * 4];   // arrival words last
 
 constexpr int kMaxScratchDevices = 64;
 static char* g_scratch_ptr[kMaxScratchDevices] = {};

@@ -60,9 +60,10 @@ static Layout layout_of(const pie_config& c) {
   l.off_ws = off; off = align_up(off + l.ws_floats * 4, kAlign);
   l.off_plan = off; off = align_up(off + attn_plan_ints(c) * 4, kAlign);
   l.off_err = off; off += kAlign;
+  l.off_arrive = off;                            // (cleared with the error page, in one launch)
+  off = align_up(off + 2 * attn_arrive_words(c) * kArriveStride * 4, kAlign);
   l.off_clock = off;
   off = align_up(off + (((size_t)c.n_layers + 1) * kClockRow + (size_t)c.n_layers * kClockWgs * 2) * 8, kAlign);
-  l.off_arrive = off; off = align_up(off + (size_t)2 * kArriveSet * 4, kAlign);
   l.d_total = off;
   l.h_total = l.h_layer_stride * c.n_layers;
   return l;
@@ -540,8 +541,8 @@ int pie_pool_init(const pie_config* cfg, void* d_base, size_t d_bytes, void* h_p
     // maps start empty, error flags clear (default stream; synchronised before returning)
     if ((rc = launch_map_fill(p->d_map[0], p->n_handles, -1, nullptr))) return fail(rc);
     if ((rc = launch_map_fill(p->d_map[1], p->n_handles, -1, nullptr))) return fail(rc);
-    if ((rc = launch_zero_u32(p->d_err, kAlign / 4, nullptr))) return fail(rc);
-    if ((rc = launch_zero_u32(p->d_arrive, 2 * kArriveSet, nullptr))) return fail(rc);
+    if ((rc = launch_zero_u32(p->d_err, (int32_t)(kAlign / 4 + 2 * attn_arrive_words(*cfg) * kArriveStride), nullptr)))
+      return fail(rc);
     if ((rc = launch_zero_u32((uint32_t*)p->d_clock, (cfg->n_layers + 1) * kClockRow * 2, nullptr))) return fail(rc);
     err = hipStreamSynchronize(nullptr);
     if (err != hipSuccess) { g_last_hip_error = (int)err; return fail(PIE_EHIP); }
