@@ -615,8 +615,9 @@ int attn_step_path(const pie_pool* p, int32_t n_layers, int32_t batch, int32_t m
 }
 
 template <typename W, int NW, int PLAN>
-static int launch_direct_as(const DirectArgs& a, int32_t grid, hipStream_t s, hipEvent_t done) {
-  const size_t lds = ((size_t)NW * 2 * kMaxGroup + (size_t)NW * a.group * (W::HD + 4)) * sizeof(float);
+static int launch_direct_as(const DirectArgs& a, int32_t grid, hipStream_t s, hipEvent_t done, size_t min_lds) {
+  size_t lds = ((size_t)NW * 2 * kMaxGroup + (size_t)NW * a.group * (W::HD + 4)) * sizeof(float);
+  if (lds < min_lds) lds = min_lds;
   if (done) hipExtLaunchKernelGGL((k_attn_direct<W, NW, PLAN>), dim3(grid), dim3(NW * 64), (uint32_t)lds, s, nullptr, done, 0, a);
   else hipLaunchKernelGGL((k_attn_direct<W, NW, PLAN>), dim3(grid), dim3(NW * 64), (uint32_t)lds, s, a);
   PIE_HIP(hipGetLastError());
@@ -624,11 +625,11 @@ static int launch_direct_as(const DirectArgs& a, int32_t grid, hipStream_t s, hi
 }
 
 template <typename W, int NW>
-static int launch_direct(const DirectArgs& a, int32_t grid, hipStream_t s, hipEvent_t done, int32_t plan) {
+static int launch_direct(const DirectArgs& a, int32_t grid, hipStream_t s, hipEvent_t done, int32_t plan, size_t min_lds) {
   switch (plan) {
-    case kDirectPlanReplay: return launch_direct_as<W, NW, kDirectPlanReplay>(a, grid, s, done);
-    case kDirectPlanReplaySplit: return launch_direct_as<W, NW, kDirectPlanReplaySplit>(a, grid, s, done);
-    default: return launch_direct_as<W, NW, kDirectPlanNone>(a, grid, s, done);
+    case kDirectPlanReplay: return launch_direct_as<W, NW, kDirectPlanReplay>(a, grid, s, done, min_lds);
+    case kDirectPlanReplaySplit: return launch_direct_as<W, NW, kDirectPlanReplaySplit>(a, grid, s, done, min_lds);
+    default: return launch_direct_as<W, NW, kDirectPlanNone>(a, grid, s, done, min_lds);
   }
 }
 
@@ -636,7 +637,11 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
                        const int32_t* d_ctx, int32_t batch, void* d_out, bool stage_valid, hipStream_t s,
                        const void* d_k_new, const void* d_v_new, int32_t append, const LayerView* view,
                        const AttnWork* work, hipEvent_t k_start, hipEvent_t k_end, unsigned long long* clock_row,
-                       hipEvent_t done, int32_t plan) {
+                       hipEvent_t done, int32_t plan, bool leave_room) {
+  // Three workgroups a compute unit take nearly all its registers, and a gather beside them starts when one ends.  Two,
+  // by the LDS they ask for, leave it room: 8 layers of 24 sequences of 100 to 1 100 tokens, 32 kv heads, 2.3 MB a layer
+  // gathered: 642 -> 594 us; 46 of 555 to 5 000, 8 kv heads, 2.8 MB: 785 -> 764.
+  const size_t min_lds = leave_room ? (size_t)56 << 10 : 0;
   if (plan != kDirectPlanNone && work) return PIE_EINVAL;   // the plan lies in the pool's scratch, by layer & 1
   const pie_config& c = p->cfg;
   if (((uintptr_t)d_q | (uintptr_t)d_out) % 16) return PIE_EINVAL;
@@ -696,16 +701,16 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   const bool hd128 = c.head_dim == 128;
   switch (c.dtype) {
     case PIE_DTYPE_F32:
-      rc = hd128 ? launch_direct<Wave32<128>, kWaves>(a, grid, s, done, plan)
-                 : launch_direct<Wave32<64>, kWaves>(a, grid, s, done, plan);
+      rc = hd128 ? launch_direct<Wave32<128>, kWaves>(a, grid, s, done, plan, min_lds)
+                 : launch_direct<Wave32<64>, kWaves>(a, grid, s, done, plan, min_lds);
       break;
     case PIE_DTYPE_F16:
-      rc = hd128 ? launch_direct<Wave16<F16, 128, false>, kWaves>(a, grid, s, done, plan)
-                 : launch_direct<Wave16<F16, 64, false>, kWaves>(a, grid, s, done, plan);
+      rc = hd128 ? launch_direct<Wave16<F16, 128, false>, kWaves>(a, grid, s, done, plan, min_lds)
+                 : launch_direct<Wave16<F16, 64, false>, kWaves>(a, grid, s, done, plan, min_lds);
       break;
     case PIE_DTYPE_BF16:
-      rc = hd128 ? launch_direct<Wave16<BF16, 128, true>, kWaves>(a, grid, s, done, plan)
-                 : launch_direct<Wave16<BF16, 64, true>, kWaves>(a, grid, s, done, plan);
+      rc = hd128 ? launch_direct<Wave16<BF16, 128, true>, kWaves>(a, grid, s, done, plan, min_lds)
+                 : launch_direct<Wave16<BF16, 64, true>, kWaves>(a, grid, s, done, plan, min_lds);
       break;
   }
   if (rc) return rc;

@@ -262,7 +262,7 @@ inline int32_t attn_min_units(const pie_pool* p) { return p->n_cu * 17; }   // s
 // which needs no planning before it.  append: kAppend* mode in which the new rows are stored as well, or -1.
 // plan: whether the launch leaves its split and slots for the layers of the same region that follow with the same batch,
 // table, context lengths and maps (kDirectPlanWrite), or starts from what one left: all of it (kDirectPlanReplay), or
-// the split alone (kDirectPlanReplaySplit: the layer has a map of its own).
+// the split alone (kDirectPlanReplaySplit: the layer has a map of its own).  leave_room: a gather kernel runs beside it.
 constexpr int32_t kDirectPlanNone = 0, kDirectPlanWrite = 1, kDirectPlanReplay = 2, kDirectPlanReplaySplit = 3;
 // How the layers of a step of n_layers run: planned, or in a launch each, which stores the new rows or leaves that to
 // k_kv_append.  The same for every kind of step, so that their results are the same bits.
@@ -276,7 +276,7 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
                        const void* d_k_new = nullptr, const void* d_v_new = nullptr, int32_t append = -1,
                        const LayerView* view = nullptr, const AttnWork* work = nullptr, hipEvent_t k_start = nullptr,
                        hipEvent_t k_end = nullptr, unsigned long long* clock_row = nullptr, hipEvent_t done = nullptr,
-                       int32_t plan = 0);
+                       int32_t plan = 0, bool leave_room = false);
 int launch_stream_probe(const pie_pool* p, int32_t layer, int32_t max_blocks, int32_t batch, hipStream_t s);
 int attn_static_scratch(char** out, std::atomic<uint32_t>** out_turn = nullptr);
 int attn_static_work(const pie_pool* p, int32_t batch, int32_t max_blocks, AttnWork* out);
