@@ -9,10 +9,9 @@
 //
 // What bounds it: for small calls a chain of dependent accesses, about 7 us from the first workgroup's start (context
 // lengths and split 1.4 us, table and map 0.7, a block 0.9, the part's state stored 1.0 and counted 0.4 to 1.3, the
-// merge 1.4); for large ones HBM.  us a call, planned before and in one launch now: one sequence of 700 tokens, 32
-// heads over 8: 24.4 and 14.0; one of 32 749, 64 over 8: 48.5 and 34.6 (134 MB); 30 of 500 to 2 500, 32 over 32: 123 and
-// 116 (650 MB); 12 of 32 768, 64 over 8: 290 and 255 (1.6 GB, 6.3 TB/s).  A layer of a step of 8 sequences of 128 to
-// 4 096 tokens, 32 over 8: 16.8 and 12.0.
+// merge 1.4); for large ones HBM.  us a call among others, planned before and in one launch now: one sequence of
+// 700 tokens, 32 heads over 8: 24.5 and 6.5; one of 32 749, 64 over 8: 48.6 and 27.3 (134 MB, 4.9 TB/s); 32 of 32 768,
+// 64 over 8: 671 and 661 (4.3 GB, 6.5 TB/s).  A layer of a step of 8 sequences of 128 to 4 096 tokens, 32 over 8: 16.8 and 11.0.
 
 #include <hip/hip_ext.h>
 
@@ -530,7 +529,7 @@ void k_attn_direct(const DirectArgs a) {
     a.plan[(size_t)at * kPlanInts + tid] = x;
   }
   // Launches take turns with two sets of arrival words.  The last arrival at a word leaves it zero; each launch also
-  // clears the set it does not use, so that whatever calls that must not overlap did to a set is gone one launch later.
+  // clears the set it does not use (256 words a workgroup), so that what calls that must not overlap did to a set is gone.
   if (const uint32_t i = blockIdx.x + (uint32_t)tid * gridDim.x; i < a.arrive_words)
     a.arrive_other[i * kArriveStride] = 0u;
   if (a.clock && tid == 0) {
@@ -574,9 +573,10 @@ size_t attn_direct_floats(const pie_config& c) { return parts_floats(c) + 2 * pl
 // Otherwise: as few units as hold every (sequence, kv head) pair and the longest context the table can name, in steps
 // of the compute units.  One workgroup a compute unit streams as fast as two or three, and every part more has to be
 // stored, counted and merged: one sequence of 32 749 tokens, 64 heads over 8, takes 33.0 us at one unit per compute
-// unit, 37.6 at three, 44.1 at six.  Beyond one, three workgroups are resident per compute unit, so multiples of three
-// (64 sequences of 500 to 2 500 tokens, 32 heads over 8: 77.6 / 72.8 / 74.9 us at two / three / six); short contexts
-// want few (60 of 60 to 300 tokens, 32 heads, a step of 8 layers: 325 us at nine, 379 at fifteen).
+// unit, 37.6 at three, 44.1 at six (6 us of each an event behind the call).  Beyond one, three workgroups are resident
+// per compute unit, so multiples of three (64 sequences of 500 to 2 500 tokens, 32 heads over 8: 77.6 / 72.8 / 74.9 us
+// at two / three / six); short contexts want few (60 of 60 to 300 tokens, 32 heads, a step of 8 layers: 325 us at nine,
+// 379 at fifteen).
 static int32_t direct_max_units(const pie_pool* p, int32_t batch, int32_t max_blocks) {
   if (p->attn_partition > 0 || p->attn_valu) return 0;
   if (batch < 1 || batch > kDirectSeqs || max_blocks < 1) return 0;
