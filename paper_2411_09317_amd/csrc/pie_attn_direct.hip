@@ -602,16 +602,19 @@ bool attn_direct(const pie_pool* p, int32_t batch, int32_t max_blocks) { return 
 // planned; 8 layers of 120 of 60 to 300, 8 kv heads: 213 against 260.  In bigger steps that would put partial-line writes
 // among every layer's reads (32 layers of 64 sequences of 1 024 to 2 048, 32 kv heads: 8 329 us against 8 056 planned),
 // so the rows of all layers are stored by one launch beside the first, as on the planned path.  There the one-launch path
-// saves the reduction, 3 to 10 us a layer, and loses about 40 us a step, because that launch finds less room beside its
-// workgroups than beside the persistent grid's: with grouped queries it gains from about 8 layers on (16 layers of 256
-// sequences of 128 to 4 096, 32 heads over 8: 3 465 us against 3 615; with host blocks 8 layers 1 782 / 1 794, 4 layers
-// 987 / 983), without from about 32 (32 layers as above: 7 994 / 8 107; with host blocks 8 164 / 8 176, 12 layers
-// 3 147 / 3 123).
+// saves the reduction, 3 to 10 us a layer, and loses some 40 us a step, because that launch finds less room beside its
+// workgroups than beside the persistent grid's.  With grouped queries it gains from about 8 layers on (256 sequences of
+// 128 to 4 096 tokens, 32 heads over 8, us planned and in one launch, both in the same memory: 8 layers 1 776 and 1 752,
+// 12 layers 2 655 and 2 577, 16 layers 3 614 and 3 517, 32 layers 7 013 and 6 960; with host blocks, 0.5 %, 16 layers 3 631
+// and 3 585, 32 layers 7 100 and 7 098).  Without grouping it does not (64 sequences of 1 024 to 2 048, 32 heads, 32
+// layers 8 041 and 8 101, with host blocks 8 155 and 8 329; 40 of 300 to 1 700, 40 heads, 32 layers 4 624 and 4 644), and
+// fewer, longer parts have fewer weights of exactly one, so that rounding the weights to f16 costs more (2.24e-4 from 64
+// bits against 2.19e-4): those steps stay planned.
 int attn_step_path(const pie_pool* p, int32_t n_layers, int32_t batch, int32_t max_blocks) {
   if (!attn_direct(p, batch, max_blocks)) return kStepPlanned;
   const int64_t pairs = (int64_t)batch * p->cfg.n_kv_heads;
   if (pairs <= 3 * (int64_t)p->n_cu || pairs * max_blocks * kBlockTokens <= (int64_t)8192 * p->n_cu) return kStepDirect;
-  return n_layers >= (p->cfg.n_q_heads > p->cfg.n_kv_heads ? 8 : 32) ? kStepDirectAppendApart : kStepPlanned;
+  return p->cfg.n_q_heads > p->cfg.n_kv_heads && n_layers >= 8 ? kStepDirectAppendApart : kStepPlanned;
 }
 
 template <typename W, int NW, int PLAN>

@@ -262,6 +262,42 @@ def test_the_layers_of_a_step_that_start_from_an_earlier_layers_split(layers, hq
     assert np.array_equal(images[0][0], images[1][0]) and np.array_equal(images[0][1], images[1][1])
 
 
+def _noise_pool(layers, hq, hkv, d, dtype, ctx, width, seed):
+    """A pool without host blocks whose caches hold noise, one block after another, and a step's device arguments."""
+    nb = I.blocks_needed(ctx, 16)
+    lib = B.Pool(layers, hq, hkv, d, 16, dtype, int(nb.sum()), 0, 0, max_batch=len(ctx), max_blocks_per_seq=width, device=GH.DEV)
+    gen = torch.Generator(device=GH.DEV).manual_seed(seed)
+    dt = GH.TORCH_DT[dtype]
+    img = lib.gpu_image()
+    for l in range(layers):
+        img[l].view(-1).view(dt).normal_(0.0, 1.0, generator=gen)
+    handles = lib.block_alloc(B.GPU, int(nb.sum()))
+    table, i = np.full((len(ctx), width), -1, np.int32), 0
+    for b, n in enumerate(nb):
+        table[b, :n] = handles[i:i + n]
+        i += n
+    q, k, v = (torch.randn((layers, len(ctx), h, d), device=GH.DEV, generator=gen).to(dt) for h in (hq, hkv, hkv))
+    return lib, q, k, v, torch.from_numpy(table).to(GH.DEV), torch.from_numpy(ctx.copy()).to(GH.DEV)
+
+
+def test_big_steps_without_grouped_queries_give_the_bits_of_the_planned_path():
+    """More than three (sequence, head) pairs per compute unit under a table that names more than 8 192 tokens a unit, one
+    query head per kv head: the layers cut the contexts as the planning kernel does, so setting the item size that kernel
+    chose changes nothing."""
+    ctx = (300 + np.arange(52) * 37 % 600).astype(np.int32)
+    lib, q, k, v, tb, cl = _noise_pool(32, 16, 16, 64, I.DTYPE_F16, ctx, 400, 5)
+    outs = []
+    for part in (0, 512):
+        lib.set_attn_partition(part)
+        out = torch.full_like(q, float("nan"))
+        lib.step(q, k, v, tb, cl, [], [], out)
+        lib.sync()
+        assert lib.check_errors() == 0 and lib.attn_partition() == 512
+        outs.append(out)
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+    lib.close()
+
+
 @pytest.mark.parametrize("batch", [1, 63, 64, 257, 1023, 1029])
 def test_planning_of_batches_around_its_rounds(batch):
     """The planning kernel scans the batch in rounds of one sequence per thread (256 or 1024 threads) and ranks the
