@@ -32,9 +32,8 @@ struct DirectArgs {
   const char* new_k;         // newest token's rows [B][Hkv][d] (see AttnArgs), or NULL
   const char* new_v;
   float* ws;                 // partial states: [unit][group][d + 4]
-  uint32_t* arrive;          // per (sequence, head unit): workgroups that have stored their part; zero between launches
-  uint32_t* arrive_other;    // the other launches' words, cleared here
-  uint32_t arrive_words;     // of each
+  uint64_t* arrive;          // per (sequence, head unit): workgroups of which launch have stored their part
+  uint64_t launch;           // this launch's number << kArriveShift
   int32_t* hdr;              // plan header, to note the nominal item size in, or NULL
   int32_t* plan;             // records and slot lists of the items (kPlan*): written, or with REPLAY read; or NULL
   unsigned long long* clock;    // as in AttnArgs
@@ -210,7 +209,7 @@ void k_attn_direct(const DirectArgs a) {
   constexpr bool REPLAY = PLAN != kDirectPlanNone, SLOTS = PLAN == kDirectPlanReplay;
 
   extern __shared__ __align__(16) float s_dyn[];
-  __shared__ uint32_t s_arrived;
+  __shared__ bool s_last;
   __shared__ __align__(16) float s_w[NT];         // weights of the parts being merged, a thread each
   float* s_m = s_dyn;                             // [NW][16]
   float* s_l = s_dyn + NW * kMaxGroup;            // [NW][16]
@@ -450,12 +449,17 @@ void k_attn_direct(const DirectArgs a) {
     if (np > 1) {
       wait_stores();
       __syncthreads();
-      uint32_t* word = a.arrive + ((size_t)b * H + g) * kArriveStride;
-      if (tid == 0)
-        s_arrived = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+      // The last arrival leaves its word zero.  What calls that must not overlap have left in a word is the number of a
+      // launch that was enqueued before this one, which the first arrival here replaces by this launch's.
+      uint64_t* word = a.arrive + ((size_t)b * H + g) * kArriveStride;
+      if (tid == 0) {
+        (void)__hip_atomic_fetch_max(word, a.launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_last = __hip_atomic_fetch_add(word, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                 a.launch + (uint64_t)(np - 1);
+      }
       __syncthreads();
-      if (s_arrived == (uint32_t)np) {            // every part is stored: merge them, in order
-        if (tid == 0) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (s_last) {                               // every part is stored: merge them, in order
+        if (tid == 0) __hip_atomic_store(word, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // A head's threads take TPH parts at a time: thread i reads part i's (M, L) and works out its weight, then
         // every thread sums its four dims over the parts, sixteen loads in flight, the weights fetched from LDS.
         // With few heads and many parts, groups of threads take a share of the parts each and meet in LDS.
@@ -528,10 +532,6 @@ void k_attn_direct(const DirectArgs a) {
     for (int i = 1; i < kPlanRec; ++i) x = tid == i ? rec[i] : x;
     a.plan[(size_t)at * kPlanInts + tid] = x;
   }
-  // Launches take turns with two sets of arrival words.  The last arrival at a word leaves it zero; each launch also
-  // clears the set it does not use (256 words a workgroup), so that what calls that must not overlap did to a set is gone.
-  if (const uint32_t i = blockIdx.x + (uint32_t)tid * gridDim.x; i < a.arrive_words)
-    a.arrive_other[i * kArriveStride] = 0u;
   if (a.clock && tid == 0) {
     const unsigned long long t = wall_clock64();
     if (a.clock_wg) {
@@ -617,6 +617,12 @@ int attn_step_path(const pie_pool* p, int32_t n_layers, int32_t batch, int32_t m
   return p->cfg.n_q_heads > p->cfg.n_kv_heads && n_layers >= 8 ? kStepDirectAppendApart : kStepPlanned;
 }
 
+// A launch in a graph has the same number in every replay, so there the words it uses are cleared ahead of it.
+__global__ __launch_bounds__(256) void k_arrive_clear(uint64_t* __restrict__ words, int32_t n) {
+  const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (i < n) words[(size_t)i * kArriveStride] = 0;
+}
+
 template <typename W, int NW, int PLAN>
 static int launch_direct_as(const DirectArgs& a, int32_t grid, hipStream_t s, hipEvent_t done, size_t min_lds) {
   size_t lds = ((size_t)NW * 2 * kMaxGroup + (size_t)NW * a.group * (W::HD + 4)) * sizeof(float);
@@ -664,12 +670,8 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   a.new_k = (const char*)d_k_new;
   a.new_v = (const char*)d_v_new;
   a.ws = work ? reinterpret_cast<float*>(work->plan) : p->d_ws;   // a call's own scratch from its start
-  uint32_t* words = work ? work->arrive : p->d_arrive;
-  const uint32_t turn = (work ? work->arrive_turn : &p->arrive_turn)->fetch_add(1, std::memory_order_relaxed) & 1u;
-  a.arrive_words = (uint32_t)(work ? kArriveWords : attn_arrive_words(c));
-  const size_t set = (size_t)a.arrive_words * kArriveStride;
-  a.arrive = words + turn * set;
-  a.arrive_other = words + (1u - turn) * set;
+  a.arrive = work ? work->arrive : p->d_arrive;
+  a.launch = ((work ? work->arrive_launches : &p->arrive_launches)->fetch_add(1, std::memory_order_relaxed) + 1) << kArriveShift;
   a.hdr = work ? nullptr : p->d_plan;
   a.block_bytes = p->block_bytes;
   a.ws_bytes = (int32_t)((work ? (size_t)kDirectRows * (c.head_dim + 4) : parts_floats(c)) * sizeof(float));
@@ -698,6 +700,13 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   if (clock_row && grid <= kClockWgs) {
     const size_t row = (size_t)(clock_row - p->d_clock) / kClockRow;
     a.clock_wg = p->d_clock + ((size_t)c.n_layers + 1) * kClockRow + row * kClockWgs * 2;
+  }
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();   // the launch will say what is wrong
+  if (capture == hipStreamCaptureStatusActive) {
+    const int32_t n = batch * H;
+    hipLaunchKernelGGL(k_arrive_clear, dim3((n + 255) / 256), dim3(256), 0, s, a.arrive, n);
+    PIE_HIP(hipGetLastError());
   }
   if (k_start) PIE_HIP(hipEventRecord(k_start, s));
   int rc = PIE_EINVAL;

@@ -46,11 +46,12 @@ constexpr int kClockOutEnd = 6;       // the layer's write-back has ended
 constexpr int kClockGrid = 7;         // workgroups of the decode kernel that wrote per-workgroup words (0: none)
 constexpr int kClockWgs = 4096;       // per-workgroup (first, last moment) pairs per layer, after the rows
 
-// Arrival words of the one-launch attention path: two sets of as many (sequence, head) pairs as it may merge at once,
-// at most kArriveWords,
-// each word in a cache line of its own (atomics on one line are served one after another, about 10 ns each).
+// Arrival words of the one-launch attention path: one for each (sequence, head) pair that it may merge at once, at most
+// kArriveWords, each in a cache line of its own (atomics on one line are served one after another, about 10 ns each).
+// A word is the launch it counts for << kArriveShift | how many workgroups have stored their part.
 constexpr int kArriveWords = 4096;
-constexpr int kArriveStride = 32;
+constexpr int kArriveStride = 16;
+constexpr int kArriveShift = 16;
 
 struct Home {
   int32_t where = -1;  // PIE_WHERE_* or -1 = unallocated
@@ -89,8 +90,8 @@ struct AttnWork {
   int32_t* plan;
   float* ws;
   size_t ws_floats;
-  uint32_t* arrive;         // two sets of words of the one-launch path, and whose turn it is
-  std::atomic<uint32_t>* arrive_turn;
+  uint64_t* arrive;         // words of the one-launch path, and how many launches have used them
+  std::atomic<uint64_t>* arrive_launches;
   int32_t n_counters;       // ticket counters the planning kernel zeroes
   int32_t lay_batch, lay_max_blocks;
 };
@@ -132,8 +133,8 @@ struct pie_pool {
   float* d_ws = nullptr;        // split-context partials
   size_t ws_floats = 0;
   int32_t* d_plan = nullptr;    // attention planning state: header, ticket counters, items, resolved tables
-  uint32_t* d_arrive = nullptr; // arrival words of the one-launch attention path
-  mutable std::atomic<uint32_t> arrive_turn{0};   // the set of them the next launch uses (its low bit)
+  uint64_t* d_arrive = nullptr; // arrival words of the one-launch attention path
+  mutable std::atomic<uint64_t> arrive_launches{0};   // launches that have used them
   int32_t n_cu = 256;           // compute units of the device
   uint32_t* d_err = nullptr;    // device error flags
   unsigned long long* d_clock = nullptr;   // clock table: (n_layers + 1) rows of kClockRow words
@@ -270,7 +271,7 @@ constexpr int kStepPlanned = 0, kStepDirect = 1, kStepDirectAppendApart = 2;
 int attn_step_path(const pie_pool* p, int32_t n_layers, int32_t batch, int32_t max_blocks);
 bool attn_direct(const pie_pool* p, int32_t batch, int32_t max_blocks);
 size_t attn_direct_floats(const pie_config& c);
-size_t attn_arrive_words(const pie_config& c);   // arrival words in a pool, each set
+size_t attn_arrive_words(const pie_config& c);   // arrival words in a pool
 int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const int32_t* d_table, int32_t max_blocks,
                        const int32_t* d_ctx, int32_t batch, void* d_out, bool stage_valid, hipStream_t s,
                        const void* d_k_new = nullptr, const void* d_v_new = nullptr, int32_t append = -1,
@@ -278,7 +279,7 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
                        hipEvent_t k_end = nullptr, unsigned long long* clock_row = nullptr, hipEvent_t done = nullptr,
                        int32_t plan = 0, bool leave_room = false);
 int launch_stream_probe(const pie_pool* p, int32_t layer, int32_t max_blocks, int32_t batch, hipStream_t s);
-int attn_static_scratch(char** out, std::atomic<uint32_t>** out_turn = nullptr);
+int attn_static_scratch(char** out, std::atomic<uint64_t>** out_launches = nullptr);
 int attn_static_work(const pie_pool* p, int32_t batch, int32_t max_blocks, AttnWork* out);
 size_t attn_plan_ints(const pie_config& c);
 size_t attn_workspace_floats(const pie_config& c);

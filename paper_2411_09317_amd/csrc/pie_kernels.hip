@@ -1231,7 +1231,7 @@ static AttnWork pool_work(const pie_pool* p) {
   w.ws = p->d_ws;
   w.ws_floats = p->ws_floats;
   w.arrive = p->d_arrive;
-  w.arrive_turn = &p->arrive_turn;
+  w.arrive_launches = &p->arrive_launches;
   w.n_counters = p->cfg.n_layers;
   w.lay_batch = p->cfg.max_batch;
   w.lay_max_blocks = p->cfg.max_blocks_per_seq;
@@ -1475,15 +1475,15 @@ int launch_stream_probe(const pie_pool* p, int32_t layer, int32_t max_blocks, in
 // address is ever handed to kernels (the array's name in host code is a host-side stand-in).
 
 constexpr size_t kStaticScratchBytes = (size_t)40 << 20;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + 2 * kArriveWords * kArriveStride * 4];   // arrival words last
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kArriveWords * kArriveStride * 8];   // arrival words last
 
 constexpr int kMaxScratchDevices = 64;
 static char* g_scratch_ptr[kMaxScratchDevices] = {};
-static std::atomic<uint32_t> g_scratch_turn[kMaxScratchDevices];   // which set of its arrival words is next
+static std::atomic<uint64_t> g_scratch_launches[kMaxScratchDevices];   // launches that have used its arrival words
 static std::mutex g_scratch_mutex;
 
 // Device address of the current device's copy of the array.
-int attn_static_scratch(char** out, std::atomic<uint32_t>** out_turn) {
+int attn_static_scratch(char** out, std::atomic<uint64_t>** out_launches) {
   int dev = -1;
   PIE_HIP(hipGetDevice(&dev));
   if (dev < 0 || dev >= kMaxScratchDevices) return PIE_EINVAL;
@@ -1495,7 +1495,7 @@ int attn_static_scratch(char** out, std::atomic<uint32_t>** out_turn) {
     g_scratch_ptr[dev] = static_cast<char*>(ptr);
   }
   *out = g_scratch_ptr[dev];
-  if (out_turn) *out_turn = &g_scratch_turn[dev];
+  if (out_launches) *out_launches = &g_scratch_launches[dev];
   return PIE_OK;
 }
 
@@ -1504,8 +1504,8 @@ int attn_static_scratch(char** out, std::atomic<uint32_t>** out_turn) {
 int attn_static_work(const pie_pool* p, int32_t batch, int32_t max_blocks, AttnWork* out) {
   if (batch < 0 || batch > kMaxPlanBatch || max_blocks < 0 || max_blocks > (1 << 19)) return PIE_EINVAL;
   char* base = nullptr;
-  std::atomic<uint32_t>* turn = nullptr;
-  const int rc = attn_static_scratch(&base, &turn);
+  std::atomic<uint64_t>* launches = nullptr;
+  const int rc = attn_static_scratch(&base, &launches);
   if (rc) return rc;
   const int32_t part = part_tokens_of(p);
   const size_t n_parts = ((size_t)max_blocks * kBlockTokens + part - 1) / part;
@@ -1515,8 +1515,8 @@ int attn_static_work(const pie_pool* p, int32_t batch, int32_t max_blocks, AttnW
   out->plan = reinterpret_cast<int32_t*>(base);
   out->ws = reinterpret_cast<float*>(base + plan_bytes);
   out->ws_floats = ws_floats;
-  out->arrive = reinterpret_cast<uint32_t*>(base + kStaticScratchBytes);
-  out->arrive_turn = turn;
+  out->arrive = reinterpret_cast<uint64_t*>(base + kStaticScratchBytes);
+  out->arrive_launches = launches;
   out->n_counters = 2;          // one is used; two keep the item records 8-byte aligned
   out->lay_batch = batch;
   out->lay_max_blocks = max_blocks;

@@ -61,7 +61,7 @@ static Layout layout_of(const pie_config& c) {
   l.off_plan = off; off = align_up(off + attn_plan_ints(c) * 4, kAlign);
   l.off_err = off; off += kAlign;
   l.off_arrive = off;                            // (cleared with the error page, in one launch)
-  off = align_up(off + 2 * attn_arrive_words(c) * kArriveStride * 4, kAlign);
+  off = align_up(off + attn_arrive_words(c) * kArriveStride * 8, kAlign);
   l.off_clock = off;
   off = align_up(off + (((size_t)c.n_layers + 1) * kClockRow + (size_t)c.n_layers * kClockWgs * 2) * 8, kAlign);
   l.d_total = off;
@@ -489,7 +489,7 @@ int pie_pool_init(const pie_config* cfg, void* d_base, size_t d_bytes, void* h_p
     p->d_plan = (int32_t*)(base + l.off_plan);
     p->d_err = (uint32_t*)(base + l.off_err);
     p->d_clock = (unsigned long long*)(base + l.off_clock);
-    p->d_arrive = (uint32_t*)(base + l.off_arrive);
+    p->d_arrive = (uint64_t*)(base + l.off_arrive);
     int rc = PIE_OK;
     {
       int dev = 0, n_cu = 0;
@@ -541,7 +541,7 @@ int pie_pool_init(const pie_config* cfg, void* d_base, size_t d_bytes, void* h_p
     // maps start empty, error flags clear (default stream; synchronised before returning)
     if ((rc = launch_map_fill(p->d_map[0], p->n_handles, -1, nullptr))) return fail(rc);
     if ((rc = launch_map_fill(p->d_map[1], p->n_handles, -1, nullptr))) return fail(rc);
-    if ((rc = launch_zero_u32(p->d_err, (int32_t)(kAlign / 4 + 2 * attn_arrive_words(*cfg) * kArriveStride), nullptr)))
+    if ((rc = launch_zero_u32(p->d_err, (int32_t)(kAlign / 4 + attn_arrive_words(*cfg) * kArriveStride * 2), nullptr)))
       return fail(rc);
     if ((rc = launch_zero_u32((uint32_t*)p->d_clock, (cfg->n_layers + 1) * kClockRow * 2, nullptr))) return fail(rc);
     err = hipStreamSynchronize(nullptr);

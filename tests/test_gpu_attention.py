@@ -131,8 +131,7 @@ ONE_LAUNCH = [
 @pytest.mark.parametrize("name,dtype,hq,hkv,d,ctx", ONE_LAUNCH, ids=[s[0] for s in ONE_LAUNCH])
 def test_one_launch_path_at_its_edges(name, dtype, hq, hkv, d, ctx):
     """The call of one launch (no item size set) against the oracle, with a table wider than the contexts, poisoned
-    unused rows and slots; again, again and from the static scratch to the same bits (the arrival words it merges
-    by take turns); and against the planned path."""
+    unused rows and slots; again, again and from the static scratch to the same bits; and against the planned path."""
     w = I.Workload(name, 1, len(ctx), hq, hkv, d, dtype, value_scale=1.0, seed=36)
     ctx = np.asarray(ctx, np.int32)
     case = I.make_case(w, ctx_lens=ctx)
@@ -186,6 +185,45 @@ def test_the_allocation_free_call_replays_from_a_graph(ctx, part):
         (lib.attn_decode if i % 2 else lib.attn_decode_static)(0, q, tb, cl, eager, s)
         torch.cuda.synchronize()
         assert torch.equal(out.view(torch.int16), eager.view(torch.int16)), i
+    assert lib.check_errors() == 0
+    del graph
+    lib.close()
+
+
+def test_what_an_overlap_left_in_the_arrival_words_does_not_reach_later_calls():
+    """Calls that overlap on one pool, which they must not, can leave the words that count a sequence's finished parts at
+    any count of a launch enqueued before.  Words planted so: the next call, and a captured call at every replay, give the
+    result of an undisturbed call and leave the words they use at zero."""
+    w = I.Workload("residue", 1, 3, 8, 2, 128, I.DTYPE_BF16, value_scale=1.0, seed=40)
+    case = I.make_case(w, ctx_lens=np.asarray([900, 1500, 400], np.int32))
+    lib, mod, table = GH.make_pools(case, int(case.n_blocks.sum()) + 1, 0, 0)
+    # the words, 128 bytes apart, lie ahead of the clock table at the end of the pool's memory
+    clock = ((w.n_layers + 1) * 8 + w.n_layers * 4096 * 2) * 8
+    pairs = w.batch * w.n_kv_heads
+    at = lib._d_off + lib.d_bytes - -(-clock // 256) * 256 - -(-pairs * 128 // 256) * 256
+    words = lib.d_buf[at:at + pairs * 128].view(torch.int64)[::16]
+    tb, cl = torch.from_numpy(table).to(GH.DEV), torch.from_numpy(case.ctx_lens).to(GH.DEV)
+    q = GH.to_dev(case.q[0], w.dtype)
+    s = torch.cuda.Stream()
+    want = torch.zeros_like(q)
+    lib.attn_decode(0, q, tb, cl, want, s)
+    torch.cuda.synchronize()
+    check(GH.from_dev(want, w.dtype), A.dense_attention(*H.dense_f64(case, 0), case.ctx_lens), w.dtype)
+    assert (words == 0).all()
+    graph, out = torch.cuda.CUDAGraph(), torch.zeros_like(q)
+    with torch.cuda.graph(graph, stream=s):
+        lib.attn_decode(0, q, tb, cl, out, s)
+    lib.attn_decode(0, q, tb, cl, torch.zeros_like(q), s)       # a number beyond the captured call's
+    torch.cuda.synchronize()
+    for residue in (1, 3, (2 << 16) + 2, (3 << 16) + 1):        # counts of no launch, of the captured one and of the last
+        for call in (lambda: lib.attn_decode(0, q, tb, cl, out, s), graph.replay, graph.replay):
+            words.fill_(residue)
+            out.fill_(float("nan"))
+            torch.cuda.synchronize()
+            call()
+            torch.cuda.synchronize()
+            assert torch.equal(out.view(torch.int16), want.view(torch.int16)), residue
+            assert (words == 0).all(), residue
     assert lib.check_errors() == 0
     del graph
     lib.close()
