@@ -502,6 +502,13 @@ void k_attn_direct(const DirectArgs a) {
               }
             }
           }
+          // A round that is not full reads its last part several times, with weights of zero for all but one.  If that
+          // part holds an infinity, or any other, the sum is made once more part by part.
+          if (!(fmaf(A.x, 0.f, fmaf(A.y, 0.f, fmaf(A.z, 0.f, A.w * 0.f))) == 0.f)) {
+            A = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int32_t s = np * sub / nsub; s < s_end; ++s)
+              axpy(A, __builtin_amdgcn_exp2f(get2(parts, part0 + s * step + HD * 4).x - M), get4(parts, part0 + d0 * 4, s * step));
+          }
           if (nsub == 1) {
             finish(c, M, L, A);
           } else {

@@ -190,6 +190,27 @@ def test_the_allocation_free_call_replays_from_a_graph(ctx, part):
     lib.close()
 
 
+@pytest.mark.parametrize("dtype,hq,hkv,d", [(I.DTYPE_F16, 4, 4, 128), (I.DTYPE_F16, 6, 2, 64), (I.DTYPE_F32, 3, 3, 64)])
+def test_an_infinite_value_gives_an_infinite_output_where_parts_are_merged(dtype, hq, hkv, d):
+    """Values beyond the type's range are stored as infinities.  One in a sequence's last part makes its dim infinite, as in
+    the oracle, and leaves the others alone: parts that fill up the last round of the merge must not touch it."""
+    ctx = np.asarray([1500, 700, 1100, 65], np.int32)
+    w = I.Workload("inf", 1, len(ctx), hq, hkv, d, dtype, value_scale=0.3, seed=41)
+    case = I.make_case(w, ctx_lens=ctx)
+    for b, c in enumerate(ctx):
+        case.k_dense[b][0, c - 1] = 0                    # a weight far from vanishing
+        case.v_dense[b][0, c - 1, :, 5] = np.inf
+        case.v_dense[b][0, c - 1, :, 38] = -np.inf
+    lib, mod, table = GH.make_pools(case, int(case.n_blocks.sum()), 0, 0)
+    q, K, V = H.dense_f64(case, 0)
+    got, ref = run_attn(lib, case, table), A.dense_attention(q, K, V, case.ctx_lens)
+    assert (ref[:, :, 5] == np.inf).all() and (ref[:, :, 38] == -np.inf).all()
+    assert (got[:, :, 5] == np.inf).all() and (got[:, :, 38] == -np.inf).all()
+    fine = [i for i in range(d) if i not in (5, 38)]
+    check(got[:, :, fine], ref[:, :, fine], dtype)
+    lib.close()
+
+
 def test_what_an_overlap_left_in_the_arrival_words_does_not_reach_later_calls():
     """Calls that overlap on one pool, which they must not, can leave the words that count a sequence's finished parts at
     any count of a launch enqueued before.  Words planted so: the next call, and a captured call at every replay, give the
