@@ -616,7 +616,9 @@ bool attn_direct(const pie_pool* p, int32_t batch, int32_t max_blocks) { return 
 // and 3 585, 32 layers 7 100 and 7 098).  Without grouping it does not (64 sequences of 1 024 to 2 048, 32 heads, 32
 // layers 8 041 and 8 101, with host blocks 8 155 and 8 329; 40 of 300 to 1 700, 40 heads, 32 layers 4 624 and 4 644), and
 // fewer, longer parts have fewer weights of exactly one, so that rounding the weights to f16 costs more (2.24e-4 from 64
-// bits against 2.19e-4): those steps stay planned.
+// bits against 2.19e-4): those steps stay planned.  The other kinds of step store a layer's rows ahead of its launch:
+// layers that move, as above with grouping, 8 layers 1 808 and 1 785 us, 16 layers 3 703 and 3 580, 32 layers 7 169 and
+// 7 094; where each launch worked the split out for itself they took 1 862, 3 818 and 7 538.
 int attn_step_path(const pie_pool* p, int32_t n_layers, int32_t batch, int32_t max_blocks) {
   if (!attn_direct(p, batch, max_blocks)) return kStepPlanned;
   const int64_t pairs = (int64_t)batch * p->cfg.n_kv_heads;

@@ -210,3 +210,51 @@ def test_adaptive_expansion_in_layers_on_hardware():
         lp.close()
         inner.close()
         ref.close()
+
+
+def test_full_batches_on_layers_that_move_and_on_growing_caches_match_the_all_resident_pool():
+    """More than three (sequence, kv head) pairs per compute unit, grouped queries, eight layers or more: the layers are one
+    launch each with the rows stored apart and start from the first layers' split.  Three tokens with layers on their way
+    to the CPU and back, and on caches that can grow: the bits and the stored rows of the pool that holds all layers."""
+    from test_gpu_attention import _noise_pool
+    n, gpu, host, on_host, hq, hkv, d, dt = 9, 7, 4, [7, 8], 16, 8, 64, I.DTYPE_BF16
+    ctx = (20 + np.arange(97) * 13 % 180).astype(np.int32) // 16 * 16 + 3      # room for the tokens that follow
+    ref, q, k, v, tb, cl = _noise_pool(n, hq, hkv, d, dt, ctx, 400, 6)
+    nb, blocks = ref.cfg.n_gpu_blocks, -(-ref.cfg.n_gpu_blocks // 64) * 64
+    inner = B.Pool(gpu, hq, hkv, d, 16, dt, nb, 0, 0, max_batch=len(ctx), max_blocks_per_seq=400, device=GH.DEV)
+    inner.block_alloc(B.GPU, nb)
+    lp = B.LayerPool(inner, n, host, on_host)
+    grow = B.Pool(n, hq, hkv, d, 16, dt, blocks, 0, 0, max_batch=len(ctx), max_blocks_per_seq=400, device=GH.DEV)
+    img = ref.gpu_image()
+    for l in range(n):
+        lp.layer_image(l).copy_(img[l])
+    grow.gpu_image()[:, :nb].copy_(img)
+    ep = B.ElasticPool(grow, 64, 2 * (blocks // 64), 2)
+    torch.cuda.synchronize()
+    s = [torch.cuda.Stream() for _ in range(3)]
+    none = np.zeros(0, dtype=np.int32)
+    try:
+        for token in range(3):
+            outs = [torch.full_like(q, float("nan")) for _ in range(3)]
+            ref.step(q, k, v, tb, cl, none, none, outs[0], *s)
+            ref.sync()
+            lp.step(q, k, v, tb, cl, outs[1], *s)
+            inner.sync()
+            ep.step(q, k, v, tb, cl, outs[2], *s)
+            grow.sync()
+            assert ref.check_errors() == 0 and inner.check_errors() == 0 and grow.check_errors() == 0
+            assert torch.isfinite(outs[0].float()).all()
+            for out in outs[1:]:
+                assert torch.equal(out.view(torch.int16), outs[0].view(torch.int16)), token
+            cl += 1
+            q, k, v = v.repeat(1, 1, hq // hkv, 1), k.flip(0), v.flip(1)
+        lp.settle()
+        for l in range(n):
+            assert torch.equal(lp.layer_image(l).cpu(), ref.gpu_image()[l].cpu()), l
+        assert torch.equal(grow.gpu_image()[:, :nb], ref.gpu_image())
+    finally:
+        ep.close()
+        grow.close()
+        lp.close()
+        inner.close()
+        ref.close()
