@@ -6,6 +6,7 @@
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
+#include "pie_attn_split.h"
 #include "pie_internal.h"
 
 namespace pie {
@@ -133,8 +134,6 @@ __device__ __forceinline__ int32_t append_slot(int32_t handle, const int32_t* __
   return take ? slot : -1;
 }
 
-constexpr int kWaves = 4;
-constexpr int kBlockTokens = 16;
 constexpr int kMaxGroup = 16;         // query heads per kv head the matrix-core kernels handle (their 16 columns)
 constexpr float kNegBig = -1.0e30f;   // finite stand-in for -inf as the initial running max
 

@@ -175,18 +175,11 @@ __device__ __forceinline__ float head_sum(float x) {
   return x;
 }
 
-// ceil(x / y) for 0 <= x, 1 <= y, x + y < 2^20, exactly: half a unit keeps the quotient off the integers by more than
-// the reciprocal's error.
-__device__ __forceinline__ int32_t div_up(int32_t x, int32_t y) {
-  return (int32_t)(((float)(x + y - 1) + 0.5f) * __builtin_amdgcn_rcpf((float)y));
-}
+struct FastRcp {
+  __device__ __forceinline__ float operator()(float y) const { return __builtin_amdgcn_rcpf(y); }
+};
 
-constexpr int kDirectLaneSeqs = 4;               // sequences per lane in the split
-constexpr int kDirectSeqs = 64 * kDirectLaneSeqs;
-constexpr int kDirectRows = 16384;               // partial states (unit, head of the group) there is room for
-constexpr int kDirectMaxUnits = 4096;
-static_assert(kDirectMaxUnits <= kArriveWords && kDirectMaxUnits <= kClockWgs, "a word per (sequence, head), a pair per workgroup");
-constexpr int kDirectMaxQuanta = 64;             // blocks per wave and unit: the slot list has a lane each
+constexpr int kDirectLaneSeqs = kDirectSeqs / 64;   // sequences per lane in the split
 
 // A step's layers share the split and, per staging region, the slots: the first layer of each region leaves what it
 // worked out for every item, and the others start from that, one access deep instead of four.  Where every layer has a
@@ -200,7 +193,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(W::kWav
 void k_attn_direct(const DirectArgs a) {
   using E = typename W::E;
   constexpr int HD = W::HD, NL = W::NL, EB = W::EB;
-  constexpr int NT = NW * 64, QUANTUM = NW * kBlockTokens;
+  constexpr int NT = NW * 64;
+  static_assert(NW == kWaves, "the split is in quanta of so many waves");
   constexpr int TILE_BYTES = kBlockTokens * HD * EB;
   constexpr int ROW = HD + 4;                     // padded LDS row of one head's accumulator
   constexpr int TPH = HD / 4;                     // threads per head when states are merged, four dims each
@@ -242,7 +236,7 @@ void k_attn_direct(const DirectArgs a) {
           const int32_t full = clamp_ctx(raw, a.max_blocks);
           if (raw > full && blockIdx.x == 0) atomicOr(a.err, PIE_DEVERR_BAD_HANDLE);
           c4[i] = full > minus ? full - minus : 0;
-          q4[i] = c4[i] > 0 ? (c4[i] + QUANTUM - 1) / QUANTUM : 1;
+          q4[i] = quanta_of(c4[i]);
         }
         total += wave_sum(q4[i]);
       }
@@ -261,26 +255,23 @@ void k_attn_direct(const DirectArgs a) {
       }
       if (tid == 0) a.hdr[1] = size;
     }
-    // quanta per part: the smallest that keeps the parts of all sequences within max_items
     auto items_of = [&](int32_t k) {
       int32_t n = 0;
 #pragma unroll
       for (int i = 0; i < kDirectLaneSeqs; ++i)
-        if (64 * i < a.batch) n += div_up(q4[i], k);   // (0 beyond the batch)
+        if (64 * i < a.batch) n += div_up(q4[i], k, FastRcp());   // (0 beyond the batch)
       return wave_sum(n);
     };
-    int32_t k = (total + a.max_items - 1) / a.max_items;
-    while (k < kDirectMaxQuanta && items_of(k) > a.max_items) k += 1 + k / 8;
-    if (k > kDirectMaxQuanta) k = kDirectMaxQuanta;
+    const int32_t k = quanta_per_part(total, a.max_items, items_of);
     int32_t n_items = 0;
 #pragma unroll
     for (int i = 0; i < kDirectLaneSeqs; ++i) {
       n4[i] = k4[i] = end4[i] = 0;
       if (64 * i < a.batch) {
-        if (q4[i] > 0) {                            // parts of a sequence as equal as whole quanta allow
-          const int32_t n = div_up(q4[i], k);
-          k4[i] = div_up(q4[i], n);
-          n4[i] = div_up(q4[i], k4[i]);
+        if (q4[i] > 0) {
+          const SeqParts parts = seq_parts(q4[i], k, FastRcp());
+          k4[i] = parts.each;
+          n4[i] = parts.n;
         }
         end4[i] = n_items + wave_scan(n4[i]);       // items up to and including the lane's sequence
         n_items = __builtin_amdgcn_readlane(end4[i], 63);
@@ -304,8 +295,8 @@ void k_attn_direct(const DirectArgs a) {
         }
     first = end - np;
     part = item - first;
-    tok0 = part * kq * QUANTUM;
-    tok1 = min(ctx_b, tok0 + kq * QUANTUM);         // <= tok0 only for an empty sequence
+    tok0 = part * kq * kQuantum;
+    tok1 = min(ctx_b, tok0 + kq * kQuantum);         // <= tok0 only for an empty sequence
     if (item >= n_items) b = -1;
     // The plan lists the items by size, largest first, so that the layers that start from it spread the large parts over
     // the compute units and end on small ones: 639 -> 617 us for 16 layers of 24 sequences of 100 to 1 100 tokens.
@@ -557,49 +548,20 @@ void k_attn_direct(const DirectArgs a) {
 
 // Its scratch in a pool: the parts, then the items' records and slot lists of the two staging regions, for as many units
 // as the pool's largest batch and widest table can make (a call's own scratch has room for any).
-static size_t pool_items(const pie_config& c) {
-  const size_t most = (size_t)kDirectMaxUnits / c.n_kv_heads + 1;
-  const size_t pool = (size_t)c.max_batch * (((size_t)c.max_blocks_per_seq + kWaves - 1) / kWaves) + 1;
-  return pool < most ? pool : most;
-}
-static size_t parts_floats(const pie_config& c) {
-  const size_t rows = pool_items(c) * c.n_q_heads;
-  return (rows < (size_t)kDirectRows ? rows : (size_t)kDirectRows) * (c.head_dim + 4);
-}
-static size_t plan_region_ints(const pie_config& c) { return pool_items(c) * kPlanInts; }
-size_t attn_arrive_words(const pie_config& c) {
-  const size_t pairs = (size_t)c.max_batch * c.n_kv_heads;
-  return pairs < (size_t)kArriveWords ? pairs : (size_t)kArriveWords;
-}
+static size_t parts_floats(const pie_config& c) { return direct_pool_rows(c) * (c.head_dim + 4); }
+static size_t plan_region_ints(const pie_config& c) { return direct_pool_items(c) * kPlanInts; }
+size_t attn_arrive_words(const pie_config& c) { return direct_pool_words(c); }
 size_t attn_direct_floats(const pie_config& c) { return parts_floats(c) + 2 * plan_region_ints(c); }
 
 // How many units the split of a call may make; 0: the call is left to the planned path, which has what this one lacks -
 // an item size set by the caller, the vector-ALU variant, fp32 with grouped queries (every query head reads the keys
 // and values again: many small items share them in the caches, 80 us against 95 to 104 for six sequences of 100 to
 // 4 000 tokens, 32 heads over 8), more sequences than the in-kernel split covers - or for which the units do not fit.
-// Otherwise: as few units as hold every (sequence, kv head) pair and the longest context the table can name, in steps
-// of the compute units.  One workgroup a compute unit streams as fast as two or three, and every part more has to be
-// stored, counted and merged: one sequence of 32 749 tokens, 64 heads over 8, takes 33.0 us at one unit per compute
-// unit, 37.6 at three, 44.1 at six (6 us of each an event behind the call).  Beyond one, three workgroups are resident
-// per compute unit, so multiples of three (64 sequences of 500 to 2 500 tokens, 32 heads over 8: 77.6 / 72.8 / 74.9 us
-// at two / three / six); short contexts want few (60 of 60 to 300 tokens, 32 heads, a step of 8 layers: 325 us at nine,
-// 379 at fifteen).
 static int32_t direct_max_units(const pie_pool* p, int32_t batch, int32_t max_blocks) {
-  if (p->attn_partition > 0 || p->attn_valu) return 0;
-  if (batch < 1 || batch > kDirectSeqs || max_blocks < 1) return 0;
   const pie_config& c = p->cfg;
-  const int64_t group = c.n_q_heads / c.n_kv_heads, tokens = (int64_t)max_blocks * kBlockTokens;
-  if (c.dtype == PIE_DTYPE_F32 && group > 1) return 0;
-  const int64_t longest = (int64_t)kDirectMaxQuanta * kWaves * kBlockTokens;
-  const int64_t least = batch * ((tokens + longest - 1) / longest) * c.n_kv_heads;
-  int64_t room = kDirectRows / group;
-  if (room > kDirectMaxUnits) room = kDirectMaxUnits;
-  if (least > room) return 0;
-  for (const int per_cu : {1, 3, 6, 9, 15}) {
-    const int64_t units = (int64_t)per_cu * p->n_cu;
-    if (units >= least && units <= room) return (int32_t)units;
-  }
-  return (int32_t)room;
+  const int32_t group = c.n_q_heads / c.n_kv_heads;
+  if (p->attn_partition > 0 || p->attn_valu || (c.dtype == PIE_DTYPE_F32 && group > 1)) return 0;
+  return direct_units(p->n_cu, c.n_kv_heads, group, batch, max_blocks);
 }
 
 bool attn_direct(const pie_pool* p, int32_t batch, int32_t max_blocks) { return direct_max_units(p, batch, max_blocks) > 0; }
@@ -700,10 +662,7 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   a.min_units = batch * second * H > attn_min_units(p) ? attn_min_units(p) : 0;
   a.max_items = max_units / H;
   a.append = append;
-  // no more workgroups than the widest context the table can hold makes units
-  const int32_t quanta = (max_blocks + kWaves - 1) / kWaves;
-  const int64_t most = (int64_t)batch * quanta * H;
-  const int32_t grid = most < max_units ? (int32_t)most : max_units;
+  const int32_t grid = direct_grid(max_units, H, batch, max_blocks);
   a.clock = clock_row;
   a.clock_wg = nullptr;
   if (clock_row && grid <= kClockWgs) {

@@ -1,0 +1,93 @@
+// How the one-launch attention cuts a call into units, and the scratch that takes: arithmetic alone, for the kernel, for
+// what launches it and for a test that runs it on the CPU over its whole range.
+//
+// A unit is one part of one sequence for one kv head, a workgroup's work.  A part is k quanta, a quantum one pass of the
+// workgroup's waves over a block each; an item is a part for all kv heads.
+#pragma once
+
+#include "pie_internal.h"
+
+namespace pie {
+
+constexpr int kWaves = 4;
+constexpr int kBlockTokens = 16;
+constexpr int kQuantum = kWaves * kBlockTokens;
+constexpr int kDirectSeqs = 256;                 // sequences the kernel splits: four to a lane
+constexpr int kDirectRows = 16384;               // partial states (unit, head of the group) there is room for
+constexpr int kDirectMaxUnits = 4096;
+constexpr int kDirectMaxQuanta = 64;             // per part: a wave's list of slots has a lane for each
+static_assert(kDirectMaxUnits <= kArriveWords && kDirectMaxUnits <= kClockWgs, "a word per (sequence, head), a pair per workgroup");
+
+// ---- on the host: units of a call, scratch of a pool ---------------------------------------------------------
+
+// How many units the split of a call may make; 0: they do not fit.  As few as hold every (sequence, kv head) pair and the
+// longest context the table can name, in steps of the compute units.  One workgroup a compute unit streams as fast as two
+// or three, and every part more has to be stored, counted and merged: one sequence of 32 749 tokens, 64 heads over 8,
+// takes 33.0 us at one unit per compute unit, 37.6 at three, 44.1 at six (6 us of each an event behind the call).  Beyond
+// one, three workgroups are resident per compute unit, so multiples of three (64 sequences of 500 to 2 500 tokens, 32
+// heads over 8: 77.6 / 72.8 / 74.9 us at two / three / six); short contexts want few (60 of 60 to 300 tokens, 32 heads, a
+// step of 8 layers: 325 us at nine, 379 at fifteen).
+inline int32_t direct_units(int32_t n_cu, int32_t n_kv_heads, int32_t group, int32_t batch, int32_t max_blocks) {
+  if (batch < 1 || batch > kDirectSeqs || max_blocks < 1) return 0;
+  const int64_t tokens = (int64_t)max_blocks * kBlockTokens, longest = (int64_t)kDirectMaxQuanta * kQuantum;
+  const int64_t least = batch * ((tokens + longest - 1) / longest) * n_kv_heads;
+  int64_t room = kDirectRows / group;
+  if (room > kDirectMaxUnits) room = kDirectMaxUnits;
+  if (least > room) return 0;
+  for (const int per_cu : {1, 3, 6, 9, 15}) {
+    const int64_t units = (int64_t)per_cu * n_cu;
+    if (units >= least && units <= room) return (int32_t)units;
+  }
+  return (int32_t)room;
+}
+// no more workgroups than the widest context the table can hold makes units
+inline int32_t direct_grid(int32_t units, int32_t n_kv_heads, int32_t batch, int32_t max_blocks) {
+  const int64_t most = (int64_t)batch * ((max_blocks + kWaves - 1) / kWaves) * n_kv_heads;
+  return most < units ? (int32_t)most : units;
+}
+// Items, partial states and arrival words a pool has room for: as many as its largest batch and widest table can make.
+inline size_t direct_pool_items(const pie_config& c) {
+  const size_t most = (size_t)kDirectMaxUnits / c.n_kv_heads + 1;
+  const size_t pool = (size_t)c.max_batch * (((size_t)c.max_blocks_per_seq + kWaves - 1) / kWaves) + 1;
+  return pool < most ? pool : most;
+}
+inline size_t direct_pool_rows(const pie_config& c) {
+  const size_t rows = direct_pool_items(c) * c.n_q_heads;
+  return rows < (size_t)kDirectRows ? rows : (size_t)kDirectRows;
+}
+inline size_t direct_pool_words(const pie_config& c) {
+  const size_t pairs = (size_t)c.max_batch * c.n_kv_heads;
+  return pairs < (size_t)kArriveWords ? pairs : (size_t)kArriveWords;
+}
+
+// ---- in the kernel: the split --------------------------------------------------------------------------------
+// rcp: the reciprocal of a float, to within one unit in its last place.
+
+// ceil(x / y) for 0 <= x, 1 <= y, x + y < 2^20, exactly: half a unit keeps the quotient off the integers by more than
+// the reciprocal's error.
+template <class Rcp>
+__host__ __device__ inline int32_t div_up(int32_t x, int32_t y, Rcp rcp) {
+  return (int32_t)(((float)(x + y - 1) + 0.5f) * rcp((float)y));
+}
+
+// quanta of a context, at least one
+__host__ __device__ inline int32_t quanta_of(int32_t ctx) { return ctx > 0 ? (ctx + kQuantum - 1) / kQuantum : 1; }
+
+// Quanta per part: within an eighth of the smallest number that keeps the parts of all sequences within max_items.
+// total: the quanta of all sequences; items_of(k): the parts they make at k quanta each.
+template <class ItemsOf>
+__host__ __device__ inline int32_t quanta_per_part(int32_t total, int32_t max_items, ItemsOf items_of) {
+  int32_t k = (total + max_items - 1) / max_items;
+  while (k < kDirectMaxQuanta && items_of(k) > max_items) k += 1 + k / 8;
+  return k < kDirectMaxQuanta ? k : kDirectMaxQuanta;
+}
+
+// A sequence of q quanta in parts of at most k, as equal as whole quanta allow: n parts of `each`, the last of what is left.
+struct SeqParts { int32_t n, each; };
+template <class Rcp>
+__host__ __device__ inline SeqParts seq_parts(int32_t q, int32_t k, Rcp rcp) {
+  const int32_t each = div_up(q, div_up(q, k, rcp), rcp);
+  return {div_up(q, each, rcp), each};
+}
+
+}  // namespace pie

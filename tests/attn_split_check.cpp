@@ -1,0 +1,99 @@
+// The one-launch attention's split and the sizes of its scratch (csrc/pie_attn_split.h, the header the kernel and its
+// launcher use), run on the CPU: for random calls on random pools every part, plan record, arrival word and workgroup is
+// in range and the parts cover every context exactly once, whichever way the reciprocal's last place falls.  Built and
+// run by tests/test_attn_split_host.py.  Prints "split ok" and exits 0.
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <random>
+#include <vector>
+#include "pie_attn_split.h"
+using namespace pie;
+#define REQUIRE(c) do { if (!(c)) { printf("FAILED line %d: %s\n", __LINE__, #c); exit(1); } } while (0)
+
+static std::mt19937_64 rng(1);
+static int32_t ri(int64_t lo, int64_t hi) { return (int32_t)(lo + (int64_t)(rng() % (uint64_t)(hi - lo + 1))); }
+template <size_t N> static int32_t pick(const int32_t (&v)[N]) { return v[rng() % N]; }
+
+struct Rcp {                                     // the correctly rounded reciprocal, or a neighbour
+  int ulp;
+  float operator()(float y) const {
+    const float r = 1.0f / y;
+    return ulp ? std::nextafter(r, ulp > 0 ? 2.0f : 0.0f) : r;
+  }
+};
+
+static void check_div_up() {
+  const int32_t end = 1 << 20;
+  auto same = [](int32_t x, int32_t y) {
+    for (const int ulp : {-1, 0, 1}) REQUIRE(div_up(x, y, Rcp{ulp}) == (x + y - 1) / y);
+  };
+  for (int32_t y = 1; y < end; y = y < 5000 ? y + 1 : y + ri(1, 997)) {
+    const int32_t top = end - 1 - y;             // x + y < 2^20
+    same(0, y);
+    same(top, y);
+    for (int i = 0; i < 24; ++i) {
+      const int32_t m = (int32_t)((int64_t)y * ri(0, top / y));   // multiples and their neighbours, where it turns over
+      for (int32_t x = m - 1; x <= m + 1; ++x)
+        if (x >= 0 && x <= top) same(x, y);
+    }
+    same(ri(0, top), y);
+  }
+}
+
+static bool check_call() {
+  pie_config c; memset(&c, 0, sizeof c);
+  c.n_kv_heads = pick({1, 2, 3, 4, 8, 12, 16, 32, 40, 64, 300});
+  const int32_t group = pick({1, 2, 3, 4, 7, 8, 16}), n_cu = pick({32, 64, 128, 256, 304});
+  c.n_q_heads = c.n_kv_heads * group;
+  c.max_batch = ri(1, 400);
+  c.max_blocks_per_seq = (int32_t)std::exp2(std::uniform_real_distribution<double>(0, ri(0, 3) ? 10 : 19)(rng));
+  const int32_t batch = ri(1, c.max_batch), width = ri(0, 1) ? ri(1, c.max_blocks_per_seq) : c.max_blocks_per_seq;
+  const int32_t H = c.n_kv_heads;
+  const int32_t units = direct_units(n_cu, H, group, batch, width);
+  if (units == 0) return false;
+  REQUIRE(batch <= kDirectSeqs && units <= kDirectMaxUnits && (int64_t)units * group <= kDirectRows);
+  const int32_t grid = direct_grid(units, H, batch, width), max_items = units / H;
+  std::vector<int32_t> ctx(batch);
+  const int kind = ri(0, 3);
+  int32_t total = 0;
+  for (int32_t& x : ctx) {
+    const int32_t most = width * kBlockTokens;
+    x = kind == 0 ? most : kind == 1 ? ri(0, most) : kind == 2 ? ri(0, std::min(most, 200)) : ri(0, 7) ? ri(0, std::min(most, 64)) : most;
+    total += quanta_of(x);
+  }
+  const Rcp rcp{ri(-1, 1)};
+  const int32_t k = quanta_per_part(total, max_items, [&](int32_t q) {
+    int32_t n = 0;
+    for (const int32_t x : ctx) n += div_up(quanta_of(x), q, rcp);
+    return n;
+  });
+  REQUIRE(k >= 1 && k <= kDirectMaxQuanta);
+  int32_t items = 0;
+  for (const int32_t x : ctx) {
+    const SeqParts p = seq_parts(quanta_of(x), k, rcp);
+    REQUIRE(p.n >= 1 && p.each >= 1 && p.each <= kDirectMaxQuanta);          // a lane of the slot list for every block of a wave
+    REQUIRE((int64_t)p.n * p.each * kQuantum >= x);                          // the parts reach the end
+    REQUIRE((int64_t)(p.n - 1) * p.each * kQuantum < std::max(x, 1));        // and none lies beyond it
+    REQUIRE(p.n < (1 << kArriveShift));                                      // what an arrival word counts
+    items += p.n;
+  }
+  REQUIRE(items <= max_items);
+  REQUIRE((int64_t)items * H <= grid);                                       // a workgroup for every unit
+  REQUIRE((size_t)items * c.n_q_heads <= direct_pool_rows(c));               // a partial state for every row of every part
+  REQUIRE((size_t)items * c.n_q_heads <= (size_t)kDirectRows);               // (also in a call's own scratch)
+  REQUIRE((size_t)((grid - 1) / H) < direct_pool_items(c));                  // a record for every place, used or not
+  REQUIRE((size_t)batch * H <= direct_pool_words(c));                        // a word for every (sequence, head)
+  REQUIRE(batch * H <= kArriveWords && grid <= kClockWgs);
+  return true;
+}
+
+int main() {
+  check_div_up();
+  int taken = 0;
+  for (int i = 0; i < 60000; ++i) taken += check_call() ? 1 : 0;
+  REQUIRE(taken > 5000);
+  printf("split ok (%d calls)\n", taken);
+  return 0;
+}
