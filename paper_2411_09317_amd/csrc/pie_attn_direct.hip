@@ -36,7 +36,7 @@ struct DirectArgs {
   uint64_t launch;           // this launch's number << kArriveShift
   int32_t* hdr;              // plan header, to note the nominal item size in, or NULL
   int32_t* plan;             // records and slot lists of the items (kPlan*): written, or with REPLAY read; or NULL
-  unsigned long long* clock;    // as in AttnArgs
+  unsigned long long* clock;    // the layer's row of the clock table and its workgroups' pairs, or NULL
   unsigned long long* clock_wg;
   size_t block_bytes;
   int32_t ws_bytes;
@@ -531,16 +531,9 @@ void k_attn_direct(const DirectArgs a) {
     a.plan[(size_t)at * kPlanInts + tid] = x;
   }
   if (a.clock && tid == 0) {
-    const unsigned long long t = wall_clock64();
-    if (a.clock_wg) {
-      a.clock_wg[2 * blockIdx.x] = t_start;
-      a.clock_wg[2 * blockIdx.x + 1] = t;
-      if (blockIdx.x == 0) a.clock[kClockGrid] = gridDim.x;
-    } else {
-      atomicMin(&a.clock[kClockKernelStart], t_start);
-      atomicMax(&a.clock[kClockKernelEnd], t);
-      atomicMax(&a.clock[kClockLayerEnd], t);
-    }
+    a.clock_wg[2 * blockIdx.x] = t_start;
+    a.clock_wg[2 * blockIdx.x + 1] = wall_clock64();
+    if (blockIdx.x == 0) a.clock[kClockGrid] = gridDim.x;
   }
 }
 
@@ -665,7 +658,7 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   const int32_t grid = direct_grid(max_units, H, batch, max_blocks);
   a.clock = clock_row;
   a.clock_wg = nullptr;
-  if (clock_row && grid <= kClockWgs) {
+  if (clock_row) {                                // (a pair for every workgroup: kDirectMaxUnits <= kClockWgs)
     const size_t row = (size_t)(clock_row - p->d_clock) / kClockRow;
     a.clock_wg = p->d_clock + ((size_t)c.n_layers + 1) * kClockRow + row * kClockWgs * 2;
   }
