@@ -27,6 +27,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
+PROBE_ORDER = "the tiles a layer reads, in the planned path's items and order (k_attn_direct cuts and orders them otherwise)"
 LINK_PEAK_GBS = 63.0           # PCIe Gen5 x16, per direction, before protocol overhead
 
 
@@ -285,13 +286,15 @@ def roofline_of(w, dw, streams, steps, warmup):
     assert dw.pool.check_errors() == 0
     k_ms = float(np.mean(prof["kernel"]))
     achieved = dw.kv_bytes_per_layer / (k_ms * 1e-3) / 1e9
-    traffic, source = traffic_from_profile(f"attn_decode_{w.name}_pmc.txt")
+    kernel = dw.pool.step_attn_kernel(w.batch, dw.table.shape[1])
+    traffic, source = traffic_from_profile(f"attn_decode_{w.name}_pmc.txt", kernel)
     res = {"tokens_per_s": w.batch / s, "ms_per_step": s * 1e3, "layers": w.n_layers,
            "attn_partition_tokens": dw.pool.attn_partition(),
-           "roofline": {"bound": "hbm", "kernel": "k_attn_direct", "achieved": achieved, "peak": HBM_PEAK_GBS,
+           "roofline": {"bound": "hbm", "kernel": kernel, "achieved": achieved, "peak": HBM_PEAK_GBS,
                         "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": source,
                         "kernel_ms": k_ms, "algorithmic_bytes_per_launch": dw.kv_bytes_per_layer,
-                        "stream_probe_ms": probe_ms, "frac_of_stream_probe": probe_ms / k_ms}}
+                        "stream_probe_ms": probe_ms, "frac_of_stream_probe": probe_ms / k_ms,
+                        "stream_probe_order": PROBE_ORDER}}
     return res, prof["kernel"].copy(), s * 1e3, achieved
 
 
@@ -463,12 +466,13 @@ def layer_fifo_leg(w, dw, m, n_steps, t_other_us, base_step_ms):
     return res
 
 
-def traffic_from_profile(name):
+def traffic_from_profile(name, kernel):
     """HBM bytes per launch measured with rocprofv3 counters, as a committed summary states them: (bytes, where
     that number comes from).  It is a figure from an earlier, separate profiler run of the same command (counters
-    cannot be collected inside this run), so the line names the file and its date beside it."""
+    cannot be collected inside this run), so the line names the file and its date beside it.  None where the file is
+    about another kernel than the one that ran here."""
     path = os.path.join(ROOT, "profiles", name)
-    if not os.path.exists(path):
+    if not os.path.exists(path) or f": {kernel} " not in open(path).readline():
         return None, None
     for line in open(path):
         if line.startswith("traffic_bytes_per_launch"):
@@ -832,6 +836,8 @@ def main():
     dw.pool.set_swap_path(args.swap_path)
     if args.attn_vector_alu:
         dw.pool.set_attn_vector_alu(True)
+    kernel = dw.pool.step_attn_kernel(w.batch, dw.table.shape[1])
+    traffic, traffic_source = traffic_from_profile(f"attn_decode_{w.name}_pmc.txt", kernel)
     if args.swap_wgs:
         dw.pool.set_swap_workgroups(args.swap_wgs)
     streams = (torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.Stream())
@@ -890,14 +896,12 @@ def main():
                                                                    "slowdown) and inflation_e2e (step time, waits "
                                                                    "included) in swap, swap_below_knee, swap_kernel.*, "
                                                                    "cfg4.fixed_fraction[], cfg5.overflow_on_host"}},
-        "roofline": {"bound": "hbm", "kernel": "k_attn_decode_mfma" if args.partition or args.attn_vector_alu else
-                     "k_attn_direct", "achieved": achieved, "peak": HBM_PEAK_GBS,
+        "roofline": {"bound": "hbm", "kernel": kernel, "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": traffic_from_profile(f"attn_decode_{w.name}_pmc.txt")[0],
-                     "traffic_source": traffic_from_profile(f"attn_decode_{w.name}_pmc.txt")[1],
+                     "traffic": traffic, "traffic_source": traffic_source,
                      "kernel_ms": k_ms, "algorithmic_bytes_per_launch": bytes_layer,
                      "stream_probe_ms": probe_ms, "stream_probe_GBps": bytes_layer / (probe_ms * 1e-3) / 1e9,
-                     "frac_of_stream_probe": probe_ms / k_ms},
+                     "frac_of_stream_probe": probe_ms / k_ms, "stream_probe_order": PROBE_ORDER},
         "per_layer_ms": {"attn_total": float(np.mean(prof["attn"])), "attn_kernel": k_ms,
                          "step_ms_events": prof["step_ms"],
                          "single_step_ms_p10_p50_p90": [p10, p50, p90]},

@@ -264,8 +264,9 @@ int pie_attn_decode_static(pie_pool* pool, int32_t layer, const void* d_q,
                            const int32_t* d_ctx_lens, int32_t batch,
                            void* d_out, void* stream);
 
-/* Calibration for the roofline of pie_attn_decode: reads exactly the K and V tiles that pie_attn_decode would
- * read for this layer, batch and table - same work items, same order, same loads - and discards them.
+/* Calibration for the roofline of the attention: reads exactly the K and V tiles that pie_attn_decode would read for
+ * this layer, batch and table, and discards them - same loads, in the work items and the order of the planned path
+ * (a call that runs as one launch cuts the contexts and orders the parts otherwise).
  * Waits for it and returns the kernel's duration in *out_ms (events around the launch on `stream`): the rate
  * at which this access pattern can stream from HBM at all. */
 int pie_attn_stream_probe_sync(pie_pool* pool, int32_t layer, const int32_t* d_block_table, int32_t max_blocks,
@@ -295,6 +296,13 @@ int pie_step(pie_pool* pool, const void* d_q_all, const void* d_k_new, const voi
              const int32_t* d_block_table, int32_t max_blocks, const int32_t* d_ctx_lens, int32_t batch,
              int32_t n_prefetch, const int32_t* h_prefetch, int32_t n_dirty, const int32_t* h_dirty,
              void* d_out_all, void* compute_stream, void* swap_in_stream, void* swap_out_stream);
+
+/* The name of the kernel that runs a layer's attention in a step of n_layers layers over `batch` sequences under a
+ * table of `max_blocks` columns, with the pool's present settings: "k_attn_direct" (one launch a layer),
+ * "k_attn_decode_mfma" or "k_attn_decode_f32" (planned once a step, with a reduction behind each layer).  The same
+ * for pie_step, pie_layer_step and pie_elastic_step.  A static string, NULL for arguments no step takes.  For
+ * measurements that name what they measured. */
+const char* pie_step_attn_kernel(pie_pool* pool, int32_t n_layers, int32_t batch, int32_t max_blocks);
 
 /* Host-homed handles among h_block_table[b][j], j < ceil(ctx/T), without repeats, in ascending order of their
  * host slot (a densely used host pool is then read as one contiguous run); and of those the tail blocks

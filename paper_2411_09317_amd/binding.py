@@ -30,7 +30,7 @@ SYMBOLS = [
     "pie_migrate", "pie_set_host_fraction", "pie_set_swap_path", "pie_set_attn_partition", "pie_get_attn_partition_sync", "pie_set_swap_workgroups",
     "pie_set_layer_compute_us", "pie_set_attn_vector_alu",
     "pie_kv_append", "pie_attn_decode", "pie_attn_decode_static", "pie_attn_stream_probe_sync",
-    "pie_step", "pie_set_async_submit", "pie_step_join_sync", "pie_prefetch_list", "pie_set_timing", "pie_set_cross_step_prefetch", "pie_set_host_presence_check", "pie_pool_sync", "pie_get_stats", "pie_get_layer_times",
+    "pie_step", "pie_step_attn_kernel", "pie_set_async_submit", "pie_step_join_sync", "pie_prefetch_list", "pie_set_timing", "pie_set_cross_step_prefetch", "pie_set_host_presence_check", "pie_pool_sync", "pie_get_stats", "pie_get_layer_times",
     "pie_check_errors_sync", "pie_controller_create", "pie_controller_destroy", "pie_controller_config",
     "pie_controller_observe", "pie_controller_level", "pie_controller_update", "pie_last_hip_error", "pie_strerror",
     "pie_version",
@@ -80,6 +80,7 @@ def _load():
     lib = C.CDLL(LIB_PATH)
     lib.pie_strerror.restype = C.c_char_p
     lib.pie_strerror.argtypes = [C.c_int]
+    lib.pie_step_attn_kernel.restype = C.c_char_p
     return lib
 
 
@@ -295,6 +296,14 @@ class Pool:
                              _dptr(ctx_lens), C.c_int32(B), C.c_int32(len(pf)), _ptr(pf), C.c_int32(len(dt)), _ptr(dt),
                              _dptr(out_all), _stream_ptr(compute_stream), _stream_ptr(swap_in_stream),
                              _stream_ptr(swap_out_stream)), "step")
+
+    def step_attn_kernel(self, batch: int, max_blocks: int, n_layers: Optional[int] = None) -> str:
+        """Name of the kernel that runs a layer's attention in such a step."""
+        name = _lib.pie_step_attn_kernel(self._h, C.c_int32(self.cfg.n_layers if n_layers is None else n_layers),
+                                         C.c_int32(batch), C.c_int32(max_blocks))
+        if name is None:
+            raise PieError(-1, "step_attn_kernel")
+        return name.decode()
 
     # ---- control ---------------------------------------------------------------------------
     def set_async_submit(self, on: bool):

@@ -917,6 +917,13 @@ int pie_attn_stream_probe_sync(pie_pool* p, int32_t layer, const int32_t* d_bloc
   return elapsed(p->lev[layer].k_start, p->lev[layer].k_end, out_ms);
 }
 
+const char* pie_step_attn_kernel(pie_pool* p, int32_t n_layers, int32_t batch, int32_t max_blocks) {
+  if (!p || n_layers < 1 || batch < 1 || max_blocks < 1) return nullptr;
+  if (batch > p->cfg.max_batch || max_blocks > p->cfg.max_blocks_per_seq || submit_drain(p)) return nullptr;
+  if (attn_step_path(p, n_layers, batch, max_blocks) != kStepPlanned) return "k_attn_direct";
+  return p->cfg.dtype == PIE_DTYPE_F32 ? "k_attn_decode_f32" : "k_attn_decode_mfma";
+}
+
 int pie_prefetch_list(pie_pool* p, const int32_t* h_block_table, int32_t max_blocks, const int32_t* h_ctx_lens,
                       int32_t batch, int32_t* out_prefetch, int32_t* out_n_prefetch, int32_t* out_dirty,
                       int32_t* out_n_dirty) {

@@ -31,6 +31,37 @@ def test_library_exports_every_declared_symbol():
     assert B.lib().pie_strerror(-2).decode().startswith("pool")
 
 
+def test_the_kernel_of_a_steps_layers_by_shape_and_settings():
+    """Small steps and big ones with grouped queries from eight layers on: one launch a layer.  What that path lacks, and big
+    steps otherwise: planned.  (A pool without a device counts 256 compute units.)"""
+    def kernel(dtype, hq, hkv, batch, width, layers, **settings):
+        p = B.Pool(2, hq, hkv, 128, 16, dtype, 8, 0, 0, max_batch=512, max_blocks_per_seq=8192, device=None)
+        for name, value in settings.items():
+            getattr(p, name)(value)
+        try:
+            return p.step_attn_kernel(batch, width, layers)
+        finally:
+            p.close()
+    one, planned, f32 = "k_attn_direct", "k_attn_decode_mfma", "k_attn_decode_f32"
+    F32, F16, BF16 = I.DTYPE_F32, I.DTYPE_F16, I.DTYPE_BF16
+    assert kernel(F16, 32, 32, 24, 69, 16) == one                      # 768 pairs
+    assert kernel(F16, 32, 32, 25, 69, 16) == one and kernel(F16, 32, 32, 25, 164, 16) == planned
+    assert kernel(F16, 32, 32, 64, 128, 32) == planned and kernel(F16, 32, 32, 64, 64, 32) == one
+    assert kernel(BF16, 32, 8, 256, 256, 8) == one and kernel(BF16, 32, 8, 256, 256, 7) == planned
+    assert kernel(BF16, 32, 8, 257, 20, 8) == planned                  # more sequences than the split covers
+    assert kernel(F16, 32, 32, 24, 2048, 16) == planned                # units that do not fit
+    assert kernel(BF16, 32, 8, 8, 256, 32, set_attn_partition=512) == planned
+    assert kernel(F16, 32, 32, 8, 64, 32, set_attn_vector_alu=True) == planned
+    assert kernel(F32, 8, 8, 4, 16, 1) == one and kernel(F32, 8, 2, 4, 16, 1) == f32
+    p = host_pool()
+    for bad in ((0, 4), (9, 4), (4, 0), (4, 65)):
+        with pytest.raises(B.PieError):
+            p.step_attn_kernel(*bad)
+    with pytest.raises(B.PieError):
+        p.step_attn_kernel(4, 4, 0)
+    p.close()
+
+
 def host_pool(n_gpu=40, n_stage=16, n_host=24, **kw):
     args = dict(n_layers=3, n_q_heads=4, n_kv_heads=2, head_dim=64, block_tokens=16, dtype=I.DTYPE_F16)
     args.update(kw)
