@@ -612,8 +612,7 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
                        const AttnWork* work, hipEvent_t k_start, hipEvent_t k_end, unsigned long long* clock_row,
                        hipEvent_t done, int32_t plan, bool leave_room) {
   // Three workgroups a compute unit take nearly all its registers, and a gather beside them starts when one ends.  Two,
-  // by the LDS they ask for, leave it room: 8 layers of 24 sequences of 100 to 1 100 tokens, 32 kv heads, 2.3 MB a layer
-  // gathered: 642 -> 594 us; 46 of 555 to 5 000, 8 kv heads, 2.8 MB: 785 -> 764.
+  // by the LDS they ask for, leave it room (step_body says when that pays, with the times).
   const size_t min_lds = leave_room ? (size_t)56 << 10 : 0;
   if (plan != kDirectPlanNone && work) return PIE_EINVAL;   // the plan lies in the pool's scratch, by layer & 1
   const pie_config& c = p->cfg;

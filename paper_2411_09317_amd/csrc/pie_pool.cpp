@@ -1063,9 +1063,14 @@ static int step_body(pie_pool* p, const StepJob& j) {
   auto now_us = [] {
     return std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now().time_since_epoch()).count();
   };
-  // Whether the prefetches go through the gather kernel and are long enough to matter (below about 1 MB a layer they
-  // cost less than the room: 207 -> 217 us for 128 KB a layer of 8 layers of 8 sequences of 500 to 2 500 tokens).
-  const bool leave_room = n_prefetch > 0 && !p->in_on_host[0] && (size_t)n_prefetch * p->block_bytes > ((size_t)1 << 20);
+  // Whether the prefetches go through the gather kernel and are long enough to be worth the room: about as long as a
+  // layer, 2 MB with grouped queries, 1 MB without.  us a step of 8 layers, without the room and with it, by MB a layer:
+  // 46 sequences of 555 to 3 000 tokens, 32 heads over 8: 0.25 552 / 572, 1.0 584 / 605, 1.5 580 / 603, 1.75 589 / 608,
+  // 2.0 618 / 620, 2.25 655 / 648, 2.5 691 / 676, 4.0 913 / 899; 90 such: 1.5 1 078 / 1 103, 2.0 1 115 / 1 108, 2.5
+  // 1 156 / 1 115, 5.0 1 435 / 1 262; 20 such, 64 heads over 8: no difference from 1.5 to 3.0; 24 of 100 to 1 100, 32
+  // heads: 0.25 399 / 396, 0.75 413 / 408, 1.0 412 / 410, 1.25 426 / 418, 1.5 454 / 439, 2.25 560 / 539, 4.0 815 / 791.
+  const size_t long_enough = (size_t)(p->cfg.n_q_heads > p->cfg.n_kv_heads ? 2 : 1) << 20;
+  const bool leave_room = n_prefetch > 0 && !p->in_on_host[0] && (size_t)n_prefetch * p->block_bytes > long_enough;
   double t_free = -1.0, layer_us = -1.0;
   for (int32_t l = 0; l < L; ++l) {
     // The presence check: the layer's staged blocks have arrived (migrations and map updates were waited
