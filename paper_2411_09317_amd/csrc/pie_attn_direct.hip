@@ -180,6 +180,7 @@ struct FastRcp {
 };
 
 constexpr int kDirectLaneSeqs = kDirectSeqs / 64;   // sequences per lane in the split
+constexpr int32_t kEarlyParts = 32;
 
 // A step's layers share the split and, per staging region, the slots: the first layer of each region leaves what it
 // worked out for every item, and the others start from that, one access deep instead of four.  Where every layer has a
@@ -367,6 +368,13 @@ void k_attn_direct(const DirectArgs a) {
         consume(kB, vB, it + 1);
       }
     }
+    // The last arrival leaves its word zero.  What calls that must not overlap have left in it is the number of a launch
+    // that was enqueued before this one: every workgroup puts this launch's in its place before it counts itself.  With
+    // few parts right before (the accesses to a word are served one after another, 10 ns each), with many here, before the
+    // waves' states are merged (the wave's wait for its stores covers it).
+    uint64_t* word = a.arrive + ((size_t)b * H + g) * kArriveStride;
+    if (np > kEarlyParts && wave == NW - 1 && lane == 0)
+      (void)__hip_atomic_fetch_max(word, a.launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     w.to_lds(s_m, s_l, s_acc, ROW, wave, G, lane);
     if (stores) {                                 // rows at or beyond tok1 are masked by index wherever they are read
       char* blk = const_cast<char*>(a.kv_layer) + (size_t)tail * a.block_bytes + (size_t)g * TILE_BYTES;
@@ -440,11 +448,8 @@ void k_attn_direct(const DirectArgs a) {
     if (np > 1) {
       wait_stores();
       __syncthreads();
-      // The last arrival leaves its word zero.  What calls that must not overlap have left in a word is the number of a
-      // launch that was enqueued before this one, which the first arrival here replaces by this launch's.
-      uint64_t* word = a.arrive + ((size_t)b * H + g) * kArriveStride;
       if (tid == 0) {
-        (void)__hip_atomic_fetch_max(word, a.launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (np <= kEarlyParts) (void)__hip_atomic_fetch_max(word, a.launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         s_last = __hip_atomic_fetch_add(word, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
                  a.launch + (uint64_t)(np - 1);
       }

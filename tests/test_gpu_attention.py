@@ -211,12 +211,14 @@ def test_an_infinite_value_gives_an_infinite_output_where_parts_are_merged(dtype
     lib.close()
 
 
-def test_what_an_overlap_left_in_the_arrival_words_does_not_reach_later_calls():
+@pytest.mark.parametrize("hq,hkv,ctx", [(8, 2, [900, 1500, 400]), (4, 1, [2048]), (4, 1, [2049])])
+def test_what_an_overlap_left_in_the_arrival_words_does_not_reach_later_calls(hq, hkv, ctx):
     """Calls that overlap on one pool, which they must not, can leave the words that count a sequence's finished parts at
     any count of a launch enqueued before.  Words planted so: the next call, and a captured call at every replay, give the
-    result of an undisturbed call and leave the words they use at zero."""
-    w = I.Workload("residue", 1, 3, 8, 2, 128, I.DTYPE_BF16, value_scale=1.0, seed=40)
-    case = I.make_case(w, ctx_lens=np.asarray([900, 1500, 400], np.int32))
+    result of an undisturbed call and leave the words they use at zero.  (Up to 24 parts a sequence, 32, and 33, from which
+    on the launch enters its number earlier.)"""
+    w = I.Workload("residue", 1, len(ctx), hq, hkv, 128, I.DTYPE_BF16, value_scale=1.0, seed=40)
+    case = I.make_case(w, ctx_lens=np.asarray(ctx, np.int32))
     lib, mod, table = GH.make_pools(case, int(case.n_blocks.sum()) + 1, 0, 0)
     # the words, 128 bytes apart, lie ahead of the clock table at the end of the pool's memory
     clock = ((w.n_layers + 1) * 8 + w.n_layers * 4096 * 2) * 8
