@@ -194,8 +194,10 @@ int pie_set_swap_path(pie_pool* pool, int32_t path);
  * [256, 4096]); longer contexts are split and reduced.  0, the default: chosen on the device for every batch,
  * from 512 / 768 / 1024 / 1536 / 2048 / 3072 / 4096, as the largest size that still leaves the persistent decode
  * grid more than about eight and a half (partition, kv head) units per workgroup (small units even out the
- * workgroups' different streaming rates, every unit has a fixed cost).  With 0, calls of up to 256 sequences and the
- * layers of small steps run as one launch with a split of its own, as fine as it takes to fill the GPU. */
+ * workgroups' different streaming rates, every unit has a fixed cost).  With 0, calls run as one launch with a split of
+ * its own, as fine as it takes to fill the GPU, if they have up to 256 sequences, their table is not so wide that the
+ * longest contexts it can name would not fit the split, and they are not fp32 with grouped queries; so do the layers of
+ * small steps, and with grouped queries those of big steps of eight layers or more (pie_step_attn_kernel). */
 int pie_set_attn_partition(pie_pool* pool, int32_t tokens);
 
 /* The size the last attention call planned with (the one set, or the one chosen by the rule above, also where a
@@ -287,8 +289,10 @@ int pie_attn_stream_probe_sync(pie_pool* pool, int32_t layer, const int32_t* d_b
  * those of host-homed tails into their staged copies on swap_out_stream once the copy has arrived, and from
  * there layer l's dirty blocks go home at once (the layer only reads them, so append and write-back run beside
  * it; swap_in_stream carries nothing but the copies, back to back).  Behind the last layer, layer 0's blocks
- * are brought in once more for the step that follows (see pie_set_cross_step_prefetch).
- * d_k_new and d_v_new must be 8-byte aligned and stay valid until the step has run.
+ * are brought in once more for the step that follows (see pie_set_cross_step_prefetch).  The rows are stored beside
+ * the attention: a sequence whose context holds the position that another sequence of the batch appends in the same
+ * step may read it before or after.  (So in pie_layer_step and pie_elastic_step.)
+ * d_k_new and d_v_new must be 16-byte aligned and stay valid until the step has run.
  * d_q_all, d_out_all: [L][batch][n_q_heads][head_dim]; d_k_new, d_v_new: [L][batch][n_kv_heads][head_dim]
  * (NULL skips the append).  Argument errors are detected before anything is enqueued; a HIP error in the
  * middle (PIE_EHIP) leaves the step partly enqueued. */

@@ -10,8 +10,8 @@
 // What bounds it: for small calls a chain of dependent accesses, about 7 us from the first workgroup's start (context
 // lengths and split 1.4 us, table and map 0.7, a block 0.9, the part's state stored 1.0 and counted 0.4 to 1.3, the
 // merge 1.4); for large ones HBM.  us a call among others, planned before and in one launch now: one sequence of
-// 700 tokens, 32 heads over 8: 24.5 and 6.5; one of 32 749, 64 over 8: 48.6 and 27.3 (134 MB, 4.9 TB/s); 32 of 32 768,
-// 64 over 8: 671 and 661 (4.3 GB, 6.5 TB/s).  A layer of a step of 8 sequences of 128 to 4 096 tokens, 32 over 8: 16.8 and 11.0.
+// 700 tokens, 32 heads over 8: 24.6 and 6.6; one of 32 749, 64 over 8: 48.6 and 27.2 (134 MB, 4.9 TB/s); 32 of 32 768,
+// 64 over 8: 671 and 661 (4.3 GB, 6.5 TB/s).  A layer of a step of 8 sequences of 128 to 4 096 tokens, 32 over 8: 16.8 and 11.2.
 
 #include <hip/hip_ext.h>
 
@@ -573,10 +573,12 @@ bool attn_direct(const pie_pool* p, int32_t batch, int32_t max_blocks) { return 
 // workgroups than beside the persistent grid's.  With grouped queries it gains from about 8 layers on (256 sequences of
 // 128 to 4 096 tokens, 32 heads over 8, us planned and in one launch, both in the same memory: 8 layers 1 776 and 1 752,
 // 12 layers 2 655 and 2 577, 16 layers 3 614 and 3 517, 32 layers 7 013 and 6 960; with host blocks, 0.5 %, 16 layers 3 631
-// and 3 585, 32 layers 7 100 and 7 098).  Without grouping it does not (64 sequences of 1 024 to 2 048, 32 heads, 32
-// layers 8 041 and 8 101, with host blocks 8 155 and 8 329; 40 of 300 to 1 700, 40 heads, 32 layers 4 624 and 4 644), and
-// fewer, longer parts have fewer weights of exactly one, so that rounding the weights to f16 costs more (2.24e-4 from 64
-// bits against 2.19e-4): those steps stay planned.  The other kinds of step store a layer's rows ahead of its launch:
+// and 3 585, 32 layers 7 100 and 7 098; 8 layers of 130 of 500 to 2 500, 64 over 8: 1 138 and 1 083; of 250 of 1 000 to
+// 3 000, 28 over 4: 1 587 and 1 501; of 100 of 4 096: 2 281 and 2 278).  Without grouping it does not (64 sequences of
+// 1 024 to 2 048, 32 heads, 32 layers 8 041 and 8 101, apart 8 088 and 8 005, in a first pass 8 148 and 8 267, with host
+// blocks 8 155 and 8 329; 40 of 300 to 1 700, 40 heads, 32 layers 4 624 and 4 644), and fewer, longer parts have fewer
+// weights of exactly one, so that rounding the weights to f16 costs more (2.24e-4 from 64 bits against 2.19e-4): those
+// steps stay planned.  The other kinds of step store a layer's rows ahead of its launch:
 // layers that move, as above with grouping, 8 layers 1 808 and 1 785 us, 16 layers 3 703 and 3 580, 32 layers 7 169 and
 // 7 094; where each launch worked the split out for itself they took 1 862, 3 818 and 7 538.
 int attn_step_path(const pie_pool* p, int32_t n_layers, int32_t batch, int32_t max_blocks) {
