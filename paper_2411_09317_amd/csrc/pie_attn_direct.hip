@@ -669,7 +669,10 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
     a.clock_wg = p->d_clock + ((size_t)c.n_layers + 1) * kClockRow + row * kClockWgs * 2;
   }
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();   // the launch will say what is wrong
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
+    (void)hipGetLastError();                      // (the default stream beside another's capture: the launch says so)
+    capture = hipStreamCaptureStatusNone;
+  }
   if (capture == hipStreamCaptureStatusActive) {
     const int32_t n = batch * H;
     hipLaunchKernelGGL(k_arrive_clear, dim3((n + 255) / 256), dim3(256), 0, s, a.arrive, n);
