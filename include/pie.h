@@ -284,9 +284,8 @@ int pie_attn_stream_probe_sync(pie_pool* pool, int32_t layer, const int32_t* d_b
  * prefetched on swap_in_stream into the other staging region meanwhile.  With a new token (d_k_new), the
  * attention reads the context without it from the cache and takes the token itself from d_k_new / d_v_new, so
  * no layer waits for the rows to be stored: those of the GPU-homed tail blocks of all layers are written by one
- * launch on swap_out_stream beside the first layers (compute_stream is ordered after it when the step ends), or, in a
- * small step, by each layer's own launch,
- * those of host-homed tails into their staged copies on swap_out_stream once the copy has arrived, and from
+ * launch, on compute_stream ahead of the first layer or on swap_out_stream beside the first layers (compute_stream is
+ * ordered after it when the step ends), those of host-homed tails into their staged copies on swap_out_stream once the copy has arrived, and from
  * there layer l's dirty blocks go home at once (the layer only reads them, so append and write-back run beside
  * it; swap_in_stream carries nothing but the copies, back to back).  Behind the last layer, layer 0's blocks
  * are brought in once more for the step that follows (see pie_set_cross_step_prefetch).  The rows are stored beside
@@ -294,15 +293,17 @@ int pie_attn_stream_probe_sync(pie_pool* pool, int32_t layer, const int32_t* d_b
  * step may read it before or after.  (So in pie_layer_step and pie_elastic_step.)
  * d_k_new and d_v_new must be 16-byte aligned and stay valid until the step has run.
  * d_q_all, d_out_all: [L][batch][n_q_heads][head_dim]; d_k_new, d_v_new: [L][batch][n_kv_heads][head_dim]
- * (NULL skips the append).  Argument errors are detected before anything is enqueued; a HIP error in the
- * middle (PIE_EHIP) leaves the step partly enqueued. */
+ * (NULL skips the append).  All layers' inputs must be there when the step runs: with nothing to prefetch, no timing and
+ * no stand-in the layers share launches, in any order.  (Memory that holds both results and inputs of the step is
+ * recognised, and its layers then run one after the other.)  Argument errors are detected before anything is enqueued; a
+ * HIP error in the middle (PIE_EHIP) leaves the step partly enqueued. */
 int pie_step(pie_pool* pool, const void* d_q_all, const void* d_k_new, const void* d_v_new,
              const int32_t* d_block_table, int32_t max_blocks, const int32_t* d_ctx_lens, int32_t batch,
              int32_t n_prefetch, const int32_t* h_prefetch, int32_t n_dirty, const int32_t* h_dirty,
              void* d_out_all, void* compute_stream, void* swap_in_stream, void* swap_out_stream);
 
 /* The name of the kernel that runs a layer's attention in a step of n_layers layers over `batch` sequences under a
- * table of `max_blocks` columns, with the pool's present settings: "k_attn_direct" (one launch a layer),
+ * table of `max_blocks` columns, with the pool's present settings: "k_attn_direct" (a launch a layer, or one for several),
  * "k_attn_decode_mfma" or "k_attn_decode_f32" (planned once a step, with a reduction behind each layer).  The same
  * for pie_step, pie_layer_step and pie_elastic_step.  A static string, NULL for arguments no step takes.  For
  * measurements that name what they measured. */

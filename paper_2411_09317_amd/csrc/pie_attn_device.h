@@ -365,4 +365,52 @@ __device__ __forceinline__ void f32_block(const uint4 (&kr)[HD / 16], const uint
   }
 }
 
+// ---- storing a sequence's newest key and value rows into its tail block --------------------------------------
+
+// by a workgroup
+__device__ __forceinline__ void append_rows(const AppendArgs& a, int32_t b, int32_t layer) {
+  const int32_t ctx = a.ctx[b];
+  if (ctx <= 0) return;
+  const int32_t pos = ctx - 1;
+  const int32_t j = pos / a.block_tokens;
+  if (j >= a.max_blocks) {
+    if (threadIdx.x == 0) atomicOr(a.err, PIE_DEVERR_BAD_HANDLE);
+    return;
+  }
+  __shared__ int32_t s_slot;
+  if (threadIdx.x == 0)
+    s_slot = append_slot(a.table[(size_t)b * a.max_blocks + j], a.map + (size_t)layer * a.map_stride, a.n_handles, a.n_gpu_blocks, a.n_slots, a.mode, true,
+                         a.err);
+  __syncthreads();
+  const int32_t slot = s_slot;
+  if (slot < 0) return;
+  // one 16-byte vector of a key row goes to one vector of the K tile; a value row is scattered element by
+  // element over the V tile's token-quad vectors
+  const int32_t v = 16 / a.elem_bytes;
+  const int32_t vec_per_row = a.head_dim / v;
+  const int32_t tile_bytes = kBlockTokens * a.head_dim * a.elem_bytes;
+  char* blk = a.kv_layer + layer * a.kv_layer_stride + (size_t)slot * a.block_bytes;
+  const char* k_new = a.k_new + layer * a.new_layer_stride;
+  const char* v_new = a.v_new + layer * a.new_layer_stride;
+  const size_t v_off = a.block_bytes / 2;
+  const int32_t t = pos % kBlockTokens;
+  const int32_t n_vec = a.n_kv_heads * vec_per_row;
+  for (int32_t i = threadIdx.x; i < n_vec; i += blockDim.x) {
+    const int32_t g = i / vec_per_row, cv = i % vec_per_row;
+    const size_t src = ((size_t)b * a.n_kv_heads + g) * a.head_dim * a.elem_bytes + (size_t)cv * 16;
+    const size_t dst = (size_t)g * tile_bytes + (size_t)k_tile_index(t, cv * v, v) * a.elem_bytes;
+    *reinterpret_cast<uint4*>(blk + dst) = *reinterpret_cast<const uint4*>(k_new + src);
+  }
+  const int32_t n_el = a.n_kv_heads * a.head_dim;
+  for (int32_t i = threadIdx.x; i < n_el; i += blockDim.x) {
+    const int32_t g = i / a.head_dim, c = i % a.head_dim;
+    const size_t src = ((size_t)b * a.n_kv_heads + g) * a.head_dim + c;
+    const size_t dst = v_off + (size_t)g * tile_bytes + (size_t)v_tile_index(t, c, v) * a.elem_bytes;
+    if (a.elem_bytes == 2)
+      *reinterpret_cast<uint16_t*>(blk + dst) = reinterpret_cast<const uint16_t*>(v_new)[src];
+    else
+      *reinterpret_cast<uint32_t*>(blk + dst) = reinterpret_cast<const uint32_t*>(v_new)[src];
+  }
+}
+
 }  // namespace pie

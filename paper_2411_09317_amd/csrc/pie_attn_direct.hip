@@ -5,13 +5,19 @@
 // time is launches, the gaps between them and a grid that mostly idles, not bytes.  Here every workgroup works out the
 // whole split for itself from the context lengths (at most four per lane, one scan), looks its blocks up through table
 // and map, streams them, and the workgroup that finishes a (sequence, kv head) last merges the partial states, adds the
-// newest token and writes the result; with new rows it also stores them.
+// newest token and writes the result; with new rows it can also store them.
+//
+// The layers of a step start from a plan that one launch ahead of them works out, and where nothing has to happen between
+// them they share a launch too (n_layers): then the chain of accesses, the tail and the gap behind it, 7 of 11 us a layer of
+// a small step, come once a step and not once a layer.  us a step, a launch a layer before and one for all now: 32 layers of
+// 8 sequences of 128 to 4 096 tokens, 32 heads over 8, 358 and 166 (888 MB, 5.3 TB/s); 16 of 24 of 100 to 1 100, 32 heads, 613
+// and 527; 16 of 256 of 128 to 4 096, 32 over 8, 3 454 and 3 383; 16 growing caches of 48 sequences, 685 and 569.
 //
 // What bounds it: for small calls a chain of dependent accesses, about 7 us from the first workgroup's start (context
 // lengths and split 1.4 us, table and map 0.7, a block 0.9, the part's state stored 1.0 and counted 0.4 to 1.3, the
 // merge 1.4); for large ones HBM.  us a call among others, planned before and in one launch now: one sequence of
 // 700 tokens, 32 heads over 8: 24.6 and 6.6; one of 32 749, 64 over 8: 48.6 and 27.2 (134 MB, 4.9 TB/s); 32 of 32 768,
-// 64 over 8: 671 and 661 (4.3 GB, 6.5 TB/s).  A layer of a step of 8 sequences of 128 to 4 096 tokens, 32 over 8: 16.8 and 11.2.
+// 64 over 8: 671 and 661 (4.3 GB, 6.5 TB/s).
 
 #include <hip/hip_ext.h>
 
@@ -21,12 +27,29 @@
 
 namespace pie {
 
-struct DirectArgs {
+struct SplitIn {             // what the split of a call follows from
+  const int32_t* ctx;
+  uint32_t* err;
+  int32_t* hdr;              // plan header, to note the nominal item size in, or NULL
+  int32_t batch, max_blocks, n_kv_heads;
+  int32_t minus;             // 1: the newest token is not read from the cache
+  int32_t min_units;         // as in k_attn_plan; 0: the size is the smallest whatever the lengths
+  int32_t max_items;         // items (all sequences' parts) the split may make
+};
+
+struct SplitArgs : SplitIn { // the plan of a step
+  const int32_t* table;
+  const int32_t* map[2];     // per staging region: handle -> slot, or NULL for no region or no slots
+  int32_t* plan[2];
+  int32_t n_handles, n_gpu_blocks, n_slots, stage_valid;
+  int32_t append;            // kAppend*, where each layer's launch stores its rows, or -1
+  int32_t places;            // items there may be: a workgroup each; those behind them store the new rows
+};
+
+struct DirectArgs : SplitIn {
   const char* kv_layer;
   const int32_t* table;      // [B][max_blocks] handles
   const int32_t* map;        // handle -> slot
-  const int32_t* ctx;
-  uint32_t* err;
   const char* q;             // [B][Hq][d]
   char* out;                 // [B][Hq][d]
   const char* new_k;         // newest token's rows [B][Hkv][d] (see AttnArgs), or NULL
@@ -34,17 +57,17 @@ struct DirectArgs {
   float* ws;                 // partial states: [unit][group][d + 4]
   uint64_t* arrive;          // per (sequence, head unit): workgroups of which launch have stored their part
   uint64_t launch;           // this launch's number << kArriveShift
-  int32_t* hdr;              // plan header, to note the nominal item size in, or NULL
-  int32_t* plan;             // records and slot lists of the items (kPlan*): written, or with REPLAY read; or NULL
+  const int32_t* plan;       // records and slot lists of the items (kPlan*), or NULL
   unsigned long long* clock;    // the layer's row of the clock table and its workgroups' pairs, or NULL
   unsigned long long* clock_wg;
   size_t block_bytes;
-  int32_t ws_bytes;
+  size_t kv_stride, q_stride, new_stride;   // bytes between the layers of the launch: caches, q and out, new rows
+  int32_t map_stride;        // entries between their maps: 0 where they share one
+  int32_t ws_bytes;          // of one layer's partial states
+  int32_t arrive_lines;      // lines of arrival words, a pair's for sixteen layers each, between those of layer l and l + 16
   float scale_log2e;
-  int32_t batch, max_blocks, n_kv_heads, group, n_q_heads;
+  int32_t group, n_q_heads;
   int32_t n_handles, n_gpu_blocks, n_slots, stage_valid;
-  int32_t min_units;         // as in k_attn_plan; 0: the size is the smallest whatever the lengths
-  int32_t max_items;         // items (all sequences' parts) the split may make
   int32_t append;            // kAppend*: store the new rows into the tail blocks this says, or -1
 };
 
@@ -182,12 +205,137 @@ struct FastRcp {
 constexpr int kDirectLaneSeqs = kDirectSeqs / 64;   // sequences per lane in the split
 constexpr int32_t kEarlyParts = 32;
 
-// A step's layers share the split and, per staging region, the slots: the first layer of each region leaves what it
-// worked out for every item, and the others start from that, one access deep instead of four.  Where every layer has a
-// map of its own (the growing caches) they share the split alone.  PLAN: kDirectPlanReplay, kDirectPlanReplaySplit, or
-// kDirectPlanNone, which also covers the launches that write the plan.
+// A step's layers share the split and, per staging region, the slots: k_attn_split works them out for every item, and
+// the layers start from that, one access deep instead of four.  Where every layer has a map of its own (the growing
+// caches) they share the split alone.  PLAN: kDirectPlanReplay, kDirectPlanReplaySplit, or kDirectPlanNone.
 constexpr int kPlanRec = 8;                      // b, tok0, tok1, parts, first item, part, tail slot, raw context length
 constexpr int kPlanInts = kPlanRec + kDirectMaxQuanta * kWaves;   // a record, then the slots of each wave's blocks
+
+struct Item {
+  int32_t b, tok0, tok1, np, first, part;         // one part of sequence b, of np from item `first`; b < 0: there is none
+  int32_t at;                                     // where in the plan its record stands (RANKED)
+};
+// The split, by one wave: lane i has the sequences i, i + 64, ...  lead: the one workgroup that reports errors and the size.
+template <bool RANKED>
+__device__ __forceinline__ Item split_item(const SplitIn& a, int32_t place, bool lead) {
+  const int32_t H = a.n_kv_heads;
+  const int lane = threadIdx.x & 63;
+  int32_t c4[kDirectLaneSeqs], q4[kDirectLaneSeqs], n4[kDirectLaneSeqs], k4[kDirectLaneSeqs], end4[kDirectLaneSeqs];
+  int32_t total = 0;
+#pragma unroll
+  for (int i = 0; i < kDirectLaneSeqs; ++i) {
+    c4[i] = q4[i] = 0;
+    if (64 * i < a.batch) {
+      const int32_t b = 64 * i + lane;
+      if (b < a.batch) {
+        const int32_t raw = a.ctx[b];
+        const int32_t full = clamp_ctx(raw, a.max_blocks);
+        if (raw > full && lead) atomicOr(a.err, PIE_DEVERR_BAD_HANDLE);
+        c4[i] = full > a.minus ? full - a.minus : 0;
+        q4[i] = quanta_of(c4[i]);
+      }
+      total += wave_sum(q4[i]);
+    }
+  }
+  if (a.hdr && lead) {                 // the item size the planning kernel would have chosen, as asked for by
+    int32_t size = auto_part(0);                  // pie_get_attn_partition_sync
+    if (a.min_units > 0) {
+#pragma unroll 1
+      for (int t = 1; t < kAutoParts; ++t) {
+        int32_t n = 0;
+#pragma unroll
+        for (int i = 0; i < kDirectLaneSeqs; ++i)
+          if (64 * i + lane < a.batch) n += c4[i] > 0 ? (c4[i] + auto_part(t) - 1) / auto_part(t) : 1;
+        if ((long long)wave_sum(n) * H > a.min_units) size = auto_part(t);
+      }
+    }
+    if (threadIdx.x == 0) a.hdr[1] = size;
+  }
+  auto items_of = [&](int32_t k) {
+    int32_t n = 0;
+#pragma unroll
+    for (int i = 0; i < kDirectLaneSeqs; ++i)
+      if (64 * i < a.batch) n += div_up(q4[i], k, FastRcp());   // (0 beyond the batch)
+    return wave_sum(n);
+  };
+  const int32_t k = quanta_per_part(total, a.max_items, items_of);
+  int32_t n_items = 0;
+#pragma unroll
+  for (int i = 0; i < kDirectLaneSeqs; ++i) {
+    n4[i] = k4[i] = end4[i] = 0;
+    if (64 * i < a.batch) {
+      if (q4[i] > 0) {
+        const SeqParts parts = seq_parts(q4[i], k, FastRcp());
+        k4[i] = parts.each;
+        n4[i] = parts.n;
+      }
+      end4[i] = n_items + wave_scan(n4[i]);       // items up to and including the lane's sequence
+      n_items = __builtin_amdgcn_readlane(end4[i], 63);
+    }
+  }
+  const int32_t item = place;
+  // one unit a workgroup: the launch has at least as many workgroups as the split can make units
+  int32_t b = 0;                                  // sequences whose items all come before this one
+#pragma unroll
+    for (int i = 0; i < kDirectLaneSeqs; ++i)
+      if (64 * i < a.batch) b += __popcll(__builtin_amdgcn_ballot_w64(64 * i + lane < a.batch && end4[i] <= item));
+  int32_t ctx_b = 0, kq = 1, end = 1, np = 1, at = place;
+#pragma unroll
+    for (int i = 0; i < kDirectLaneSeqs; ++i)
+      if (b >> 6 == i) {
+        ctx_b = __builtin_amdgcn_readlane(c4[i], b & 63);
+        kq = __builtin_amdgcn_readlane(k4[i], b & 63);
+        np = __builtin_amdgcn_readlane(n4[i], b & 63);
+        end = __builtin_amdgcn_readlane(end4[i], b & 63);
+      }
+  const int32_t first = end - np, part = item - first;
+  const int32_t tok0 = part * kq * kQuantum;
+  const int32_t tok1 = min(ctx_b, tok0 + kq * kQuantum);       // <= tok0 only for an empty sequence
+  if (item >= n_items) b = -1;
+  // The plan lists the items by size, largest first, so that the layers that start from it spread the large parts over
+  // the compute units and end on small ones: 639 -> 617 us for 16 layers of 24 sequences of 100 to 1 100 tokens.
+  if (RANKED && b >= 0) {
+    int32_t before = 0;
+#pragma unroll
+    for (int i = 0; i < kDirectLaneSeqs; ++i)
+      if (64 * i < a.batch) before += k4[i] > kq || (k4[i] == kq && 64 * i + lane < b) ? n4[i] : 0;
+    at = wave_sum(before) + part;
+  }
+  return {b, tok0, tok1, np, first, part, at};
+}
+
+// Ahead of a step's layers: their plan, a workgroup to an item and a lane to a block, and the new rows of all layers.
+__global__ __launch_bounds__(kWaves * 64) void k_step_begin(const SplitArgs a, const AppendArgs rows) {
+  if ((int32_t)blockIdx.x >= a.places) {
+    const int32_t i = blockIdx.x - a.places;
+    append_rows(rows, i % a.batch, i / a.batch);
+    return;
+  }
+  const int32_t place = blockIdx.x, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const Item it = split_item<true>(a, place, place == 0);
+  const int32_t jb = it.tok0 / kBlockTokens + wave + kWaves * lane;
+  const bool live = it.b >= 0 && jb * kBlockTokens < it.tok1;
+  const int32_t ctx_raw = it.b >= 0 ? a.ctx[it.b] : 0, jt = (ctx_raw - 1) / kBlockTokens;
+  const bool has_tail = a.append >= 0 && it.part == it.np - 1 && ctx_raw > 0;
+  const int32_t* row = a.table + (size_t)(it.b >= 0 ? it.b : 0) * a.max_blocks;
+  const int32_t handle = live ? row[jb] : -1, tail = has_tail && jt < a.max_blocks ? row[jt] : -1;
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    if (!a.plan[r]) continue;
+    int32_t* rec = a.plan[r] + (size_t)it.at * kPlanInts;
+    int32_t tail_slot = -1;
+    if (a.map[r] && has_tail)
+      tail_slot = append_slot(tail, a.map[r], a.n_handles, a.n_gpu_blocks, a.n_slots, a.append, threadIdx.x == 0, a.err);
+    if (a.map[r] && live)
+      rec[kPlanRec + wave * kDirectMaxQuanta + lane] =
+          resolve_slot(handle, a.map[r], a.n_handles, a.n_gpu_blocks, a.n_slots, a.stage_valid != 0, a.err);
+    if (threadIdx.x == 0) {
+      *reinterpret_cast<int4*>(rec) = make_int4(it.b, it.tok0, it.tok1, it.np);
+      *reinterpret_cast<int4*>(rec + 4) = make_int4(it.first, it.part, tail_slot, ctx_raw);
+    }
+  }
+}
 
 template <typename W, int NW, int PLAN>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(W::kWavesPerEu, 8)))
@@ -215,106 +363,31 @@ void k_attn_direct(const DirectArgs a) {
   const int32_t G = a.group, H = a.n_kv_heads;
   // (no store comes before the uniform loads below: they are then scalar loads)
   const unsigned long long t_start = a.clock ? wall_clock64() : 0ull;
-  const int32_t unit = blockIdx.x;
-  const int32_t place = unit / H, g = unit - place * H;
-  int32_t at = place;                             // where in the plan this item's record stands
-  int32_t b, ctx_raw, tok0, tok1, np, first, part, tail;   // this unit: one part of sequence b, of np from item `first`
+  // kv heads innermost: their tiles lie side by side; then the layers, so that all of them come with their largest items
+  const int32_t g = blockIdx.x, layer = blockIdx.y, place = blockIdx.z;
+  const bool lead = (g | layer | place) == 0;
+  const char* kv_layer = a.kv_layer + layer * a.kv_stride;
+  const int32_t* map = a.map + (size_t)layer * a.map_stride;
+  const char* q_in = a.q + layer * a.q_stride;
+  char* const out = a.out + layer * a.q_stride;
+  const char* new_k = a.new_k ? a.new_k + layer * a.new_stride : nullptr;
+  const char* new_v = a.new_k ? a.new_v + layer * a.new_stride : nullptr;
+  int32_t b, ctx_raw, tok0, tok1, np, first, part, tail = -1;   // this unit: one part of sequence b, of np from item `first`
+  int32_t slots = -1;                             // of this wave's blocks, one to a lane
+  if constexpr (SLOTS) slots = a.plan[(size_t)place * kPlanInts + kPlanRec + wave * kDirectMaxQuanta + lane];
   if constexpr (REPLAY) {
     const int32_t* rec = a.plan + (size_t)place * kPlanInts;
     b = rec[0]; tok0 = rec[1]; tok1 = rec[2]; np = rec[3]; first = rec[4]; part = rec[5]; tail = rec[6]; ctx_raw = rec[7];
   } else {
-    // ---- the split: every wave computes the same one.  Lane i has the sequences i, i + 64, ...
-    const int32_t minus = a.new_k ? 1 : 0;          // the newest token is not read from the cache
-    int32_t c4[kDirectLaneSeqs], q4[kDirectLaneSeqs], n4[kDirectLaneSeqs], k4[kDirectLaneSeqs], end4[kDirectLaneSeqs];
-    int32_t total = 0;
-#pragma unroll
-    for (int i = 0; i < kDirectLaneSeqs; ++i) {
-      c4[i] = q4[i] = 0;
-      if (64 * i < a.batch) {
-        const int32_t b = 64 * i + lane;
-        if (b < a.batch) {
-          const int32_t raw = a.ctx[b];
-          const int32_t full = clamp_ctx(raw, a.max_blocks);
-          if (raw > full && blockIdx.x == 0) atomicOr(a.err, PIE_DEVERR_BAD_HANDLE);
-          c4[i] = full > minus ? full - minus : 0;
-          q4[i] = quanta_of(c4[i]);
-        }
-        total += wave_sum(q4[i]);
-      }
-    }
-    if (a.hdr && blockIdx.x == 0) {                 // the item size the planning kernel would have chosen, as asked for by
-      int32_t size = auto_part(0);                  // pie_get_attn_partition_sync
-      if (a.min_units > 0) {
-#pragma unroll 1
-        for (int t = 1; t < kAutoParts; ++t) {
-          int32_t n = 0;
-#pragma unroll
-          for (int i = 0; i < kDirectLaneSeqs; ++i)
-            if (64 * i + lane < a.batch) n += c4[i] > 0 ? (c4[i] + auto_part(t) - 1) / auto_part(t) : 1;
-          if ((long long)wave_sum(n) * H > a.min_units) size = auto_part(t);
-        }
-      }
-      if (tid == 0) a.hdr[1] = size;
-    }
-    auto items_of = [&](int32_t k) {
-      int32_t n = 0;
-#pragma unroll
-      for (int i = 0; i < kDirectLaneSeqs; ++i)
-        if (64 * i < a.batch) n += div_up(q4[i], k, FastRcp());   // (0 beyond the batch)
-      return wave_sum(n);
-    };
-    const int32_t k = quanta_per_part(total, a.max_items, items_of);
-    int32_t n_items = 0;
-#pragma unroll
-    for (int i = 0; i < kDirectLaneSeqs; ++i) {
-      n4[i] = k4[i] = end4[i] = 0;
-      if (64 * i < a.batch) {
-        if (q4[i] > 0) {
-          const SeqParts parts = seq_parts(q4[i], k, FastRcp());
-          k4[i] = parts.each;
-          n4[i] = parts.n;
-        }
-        end4[i] = n_items + wave_scan(n4[i]);       // items up to and including the lane's sequence
-        n_items = __builtin_amdgcn_readlane(end4[i], 63);
-      }
-    }
-    const int32_t item = place;
-    // one unit a workgroup: the launch has at least as many workgroups as the split can make units
-    b = 0;                                          // sequences whose items all come before this one
-#pragma unroll
-      for (int i = 0; i < kDirectLaneSeqs; ++i)
-        if (64 * i < a.batch) b += __popcll(__builtin_amdgcn_ballot_w64(64 * i + lane < a.batch && end4[i] <= item));
-    int32_t ctx_b = 0, kq = 1, end = 1;
-    np = 1;
-#pragma unroll
-      for (int i = 0; i < kDirectLaneSeqs; ++i)
-        if (b >> 6 == i) {
-          ctx_b = __builtin_amdgcn_readlane(c4[i], b & 63);
-          kq = __builtin_amdgcn_readlane(k4[i], b & 63);
-          np = __builtin_amdgcn_readlane(n4[i], b & 63);
-          end = __builtin_amdgcn_readlane(end4[i], b & 63);
-        }
-    first = end - np;
-    part = item - first;
-    tok0 = part * kq * kQuantum;
-    tok1 = min(ctx_b, tok0 + kq * kQuantum);         // <= tok0 only for an empty sequence
-    if (item >= n_items) b = -1;
-    // The plan lists the items by size, largest first, so that the layers that start from it spread the large parts over
-    // the compute units and end on small ones: 639 -> 617 us for 16 layers of 24 sequences of 100 to 1 100 tokens.
-    if (a.plan && b >= 0) {
-      int32_t before = 0;
-#pragma unroll
-      for (int i = 0; i < kDirectLaneSeqs; ++i)
-        if (64 * i < a.batch) before += k4[i] > kq || (k4[i] == kq && 64 * i + lane < b) ? n4[i] : 0;
-      at = wave_sum(before) + part;
-    }
+    const Item it = split_item<false>(a, place, lead);
+    b = it.b; tok0 = it.tok0; tok1 = it.tok1; np = it.np; first = it.first; part = it.part;
     ctx_raw = b >= 0 ? a.ctx[b] : 0;
   }
   if constexpr (!SLOTS) {                         // where this sequence's newest token goes, if its last part's
     tail = -1;                                    // workgroups store it
     if (a.append >= 0 && b >= 0 && part == np - 1 && ctx_raw > 0) {
       const int32_t j = (ctx_raw - 1) / kBlockTokens;
-      tail = append_slot(j < a.max_blocks ? a.table[(size_t)b * a.max_blocks + j] : -1, a.map, a.n_handles, a.n_gpu_blocks,
+      tail = append_slot(j < a.max_blocks ? a.table[(size_t)b * a.max_blocks + j] : -1, map, a.n_handles, a.n_gpu_blocks,
                          a.n_slots, a.append, tid == 0, a.err);
     }
   }
@@ -324,31 +397,17 @@ void k_attn_direct(const DirectArgs a) {
     const int32_t n_it = (jb1 - jb0 - wave + NW - 1) / NW;  // blocks of this wave: jb0 + wave + NW * it; <= 64
     const size_t row0 = (size_t)b * a.n_q_heads + (size_t)g * G;
 
-    const bool stores = a.append >= 0 && tail >= 0;
-    uint4 k_row;
-    uint32_t v_el = 0;
-    if (stores) {
-      const size_t row = ((size_t)b * H + g) * HD * EB;
-      if (tid < HD * EB / 16) k_row = *reinterpret_cast<const uint4*>(a.new_k + row + (size_t)tid * 16);
-      if (tid < HD) v_el = EB == 2 ? *reinterpret_cast<const uint16_t*>(a.new_v + row + (size_t)tid * 2)
-                                   : *reinterpret_cast<const uint32_t*>(a.new_v + row + (size_t)tid * 4);
-    }
-
-    int32_t slots = -1;
-    int32_t* list = a.plan + (size_t)at * kPlanInts + kPlanRec + wave * kDirectMaxQuanta;
-    if (SLOTS)
-      slots = list[lane];                         // (the lanes beyond n_it read what nobody uses)
-    else if (lane < n_it)
-      slots = resolve_slot(a.table[(size_t)b * a.max_blocks + jb0 + wave + NW * lane], a.map, a.n_handles, a.n_gpu_blocks,
+    if (!SLOTS && lane < n_it)                    // (with SLOTS the lanes beyond n_it hold what nobody uses)
+      slots = resolve_slot(a.table[(size_t)b * a.max_blocks + jb0 + wave + NW * lane], map, a.n_handles, a.n_gpu_blocks,
                            a.n_slots, a.stage_valid != 0, a.err);
     W w;
-    w.load_q(a.q, row0, G, lane, a.scale_log2e);
+    w.load_q(q_in, row0, G, lane, a.scale_log2e);
     w.reset();
     uint4 kA[NL], vA[NL], kB[NL], vB[NL];
     auto load_tile = [&](uint4 (&kr)[NL], uint4 (&vr)[NL], int32_t it) {
       int32_t slot = __builtin_amdgcn_readlane(slots, it);
       slot = slot < 0 ? 0 : slot;                 // flagged blocks are masked when consumed
-      const char* kp = a.kv_layer + (size_t)slot * a.block_bytes + (size_t)g * TILE_BYTES + (size_t)lane * 16;
+      const char* kp = kv_layer + (size_t)slot * a.block_bytes + (size_t)g * TILE_BYTES + (size_t)lane * 16;
 #pragma unroll
       for (int i = 0; i < NL; ++i) kr[i] = nt_load16(kp + (size_t)i * 1024);
 #pragma unroll
@@ -359,7 +418,6 @@ void k_attn_direct(const DirectArgs a) {
       w.block(kr, vr, (jb0 + wave + NW * it) * kBlockTokens, present ? tok1 : 0, lane, a.scale_log2e);
     };
     if (n_it > 0) load_tile(kA, vA, 0);
-    if (!REPLAY && a.plan && g == 0) list[lane] = slots;
     for (int32_t it = 0; it < n_it; it += 2) {
       if (it + 1 < n_it) load_tile(kB, vB, it + 1);
       consume(kA, vA, it);
@@ -372,14 +430,23 @@ void k_attn_direct(const DirectArgs a) {
     // that was enqueued before this one: every workgroup puts this launch's in its place before it counts itself.  With
     // few parts right before (the accesses to a word are served one after another, 10 ns each), with many here, before the
     // waves' states are merged (the wave's wait for its stores covers it).
-    uint64_t* word = a.arrive + ((size_t)b * H + g) * kArriveStride;
+    uint64_t* word = a.arrive + ((size_t)(layer / kArriveStride) * a.arrive_lines + (size_t)b * H + g) * kArriveStride + layer % kArriveStride;
     if (np > kEarlyParts && wave == NW - 1 && lane == 0)
       (void)__hip_atomic_fetch_max(word, a.launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool stores = a.append >= 0 && tail >= 0;
+    uint4 k_piece;
+    uint32_t v_el = 0;
+    if (stores) {
+      const size_t row = ((size_t)b * H + g) * HD * EB;
+      if (tid < HD * EB / 16) k_piece = *reinterpret_cast<const uint4*>(new_k + row + (size_t)tid * 16);
+      if (tid < HD) v_el = EB == 2 ? *reinterpret_cast<const uint16_t*>(new_v + row + (size_t)tid * 2)
+                                   : *reinterpret_cast<const uint32_t*>(new_v + row + (size_t)tid * 4);
+    }
     w.to_lds(s_m, s_l, s_acc, ROW, wave, G, lane);
     if (stores) {                                 // rows at or beyond tok1 are masked by index wherever they are read
-      char* blk = const_cast<char*>(a.kv_layer) + (size_t)tail * a.block_bytes + (size_t)g * TILE_BYTES;
+      char* blk = const_cast<char*>(kv_layer) + (size_t)tail * a.block_bytes + (size_t)g * TILE_BYTES;
       const int32_t t = (ctx_raw - 1) % kBlockTokens, v = 16 / EB;
-      if (tid < HD * EB / 16) *reinterpret_cast<uint4*>(blk + (size_t)k_tile_index(t, tid * v, v) * EB) = k_row;
+      if (tid < HD * EB / 16) *reinterpret_cast<uint4*>(blk + (size_t)k_tile_index(t, tid * v, v) * EB) = k_piece;
       if (tid < HD) {
         char* dst = blk + a.block_bytes / 2 + (size_t)v_tile_index(t, tid, v) * EB;
         if (EB == 2) *reinterpret_cast<uint16_t*>(dst) = (uint16_t)v_el;
@@ -392,14 +459,14 @@ void k_attn_direct(const DirectArgs a) {
     const int32_t cols = G * TPH;
     // The newest token's part is (q . k, 1, v).  Its rows are read here, for the thread's first column, so that they
     // have arrived when the last step needs them.
-    const bool add_new = a.new_k && ctx_raw > 0;
+    const bool add_new = new_k && ctx_raw > 0;
     const size_t kv_row = ((size_t)b * H + g) * HD;
     float4 qd, kd, vd;
     auto read_new = [&](int c) {
       const int d0 = 4 * (c % TPH);
-      qd = load_elem4<E>(a.q, (row0 + c / TPH) * HD + d0);
-      kd = load_elem4<E>(a.new_k, kv_row + d0);
-      vd = load_elem4<E>(a.new_v, kv_row + d0);
+      qd = load_elem4<E>(q_in, (row0 + c / TPH) * HD + d0);
+      kd = load_elem4<E>(new_k, kv_row + d0);
+      vd = load_elem4<E>(new_v, kv_row + d0);
     };
     if (add_new && tid < cols) read_new(tid);
     auto finish = [&](int c, float M, float L, float4 A) {
@@ -416,8 +483,8 @@ void k_attn_direct(const DirectArgs a) {
         axpy(A, w_new, vd);
       }
       const bool some = L > 0.f;
-      store_elem2<E>(a.out, row * HD + d0, make_float2(some ? A.x / L : 0.f, some ? A.y / L : 0.f));
-      store_elem2<E>(a.out, row * HD + d0 + 2, make_float2(some ? A.z / L : 0.f, some ? A.w / L : 0.f));
+      store_elem2<E>(out, row * HD + d0, make_float2(some ? A.x / L : 0.f, some ? A.y / L : 0.f));
+      store_elem2<E>(out, row * HD + d0 + 2, make_float2(some ? A.z / L : 0.f, some ? A.w / L : 0.f));
     };
     // n states in LDS (the waves', or the merging groups') into one
     auto merge_lds = [&](int n, int h, int d0, float& M, float& L, float4& A) {
@@ -431,7 +498,7 @@ void k_attn_direct(const DirectArgs a) {
         axpy(A, wt, *reinterpret_cast<const float4*>(&s_acc[((size_t)i * G + h) * ROW + d0]));
       }
     };
-    const __amdgpu_buffer_rsrc_t parts = parts_rsrc(a.ws, a.ws_bytes);
+    const __amdgpu_buffer_rsrc_t parts = parts_rsrc(a.ws + (size_t)layer * (a.ws_bytes / 4), a.ws_bytes);
     for (int c = tid; c < cols; c += NT) {
       const int h = c / TPH, d0 = 4 * (c % TPH);
       float M, L;
@@ -528,17 +595,11 @@ void k_attn_direct(const DirectArgs a) {
       }
     }
   }
-  if (!REPLAY && a.plan && g == 0 && tid < kPlanRec) {
-    const int32_t rec[kPlanRec] = {b, tok0, tok1, np, first, part, tail, ctx_raw};
-    int32_t x = rec[0];
-#pragma unroll
-    for (int i = 1; i < kPlanRec; ++i) x = tid == i ? rec[i] : x;
-    a.plan[(size_t)at * kPlanInts + tid] = x;
-  }
   if (a.clock && tid == 0) {
-    a.clock_wg[2 * blockIdx.x] = t_start;
-    a.clock_wg[2 * blockIdx.x + 1] = wall_clock64();
-    if (blockIdx.x == 0) a.clock[kClockGrid] = gridDim.x;
+    const int32_t wg = place * H + g;              // (a launch that notes its times has one layer)
+    a.clock_wg[2 * wg] = t_start;
+    a.clock_wg[2 * wg + 1] = wall_clock64();
+    if (wg == 0) a.clock[kClockGrid] = gridDim.x * gridDim.z;
   }
 }
 
@@ -546,9 +607,11 @@ void k_attn_direct(const DirectArgs a) {
 
 // Its scratch in a pool: the parts, then the items' records and slot lists of the two staging regions, for as many units
 // as the pool's largest batch and widest table can make (a call's own scratch has room for any).
-static size_t parts_floats(const pie_config& c) { return direct_pool_rows(c) * (c.head_dim + 4); }
+static size_t parts_floats(const pie_config& c) { return direct_step_rows(c) * (c.head_dim + 4); }
 static size_t plan_region_ints(const pie_config& c) { return direct_pool_items(c) * kPlanInts; }
-size_t attn_arrive_words(const pie_config& c) { return direct_pool_words(c); }
+size_t attn_arrive_lines(const pie_config& c) {
+  return direct_pool_words(c) * (((size_t)c.n_layers + kArriveStride - 1) / kArriveStride);
+}
 size_t attn_direct_floats(const pie_config& c) { return parts_floats(c) + 2 * plan_region_ints(c); }
 
 // How many units the split of a call may make; 0: the call is left to the planned path, which has what this one lacks -
@@ -564,23 +627,22 @@ static int32_t direct_max_units(const pie_pool* p, int32_t batch, int32_t max_bl
 
 bool attn_direct(const pie_pool* p, int32_t batch, int32_t max_blocks) { return direct_max_units(p, batch, max_blocks) > 0; }
 
-// A step's layers.  Up to three (sequence, kv head) pairs per compute unit, or with short contexts, each layer's launch
-// stores its new rows as well: 16 layers of 24 sequences of 100 to 1 100 tokens, 32 kv heads: 606 us against 721
-// planned; 8 layers of 120 of 60 to 300, 8 kv heads: 213 against 260.  In bigger steps that would put partial-line writes
-// among every layer's reads (32 layers of 64 sequences of 1 024 to 2 048, 32 kv heads: 8 329 us against 8 056 planned),
-// so the rows of all layers are stored by one launch beside the first, as on the planned path.  There the one-launch path
-// saves the reduction, 3 to 10 us a layer, and loses some 40 us a step, because that launch finds less room beside its
-// workgroups than beside the persistent grid's.  With grouped queries it gains from about 8 layers on (256 sequences of
-// 128 to 4 096 tokens, 32 heads over 8, us planned and in one launch, both in the same memory: 8 layers 1 776 and 1 752,
-// 12 layers 2 655 and 2 577, 16 layers 3 614 and 3 517, 32 layers 7 013 and 6 960; with host blocks, 0.5 %, 16 layers 3 631
-// and 3 585, 32 layers 7 100 and 7 098; 8 layers of 130 of 500 to 2 500, 64 over 8: 1 138 and 1 083; of 250 of 1 000 to
-// 3 000, 28 over 4: 1 587 and 1 501; of 100 of 4 096: 2 281 and 2 278).  Without grouping it does not (64 sequences of
-// 1 024 to 2 048, 32 heads, 32 layers 8 041 and 8 101, apart 8 088 and 8 005, in a first pass 8 148 and 8 267, with host
-// blocks 8 155 and 8 329; 40 of 300 to 1 700, 40 heads, 32 layers 4 624 and 4 644), and fewer, longer parts have fewer
-// weights of exactly one, so that rounding the weights to f16 costs more (2.24e-4 from 64 bits against 2.19e-4): those
-// steps stay planned.  The other kinds of step store a layer's rows ahead of its launch:
-// layers that move, as above with grouping, 8 layers 1 808 and 1 785 us, 16 layers 3 703 and 3 580, 32 layers 7 169 and
-// 7 094; where each launch worked the split out for itself they took 1 862, 3 818 and 7 538.
+// A step's layers.  Without grouped queries, more than three (sequence, kv head) pairs per compute unit over long contexts
+// stay planned.  One launch a layer does not pay there (64 sequences of 1 024 to 2 048 tokens, 32 heads, 32 layers, us
+// planned and in one launch each: 8 041 and 8 101, apart 8 088 and 8 005, in a first pass 8 148 and 8 267, with host blocks
+// 8 155 and 8 329; 40 of 300 to 1 700, 40 heads, 32 layers 4 624 and 4 644), and fewer, longer parts have fewer weights of
+// exactly one, so that rounding the weights to f16 costs more (2.24e-4 from 64 bits against 2.19e-4).  With grouped queries it
+// gains from about 8 layers on (256 sequences of 128 to 4 096 tokens, 32 heads over 8: 8 layers 1 776 and 1 752, 16 layers 3 614
+// and 3 517; with host blocks, 0.5 %, 16 layers 3 631 and 3 585, 32 layers 7 100 and 7 098).
+//
+// The rows of all layers are stored by the launch ahead of the first.  What they cost is the lines they touch, 24 a pair, each
+// of them 110 to 250 ps of memory time, more the more they come among reads: us a step with them in every layer's part of
+// the launch, in a launch beside it on another stream, and ahead of it (without any): 16 layers of 24 sequences of 100 to
+// 1 100 tokens, 32 heads 569, 563 and 527 (490); 16 of 256 of 128 to 4 096, 32 over 8 3 518, 3 390 and 3 383 (3 303); 8 of 60 of
+// 60 to 300, 32 over 8 296, 307 and 292 (259); 8 of 30 of 60 to 300, 32 heads 168, 181 and 171 (144).  Stored as whole lines,
+// what else is in them read first, they cost the same.  Layers that move store their rows a layer at a time: in its launch,
+// or in big steps (kStepDirectAppendApart) ahead of it, 8 layers as above with grouping 1 808 and 1 785 us planned and so, 16
+// layers 3 703 and 3 580, 32 layers 7 169 and 7 094.
 int attn_step_path(const pie_pool* p, int32_t n_layers, int32_t batch, int32_t max_blocks) {
   if (!attn_direct(p, batch, max_blocks)) return kStepPlanned;
   const int64_t pairs = (int64_t)batch * p->cfg.n_kv_heads;
@@ -588,24 +650,34 @@ int attn_step_path(const pie_pool* p, int32_t n_layers, int32_t batch, int32_t m
   return p->cfg.n_q_heads > p->cfg.n_kv_heads && n_layers >= 8 ? kStepDirectAppendApart : kStepPlanned;
 }
 
+// How many layers of a step one launch may take: as many as the pool has room for parts of.
+int32_t attn_step_layers(const pie_pool* p, int32_t batch, int32_t max_blocks) {
+  const pie_config& c = p->cfg;
+  const int32_t units = direct_max_units(p, batch, max_blocks);
+  if (units <= 0) return 0;
+  const size_t rows = (size_t)(direct_grid(units, c.n_kv_heads, batch, max_blocks) / c.n_kv_heads) * c.n_q_heads;
+  const size_t n = direct_step_rows(c) / (rows ? rows : 1);
+  return n < (size_t)c.n_layers ? (int32_t)n : c.n_layers;
+}
+
 // A launch in a graph has the same number in every replay, so there the words it uses are cleared ahead of it.
 __global__ __launch_bounds__(256) void k_arrive_clear(uint64_t* __restrict__ words, int32_t n) {
   const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (i < n) words[(size_t)i * kArriveStride] = 0;
+  if (i < n) words[i] = 0;
 }
 
 template <typename W, int NW, int PLAN>
-static int launch_direct_as(const DirectArgs& a, int32_t grid, hipStream_t s, hipEvent_t done, size_t min_lds) {
+static int launch_direct_as(const DirectArgs& a, dim3 grid, hipStream_t s, hipEvent_t done, size_t min_lds) {
   size_t lds = ((size_t)NW * 2 * kMaxGroup + (size_t)NW * a.group * (W::HD + 4)) * sizeof(float);
   if (lds < min_lds) lds = min_lds;
-  if (done) hipExtLaunchKernelGGL((k_attn_direct<W, NW, PLAN>), dim3(grid), dim3(NW * 64), (uint32_t)lds, s, nullptr, done, 0, a);
-  else hipLaunchKernelGGL((k_attn_direct<W, NW, PLAN>), dim3(grid), dim3(NW * 64), (uint32_t)lds, s, a);
+  if (done) hipExtLaunchKernelGGL((k_attn_direct<W, NW, PLAN>), grid, dim3(NW * 64), (uint32_t)lds, s, nullptr, done, 0, a);
+  else hipLaunchKernelGGL((k_attn_direct<W, NW, PLAN>), grid, dim3(NW * 64), (uint32_t)lds, s, a);
   PIE_HIP(hipGetLastError());
   return PIE_OK;
 }
 
 template <typename W, int NW>
-static int launch_direct(const DirectArgs& a, int32_t grid, hipStream_t s, hipEvent_t done, int32_t plan, size_t min_lds) {
+static int launch_direct(const DirectArgs& a, dim3 grid, hipStream_t s, hipEvent_t done, int32_t plan, size_t min_lds) {
   switch (plan) {
     case kDirectPlanReplay: return launch_direct_as<W, NW, kDirectPlanReplay>(a, grid, s, done, min_lds);
     case kDirectPlanReplaySplit: return launch_direct_as<W, NW, kDirectPlanReplaySplit>(a, grid, s, done, min_lds);
@@ -613,15 +685,62 @@ static int launch_direct(const DirectArgs& a, int32_t grid, hipStream_t s, hipEv
   }
 }
 
+static int32_t* plan_region(const pie_pool* p, int region) {
+  return reinterpret_cast<int32_t*>(p->d_ws + parts_floats(p->cfg)) + region * plan_region_ints(p->cfg);
+}
+
+static void fill_split(const pie_pool* p, const int32_t* d_ctx, int32_t batch, int32_t max_blocks, int32_t max_units,
+                       bool without_last, SplitIn* a) {
+  const int32_t H = p->cfg.n_kv_heads;
+  a->ctx = d_ctx;
+  a->err = p->d_err;
+  a->hdr = p->d_plan;
+  a->batch = batch;
+  a->max_blocks = max_blocks;
+  a->n_kv_heads = H;
+  a->minus = without_last ? 1 : 0;
+  const int64_t second = ((int64_t)max_blocks * kBlockTokens + auto_part(1) - 1) / auto_part(1);
+  a->min_units = batch * second * H > attn_min_units(p) ? attn_min_units(p) : 0;
+  a->max_items = max_units / H;
+}
+
+int launch_step_begin(const pie_pool* p, const int32_t* d_table, int32_t max_blocks, const int32_t* d_ctx, int32_t batch,
+                      bool stage_valid, bool without_last, int32_t append, int32_t regions, hipStream_t s,
+                      const AppendArgs* rows, int32_t n_layers) {
+  const pie_config& c = p->cfg;
+  const int32_t H = c.n_kv_heads, max_units = direct_max_units(p, batch, max_blocks);
+  if (max_units <= 0 || regions < 0 || regions > 2) return PIE_EINVAL;
+  SplitArgs a = {};
+  fill_split(p, d_ctx, batch, max_blocks, max_units, without_last, &a);
+  a.table = d_table;
+  for (int r = 0; r < 2; ++r) {
+    a.map[r] = r < regions ? p->d_map[r] : nullptr;
+    a.plan[r] = r < (regions ? regions : 1) ? plan_region(p, r) : nullptr;
+  }
+  a.n_handles = p->n_handles;
+  a.n_gpu_blocks = c.n_gpu_blocks;
+  a.n_slots = c.n_gpu_blocks + 2 * c.n_stage_blocks;
+  a.stage_valid = stage_valid ? 1 : 0;
+  a.append = append;
+  a.places = direct_grid(max_units, H, batch, max_blocks) / H;
+  const int64_t grid = a.places + (rows ? (int64_t)batch * n_layers : 0);
+  if (grid > INT32_MAX) return PIE_EINVAL;
+  hipLaunchKernelGGL(k_step_begin, dim3((uint32_t)grid), dim3(kWaves * 64), 0, s, a, rows ? *rows : AppendArgs{});
+  PIE_HIP(hipGetLastError());
+  return PIE_OK;
+}
+
 int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const int32_t* d_table, int32_t max_blocks,
                        const int32_t* d_ctx, int32_t batch, void* d_out, bool stage_valid, hipStream_t s,
                        const void* d_k_new, const void* d_v_new, int32_t append, const LayerView* view,
                        const AttnWork* work, hipEvent_t k_start, hipEvent_t k_end, unsigned long long* clock_row,
-                       hipEvent_t done, int32_t plan, bool leave_room) {
+                       hipEvent_t done, int32_t plan, bool leave_room, int32_t n_layers, int32_t region) {
   // Three workgroups a compute unit take nearly all its registers, and a gather beside them starts when one ends.  Two,
   // by the LDS they ask for, leave it room (step_body says when that pays, with the times).
   const size_t min_lds = leave_room ? (size_t)56 << 10 : 0;
-  if (plan != kDirectPlanNone && work) return PIE_EINVAL;   // the plan lies in the pool's scratch, by layer & 1
+  if (plan != kDirectPlanNone && work) return PIE_EINVAL;   // the plan lies in the pool's scratch, by region
+  if (region < 0) region = view ? 0 : layer & 1;
+  if (region > 1 || (view && region)) return PIE_EINVAL;
   const pie_config& c = p->cfg;
   if (((uintptr_t)d_q | (uintptr_t)d_out) % 16) return PIE_EINVAL;
   if (c.n_gpu_blocks + 2 * c.n_stage_blocks <= 0) return PIE_EINVAL;
@@ -629,12 +748,14 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   if (((uintptr_t)d_k_new | (uintptr_t)d_v_new) % 16) return PIE_EINVAL;
   const int32_t group = c.n_q_heads / c.n_kv_heads, H = c.n_kv_heads, max_units = direct_max_units(p, batch, max_blocks);
   if (max_units <= 0) return PIE_EINVAL;
+  const int32_t places = direct_grid(max_units, H, batch, max_blocks) / H;   // the items there may be, at most max_units / H
+  if (n_layers < 1 || (n_layers > 1 && (work || clock_row || n_layers > attn_step_layers(p, batch, max_blocks)))) return PIE_EINVAL;
   DirectArgs a;
   a.kv_layer = view ? view->kv_base : p->d_kv + (size_t)layer * p->d_layer_stride;
   a.table = d_table;
-  a.map = view ? view->map : p->d_map[layer & 1];
-  a.ctx = d_ctx;
-  a.err = p->d_err;
+  a.map = view ? view->map : p->d_map[region];
+  fill_split(p, d_ctx, batch, max_blocks, max_units, d_k_new != nullptr, &a);
+  if (work) a.hdr = nullptr;
   a.q = (const char*)d_q;
   a.out = (char*)d_out;
   a.new_k = (const char*)d_k_new;
@@ -642,26 +763,23 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   a.ws = work ? reinterpret_cast<float*>(work->plan) : p->d_ws;   // a call's own scratch from its start
   a.arrive = work ? work->arrive : p->d_arrive;
   a.launch = ((work ? work->arrive_launches : &p->arrive_launches)->fetch_add(1, std::memory_order_relaxed) + 1) << kArriveShift;
-  a.hdr = work ? nullptr : p->d_plan;
   a.block_bytes = p->block_bytes;
-  a.ws_bytes = (int32_t)((work ? (size_t)kDirectRows * (c.head_dim + 4) : parts_floats(c)) * sizeof(float));
-  a.plan = plan == kDirectPlanNone ? nullptr
-                                   : reinterpret_cast<int32_t*>(p->d_ws + parts_floats(c)) + (view ? 0 : layer & 1) * plan_region_ints(c);
+  a.kv_stride = view ? 0 : p->d_layer_stride;     // (the caches that grow share their memory and have a map each)
+  a.map_stride = view ? view->n_handles : 0;
+  a.q_stride = (size_t)batch * c.n_q_heads * c.head_dim * p->elem_bytes;
+  a.new_stride = (size_t)batch * H * c.head_dim * p->elem_bytes;
+  a.ws_bytes = places * c.n_q_heads * (c.head_dim + 4) * (int32_t)sizeof(float);
+  a.arrive_lines = work ? kArriveWords : (int32_t)direct_pool_words(c);
+  a.plan = plan == kDirectPlanNone ? nullptr : plan_region(p, region);
   a.scale_log2e = p->scale_log2e;
-  a.batch = batch;
-  a.max_blocks = max_blocks;
-  a.n_kv_heads = H;
   a.group = group;
   a.n_q_heads = c.n_q_heads;
   a.n_handles = view ? view->n_handles : p->n_handles;
   a.n_gpu_blocks = view ? view->n_slots : c.n_gpu_blocks;
   a.n_slots = view ? view->n_slots : c.n_gpu_blocks + 2 * c.n_stage_blocks;
   a.stage_valid = stage_valid ? 1 : 0;
-  const int64_t second = ((int64_t)max_blocks * kBlockTokens + auto_part(1) - 1) / auto_part(1);
-  a.min_units = batch * second * H > attn_min_units(p) ? attn_min_units(p) : 0;
-  a.max_items = max_units / H;
   a.append = append;
-  const int32_t grid = direct_grid(max_units, H, batch, max_blocks);
+  const dim3 grid(H, n_layers, places);
   a.clock = clock_row;
   a.clock_wg = nullptr;
   if (clock_row) {                                // (a pair for every workgroup: kDirectMaxUnits <= kClockWgs)
@@ -674,7 +792,7 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
     capture = hipStreamCaptureStatusNone;
   }
   if (capture == hipStreamCaptureStatusActive) {
-    const int32_t n = batch * H;
+    const int32_t n = ((n_layers - 1) / kArriveStride * a.arrive_lines + batch * H) * kArriveStride;
     hipLaunchKernelGGL(k_arrive_clear, dim3((n + 255) / 256), dim3(256), 0, s, a.arrive, n);
     PIE_HIP(hipGetLastError());
   }

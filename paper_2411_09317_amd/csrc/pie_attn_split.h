@@ -58,6 +58,14 @@ inline size_t direct_pool_rows(const pie_config& c) {
   const size_t rows = direct_pool_items(c) * c.n_q_heads;
   return rows < (size_t)kDirectRows ? rows : (size_t)kDirectRows;
 }
+// and for the layers of a step that share a launch: every layer's, but no more than a 64th of what the caches take or 32 MB
+inline size_t direct_step_rows(const pie_config& c) {
+  const size_t one = direct_pool_rows(c), all = one * (size_t)c.n_layers;
+  const size_t token = (size_t)2 * c.n_kv_heads * c.head_dim * (c.dtype == PIE_DTYPE_F32 ? 4 : 2);
+  const size_t share = (size_t)c.n_layers * c.n_gpu_blocks * c.block_tokens * token / 64, least = (size_t)32 << 20;
+  const size_t some = (share > least ? share : least) / ((size_t)(c.head_dim + 4) * 4);
+  return some <= one ? one : some < all ? some : all;
+}
 inline size_t direct_pool_words(const pie_config& c) {
   const size_t pairs = (size_t)c.max_batch * c.n_kv_heads;
   return pairs < (size_t)kArriveWords ? pairs : (size_t)kArriveWords;

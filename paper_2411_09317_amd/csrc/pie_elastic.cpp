@@ -186,6 +186,7 @@ struct pie_elastic_pool {
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
   std::vector<hipEvent_t> ev_layer;    // last compute work on a layer
   std::vector<uint8_t> ev_layer_rec;
+  std::vector<int32_t> ev_of;          // whose event a layer's last work completes: layers that share a launch share the last's
   pie_layer_stats stats;
   int32_t prev_layer = -1;
   int32_t live_chunks = -1;            // chunks of a cache that hold live blocks (-1: all)
@@ -206,6 +207,14 @@ int send_map(pie_elastic_pool* lp, int32_t j, hipStream_t s) {
   list.n = (int32_t)c.size();
   std::copy(c.begin(), c.end(), list.chunk);
   return pie::launch_chunk_map_fill(lp->d_maps + (size_t)j * lp->H, lp->H, lp->C, list, s);
+}
+
+// Every layer is on the GPU and the protocol would move none: its checks change nothing, whichever layer computes.
+bool all_settled(const pie_layer_sched* s) {
+  if (s->moving_in >= 0 || s->moving_out >= 0 || s->oversubscribed()) return false;
+  for (const pie_layer_entry& e : s->table)
+    if (e.state != PIE_LAYER_GPU) return false;
+  return true;
 }
 
 int on_out_complete(pie_elastic_pool* lp, hipStream_t cs) {
@@ -259,7 +268,7 @@ int copy_chunks(pie_elastic_pool* lp, int kind, char* host_image, const std::vec
 int start_moves(pie_elastic_pool* lp, const pie_layer_action& a, hipStream_t cs, hipStream_t is, hipStream_t os) {
   int rc_copy;
   if (a.out_layer >= 0) {
-    if (lp->ev_layer_rec[a.out_layer]) PIE_HIP(hipEventSynchronize(lp->ev_layer[a.out_layer]));
+    if (lp->ev_layer_rec[a.out_layer]) PIE_HIP(hipEventSynchronize(lp->ev_layer[lp->ev_of[a.out_layer]]));
     const std::vector<int32_t>& c = lp->book->chunks[a.out_layer];
     // only the chunks that hold live blocks travel; the others are simply given up
     const size_t n_carry = lp->live_chunks < 0 ? c.size() : std::min(c.size(), (size_t)lp->live_chunks);
@@ -332,6 +341,7 @@ int pie_elastic_create(pie_pool* pool, int32_t chunk_blocks, int32_t max_chunks_
   }
   lp->ev_layer.assign(lp->n, nullptr);
   lp->ev_layer_rec.assign(lp->n, 0);
+  for (int32_t j = 0; j < lp->n; ++j) lp->ev_of.push_back(j);
   bool ok = hipEventCreateWithFlags(&lp->ev_in, hipEventDisableTiming) == hipSuccess &&
             hipEventCreateWithFlags(&lp->ev_out, hipEventDisableTiming) == hipSuccess;
   for (hipEvent_t& e : lp->ev_layer) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
@@ -438,6 +448,7 @@ int pie_elastic_move_blocks(pie_elastic_pool* lp, int32_t n, const int32_t* src,
         if ((rc = pie::launch_swap_copy(lp->pool->d_kv, lp->pool->d_kv, bb, pairs, 32, cs, 25604))) return rc;
       }
       PIE_HIP(hipEventRecord(lp->ev_layer[j], cs));                  // a later swap-out of the layer waits for this
+      lp->ev_of[j] = j;
       lp->ev_layer_rec[j] = 1;
     } else {
       // in CPU memory: inside its image; a source beyond what it carries holds nothing for this layer yet
@@ -521,6 +532,42 @@ int pie_elastic_step(pie_elastic_pool* lp, const void* d_q_all, const void* d_k_
   const bool direct = path != pie::kStepPlanned, append_apart = d_k_new && path != pie::kStepDirect;
   if (!direct && (rc = pie::launch_attn_plan(p, d_ctx_lens, batch, max_blocks, cs, false, nullptr, d_k_new != nullptr)))
     return rc;
+  // The layers share the split; every one looks its blocks up through a map of its own.  While all are on the GPU and none
+  // has to move, nothing is to be done between them and they share a launch.
+  const bool split_once = direct && lp->n > 1 &&
+                          pie::layers_apart(d_out_all, d_q_all, lp->n * q_stride, d_k_new, d_v_new, lp->n * kv_stride);
+  const bool together = split_once && all_settled(lp->sched) && !(p->layer_compute_us > 0.f);
+  const pie::LayerView first{p->d_kv, lp->d_maps, lp->H, lp->N * lp->C};
+  if (split_once) {
+    pie::AppendArgs rows;
+    const bool store = together && d_k_new;
+    if (store && (rc = pie::append_args(p, 0, lp->n, d_k_new, d_v_new, d_block_table, max_blocks, d_ctx_lens, batch,
+                                        pie::kAppendGpuStrict, &first, &rows)))
+      return rc;
+    if ((rc = pie::launch_step_begin(p, d_block_table, max_blocks, d_ctx_lens, batch, false, d_k_new != nullptr, -1, 0, cs,
+                                     store ? &rows : nullptr, lp->n)))
+      return rc;
+  }
+  if (together) {
+    for (int32_t k = 0, m; k < lp->n; k += m) {
+      m = std::min(pie::attn_step_layers(p, batch, max_blocks), lp->n - k);
+      const pie::LayerView view{p->d_kv, lp->d_maps + (size_t)k * lp->H, lp->H, lp->N * lp->C};
+      if ((rc = pie::launch_attn_direct(p, k, (const char*)d_q_all + k * q_stride, d_block_table, max_blocks, d_ctx_lens, batch,
+                                        (char*)d_out_all + k * q_stride, false, cs,
+                                        d_k_new ? (const char*)d_k_new + k * kv_stride : nullptr,
+                                        d_k_new ? (const char*)d_v_new + k * kv_stride : nullptr, -1, &view, nullptr, nullptr,
+                                        nullptr, nullptr, k + m == lp->n ? lp->ev_layer[lp->n - 1] : nullptr,
+                                        pie::kDirectPlanReplaySplit, false, m)))
+        return rc;
+    }
+    for (int32_t k = 0; k < lp->n; ++k) {
+      lp->ev_of[k] = lp->n - 1;
+      lp->ev_layer_rec[k] = 1;
+    }
+    lp->prev_layer = lp->n - 1;
+    ++lp->stats.n_steps;
+    return PIE_OK;
+  }
   for (int32_t k = 0; k < lp->n; ++k) {
     // the presence check: wait until the layer is physically on the GPU
     if ((rc = poll_moves(lp, cs))) return rc;
@@ -556,7 +603,7 @@ int pie_elastic_step(pie_elastic_pool* lp, const void* d_q_all, const void* d_k_
     if (direct) {
       if ((rc = pie::launch_attn_direct(p, k, q_k, d_block_table, max_blocks, d_ctx_lens, batch, out_k, false, cs, k_k, v_k,
                                         d_k_new && !append_apart ? pie::kAppendGpuStrict : -1, &view, nullptr, nullptr, nullptr, nullptr,
-                                        done, k == 0 ? pie::kDirectPlanWrite : pie::kDirectPlanReplaySplit)))
+                                        done, split_once ? pie::kDirectPlanReplaySplit : pie::kDirectPlanNone)))
         return rc;
     } else {
       if ((rc = pie::launch_attn_resolve(p, d_block_table, d_ctx_lens, batch, max_blocks, true, false, false, false, cs,
@@ -568,6 +615,7 @@ int pie_elastic_step(pie_elastic_pool* lp, const void* d_q_all, const void* d_k_
     }
     if (p->layer_compute_us > 0.f && (rc = pie::launch_busy(p->layer_compute_us, p->wall_clock_khz, cs))) return rc;
     if (!done) PIE_HIP(hipEventRecord(lp->ev_layer[k], cs));
+    lp->ev_of[k] = k;
     lp->ev_layer_rec[k] = 1;
     // The protocol's two checks belong to the moment this layer starts computing, which is when the previous
     // one has ended: the host waits for that (this layer's work is already queued behind it), then looks.

@@ -261,23 +261,52 @@ int launch_attn_decode(const pie_pool* p, int32_t layer, const void* d_q, int32_
 inline int32_t attn_min_units(const pie_pool* p) { return p->n_cu * 17; }   // see k_attn_plan
 // The one-launch attention path (pie_attn_direct.hip): whether it takes a call, and the launch,
 // which needs no planning before it.  append: kAppend* mode in which the new rows are stored as well, or -1.
-// plan: whether the launch leaves its split and slots for the layers of the same region that follow with the same batch,
-// table, context lengths and maps (kDirectPlanWrite), or starts from what one left: all of it (kDirectPlanReplay), or
-// the split alone (kDirectPlanReplaySplit: the layer has a map of its own).  leave_room: a gather kernel runs beside it.
-constexpr int32_t kDirectPlanNone = 0, kDirectPlanWrite = 1, kDirectPlanReplay = 2, kDirectPlanReplaySplit = 3;
-// How the layers of a step of n_layers run: planned, or in a launch each, which stores the new rows or leaves that to
-// k_kv_append.  The same for every kind of step, so that their results are the same bits.
+// plan: whether the launch works its split and slots out for itself, or starts from what launch_attn_split left with the
+// same batch, table, context lengths and maps: all of it (kDirectPlanReplay), or the split alone (kDirectPlanReplaySplit:
+// the layer has a map of its own).  leave_room: a gather kernel runs beside it.  n_layers: the launch takes so many layers
+// from `layer` on, at most attn_step_layers.  region: whose map and plan it reads; -1: the layer's.
+constexpr int32_t kDirectPlanNone = 0, kDirectPlanReplay = 1, kDirectPlanReplaySplit = 2;
+// How the layers of a step of n_layers run: planned, or by k_attn_direct, whose launches where layers move store the new
+// rows or leave that to k_kv_append.  The same for every kind of step, so that their results are the same bits.
 constexpr int kStepPlanned = 0, kStepDirect = 1, kStepDirectAppendApart = 2;
 int attn_step_path(const pie_pool* p, int32_t n_layers, int32_t batch, int32_t max_blocks);
 bool attn_direct(const pie_pool* p, int32_t batch, int32_t max_blocks);
 size_t attn_direct_floats(const pie_config& c);
-size_t attn_arrive_words(const pie_config& c);   // arrival words in a pool
+size_t attn_arrive_lines(const pie_config& c);   // lines of arrival words in a pool
+// The new rows of one or more layers, to be stored into their tail blocks.
+struct AppendArgs {
+  char* kv_layer;            // device pool base of this layer
+  const int32_t* map;
+  uint32_t* err;
+  const char* k_new;         // [B][Hkv][d]
+  const char* v_new;
+  const int32_t* table;
+  const int32_t* ctx;
+  size_t block_bytes;
+  size_t kv_layer_stride;    // bytes between layers in the pool ...
+  size_t new_layer_stride;   // ... and in k_new / v_new
+  int32_t map_stride;        // ... and entries between their maps (0: one for all)
+  int32_t max_blocks, n_handles, n_gpu_blocks, n_slots, n_kv_heads, head_dim, block_tokens, elem_bytes;
+  int32_t mode;              // kAppend*: which tail blocks this launch writes
+};
+int append_args(const pie_pool* p, int32_t layer, int32_t n_layers, const void* d_k, const void* d_v, const int32_t* d_table,
+                int32_t max_blocks, const int32_t* d_ctx, int32_t batch, int32_t mode, const LayerView* view, AppendArgs* out);
+int launch_step_begin(const pie_pool* p, const int32_t* d_table, int32_t max_blocks, const int32_t* d_ctx, int32_t batch,
+                      bool stage_valid, bool without_last, int32_t append, int32_t regions, hipStream_t s,
+                      const AppendArgs* rows = nullptr, int32_t n_layers = 0);
+// Whether layers may run together that were to run in order: none of their results lies where another's input does.
+inline bool layers_apart(const void* out, const void* q, size_t q_bytes, const void* k, const void* v, size_t kv_bytes) {
+  const uintptr_t o = (uintptr_t)out;
+  auto clear_of = [&](const void* in, size_t n) { return !in || o + q_bytes <= (uintptr_t)in || (uintptr_t)in + n <= o; };
+  return clear_of(q, q_bytes) && clear_of(k, kv_bytes) && clear_of(v, kv_bytes);
+}
+int32_t attn_step_layers(const pie_pool* p, int32_t batch, int32_t max_blocks);
 int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const int32_t* d_table, int32_t max_blocks,
                        const int32_t* d_ctx, int32_t batch, void* d_out, bool stage_valid, hipStream_t s,
                        const void* d_k_new = nullptr, const void* d_v_new = nullptr, int32_t append = -1,
                        const LayerView* view = nullptr, const AttnWork* work = nullptr, hipEvent_t k_start = nullptr,
                        hipEvent_t k_end = nullptr, unsigned long long* clock_row = nullptr, hipEvent_t done = nullptr,
-                       int32_t plan = 0, bool leave_room = false);
+                       int32_t plan = 0, bool leave_room = false, int32_t n_layers = 1, int32_t region = -1);
 int launch_stream_probe(const pie_pool* p, int32_t layer, int32_t max_blocks, int32_t batch, hipStream_t s);
 int attn_static_scratch(char** out, std::atomic<uint64_t>** out_launches = nullptr);
 int attn_static_work(const pie_pool* p, int32_t batch, int32_t max_blocks, AttnWork* out);

@@ -241,78 +241,15 @@ int launch_swap_copy(char* dst_layer_base, const char* src_layer_base, size_t bl
 // KV append: one workgroup per sequence copies the new token's key and value rows into its tail block
 // ---------------------------------------------------------------------------------------------------
 
-constexpr int kAppendBlockTokens = 16;
-
-struct AppendArgs {
-  char* kv_layer;            // device pool base of this layer
-  const int32_t* map;
-  uint32_t* err;
-  const char* k_new;         // [B][Hkv][d]
-  const char* v_new;
-  const int32_t* table;
-  const int32_t* ctx;
-  size_t block_bytes;
-  size_t kv_layer_stride;    // blockIdx.y walks layers: bytes between layers in the pool ...
-  size_t new_layer_stride;   // ... and in k_new / v_new
-  int32_t max_blocks, n_handles, n_gpu_blocks, n_slots, n_kv_heads, head_dim, block_tokens, elem_bytes;
-  int32_t mode;              // kAppend*: which tail blocks this launch writes
-};
-
-__global__ __launch_bounds__(256) void k_kv_append(const AppendArgs a) {
-  const int32_t b = blockIdx.x;
-  const int32_t ctx = a.ctx[b];
-  if (ctx <= 0) return;
-  const int32_t pos = ctx - 1;
-  const int32_t j = pos / a.block_tokens;
-  if (j >= a.max_blocks) {
-    if (threadIdx.x == 0) atomicOr(a.err, PIE_DEVERR_BAD_HANDLE);
-    return;
-  }
-  __shared__ int32_t s_slot;
-  if (threadIdx.x == 0)
-    s_slot = append_slot(a.table[(size_t)b * a.max_blocks + j], a.map, a.n_handles, a.n_gpu_blocks, a.n_slots, a.mode, true,
-                         a.err);
-  __syncthreads();
-  const int32_t slot = s_slot;
-  if (slot < 0) return;
-  // one 16-byte vector of a key row goes to one vector of the K tile; a value row is scattered element by
-  // element over the V tile's token-quad vectors
-  const int32_t v = 16 / a.elem_bytes;
-  const int32_t vec_per_row = a.head_dim / v;
-  const int32_t tile_bytes = kAppendBlockTokens * a.head_dim * a.elem_bytes;
-  char* blk = a.kv_layer + blockIdx.y * a.kv_layer_stride + (size_t)slot * a.block_bytes;
-  const char* k_new = a.k_new + blockIdx.y * a.new_layer_stride;
-  const char* v_new = a.v_new + blockIdx.y * a.new_layer_stride;
-  const size_t v_off = a.block_bytes / 2;
-  const int32_t t = pos % kAppendBlockTokens;
-  const int32_t n_vec = a.n_kv_heads * vec_per_row;
-  for (int32_t i = threadIdx.x; i < n_vec; i += blockDim.x) {
-    const int32_t g = i / vec_per_row, cv = i % vec_per_row;
-    const size_t src = ((size_t)b * a.n_kv_heads + g) * a.head_dim * a.elem_bytes + (size_t)cv * 16;
-    const size_t dst = (size_t)g * tile_bytes + (size_t)k_tile_index(t, cv * v, v) * a.elem_bytes;
-    *reinterpret_cast<uint4*>(blk + dst) = *reinterpret_cast<const uint4*>(k_new + src);
-  }
-  const int32_t n_el = a.n_kv_heads * a.head_dim;
-  for (int32_t i = threadIdx.x; i < n_el; i += blockDim.x) {
-    const int32_t g = i / a.head_dim, c = i % a.head_dim;
-    const size_t src = ((size_t)b * a.n_kv_heads + g) * a.head_dim + c;
-    const size_t dst = v_off + (size_t)g * tile_bytes + (size_t)v_tile_index(t, c, v) * a.elem_bytes;
-    if (a.elem_bytes == 2)
-      *reinterpret_cast<uint16_t*>(blk + dst) = reinterpret_cast<const uint16_t*>(v_new)[src];
-    else
-      *reinterpret_cast<uint32_t*>(blk + dst) = reinterpret_cast<const uint32_t*>(v_new)[src];
-  }
-}
+__global__ __launch_bounds__(256) void k_kv_append(const AppendArgs a) { append_rows(a, blockIdx.x, blockIdx.y); }
 
 // Appends for n_layers consecutive layers starting at `layer` in one launch.  With n_layers > 1 only modes
 // that leave staged copies alone make sense (staging regions hold one layer each).
-int launch_kv_append(const pie_pool* p, int32_t layer, int32_t n_layers, const void* d_k, const void* d_v,
-                     const int32_t* d_table, int32_t max_blocks, const int32_t* d_ctx, int32_t batch,
-                     int32_t mode, hipStream_t s, const LayerView* view) {
+int append_args(const pie_pool* p, int32_t layer, int32_t n_layers, const void* d_k, const void* d_v, const int32_t* d_table,
+                int32_t max_blocks, const int32_t* d_ctx, int32_t batch, int32_t mode, const LayerView* view, AppendArgs* out) {
   if (((uintptr_t)d_k | (uintptr_t)d_v) % 16) return PIE_EINVAL;
   if (n_layers < 1 || (n_layers > 1 && (mode == kAppendPresent || mode == kAppendStaged))) return PIE_EINVAL;
-  if (view && n_layers != 1) return PIE_EINVAL;
-  AppendArgs a;
+  AppendArgs& a = *out;
   a.kv_layer = p->d_kv + (size_t)layer * p->d_layer_stride;
   a.map = p->d_map[layer & 1];
   a.err = p->d_err;
@@ -323,6 +260,7 @@ int launch_kv_append(const pie_pool* p, int32_t layer, int32_t n_layers, const v
   a.block_bytes = p->block_bytes;
   a.kv_layer_stride = p->d_layer_stride;
   a.new_layer_stride = (size_t)batch * p->cfg.n_kv_heads * p->cfg.head_dim * p->elem_bytes;
+  a.map_stride = 0;
   a.max_blocks = max_blocks;
   a.n_handles = p->n_handles;
   a.n_gpu_blocks = p->cfg.n_gpu_blocks;
@@ -334,10 +272,21 @@ int launch_kv_append(const pie_pool* p, int32_t layer, int32_t n_layers, const v
   a.mode = mode;
   if (view) {                                    // the layer's blocks live elsewhere: all of them "GPU-homed" there
     a.kv_layer = view->kv_base;
+    a.kv_layer_stride = 0;
     a.map = view->map;
-    a.n_handles = view->n_handles;
+    a.map_stride = a.n_handles = view->n_handles;
     a.n_gpu_blocks = a.n_slots = view->n_slots;
   }
+  return PIE_OK;
+}
+
+int launch_kv_append(const pie_pool* p, int32_t layer, int32_t n_layers, const void* d_k, const void* d_v,
+                     const int32_t* d_table, int32_t max_blocks, const int32_t* d_ctx, int32_t batch,
+                     int32_t mode, hipStream_t s, const LayerView* view) {
+  if (view && n_layers != 1) return PIE_EINVAL;
+  AppendArgs a;
+  const int rc = append_args(p, layer, n_layers, d_k, d_v, d_table, max_blocks, d_ctx, batch, mode, view, &a);
+  if (rc) return rc;
   hipLaunchKernelGGL(k_kv_append, dim3(batch, n_layers), dim3(256), 0, s, a);
   PIE_HIP(hipGetLastError());
   return PIE_OK;

@@ -379,7 +379,11 @@ int pie_layer_step(pie_layer_pool* lp, const void* d_q_all, const void* d_k_new,
   // the layers may be one launch each, in small steps appends included (pie_attn_direct.hip)
   const int path = pie::attn_step_path(p, lp->n_layers, batch, max_blocks);
   const bool direct = path != pie::kStepPlanned, append_apart = d_k_new && path != pie::kStepDirect;
-  bool split_left[2] = {false, false};           // whether a layer in a GPU slot of this parity has left split and slots
+  // (layers move, so each stores its own rows; the split and the slots of both maps are worked out once)
+  if (direct && lp->n_layers > 1 &&
+      (rc = pie::launch_step_begin(p, d_block_table, max_blocks, d_ctx_lens, batch, false, d_k_new != nullptr,
+                                   d_k_new && !append_apart ? pie::kAppendGpuStrict : -1, 2, cs)))
+    return rc;
   for (int32_t k = 0; k < lp->n_layers; ++k) {
     // one ticket counter per launch since the last planning kernel; there are as many as GPU slots
     if (!direct && k % n_slots == 0) {
@@ -421,12 +425,10 @@ int pie_layer_step(pie_layer_pool* lp, const void* d_q_all, const void* d_k_new,
       return rc;
     if (direct) {
       // every layer's blocks are in the same slots of its image, and a slot's parity says which map is read
-      const int32_t plan = lp->n_layers <= 2 ? pie::kDirectPlanNone
-                           : split_left[slot & 1] ? pie::kDirectPlanReplay : pie::kDirectPlanWrite;
-      split_left[slot & 1] = true;
       if ((rc = pie::launch_attn_direct(p, slot, q_k, d_block_table, max_blocks, d_ctx_lens, batch, out_k, false, cs, k_k,
                                         v_k, d_k_new && !append_apart ? pie::kAppendGpuStrict : -1, nullptr, nullptr, nullptr,
-                                        nullptr, nullptr, done, plan)))
+                                        nullptr, nullptr, done,
+                                        lp->n_layers == 1 ? pie::kDirectPlanNone : pie::kDirectPlanReplay)))
         return rc;
     } else {
       if ((rc = pie::launch_attn_decode(p, slot, q_k, max_blocks, d_ctx_lens, batch, out_k, cs, nullptr, nullptr,

@@ -61,7 +61,7 @@ static Layout layout_of(const pie_config& c) {
   l.off_plan = off; off = align_up(off + attn_plan_ints(c) * 4, kAlign);
   l.off_err = off; off += kAlign;
   l.off_arrive = off;                            // (cleared with the error page, in one launch)
-  off = align_up(off + attn_arrive_words(c) * kArriveStride * 8, kAlign);
+  off = align_up(off + attn_arrive_lines(c) * kArriveStride * 8, kAlign);
   l.off_clock = off;
   off = align_up(off + (((size_t)c.n_layers + 1) * kClockRow + (size_t)c.n_layers * kClockWgs * 2) * 8, kAlign);
   l.d_total = off;
@@ -541,7 +541,7 @@ int pie_pool_init(const pie_config* cfg, void* d_base, size_t d_bytes, void* h_p
     // maps start empty, error flags clear (default stream; synchronised before returning)
     if ((rc = launch_map_fill(p->d_map[0], p->n_handles, -1, nullptr))) return fail(rc);
     if ((rc = launch_map_fill(p->d_map[1], p->n_handles, -1, nullptr))) return fail(rc);
-    if ((rc = launch_zero_u32(p->d_err, (int32_t)(kAlign / 4 + attn_arrive_words(*cfg) * kArriveStride * 2), nullptr)))
+    if ((rc = launch_zero_u32(p->d_err, (int32_t)(kAlign / 4 + attn_arrive_lines(*cfg) * kArriveStride * 2), nullptr)))
       return fail(rc);
     if ((rc = launch_zero_u32((uint32_t*)p->d_clock, (cfg->n_layers + 1) * kClockRow * 2, nullptr))) return fail(rc);
     err = hipStreamSynchronize(nullptr);
@@ -1014,18 +1014,22 @@ static int step_body(pie_pool* p, const StepJob& j) {
   if ((rc = wait_if(cs, p->ev_migrate, p->ev_migrate_rec))) return rc;
   if ((rc = flush_map(p, cs))) return rc;
   // With a new token, the attention reads the context without it from the cache and takes the token itself from
-  // the new rows (the reduction kernel adds it), so no layer waits for the appends that store the rows: the one
-  // launch for the GPU-homed tail blocks of every layer runs on the write-back stream beside the first layers
-  // (the compute stream waits for it when the step ends, and then only if the host does not see it finished),
-  // and the host-homed tails get theirs on the same stream once the copy that stages them for a layer has
-  // arrived, just ahead of their write-back.
+  // the new rows (the reduction kernel adds it), so no layer waits for the appends that store the rows.  Those of the
+  // GPU-homed tail blocks of every layer are stored by one launch: with k_attn_direct by the one ahead of the layers, with
+  // the planned kernels by one on the write-back stream beside the first layers (the compute stream waits for it when the
+  // step ends, and then only if the host does not see it finished).  The host-homed tails get theirs on the write-back
+  // stream once the copy that stages them for a layer has arrived, just ahead of their write-back.
   const bool with_new = d_k_new != nullptr;
   const bool staged_tails = with_new && n_dirty > 0;
   const int32_t append_mode = staged_tails ? kAppendGpuHomed : kAppendGpuStrict;
-  // The layers may be one launch each, which in small steps stores the GPU-homed tails' rows too (pie_attn_direct.hip).
   const int path = attn_step_path(p, L, batch, max_blocks);
   const bool direct = path != kStepPlanned;
-  const bool append_apart = with_new && path != kStepDirect;
+  const bool append_apart = with_new && !direct;
+  // All layers' inputs are there when the step is called.  So where nothing is staged and nothing measured between them
+  // they share launches, and a plan in any case - unless a layer's result lies where another layer's input is.
+  const bool apart = layers_apart(d_out_all, d_q_all, L * q_stride, d_k_new, d_v_new, L * kv_stride);
+  const bool planned_once = direct && L > 1 && apart;
+  const bool together = planned_once && n_prefetch == 0 && !timed && !clocked && !(p->layer_compute_us > 0.f);
   if (append_apart || staged_tails) {            // the appends read the maps sent above
     PIE_HIP(hipEventRecord(p->ev_map, cs));
     p->ev_map_rec = true;
@@ -1037,6 +1041,15 @@ static int step_body(pie_pool* p, const StepJob& j) {
   if (!direct &&
       (rc = launch_attn_resolve(p, d_block_table, d_ctx_lens, batch, max_blocks, true, true, L > 1, true, cs)))
     return rc;
+  if (planned_once) {
+    AppendArgs rows;
+    if (with_new && (rc = append_args(p, 0, L, d_k_new, d_v_new, d_block_table, max_blocks, d_ctx_lens, batch, append_mode,
+                                      nullptr, &rows)))
+      return rc;
+    if ((rc = launch_step_begin(p, d_block_table, max_blocks, d_ctx_lens, batch, true, with_new, -1, together ? 1 : 2, cs,
+                                with_new ? &rows : nullptr, L)))
+      return rc;
+  }
   if (with_new) note_stream(p, os);
   if ((append_apart || staged_tails) && os != cs) PIE_HIP(hipStreamWaitEvent(os, p->ev_map, 0));
   if (append_apart) {
@@ -1072,7 +1085,20 @@ static int step_body(pie_pool* p, const StepJob& j) {
   const size_t long_enough = (size_t)(p->cfg.n_q_heads > p->cfg.n_kv_heads ? 2 : 1) << 20;
   const bool leave_room = n_prefetch > 0 && !p->in_on_host[0] && (size_t)n_prefetch * p->block_bytes > long_enough;
   double t_free = -1.0, layer_us = -1.0;
-  for (int32_t l = 0; l < L; ++l) {
+  if (together) {
+    const int32_t most = attn_step_layers(p, batch, max_blocks);
+    for (int32_t l = 0, n; l < L; l += n) {
+      n = std::min(most, L - l);
+      const char* q_l = (const char*)d_q_all + l * q_stride;
+      char* out_l = (char*)d_out_all + l * q_stride;
+      const char* k_l = with_new ? (const char*)d_k_new + l * kv_stride : nullptr;
+      const char* v_l = with_new ? (const char*)d_v_new + l * kv_stride : nullptr;
+      if ((rc = launch_attn_direct(p, l, q_l, d_block_table, max_blocks, d_ctx_lens, batch, out_l, true, cs, k_l, v_l, -1,
+                                   nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, kDirectPlanReplay, false, n, 0)))
+        return rc;
+    }
+  }
+  for (int32_t l = 0; l < L && !together; ++l) {
     // The presence check: the layer's staged blocks have arrived (migrations and map updates were waited
     // for and sent once, at the start of the step).  A wait on the compute stream costs about 8 us even when
     // the event has long completed, so the host first looks for itself: the layer before is still computing,
@@ -1104,8 +1130,8 @@ static int step_body(pie_pool* p, const StepJob& j) {
     hipEvent_t done = standin ? nullptr : read_done;
     if (direct)
       rc = launch_attn_direct(p, l, q_l, d_block_table, max_blocks, d_ctx_lens, batch, out_l, true, cs, k_l, v_l,
-                              with_new && !append_apart ? append_mode : -1, nullptr, nullptr, k_start, k_end, clock_row(l), done,
-                              L <= 2 ? kDirectPlanNone : l < 2 ? kDirectPlanWrite : kDirectPlanReplay, leave_room);
+                              with_new && !planned_once ? append_mode : -1, nullptr, nullptr, k_start, k_end, clock_row(l), done,
+                              planned_once ? kDirectPlanReplay : kDirectPlanNone, leave_room);
     else
       rc = launch_attn_decode(p, l, q_l, max_blocks, d_ctx_lens, batch, out_l, cs, k_start, k_end, -1, clock_row(l),
                               nullptr, done, nullptr, k_l, v_l);

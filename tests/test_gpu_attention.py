@@ -359,6 +359,55 @@ def test_big_steps_without_grouped_queries_give_the_bits_of_the_planned_path():
     lib.close()
 
 
+@pytest.mark.parametrize("layers,hq,hkv,d,dtype,ctx,width", [
+    (2, 8, 8, 64, I.DTYPE_F32, [1, 300, 64], 19),
+    (17, 8, 2, 128, I.DTYPE_BF16, [700, 1, 16, 17, 0, 1000], 64),              # a second line of arrival words
+    (33, 4, 1, 64, I.DTYPE_F16, [2100], 140),                                  # a third
+    (5, 64, 8, 128, I.DTYPE_BF16, [1 + i % 16 for i in range(250)], 3),        # scratch for three layers a launch
+])
+def test_layers_that_share_a_launch_give_the_bits_of_a_launch_each(layers, hq, hkv, d, dtype, ctx, width):
+    """A step whose layers share launches against the same step with events between its layers, which keep them apart:
+    results and caches, bit for bit; once more from a graph; and where a layer's result is the next one's query, which the
+    step must notice, against layer-by-layer calls."""
+    ctx = np.asarray(ctx, np.int32)
+    lib, q, k, v, tb, cl = _noise_pool(layers, hq, hkv, d, dtype, ctx, width, 6)
+    save = lib.gpu_image().clone()
+    s, got = torch.cuda.Stream(), []
+    for timing in (B.TIMING_EVENTS, B.TIMING_OFF):
+        lib.set_timing(timing)
+        lib.gpu_image().copy_(save)
+        out = torch.full_like(q, float("nan"))
+        torch.cuda.synchronize()
+        lib.step(q, k, v, tb, cl, [], [], out, s, s, s)
+        lib.sync()
+        assert lib.check_errors() == 0
+        got.append((out, lib.gpu_image().clone()))
+    bits = torch.int32 if dtype == I.DTYPE_F32 else torch.int16
+    assert torch.equal(got[0][0].view(bits), got[1][0].view(bits)) and torch.equal(got[0][1], got[1][1])
+    assert not torch.equal(got[0][1], save)
+    graph, out = torch.cuda.CUDAGraph(), torch.full_like(q, float("nan"))
+    with torch.cuda.graph(graph, stream=s):
+        lib.step(q, None, None, tb, cl, [], [], out, s, s, s)
+    for _ in range(3):
+        want = torch.full_like(q, float("nan"))
+        lib.step(q, None, None, tb, cl, [], [], want, s, s, s)
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(bits), want.view(bits))
+    del graph
+    both = torch.cat([q, torch.full_like(q[:1], float("nan"))])       # layer l's result is layer l + 1's query
+    chain, want = both.clone(), both.clone()
+    torch.cuda.synchronize()
+    lib.step(chain[:-1], None, None, tb, cl, [], [], chain[1:], s, s, s)
+    lib.set_timing(B.TIMING_EVENTS)
+    lib.step(want[:-1], None, None, tb, cl, [], [], want[1:], s, s, s)
+    lib.sync()
+    assert torch.equal(chain.view(bits), want.view(bits)) and lib.check_errors() == 0
+    lib.close()
+
+
 @pytest.mark.parametrize("batch", [1, 63, 64, 257, 1023, 1029])
 def test_planning_of_batches_around_its_rounds(batch):
     """The planning kernel scans the batch in rounds of one sequence per thread (256 or 1024 threads) and ranks the
