@@ -257,7 +257,8 @@ int launch_attn_decode(const pie_pool* p, int32_t layer, const void* d_q, int32_
                        hipEvent_t k_end = nullptr, int32_t ticket_index = -1,
                        unsigned long long* clock_row = nullptr, const LayerView* view = nullptr,
                        hipEvent_t done = nullptr, const AttnWork* work = nullptr, const void* d_k_new = nullptr,
-                       const void* d_v_new = nullptr);
+                       const void* d_v_new = nullptr, int32_t n_layers = 1);
+int32_t attn_planned_layers(const pie_pool* p, int32_t batch, int32_t max_blocks);
 inline int32_t attn_min_units(const pie_pool* p) { return p->n_cu * 17; }   // see k_attn_plan
 // The one-launch attention path (pie_attn_direct.hip): whether it takes a call, and the launch,
 // which needs no planning before it.  append: kAppend* mode in which the new rows are stored as well, or -1.

@@ -498,6 +498,12 @@ struct AttnArgs {
   // that writes the rows into the cache.
   const char* new_k;
   const char* new_v;
+  // The layers of the launch, `kv_layer`, q, out, the new rows and the workspace being the first one's: bytes (of the
+  // workspace: floats) from one to the next.  They share the items and the slots.
+  // (All layers of a step at once, where nothing happens between them, have one ramp, one tail and one reduction: 32 layers
+  // of 64 sequences of 1 024 to 2 048 tokens, 32 heads, 8 039 us in a launch and a reduction each, 7 924 so.)
+  int32_t n_layers;
+  size_t kv_stride, q_stride, new_stride, ws_stride;
 };
 
 // LDS floats the MFMA kernel needs for `group` query heads per kv head
@@ -536,7 +542,8 @@ void k_attn_decode_mfma(const AttnArgs a) {
   const int32_t G = a.group;
   const int32_t n_q_heads = a.n_kv_heads * G;
   const uint32_t n_kv = (uint32_t)a.n_kv_heads;
-  const uint32_t max_units = (uint32_t)a.max_items * n_kv;        // what the item and slot lists have room for
+  const uint32_t per_item = n_kv * (uint32_t)a.n_layers;          // units: its kv heads, layer by layer
+  const uint32_t max_units = (uint32_t)a.max_items * per_item;    // what the item and slot lists have room for
   const size_t v_off = a.block_bytes / 2;
   const int32_t part_tokens = a.hdr[1];                           // the item size the planning kernel noted
   const int32_t bpi = part_tokens / kBlockTokens;                 // blocks per item, <= 64 * kWaves
@@ -564,27 +571,28 @@ void k_attn_decode_mfma(const AttnArgs a) {
     r = make_uint2(0, 0);
     sl = -1;
     if (u < max_units) {
-      const uint32_t item = u / n_kv;
+      const uint32_t item = u / per_item;
       r = a.items[item];
       if (lane < my_n) sl = a.slots[(size_t)item * bpi + wave + kWaves * lane];
     }
   };
   // this lane's part of the B operand of the first product: head `col` of the group, dims 32 kc + 8 quad ..
-  auto load_q = [&](uint4 (&qr)[NKC], int32_t b, int32_t g) {
+  auto load_q = [&](uint4 (&qr)[NKC], int32_t b, int32_t layer, int32_t g) {
+    const char* q = a.q + layer * a.q_stride;
 #pragma unroll
     for (int kc = 0; kc < NKC; ++kc) {
       qr[kc] = make_uint4(0, 0, 0, 0);
       const int head = VALU ? 0 : col;            // on the vector ALU every lane works for the one head
       if (head < G)
-        qr[kc] = *reinterpret_cast<const uint4*>(a.q + (((size_t)b * n_q_heads + g * G + head) * HD + 32 * kc + 8 * quad) * 2);
+        qr[kc] = *reinterpret_cast<const uint4*>(q + (((size_t)b * n_q_heads + g * G + head) * HD + 32 * kc + 8 * quad) * 2);
     }
   };
   // Two register sets: while one block is consumed the next is already in flight.
   uint4 kA[NKC], vA[NKC], kB[NKC], vB[NKC];
-  auto load_tile = [&](uint4 (&kr)[NKC], uint4 (&vr)[NKC], int32_t slots, int32_t it, int32_t g) {
+  auto load_tile = [&](uint4 (&kr)[NKC], uint4 (&vr)[NKC], int32_t slots, int32_t it, int32_t layer, int32_t g) {
     int32_t slot = __shfl(slots, it, 64);
     slot = slot < 0 ? 0 : slot;                                    // flagged blocks are masked when consumed
-    const char* kp = a.kv_layer + (size_t)slot * a.block_bytes + (size_t)g * TILE_BYTES + (size_t)lane * 16;
+    const char* kp = a.kv_layer + layer * a.kv_stride + (size_t)slot * a.block_bytes + (size_t)g * TILE_BYTES + (size_t)lane * 16;
 #pragma unroll
     for (int i = 0; i < NKC; ++i) kr[i] = nt_load16(kp + (size_t)i * 1024);
 #pragma unroll
@@ -603,14 +611,16 @@ void k_attn_decode_mfma(const AttnArgs a) {
   uint4 qreg[NKC];
   fetch_meta(unit, rec, my_slot);
   fetch_meta(next, rec_next, my_slot_next);
-  const uint32_t n_units = (uint32_t)a.hdr[0] * n_kv;              // <= max_units
+  const uint32_t n_units = (uint32_t)a.hdr[0] * per_item;          // <= max_units
+  auto layer_of = [&](uint32_t u) { return (int32_t)(u % per_item / n_kv); };
   if (unit < n_units) {
-    load_q(qreg, (int32_t)(rec.x & 0xffffu), (int32_t)(unit % n_kv));
-    if (wave_blocks(rec) > 0) load_tile(kA, vA, my_slot, 0, (int32_t)(unit % n_kv));
+    const int32_t layer = layer_of(unit), g = (int32_t)(unit % n_kv);
+    load_q(qreg, (int32_t)(rec.x & 0xffffu), layer, g);
+    if (wave_blocks(rec) > 0) load_tile(kA, vA, my_slot, 0, layer, g);
   }
 
   while (unit < n_units) {                       // every workgroup ends on a ticket past the last unit
-    const int32_t g = (int32_t)(unit % n_kv);
+    const int32_t layer = layer_of(unit), g = (int32_t)(unit % n_kv);
     const int32_t b = (int32_t)(rec.x & 0xffffu), part = (int32_t)(rec.x >> 16);
     const int32_t ctx_b = (int32_t)rec.y;                          // clamped context length of the sequence
     const int32_t tok0 = part * part_tokens;
@@ -707,10 +717,10 @@ void k_attn_decode_mfma(const AttnArgs a) {
     const int32_t it_ticket = n_it > 2 ? ((n_it / 2) & ~1) : 0;
     for (int32_t it = 0; it < n_it; it += 2) {
       if (it == it_ticket && threadIdx.x == 0) after_next = 2 * gridDim.x + atomicAdd(a.counter, 1u);
-      if (it + 1 < n_it) load_tile(kB, vB, my_slot, it + 1, g);
+      if (it + 1 < n_it) load_tile(kB, vB, my_slot, it + 1, layer, g);
       if constexpr (VALU) consume_valu(kA, vA, it); else consume(kA, vA, it);
       if (it + 1 < n_it) {
-        if (it + 2 < n_it) load_tile(kA, vA, my_slot, it + 2, g);
+        if (it + 2 < n_it) load_tile(kA, vA, my_slot, it + 2, layer, g);
         if constexpr (VALU) consume_valu(kB, vB, it + 1); else consume(kB, vB, it + 1);
       }
     }
@@ -718,9 +728,9 @@ void k_attn_decode_mfma(const AttnArgs a) {
 
     // behind the stream: the next unit's first block and query rows arrive while this unit's result is merged
     if (next < n_units) {
-      const int32_t g_next = (int32_t)(next % n_kv);
-      if (wave_blocks(rec_next) > 0) load_tile(kA, vA, my_slot_next, 0, g_next);
-      load_q(qreg, (int32_t)(rec_next.x & 0xffffu), g_next);
+      const int32_t layer_next = layer_of(next), g_next = (int32_t)(next % n_kv);
+      if (wave_blocks(rec_next) > 0) load_tile(kA, vA, my_slot_next, 0, layer_next, g_next);
+      load_q(qreg, (int32_t)(rec_next.x & 0xffffu), layer_next, g_next);
     }
 
     // merge the kWaves partial states: lane (quad, col) holds O[16 n + 4 quad + r][head col]
@@ -770,9 +780,9 @@ void k_attn_decode_mfma(const AttnArgs a) {
       }
       const size_t orow = (size_t)b * n_q_heads + hq0 + h;
       if (np_b == 1 && !a.new_k) {               // the only partition of its sequence: this is the result
-        store_elem<E>(a.out, orow * HD + dim, L > 0.f ? A / L : 0.f);
+        store_elem<E>(a.out + layer * a.q_stride, orow * HD + dim, L > 0.f ? A / L : 0.f);
       } else {
-        float* w = a.ws + (orow * a.n_parts + part) * (HD + 2);
+        float* w = a.ws + layer * a.ws_stride + (orow * a.n_parts + part) * (HD + 2);
         if (dim == 0) {
           w[0] = M;
           w[1] = L;
@@ -989,17 +999,23 @@ __global__ __launch_bounds__(256) void k_attn_reduce_heads(const AttnArgs a, int
   const int32_t hq = (int32_t)blockIdx.x * HPW + threadIdx.x / TPH;
   const ReduceRow r = reduce_row(a, b);
   if (r.skip) return;
+  const int32_t layer = blockIdx.z;
+  const char* q = a.q + layer * a.q_stride;
+  char* const out = a.out + layer * a.q_stride;
+  const char* const new_k = a.new_k + layer * a.new_stride;       // (followed only if there are any)
+  const char* const new_v = a.new_v + layer * a.new_stride;
+  const float* const ws = a.ws + layer * a.ws_stride;
   if (hq < n_q_heads) {
     const size_t row = (size_t)b * n_q_heads + hq;
     float qk = 0.f;
     float2 v_new = make_float2(0.f, 0.f);
     if (r.add_new) {
       const size_t kv_row = ((size_t)b * a.n_kv_heads + hq / a.group) * HD;
-      const float2 q2 = load_elem2<E>(a.q, row * HD + d0), k2 = load_elem2<E>(a.new_k, kv_row + d0);
+      const float2 q2 = load_elem2<E>(q, row * HD + d0), k2 = load_elem2<E>(new_k, kv_row + d0);
       qk = fmaf(q2.x, k2.x, q2.y * k2.y);
-      v_new = load_elem2<E>(a.new_v, kv_row + d0);
+      v_new = load_elem2<E>(new_v, kv_row + d0);
     }
-    const float* w = a.ws + row * a.n_parts * (HD + 2);
+    const float* w = ws + row * a.n_parts * (HD + 2);
     float M = kNegBig, L = 0.f;
     float2 A = make_float2(0.f, 0.f);
     for (int32_t s0 = 0; s0 < r.np; s0 += UNR) {
@@ -1041,7 +1057,7 @@ __global__ __launch_bounds__(256) void k_attn_reduce_heads(const AttnArgs a, int
       A.y = fmaf(A.y, w_old, w_new * v_new.y);
     }
     const float inv = L > 0.f ? 1.f / L : 0.f;
-    store_elem2<E>(a.out, row * HD + d0, make_float2(L > 0.f ? A.x * inv : 0.f, L > 0.f ? A.y * inv : 0.f));
+    store_elem2<E>(out, row * HD + d0, make_float2(L > 0.f ? A.x * inv : 0.f, L > 0.f ? A.y * inv : 0.f));
   }
   // the last workgroups dispatched are the last to end, to within a few of them: those of the last sequence
   // and one per 16 sequences note the time
@@ -1060,14 +1076,20 @@ __global__ __launch_bounds__(256) void k_attn_reduce(const AttnArgs a, int32_t n
   const int dim = threadIdx.x % HD, sub = threadIdx.x / HD;
   const ReduceRow r = reduce_row(a, b);
   if (r.skip) return;
+  const int32_t layer = blockIdx.z;
+  const char* q = a.q + layer * a.q_stride;
+  char* const out = a.out + layer * a.q_stride;
+  const char* const new_k = a.new_k + layer * a.new_stride;       // (followed only if there are any)
+  const char* const new_v = a.new_v + layer * a.new_stride;
+  const float* const ws = a.ws + layer * a.ws_stride;
   const size_t row = (size_t)b * n_q_heads + hq;
   float qk = 0.f, v_new = 0.f;
   if (r.add_new && sub == 0) {
     const size_t kv_row = ((size_t)b * a.n_kv_heads + hq / a.group) * HD;
-    qk = load_elem<E>(a.q, row * HD + dim) * load_elem<E>(a.new_k, kv_row + dim);
-    v_new = load_elem<E>(a.new_v, kv_row + dim);
+    qk = load_elem<E>(q, row * HD + dim) * load_elem<E>(new_k, kv_row + dim);
+    v_new = load_elem<E>(new_v, kv_row + dim);
   }
-  const float* w = a.ws + row * a.n_parts * (HD + 2);
+  const float* w = ws + row * a.n_parts * (HD + 2);
   float M = kNegBig, L = 0.f, A = 0.f;
   for (int32_t s0 = sub; s0 < r.np; s0 += NSUB * UNR) {
     float mi[UNR], li[UNR], ai[UNR];
@@ -1125,7 +1147,7 @@ __global__ __launch_bounds__(256) void k_attn_reduce(const AttnArgs a, int32_t n
       Lt = fmaf(Lt, w_old, w_new);
       At = fmaf(At, w_old, w_new * v_new);
     }
-    store_elem<E>(a.out, row * HD + dim, Lt > 0.f ? At / Lt : 0.f);
+    store_elem<E>(out, row * HD + dim, Lt > 0.f ? At / Lt : 0.f);
   }
   if (a.clock && threadIdx.x == 0 && (b == (int32_t)gridDim.y - 1 || (hq == 0 && (b & 15) == 15)))
     atomicMax(&a.clock[kClockLayerEnd], wall_clock64());
@@ -1262,10 +1284,10 @@ template <typename E, int HD>
 static void launch_reduce(const AttnArgs& a, int32_t batch, int32_t n_q_heads, hipStream_t s, hipEvent_t done) {
   if (a.n_parts <= 8) {                           // few partitions per sequence: several heads per workgroup
     constexpr int HPW = 512 / HD;
-    hipExtLaunchKernelGGL((k_attn_reduce_heads<E, HD>), dim3((n_q_heads + HPW - 1) / HPW, batch), dim3(256), 0, s,
+    hipExtLaunchKernelGGL((k_attn_reduce_heads<E, HD>), dim3((n_q_heads + HPW - 1) / HPW, batch, a.n_layers), dim3(256), 0, s,
                           nullptr, done, 0, a, n_q_heads);
   } else {
-    hipExtLaunchKernelGGL((k_attn_reduce<E, HD>), dim3(n_q_heads, batch), dim3(256), 0, s, nullptr, done, 0, a,
+    hipExtLaunchKernelGGL((k_attn_reduce<E, HD>), dim3(n_q_heads, batch, a.n_layers), dim3(256), 0, s, nullptr, done, 0, a,
                           n_q_heads);
   }
 }
@@ -1320,6 +1342,20 @@ static int launch_f32(const AttnArgs& a, int32_t batch, int32_t n_q_heads, int32
   return PIE_OK;
 }
 
+// How many layers of a planned step one launch may take: as many as the pool has room for partials of.  (The fp32 kernel,
+// which is not tuned, takes them one by one.)
+int32_t attn_planned_layers(const pie_pool* p, int32_t batch, int32_t max_blocks) {
+  const pie_config& c = p->cfg;
+  if (c.dtype == PIE_DTYPE_F32) return 1;
+  const int32_t part = part_tokens_of(p);
+  const size_t items = (size_t)batch * (((size_t)max_blocks * kBlockTokens + part - 1) / part);
+  if (!items) return 1;
+  size_t n = p->ws_floats / (items * c.n_q_heads * (c.head_dim + 2));
+  const size_t units = (size_t)1 << 31;           // (numbered in 32 bits, the grid's tickets beyond the last among them)
+  if (n > units / (items * c.n_kv_heads)) n = units / (items * c.n_kv_heads);
+  return n < 1 ? 1 : n < (size_t)c.n_layers ? (int32_t)n : c.n_layers;
+}
+
 // Needs launch_attn_plan and launch_attn_resolve (for region layer & 1) earlier on the same stream, with the
 // same batch, table width and context lengths.  d_k_new / d_v_new: the newest token's rows of this layer, taken
 // from there instead of from the cache (the planning launch must have been told: without_last); NULL = the cache
@@ -1327,7 +1363,7 @@ static int launch_f32(const AttnArgs& a, int32_t batch, int32_t n_q_heads, int32
 int launch_attn_decode(const pie_pool* p, int32_t layer, const void* d_q, int32_t max_blocks, const int32_t* d_ctx,
                        int32_t batch, void* d_out, hipStream_t s, hipEvent_t k_start, hipEvent_t k_end,
                        int32_t ticket_index, unsigned long long* clock_row, const LayerView* view, hipEvent_t done,
-                       const AttnWork* work, const void* d_k_new, const void* d_v_new) {
+                       const AttnWork* work, const void* d_k_new, const void* d_v_new, int32_t n_layers) {
   const pie_config& c = p->cfg;
   const AttnWork w = work ? *work : pool_work(p);
   if (((uintptr_t)d_q | (uintptr_t)d_out) % 16) return PIE_EINVAL;
@@ -1337,7 +1373,10 @@ int launch_attn_decode(const pie_pool* p, int32_t layer, const void* d_q, int32_
   const int32_t part = part_tokens_of(p);
   const int32_t max_tokens = max_blocks * kBlockTokens;
   const int32_t n_parts = (max_tokens + part - 1) / part;
-  if ((size_t)batch * c.n_q_heads * n_parts * (c.head_dim + 2) > w.ws_floats) return PIE_ENOMEM;
+  const size_t layer_floats = (size_t)batch * c.n_q_heads * n_parts * (c.head_dim + 2);
+  if (layer_floats > w.ws_floats) return PIE_ENOMEM;
+  if (n_layers < 1 || (n_layers > 1 && (work || view || clock_row || n_layers > attn_planned_layers(p, batch, max_blocks))))
+    return PIE_EINVAL;
   if (batch > w.lay_batch || max_blocks > w.lay_max_blocks) return PIE_EINVAL;
 
   AttnArgs a;
@@ -1366,6 +1405,11 @@ int launch_attn_decode(const pie_pool* p, int32_t layer, const void* d_q, int32_
   if (((uintptr_t)d_k_new | (uintptr_t)d_v_new) % 8) return PIE_EINVAL;   // the reduction loads two elements at once
   a.new_k = (const char*)d_k_new;
   a.new_v = (const char*)d_v_new;
+  a.n_layers = n_layers;
+  a.kv_stride = p->d_layer_stride;
+  a.q_stride = (size_t)batch * c.n_q_heads * c.head_dim * p->elem_bytes;
+  a.new_stride = (size_t)batch * c.n_kv_heads * c.head_dim * p->elem_bytes;
+  a.ws_stride = layer_floats;
   const bool hd128 = c.head_dim == 128;
   const int32_t row = clock_row ? (int32_t)((clock_row - p->d_clock) / kClockRow) : 0;
   switch (c.dtype) {

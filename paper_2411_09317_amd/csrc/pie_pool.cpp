@@ -1029,7 +1029,7 @@ static int step_body(pie_pool* p, const StepJob& j) {
   // they share launches, and a plan in any case - unless a layer's result lies where another layer's input is.
   const bool apart = layers_apart(d_out_all, d_q_all, L * q_stride, d_k_new, d_v_new, L * kv_stride);
   const bool planned_once = direct && L > 1 && apart;
-  const bool together = planned_once && n_prefetch == 0 && !timed && !clocked && !(p->layer_compute_us > 0.f);
+  const bool together = apart && L > 1 && n_prefetch == 0 && !timed && !clocked && !(p->layer_compute_us > 0.f);
   if (append_apart || staged_tails) {            // the appends read the maps sent above
     PIE_HIP(hipEventRecord(p->ev_map, cs));
     p->ev_map_rec = true;
@@ -1086,16 +1086,20 @@ static int step_body(pie_pool* p, const StepJob& j) {
   const bool leave_room = n_prefetch > 0 && !p->in_on_host[0] && (size_t)n_prefetch * p->block_bytes > long_enough;
   double t_free = -1.0, layer_us = -1.0;
   if (together) {
-    const int32_t most = attn_step_layers(p, batch, max_blocks);
+    const int32_t most = direct ? attn_step_layers(p, batch, max_blocks) : attn_planned_layers(p, batch, max_blocks);
     for (int32_t l = 0, n; l < L; l += n) {
       n = std::min(most, L - l);
       const char* q_l = (const char*)d_q_all + l * q_stride;
       char* out_l = (char*)d_out_all + l * q_stride;
       const char* k_l = with_new ? (const char*)d_k_new + l * kv_stride : nullptr;
       const char* v_l = with_new ? (const char*)d_v_new + l * kv_stride : nullptr;
-      if ((rc = launch_attn_direct(p, l, q_l, d_block_table, max_blocks, d_ctx_lens, batch, out_l, true, cs, k_l, v_l, -1,
-                                   nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, kDirectPlanReplay, false, n, 0)))
-        return rc;
+      if (direct)
+        rc = launch_attn_direct(p, l, q_l, d_block_table, max_blocks, d_ctx_lens, batch, out_l, true, cs, k_l, v_l, -1, nullptr,
+                                nullptr, nullptr, nullptr, nullptr, nullptr, kDirectPlanReplay, false, n, 0);
+      else
+        rc = launch_attn_decode(p, l, q_l, max_blocks, d_ctx_lens, batch, out_l, cs, nullptr, nullptr, -1, nullptr, nullptr,
+                                nullptr, nullptr, k_l, v_l, n);
+      if (rc) return rc;
     }
   }
   for (int32_t l = 0; l < L && !together; ++l) {

@@ -364,6 +364,8 @@ def test_big_steps_without_grouped_queries_give_the_bits_of_the_planned_path():
     (17, 8, 2, 128, I.DTYPE_BF16, [700, 1, 16, 17, 0, 1000], 64),              # a second line of arrival words
     (33, 4, 1, 64, I.DTYPE_F16, [2100], 140),                                  # a third
     (5, 64, 8, 128, I.DTYPE_BF16, [1 + i % 16 for i in range(250)], 3),        # scratch for three layers a launch
+    (9, 16, 16, 64, I.DTYPE_F16, [300 + i * 37 % 600 for i in range(52)], 400),    # planned, all layers at once
+    (3, 16, 4, 64, I.DTYPE_F16, [64 + i % 3 for i in range(260)], 9),          # planned: more sequences than the split takes
 ])
 def test_layers_that_share_a_launch_give_the_bits_of_a_launch_each(layers, hq, hkv, d, dtype, ctx, width):
     """A step whose layers share launches against the same step with events between its layers, which keep them apart:
