@@ -236,7 +236,7 @@ int launch_map_fill(int32_t* d_map, int32_t n, int32_t value, hipStream_t s);
 int launch_map_patch(int32_t* d_map, const MapPatch& patch, hipStream_t s);
 int launch_zero_u32(uint32_t* d, int32_t n, hipStream_t s);
 int launch_swap_copy(char* dst_layer_base, const char* src_layer_base, size_t block_bytes, const SwapPairs& pairs,
-                     int n_wgs, hipStream_t s, int shape = 0, size_t transfer_bytes = 0);
+                     int n_wgs, hipStream_t s, int shape = 0, size_t transfer_bytes = 0, hipEvent_t done = nullptr);
 // which tail blocks an append launch writes (a tail block is GPU-homed, staged for the layer, or neither)
 constexpr int32_t kAppendPresent = 0;     // GPU-homed or staged; neither raises NOT_PRESENT
 constexpr int32_t kAppendGpuStrict = 1;   // GPU-homed; anything else raises NOT_PRESENT (the layer's region is not valid)

@@ -196,12 +196,16 @@ __global__ __launch_bounds__(THREADS) void k_swap_copy(char* __restrict__ dst_ba
 
 template <int THREADS, int UNROLL>
 static int launch_swap_copy_as(char* dst_layer_base, const char* src_layer_base, size_t block_bytes,
-                               const SwapPairs& pairs, int n_wgs, hipStream_t s) {
+                               const SwapPairs& pairs, int n_wgs, hipStream_t s, hipEvent_t done) {
   constexpr size_t kPiece = (size_t)THREADS * 16 * UNROLL;
   const size_t pieces = ((block_bytes + kPiece - 1) / kPiece) * (size_t)pairs.n;
   const int grid = (int)(pieces < (size_t)n_wgs ? pieces : (size_t)n_wgs);
-  hipLaunchKernelGGL((k_swap_copy<THREADS, UNROLL>), dim3(grid), dim3(THREADS), 0, s, dst_layer_base, src_layer_base,
-                     block_bytes, pairs);
+  if (done)
+    hipExtLaunchKernelGGL((k_swap_copy<THREADS, UNROLL>), dim3(grid), dim3(THREADS), 0, s, nullptr, done, 0, dst_layer_base,
+                          src_layer_base, block_bytes, pairs);
+  else
+    hipLaunchKernelGGL((k_swap_copy<THREADS, UNROLL>), dim3(grid), dim3(THREADS), 0, s, dst_layer_base, src_layer_base,
+                       block_bytes, pairs);
   PIE_HIP(hipGetLastError());
   return PIE_OK;
 }
@@ -223,16 +227,16 @@ static int launch_swap_copy_as(char* dst_layer_base, const char* src_layer_base,
 constexpr size_t kGatherSmallBytes = (size_t)12 << 20;
 
 int launch_swap_copy(char* dst_layer_base, const char* src_layer_base, size_t block_bytes, const SwapPairs& pairs,
-                     int n_wgs, hipStream_t s, int shape, size_t transfer_bytes) {
+                     int n_wgs, hipStream_t s, int shape, size_t transfer_bytes, hipEvent_t done) {
   if (pairs.n <= 0) return PIE_OK;
   if (block_bytes % 16 || n_wgs < 1) return PIE_EINVAL;
   if (shape == 0) shape = (transfer_bytes ? transfer_bytes : block_bytes * pairs.n) <= kGatherSmallBytes ? 25604 : 6416;
   switch (shape) {
-    case 6404: return launch_swap_copy_as<64, 4>(dst_layer_base, src_layer_base, block_bytes, pairs, n_wgs, s);
-    case 6416: return launch_swap_copy_as<64, 16>(dst_layer_base, src_layer_base, block_bytes, pairs, n_wgs, s);
-    case 25602: return launch_swap_copy_as<256, 2>(dst_layer_base, src_layer_base, block_bytes, pairs, n_wgs, s);
-    case 25604: return launch_swap_copy_as<256, 4>(dst_layer_base, src_layer_base, block_bytes, pairs, n_wgs, s);
-    case 102416: return launch_swap_copy_as<1024, 16>(dst_layer_base, src_layer_base, block_bytes, pairs, n_wgs, s);
+    case 6404: return launch_swap_copy_as<64, 4>(dst_layer_base, src_layer_base, block_bytes, pairs, n_wgs, s, done);
+    case 6416: return launch_swap_copy_as<64, 16>(dst_layer_base, src_layer_base, block_bytes, pairs, n_wgs, s, done);
+    case 25602: return launch_swap_copy_as<256, 2>(dst_layer_base, src_layer_base, block_bytes, pairs, n_wgs, s, done);
+    case 25604: return launch_swap_copy_as<256, 4>(dst_layer_base, src_layer_base, block_bytes, pairs, n_wgs, s, done);
+    case 102416: return launch_swap_copy_as<1024, 16>(dst_layer_base, src_layer_base, block_bytes, pairs, n_wgs, s, done);
     default: return PIE_EINVAL;
   }
 }

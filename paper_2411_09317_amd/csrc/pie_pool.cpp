@@ -211,9 +211,10 @@ static CopyPlan plan_copy(const pie_pool* p, const std::vector<int32_t>& src, co
   return cp;
 }
 
-// kind: 0 host->device, 1 device->host.
+// kind: 0 host->device, 1 device->host.  done: an event that completes with the last copy, or NULL; only for those that
+// the kernel makes (rides_on_copy).
 static int copy_blocks(pie_pool* p, int kind, int32_t layer, const std::vector<int32_t>& src,
-                       const std::vector<int32_t>& dst, const CopyPlan& cp, hipStream_t s) {
+                       const std::vector<int32_t>& dst, const CopyPlan& cp, hipStream_t s, hipEvent_t done) {
   const size_t n = src.size();
   if (!n) return PIE_OK;
   if (cp.path == PIE_SWAP_DMA) {
@@ -241,7 +242,7 @@ static int copy_blocks(pie_pool* p, int kind, int32_t layer, const std::vector<i
       ++i;
     }
     int rc = launch_swap_copy(dst_base, src_base, p->block_bytes, pairs, p->swap_wgs, s, p->swap_shape,
-                              n * p->block_bytes);
+                              n * p->block_bytes, i == n ? done : nullptr);
     if (rc) return rc;
   }
   return PIE_OK;
@@ -308,6 +309,12 @@ static int note(const Mark& m, hipStream_t s) {
   return PIE_OK;
 }
 
+// Whether a swap's event completes with its last copy kernel; recorded behind it, it is a packet of its own that the next
+// copy on the stream waits for: two swap-ins of 6.3 MB in a row, 271 -> 263 us.  Not where something is noted in between.
+static bool rides_on_copy(const CopyPlan& cp, int32_t n, const Mark& after) {
+  return n > 0 && cp.path == PIE_SWAP_KERNEL && !after.ev && !after.clk;
+}
+
 // skip_copy: the region already holds exactly these blocks of this layer (brought in behind the previous
 // step's last layer); only the ordering and the completion event are enqueued.
 static int swap_in_impl(pie_pool* p, int32_t layer, int32_t n, const int32_t* handles, hipStream_t s,
@@ -341,13 +348,14 @@ static int swap_in_impl(pie_pool* p, int32_t layer, int32_t n, const int32_t* ha
   if ((rc = order_after(s, p->ev_read[r], p->ev_read_rec[r], on_host))) return rc;
   if ((rc = order_after(s, p->ev_out[r], p->ev_out_rec[r], on_host))) return rc;
   if ((rc = order_after(s, p->ev_migrate, p->ev_migrate_rec, on_host))) return rc;
+  const bool rides = !skip_copy && rides_on_copy(cp, n, t1);
   if (!skip_copy) {
     if ((rc = note(t0, s))) return rc;
-    if ((rc = copy_blocks(p, 0, layer, src, dst, cp, s))) return rc;
+    if ((rc = copy_blocks(p, 0, layer, src, dst, cp, s, rides ? p->ev_in[r] : nullptr))) return rc;
     if ((rc = note(t1, s))) return rc;
   }
   // phase two happens when this event completes
-  PIE_HIP(hipEventRecord(p->ev_in[r], s));
+  if (!rides) PIE_HIP(hipEventRecord(p->ev_in[r], s));
   p->ev_in_rec[r] = true;
   if (!skip_copy) p->bytes_in += (uint64_t)n * p->block_bytes;
   return PIE_OK;
@@ -382,10 +390,11 @@ static int swap_out_impl(pie_pool* p, int32_t layer, int32_t n, const int32_t* h
   if (job && (rc = launch_kv_append(p, layer, 1, job->d_k, job->d_v, job->d_table, job->max_blocks, job->d_ctx,
                                     job->batch, kAppendStaged, s)))
     return rc;
+  const bool rides = rides_on_copy(cp, n, t1);
   if ((rc = note(t0, s))) return rc;
-  if ((rc = copy_blocks(p, 1, layer, src, dst, cp, s))) return rc;
+  if ((rc = copy_blocks(p, 1, layer, src, dst, cp, s, rides ? p->ev_out[r] : nullptr))) return rc;
   if ((rc = note(t1, s))) return rc;
-  PIE_HIP(hipEventRecord(p->ev_out[r], s));
+  if (!rides) PIE_HIP(hipEventRecord(p->ev_out[r], s));
   p->ev_out_rec[r] = true;
   p->bytes_out += (uint64_t)n * p->block_bytes;
   return PIE_OK;
@@ -745,7 +754,7 @@ int pie_migrate(pie_pool* p, int32_t n, const int32_t* handles, int32_t to_where
       if ((rc = order_after(s, p->ev_out[r], p->ev_out_rec[r], on_host))) return rc;
     }
     for (int32_t layer = 0; layer < p->cfg.n_layers; ++layer)
-      if ((rc = copy_blocks(p, to_where == PIE_WHERE_GPU ? 0 : 1, layer, src, dst, cp, s))) return rc;
+      if ((rc = copy_blocks(p, to_where == PIE_WHERE_GPU ? 0 : 1, layer, src, dst, cp, s, nullptr))) return rc;
     PIE_HIP(hipEventRecord(p->ev_migrate, s));
     p->ev_migrate_rec = true;
   }
