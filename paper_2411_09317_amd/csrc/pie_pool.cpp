@@ -1037,8 +1037,10 @@ static int step_body(pie_pool* p, const StepJob& j) {
   // All layers' inputs are there when the step is called.  So where nothing is staged and nothing measured between them
   // they share launches, and a plan in any case - unless a layer's result lies where another layer's input is.
   const bool apart = layers_apart(d_out_all, d_q_all, L * q_stride, d_k_new, d_v_new, L * kv_stride);
-  const bool planned_once = direct && L > 1 && apart;
   const bool together = apart && L > 1 && n_prefetch == 0 && !timed && !clocked && !(p->layer_compute_us > 0.f);
+  // (by themselves, few layers do better to work the split out each: 8 sequences of 100 to 2 000 tokens, 32 heads over 8, 0.6 %
+  // on the host, us a step with a plan and without: 2 layers 66 and 63, 3 layers 100 and 95, 4 layers 114 and 113)
+  const bool planned_once = direct && apart && L > (together ? 1 : 3);
   if (append_apart || staged_tails) {            // the appends read the maps sent above
     PIE_HIP(hipEventRecord(p->ev_map, cs));
     p->ev_map_rec = true;
