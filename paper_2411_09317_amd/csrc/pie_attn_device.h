@@ -112,6 +112,15 @@ __device__ __forceinline__ int32_t resolve_slot(int32_t handle, const int32_t* _
   return slot;
 }
 
+// The same for a slot that has been looked up already, if the handle is one.
+__device__ __forceinline__ int32_t check_slot(int32_t handle, int32_t slot, int32_t n_handles, int32_t n_gpu_blocks,
+                                              int32_t n_slots, bool stage_valid, uint32_t* __restrict__ err) {
+  const bool known = handle >= 0 && handle < n_handles;
+  const bool present = known && slot >= 0 && slot < n_slots && (slot < n_gpu_blocks || stage_valid);
+  if (!present) atomicOr(err, known ? PIE_DEVERR_NOT_PRESENT : PIE_DEVERR_BAD_HANDLE);
+  return present ? slot : -1;
+}
+
 // The slot of the tail block a new row goes to, or -1: which tail blocks a launch writes is its kAppend* mode.
 __device__ __forceinline__ int32_t append_slot(int32_t handle, const int32_t* __restrict__ map, int32_t n_handles,
                                                int32_t n_gpu_blocks, int32_t n_slots, int32_t mode, bool report,
@@ -162,6 +171,11 @@ template <> struct Mfma<F16> {
   }
   __device__ static uint2 round(const f32x4& p) { return bits_as<uint2>(__builtin_convertvector(p, f16x4)); }
   __device__ static f32x4 widen(const uint2& r) { return __builtin_convertvector(bits_as<f16x4>(r), f32x4); }
+  // values for a residue of weights, which is zero where a weight needs no rounding: an infinity times it must not be NaN
+  __device__ static uint2 bounded(const uint2& v) {
+    const f16x4 most = {(_Float16)65504.f, (_Float16)65504.f, (_Float16)65504.f, (_Float16)65504.f};
+    return bits_as<uint2>(__builtin_elementwise_max(__builtin_elementwise_min(bits_as<f16x4>(v), most), -most));
+  }
 };
 template <> struct Mfma<BF16> {
   __device__ static f32x4 qk(const uint4& a, const uint4& b, f32x4 c) {
@@ -179,6 +193,7 @@ template <> struct Mfma<BF16> {
     f[3] = __uint_as_float(r.y & 0xffff0000u);
     return f;
   }
+  __device__ static uint2 bounded(const uint2& v) { return v; }   // (an infinity among bf16 values gives NaN)
 };
 
 // Two-element dot products on the vector ALU (v_dot2_f32_f16 / v_dot2_f32_bf16): c + a.x b.x + a.y b.y with the
@@ -322,8 +337,8 @@ __device__ __forceinline__ void mfma_block(uint4 (&kr)[HD / 32], uint4 (&vr)[HD 
     o[2 * i] = MM::pv(v0, p_hi, o[2 * i]);
     o[2 * i + 1] = MM::pv(v1, p_hi, o[2 * i + 1]);
     if (SPLIT) {
-      o[2 * i] = MM::pv(v0, p_lo, o[2 * i]);
-      o[2 * i + 1] = MM::pv(v1, p_lo, o[2 * i + 1]);
+      o[2 * i] = MM::pv(MM::bounded(v0), p_lo, o[2 * i]);
+      o[2 * i + 1] = MM::pv(MM::bounded(v1), p_lo, o[2 * i + 1]);
     }
   }
 }

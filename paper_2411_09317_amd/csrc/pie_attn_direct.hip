@@ -15,7 +15,7 @@
 //
 // What bounds it: for small calls a chain of dependent accesses, about 7 us from the first workgroup's start (context
 // lengths and split 1.4 us, table and map 0.7, a block 0.9, the part's state stored 1.0 and counted 0.4 to 1.3, the
-// merge 1.4); for large ones HBM.  us a call among others, planned before and in one launch now: one sequence of
+// merge 1.4); so short contexts are not cut (attn_whole) and need neither split nor merge.  For large ones HBM bounds it.  us a call among others, planned before and in one launch now: one sequence of
 // 700 tokens, 32 heads over 8: 24.6 and 6.6; one of 32 749, 64 over 8: 48.6 and 27.2 (134 MB, 4.9 TB/s); 32 of 32 768,
 // 64 over 8: 671 and 661 (4.3 GB, 6.5 TB/s).
 
@@ -204,6 +204,8 @@ struct FastRcp {
 
 constexpr int kDirectLaneSeqs = kDirectSeqs / 64;   // sequences per lane in the split
 constexpr int32_t kEarlyParts = 32;
+constexpr int kWholeWaves = 8;                    // of a workgroup that takes a whole context
+constexpr size_t kWholeBytes = (size_t)256 << 10;
 
 // A step's layers share the split and, per staging region, the slots: k_attn_split works them out for every item, and
 // the layers start from that, one access deep instead of four.  Where every layer has a map of its own (the growing
@@ -338,12 +340,13 @@ __global__ __launch_bounds__(kWaves * 64) void k_step_begin(const SplitArgs a, c
 }
 
 template <typename W, int NW, int PLAN>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(W::kWavesPerEu, 8)))
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW > kWaves ? NW / 4 : W::kWavesPerEu, 8)))
 void k_attn_direct(const DirectArgs a) {
   using E = typename W::E;
   constexpr int HD = W::HD, NL = W::NL, EB = W::EB;
   constexpr int NT = NW * 64;
-  static_assert(NW == kWaves, "the split is in quanta of so many waves");
+  constexpr bool WHOLE = NW == kWholeWaves;       // nothing is cut: a workgroup to a (sequence, kv head)
+  static_assert(NW == kWaves || (WHOLE && PLAN == kDirectPlanNone), "the split is in quanta of so many waves");
   constexpr int TILE_BYTES = kBlockTokens * HD * EB;
   constexpr int ROW = HD + 4;                     // padded LDS row of one head's accumulator
   constexpr int TPH = HD / 4;                     // threads per head when states are merged, four dims each
@@ -373,11 +376,25 @@ void k_attn_direct(const DirectArgs a) {
   const char* new_k = a.new_k ? a.new_k + layer * a.new_stride : nullptr;
   const char* new_v = a.new_k ? a.new_v + layer * a.new_stride : nullptr;
   int32_t b, ctx_raw, tok0, tok1, np, first, part, tail = -1;   // this unit: one part of sequence b, of np from item `first`
-  int32_t slots = -1;                             // of this wave's blocks, one to a lane
+  int32_t slots = -1, handle = -1;                // of this wave's blocks, one to a lane
   if constexpr (SLOTS) slots = a.plan[(size_t)place * kPlanInts + kPlanRec + wave * kDirectMaxQuanta + lane];
   if constexpr (REPLAY) {
     const int32_t* rec = a.plan + (size_t)place * kPlanInts;
     b = rec[0]; tok0 = rec[1]; tok1 = rec[2]; np = rec[3]; first = rec[4]; part = rec[5]; tail = rec[6]; ctx_raw = rec[7];
+  } else if constexpr (WHOLE) {                   // (place: the sequence)
+    const int32_t j = wave + NW * lane;           // its blocks, as many as the table has, looked up beside its length
+    if (j < a.max_blocks) handle = a.table[(size_t)place * a.max_blocks + j];
+    if (handle >= 0 && handle < a.n_handles) slots = map[handle];
+    b = place;
+    ctx_raw = a.ctx[b];
+    const int32_t full = clamp_ctx(ctx_raw, a.max_blocks);
+    if (ctx_raw > full && g == 0) atomicOr(a.err, PIE_DEVERR_BAD_HANDLE);
+    tok0 = 0;
+    tok1 = full > a.minus ? full - a.minus : 0;
+    np = 1;
+    first = place;
+    part = 0;
+    if (lead && a.hdr && tid == 0) a.hdr[1] = auto_part(0);   // (what the planning rule chooses for tables so narrow)
   } else {
     const Item it = split_item<false>(a, place, lead);
     b = it.b; tok0 = it.tok0; tok1 = it.tok1; np = it.np; first = it.first; part = it.part;
@@ -397,7 +414,9 @@ void k_attn_direct(const DirectArgs a) {
     const int32_t n_it = (jb1 - jb0 - wave + NW - 1) / NW;  // blocks of this wave: jb0 + wave + NW * it; <= 64
     const size_t row0 = (size_t)b * a.n_q_heads + (size_t)g * G;
 
-    if (!SLOTS && lane < n_it)                    // (with SLOTS the lanes beyond n_it hold what nobody uses)
+    if (WHOLE)
+      slots = lane < n_it ? check_slot(handle, slots, a.n_handles, a.n_gpu_blocks, a.n_slots, a.stage_valid != 0, a.err) : -1;
+    else if (!SLOTS && lane < n_it)               // (with SLOTS the lanes beyond n_it hold what nobody uses)
       slots = resolve_slot(a.table[(size_t)b * a.max_blocks + jb0 + wave + NW * lane], map, a.n_handles, a.n_gpu_blocks,
                            a.n_slots, a.stage_valid != 0, a.err);
     W w;
@@ -431,7 +450,7 @@ void k_attn_direct(const DirectArgs a) {
     // few parts right before (the accesses to a word are served one after another, 10 ns each), with many here, before the
     // waves' states are merged (the wave's wait for its stores covers it).
     uint64_t* word = a.arrive + ((size_t)(layer / kArriveStride) * a.arrive_lines + (size_t)b * H + g) * kArriveStride + layer % kArriveStride;
-    if (np > kEarlyParts && wave == NW - 1 && lane == 0)
+    if (!WHOLE && np > kEarlyParts && wave == NW - 1 && lane == 0)
       (void)__hip_atomic_fetch_max(word, a.launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const bool stores = a.append >= 0 && tail >= 0;
     uint4 k_piece;
@@ -504,7 +523,7 @@ void k_attn_direct(const DirectArgs a) {
       float M, L;
       float4 A;
       merge_lds(NW, h, d0, M, L, A);
-      if (np == 1) {
+      if (WHOLE || np == 1) {
         finish(c, M, L, A);
       } else {
         const int32_t off = (((first + part) * H + g) * G + h) * PART;
@@ -512,7 +531,7 @@ void k_attn_direct(const DirectArgs a) {
         if (d0 == 0) put2(parts, off + HD * 4, M, L);
       }
     }
-    if (np > 1) {
+    if (!WHOLE && np > 1) {
       wait_stores();
       __syncthreads();
       if (tid == 0) {
@@ -730,11 +749,25 @@ int launch_step_begin(const pie_pool* p, const int32_t* d_table, int32_t max_blo
   return PIE_OK;
 }
 
+// Calls and one-layer steps whose table cannot name more than 256 KB of keys and values a kv head, with no more heads than
+// compute units, are not cut: what a few more passes over blocks cost is less than storing, counting and merging parts, up
+// to there.  us a call, cut and whole: 9 sequences, 12 heads of 64, f16, of up to 128 / 300 / 601 / 800 / 1 000 tokens (256
+// KB): 6.1 / 6.4 / 6.7 / 7.6 / 7.7 and 4.4 / 4.4 / 4.7 / 5.5 / 5.7; 4 sequences, 32 heads over 8, of up to 128 / 256 / 400 /
+// 512 tokens (256 KB): 6.5 / 6.5 / 6.5 / 6.6 and 4.4 / 5.0 / 5.7 / 6.5; one of 700 (358 KB) 6.6 and 8.3.
+static bool attn_whole(const pie_pool* p, int32_t batch, int32_t max_blocks) {
+  return (int64_t)batch * p->cfg.n_kv_heads <= p->n_cu && (size_t)max_blocks * (p->block_bytes / p->cfg.n_kv_heads) <= kWholeBytes;
+}
+
+template <typename W>
+static int launch_whole(const DirectArgs& a, dim3 grid, hipStream_t s, hipEvent_t done, size_t min_lds) {
+  return launch_direct_as<W, kWholeWaves, kDirectPlanNone>(a, grid, s, done, min_lds);
+}
+
 int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const int32_t* d_table, int32_t max_blocks,
                        const int32_t* d_ctx, int32_t batch, void* d_out, bool stage_valid, hipStream_t s,
                        const void* d_k_new, const void* d_v_new, int32_t append, const LayerView* view,
                        const AttnWork* work, hipEvent_t k_start, hipEvent_t k_end, unsigned long long* clock_row,
-                       hipEvent_t done, int32_t plan, bool leave_room, int32_t n_layers, int32_t region) {
+                       hipEvent_t done, int32_t plan, bool leave_room, int32_t n_layers, int32_t region, bool alone) {
   // Three workgroups a compute unit take nearly all its registers, and a gather beside them starts when one ends.  Two,
   // by the LDS they ask for, leave it room (step_body says when that pays, with the times).
   const size_t min_lds = leave_room ? (size_t)56 << 10 : 0;
@@ -799,17 +832,26 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   if (k_start) PIE_HIP(hipEventRecord(k_start, s));
   int rc = PIE_EINVAL;
   const bool hd128 = c.head_dim == 128;
+  const bool whole = alone && plan == kDirectPlanNone && attn_whole(p, batch, max_blocks);
+  const dim3 pairs(H, 1, batch);
   switch (c.dtype) {
     case PIE_DTYPE_F32:
-      rc = hd128 ? launch_direct<Wave32<128>, kWaves>(a, grid, s, done, plan, min_lds)
+      if (whole) rc = hd128 ? launch_whole<Wave32<128>>(a, pairs, s, done, min_lds) : launch_whole<Wave32<64>>(a, pairs, s, done, min_lds);
+      else rc = hd128 ? launch_direct<Wave32<128>, kWaves>(a, grid, s, done, plan, min_lds)
                  : launch_direct<Wave32<64>, kWaves>(a, grid, s, done, plan, min_lds);
       break;
     case PIE_DTYPE_F16:
-      rc = hd128 ? launch_direct<Wave16<F16, 128, false>, kWaves>(a, grid, s, done, plan, min_lds)
+      if (whole)
+        rc = hd128 ? launch_whole<Wave16<F16, 128, true>>(a, pairs, s, done, min_lds)
+                   : launch_whole<Wave16<F16, 64, true>>(a, pairs, s, done, min_lds);
+      else rc = hd128 ? launch_direct<Wave16<F16, 128, false>, kWaves>(a, grid, s, done, plan, min_lds)
                  : launch_direct<Wave16<F16, 64, false>, kWaves>(a, grid, s, done, plan, min_lds);
       break;
     case PIE_DTYPE_BF16:
-      rc = hd128 ? launch_direct<Wave16<BF16, 128, true>, kWaves>(a, grid, s, done, plan, min_lds)
+      if (whole)
+        rc = hd128 ? launch_whole<Wave16<BF16, 128, true>>(a, pairs, s, done, min_lds)
+                   : launch_whole<Wave16<BF16, 64, true>>(a, pairs, s, done, min_lds);
+      else rc = hd128 ? launch_direct<Wave16<BF16, 128, true>, kWaves>(a, grid, s, done, plan, min_lds)
                  : launch_direct<Wave16<BF16, 64, true>, kWaves>(a, grid, s, done, plan, min_lds);
       break;
   }

@@ -603,7 +603,8 @@ int pie_elastic_step(pie_elastic_pool* lp, const void* d_q_all, const void* d_k_
     if (direct) {
       if ((rc = pie::launch_attn_direct(p, k, q_k, d_block_table, max_blocks, d_ctx_lens, batch, out_k, false, cs, k_k, v_k,
                                         d_k_new && !append_apart ? pie::kAppendGpuStrict : -1, &view, nullptr, nullptr, nullptr, nullptr,
-                                        done, split_once ? pie::kDirectPlanReplaySplit : pie::kDirectPlanNone)))
+                                        done, split_once ? pie::kDirectPlanReplaySplit : pie::kDirectPlanNone, false, 1, -1,
+                                        lp->n == 1)))
         return rc;
     } else {
       if ((rc = pie::launch_attn_resolve(p, d_block_table, d_ctx_lens, batch, max_blocks, true, false, false, false, cs,

@@ -428,7 +428,8 @@ int pie_layer_step(pie_layer_pool* lp, const void* d_q_all, const void* d_k_new,
       if ((rc = pie::launch_attn_direct(p, slot, q_k, d_block_table, max_blocks, d_ctx_lens, batch, out_k, false, cs, k_k,
                                         v_k, d_k_new && !append_apart ? pie::kAppendGpuStrict : -1, nullptr, nullptr, nullptr,
                                         nullptr, nullptr, done,
-                                        lp->n_layers == 1 ? pie::kDirectPlanNone : pie::kDirectPlanReplay)))
+                                        lp->n_layers == 1 ? pie::kDirectPlanNone : pie::kDirectPlanReplay, false, 1,
+                                        -1, lp->n_layers == 1)))
         return rc;
     } else {
       if ((rc = pie::launch_attn_decode(p, slot, q_k, max_blocks, d_ctx_lens, batch, out_k, cs, nullptr, nullptr,

@@ -856,7 +856,8 @@ static int attn_decode_impl(pie_pool* p, int32_t layer, const void* d_q, const i
   if ((rc = compute_prologue(p, layer, s, &stage_valid))) return rc;
   if (attn_direct(p, batch, max_blocks)) {
     if ((rc = launch_attn_direct(p, layer, d_q, d_block_table, max_blocks, d_ctx_lens, batch, d_out, stage_valid, s,
-                                 nullptr, nullptr, -1, nullptr, work)))
+                                 nullptr, nullptr, -1, nullptr, work, nullptr, nullptr, nullptr, nullptr, kDirectPlanNone,
+                                 false, 1, -1, true)))
       return rc;
     return compute_epilogue(p, layer, s);
   }
@@ -1146,7 +1147,7 @@ static int step_body(pie_pool* p, const StepJob& j) {
     if (direct)
       rc = launch_attn_direct(p, l, q_l, d_block_table, max_blocks, d_ctx_lens, batch, out_l, true, cs, k_l, v_l,
                               with_new && !planned_once ? append_mode : -1, nullptr, nullptr, k_start, k_end, clock_row(l), done,
-                              planned_once ? kDirectPlanReplay : kDirectPlanNone, leave_room);
+                              planned_once ? kDirectPlanReplay : kDirectPlanNone, leave_room, 1, -1, L == 1);
     else
       rc = launch_attn_decode(p, l, q_l, max_blocks, d_ctx_lens, batch, out_l, cs, k_start, k_end, -1, clock_row(l),
                               nullptr, done, nullptr, k_l, v_l);

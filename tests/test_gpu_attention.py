@@ -410,6 +410,59 @@ def test_layers_that_share_a_launch_give_the_bits_of_a_launch_each(layers, hq, h
     lib.close()
 
 
+@pytest.mark.parametrize("hq,hkv,d,dtype,ctx,width", [
+    (12, 12, 64, I.DTYPE_F16, [601, 1, 0, 15, 16, 17, 127, 128, 129], 64),     # as wide as is not cut
+    (12, 12, 64, I.DTYPE_F16, [601, 1, 0, 15, 16, 17, 1040, 128, 129], 65),    # and one block wider
+    (16, 2, 128, I.DTYPE_F16, [512, 300], 32),
+    (16, 1, 128, I.DTYPE_BF16, [512, 65, 128], 32),
+    (28, 4, 128, I.DTYPE_BF16, [100 + 6 * i for i in range(64)], 32),          # a head for every compute unit
+    (28, 4, 128, I.DTYPE_BF16, [100 + 6 * i for i in range(65)], 32),          # and more
+    (8, 8, 64, I.DTYPE_F32, [512, 1, 77], 32),
+    (2, 2, 128, I.DTYPE_F32, [256, 255, 3], 16),
+])
+def test_short_contexts_that_are_not_cut(hq, hkv, d, dtype, ctx, width):
+    """Around the table width and the number of heads up to which a workgroup takes a whole context: the call and the
+    one-layer step with new rows against the oracle, the step's stored rows against those of a planned step.  For f16 an
+    infinity among the values stays one, and the dims beside it what they are."""
+    ctx = np.asarray(ctx, np.int32)
+    w = I.Workload("whole", 1, len(ctx), hq, hkv, d, dtype, value_scale=0.5, seed=47)
+    case = I.make_case(w, ctx_lens=ctx)
+    live = np.nonzero(ctx)[0]
+    dims = np.arange(d)
+    if dtype == I.DTYPE_F16:
+        for b in live:
+            case.k_dense[b][0, 0] = 0                    # a weight far from vanishing
+            case.v_dense[b][0, 0, :, 5] = np.inf
+        dims = dims[dims != 5]
+    n = int(case.n_blocks.sum()) + 2
+    q, K, V = H.dense_f64(case, 0)
+    ref = A.dense_attention(q[live], [K[b] for b in live], [V[b] for b in live], ctx[live])
+    images = []
+    for part in (0, 512):
+        lib, mod, table = GH.make_pools(case, n, 2, 2, upto_ctx=np.maximum(ctx - 1, 0), max_blocks=width)
+        lib.set_attn_partition(part)
+        k, v = (GH.to_dev(np.stack([np.stack([x[0, ctx[b] - 1] if ctx[b] else np.zeros((hkv, d), x.dtype)
+                                              for b, x in enumerate(dense)])]), dtype) for dense in (case.k_dense, case.v_dense))
+        qd, tb, cl = GH.to_dev(case.q, dtype), torch.from_numpy(table).to(GH.DEV), torch.from_numpy(ctx).to(GH.DEV)
+        outs = [torch.full_like(qd, float("nan")) for _ in range(2)]
+        lib.step(qd, k, v, tb, cl, [], [], outs[0])
+        lib.attn_decode(0, qd[0], tb, cl, outs[1][0])
+        lib.sync()
+        assert lib.check_errors() == 0
+        for out in outs:
+            got = GH.from_dev(out, dtype)[0]
+            check(got[live][:, :, dims], ref[:, :, dims], dtype)
+            assert dtype != I.DTYPE_F16 or (got[live][:, :, 5] == np.inf).all()
+            assert (np.delete(got, live, axis=0) == 0).all()
+        images.append(GH.images_of(lib)[0])
+        if part == 0:                                    # what no table may hold is reported, not followed
+            tb[live[0], 0] = 1 << 29
+            lib.attn_decode(0, qd[0], tb, cl, outs[1][0])
+            assert lib.check_errors() & 1
+        lib.close()
+    assert np.array_equal(images[0], images[1])
+
+
 @pytest.mark.parametrize("batch", [1, 63, 64, 257, 1023, 1029])
 def test_planning_of_batches_around_its_rounds(batch):
     """The planning kernel scans the batch in rounds of one sequence per thread (256 or 1024 threads) and ranks the
