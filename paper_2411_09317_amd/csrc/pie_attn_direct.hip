@@ -422,7 +422,7 @@ void k_attn_direct(const DirectArgs a) {
     W w;
     w.load_q(q_in, row0, G, lane, a.scale_log2e);
     w.reset();
-    uint4 kA[NL], vA[NL], kB[NL], vB[NL];
+    uint4 kr[NL], vr[NL];
     auto load_tile = [&](uint4 (&kr)[NL], uint4 (&vr)[NL], int32_t it) {
       int32_t slot = __builtin_amdgcn_readlane(slots, it);
       slot = slot < 0 ? 0 : slot;                 // flagged blocks are masked when consumed
@@ -431,18 +431,33 @@ void k_attn_direct(const DirectArgs a) {
       for (int i = 0; i < NL; ++i) kr[i] = nt_load16(kp + (size_t)i * 1024);
 #pragma unroll
       for (int i = 0; i < NL; ++i) vr[i] = nt_load16(kp + a.block_bytes / 2 + (size_t)i * 1024);
+      if (EB == 2) __builtin_amdgcn_sched_barrier(0);
     };
     auto consume = [&](uint4 (&kr)[NL], uint4 (&vr)[NL], int32_t it) {
       const bool present = __builtin_amdgcn_readlane(slots, it) >= 0;
       w.block(kr, vr, (jb0 + wave + NW * it) * kBlockTokens, present ? tok1 : 0, lane, a.scale_log2e);
     };
-    if (n_it > 0) load_tile(kA, vA, 0);
-    for (int32_t it = 0; it < n_it; it += 2) {
-      if (it + 1 < n_it) load_tile(kB, vB, it + 1);
-      consume(kA, vA, it);
-      if (it + 1 < n_it) {
-        if (it + 2 < n_it) load_tile(kA, vA, it + 2);
-        consume(kB, vB, it + 1);
+    // One block of a wave is in flight, all of it requested before any of it is waited for.  The compute unit's other waves
+    // keep the memory busy, and more in flight is less: reads of 4 KiB tiles alone reach 7.07 / 6.95 / 6.83 TB/s with 32 / 64 /
+    // 96 KB of them in flight a compute unit.  Two blocks a wave and one, us: 16 layers of 256 sequences of 128 to 4 096
+    // tokens, 32 heads over 8, 3 368 and 3 340; 32 layers of 8 such 165.4 and 162.1; one sequence of 32 749, 64 over 8, 25.5 and
+    // 24.9; 32 of 32 768 673 and 669.  (Keys, then values when the keys are there: 3 505, 182, 29.8, 694.)
+    // fp32, on the vector ALU, keeps two (6 sequences of 100 to 4 000 tokens, 8 heads of 128: 23.7 and 24.3).
+    if constexpr (EB == 2) {
+      for (int32_t it = 0; it < n_it; ++it) {
+        load_tile(kr, vr, it);
+        consume(kr, vr, it);
+      }
+    } else {
+      uint4 kB[NL], vB[NL];
+      if (n_it > 0) load_tile(kr, vr, 0);
+      for (int32_t it = 0; it < n_it; it += 2) {
+        if (it + 1 < n_it) load_tile(kB, vB, it + 1);
+        consume(kr, vr, it);
+        if (it + 1 < n_it) {
+          if (it + 2 < n_it) load_tile(kr, vr, it + 2);
+          consume(kB, vB, it + 1);
+        }
       }
     }
     // The last arrival leaves its word zero.  What calls that must not overlap have left in it is the number of a launch
@@ -768,9 +783,11 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
                        const void* d_k_new, const void* d_v_new, int32_t append, const LayerView* view,
                        const AttnWork* work, hipEvent_t k_start, hipEvent_t k_end, unsigned long long* clock_row,
                        hipEvent_t done, int32_t plan, bool leave_room, int32_t n_layers, int32_t region, bool alone) {
-  // Three workgroups a compute unit take nearly all its registers, and a gather beside them starts when one ends.  Two,
-  // by the LDS they ask for, leave it room (step_body says when that pays, with the times).
-  const size_t min_lds = leave_room ? (size_t)56 << 10 : 0;
+  // How many workgroups a compute unit holds, by the LDS they ask for: three, where head_dim 128 in 16 bits leaves registers
+  // for four (16 layers as above 3 392 us with four, 3 340 with three; it is 3 300 with two, but 32 layers of eight sequences
+  // take 170 then and not 162, and the lengths are not known here).  Two where a gather beside them needs room to start
+  // before one ends (step_body says when that pays, with the times).
+  const size_t min_lds = leave_room ? (size_t)56 << 10 : p->cfg.head_dim == 128 && p->cfg.dtype != PIE_DTYPE_F32 ? (size_t)41 << 10 : 0;
   if (plan != kDirectPlanNone && work) return PIE_EINVAL;   // the plan lies in the pool's scratch, by region
   if (region < 0) region = view ? 0 : layer & 1;
   if (region > 1 || (view && region)) return PIE_EINVAL;
