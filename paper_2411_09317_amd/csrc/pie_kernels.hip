@@ -309,7 +309,7 @@ int launch_kv_append(const pie_pool* p, int32_t layer, int32_t n_layers, const v
 // end of the launch, and pays the launch ramp once.  A workgroup of kWaves wavefronts handles one unit and
 // all G <= 16 query heads that share the kv head; wave w takes blocks w, w + kWaves, ... of the item.
 // Per block a wave issues head_dim/32 K loads and head_dim/32 V loads of 16 bytes per lane, each covering
-// 1 KiB contiguous, non-temporal (every KV byte is read once), double-buffered in registers.  The loaded
+// 1 KiB contiguous, non-temporal (every KV byte is read once).  The loaded
 // vectors are matrix-core operands as they are:
 //   S[token][head]  = sum_c K[token][c] Q[head][c]      head_dim/32 x  v_mfma_f32_16x16x32   (A = K, B = Q)
 //   O[dim][head]   += sum_t V[t][dim] P[t][head]        head_dim/16 x  v_mfma_f32_16x16x16   (A = V, B = P)
@@ -541,7 +541,8 @@ void k_attn_decode_mfma(const AttnArgs a) {
   float* s_l = s_dyn + kWaves * kMaxGroup;        // [kWaves][16]
   float* s_acc = s_dyn + 2 * kWaves * kMaxGroup;  // [kWaves][G][ROW]
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, quad = lane >> 4;    // MFMA column (query head of the group) and 4-row group
   const int32_t G = a.group;
   const int32_t n_q_heads = a.n_kv_heads * G;
@@ -591,16 +592,18 @@ void k_attn_decode_mfma(const AttnArgs a) {
         qr[kc] = *reinterpret_cast<const uint4*>(q + (((size_t)b * n_q_heads + g * G + head) * HD + 32 * kc + 8 * quad) * 2);
     }
   };
-  // Two register sets: while one block is consumed the next is already in flight.
-  uint4 kA[NKC], vA[NKC], kB[NKC], vB[NKC];
-  auto load_tile = [&](uint4 (&kr)[NKC], uint4 (&vr)[NKC], int32_t slots, int32_t it, int32_t layer, int32_t g) {
-    int32_t slot = __shfl(slots, it, 64);
+  // One block of a wave is in flight, all of it requested before any of it is waited for: the other waves keep the memory
+  // busy, and more in flight is not faster (see k_attn_direct).
+  uint4 kr[NKC], vr[NKC];
+  auto load_tile = [&](int32_t slots, int32_t it, int32_t layer, int32_t g) {
+    int32_t slot = __builtin_amdgcn_readlane(slots, it);
     slot = slot < 0 ? 0 : slot;                                    // flagged blocks are masked when consumed
     const char* kp = a.kv_layer + layer * a.kv_stride + (size_t)slot * a.block_bytes + (size_t)g * TILE_BYTES + (size_t)lane * 16;
 #pragma unroll
     for (int i = 0; i < NKC; ++i) kr[i] = nt_load16(kp + (size_t)i * 1024);
 #pragma unroll
     for (int i = 0; i < NKC; ++i) vr[i] = nt_load16(kp + v_off + (size_t)i * 1024);
+    __builtin_amdgcn_sched_barrier(0);
   };
   // blocks of unit (r, u) this wave handles: j = jb0 + wave + kWaves * it, it < n_it (<= 0: nothing)
   auto wave_blocks = [&](const uint2& r) {
@@ -620,7 +623,7 @@ void k_attn_decode_mfma(const AttnArgs a) {
   if (unit < n_units) {
     const int32_t layer = layer_of(unit), g = (int32_t)(unit % n_kv);
     load_q(qreg, (int32_t)(rec.x & 0xffffu), layer, g);
-    if (wave_blocks(rec) > 0) load_tile(kA, vA, my_slot, 0, layer, g);
+    if (wave_blocks(rec) > 0) load_tile(my_slot, 0, layer, g);
   }
 
   while (unit < n_units) {                       // every workgroup ends on a ticket past the last unit
@@ -644,9 +647,9 @@ void k_attn_decode_mfma(const AttnArgs a) {
 
     // VALU form of one block: lane (quad, i = lane & 15).  K load kc holds token i, dims 32 kc + 8 quad ..;
     // V load holds tokens 4 quad .. 4 quad + 3 of dims 32 ld + i (x, y) and 32 ld + 16 + i (z, w).
-    auto consume_valu = [&](uint4 (&kr)[NKC], uint4 (&vr)[NKC], int32_t it) {
+    auto consume_valu = [&](int32_t it) {
       const int32_t t_first = (jb0 + wave + kWaves * it) * kBlockTokens;
-      const bool present = __shfl(my_slot, it, 64) >= 0;
+      const bool present = __builtin_amdgcn_readlane(my_slot, it) >= 0;
       const int32_t limit = present ? tok1 : 0;
       float d = 0.f;
 #pragma unroll
@@ -708,32 +711,28 @@ void k_attn_decode_mfma(const AttnArgs a) {
       }
     };
 
-    auto consume = [&](uint4 (&kr)[NKC], uint4 (&vr)[NKC], int32_t it) {
-      const bool present = __shfl(my_slot, it, 64) >= 0;                      // a missing block contributes nothing
+    auto consume = [&](int32_t it) {
+      const bool present = __builtin_amdgcn_readlane(my_slot, it) >= 0;                      // a missing block contributes nothing
       mfma_block<E, HD, SPLIT>(kr, vr, qreg, (jb0 + wave + kWaves * it) * kBlockTokens, present ? tok1 : 0, quad,
                                a.scale_log2e, m, l, o);
     };
 
     // The ticket after next is requested half way through the stream: late enough that the counter is not
     // hit by every workgroup at once, early enough that the answer is there when the unit ends.  Block 0 of
-    // the unit is already on its way in kA / vA.
+    // the unit is already on its way.
     uint32_t after_next = 0;
-    const int32_t it_ticket = n_it > 2 ? ((n_it / 2) & ~1) : 0;
-    for (int32_t it = 0; it < n_it; it += 2) {
+    const int32_t it_ticket = n_it / 2;
+    for (int32_t it = 0; it < n_it; ++it) {
       if (it == it_ticket && threadIdx.x == 0) after_next = 2 * gridDim.x + atomicAdd(a.counter, 1u);
-      if (it + 1 < n_it) load_tile(kB, vB, my_slot, it + 1, layer, g);
-      if constexpr (VALU) consume_valu(kA, vA, it); else consume(kA, vA, it);
-      if (it + 1 < n_it) {
-        if (it + 2 < n_it) load_tile(kA, vA, my_slot, it + 2, layer, g);
-        if constexpr (VALU) consume_valu(kB, vB, it + 1); else consume(kB, vB, it + 1);
-      }
+      if constexpr (VALU) consume_valu(it); else consume(it);
+      if (it + 1 < n_it) load_tile(my_slot, it + 1, layer, g);
     }
     if (n_it <= 0 && threadIdx.x == 0) after_next = 2 * gridDim.x + atomicAdd(a.counter, 1u);
 
     // behind the stream: the next unit's first block and query rows arrive while this unit's result is merged
     if (next < n_units) {
       const int32_t layer_next = layer_of(next), g_next = (int32_t)(next % n_kv);
-      if (wave_blocks(rec_next) > 0) load_tile(kA, vA, my_slot_next, 0, layer_next, g_next);
+      if (wave_blocks(rec_next) > 0) load_tile(my_slot_next, 0, layer_next, g_next);
       load_q(qreg, (int32_t)(rec_next.x & 0xffffu), layer_next, g_next);
     }
 
@@ -1300,7 +1299,9 @@ template <typename E, int HD, bool SPLIT, bool VALU = false>
 static int launch_mfma(const pie_pool* p, AttnArgs a, int32_t layer_row, int32_t batch, int32_t n_q_heads,
                        hipStream_t s, hipEvent_t e0, hipEvent_t e1, hipEvent_t done) {
   const size_t lds = mfma_lds_floats<HD>(a.group) * sizeof(float);
-  // as many workgroups as fit on the GPU at once; the ticket counter hands out the work
+  // As many workgroups as fit on the GPU at once, at most two a compute unit (four with head_dim 64): more only ask for more
+  // at a time (32 layers of 64 sequences of 1 024 to 2 048 tokens, 32 heads, one / two / three: 8 457 / 7 962 / 7 980 us; 2 of
+  // 256 of 128 to 4 096, 32 over 8: 485 / 441 / 454).  The ticket counter hands out the work.
   static int wgs_per_cu[kMaxGroup + 1] = {};
   if (wgs_per_cu[a.group] == 0) {
     int n = 0;
@@ -1309,7 +1310,7 @@ static int launch_mfma(const pie_pool* p, AttnArgs a, int32_t layer_row, int32_t
       (void)hipGetLastError();
       n = 2;
     }
-    wgs_per_cu[a.group] = n;
+    wgs_per_cu[a.group] = n < 256 / HD ? n : 256 / HD;
   }
   const int grid = p->n_cu * wgs_per_cu[a.group];
   if (a.clock && grid <= kClockWgs)
