@@ -684,9 +684,23 @@ int attn_step_path(const pie_pool* p, int32_t n_layers, int32_t batch, int32_t m
   return p->cfg.n_q_heads > p->cfg.n_kv_heads && n_layers >= 8 ? kStepDirectAppendApart : kStepPlanned;
 }
 
+// Where the table cannot name more than 256 KB of keys and values a kv head contexts are not cut: what a few more passes
+// over blocks cost is less than storing, counting and merging parts, up to there.  us a call, cut and whole: 9 sequences, 12 heads of 64, f16, of up to 128 / 300 / 601 / 800 / 1 000 tokens (256
+// KB): 6.1 / 6.4 / 6.7 / 7.6 / 7.7 and 4.4 / 4.4 / 4.7 / 5.5 / 5.7; 4 sequences, 32 heads over 8, of up to 128 / 256 / 400 /
+// 512 tokens (256 KB): 6.5 / 6.5 / 6.5 / 6.6 and 4.4 / 5.0 / 5.7 / 6.5; one of 700 (358 KB) 6.6 and 8.3; 60 of
+// up to 256 11.2 and 8.8, 256 of up to 512 60.7 and 56.6; 110 of up to 300, 32 heads, f16, 58.2 and 55.3.  In steps
+// up to four heads a compute unit: beyond, their plan with the longest items first is better (8 layers of 30 sequences of 60
+// to 300, 32 heads, 171 and 154; of 120, 32 over 8, 160 and 154; of 190 208 and 227; of 250 288 and 308).  A rule on the shape
+// alone, the same for every kind of step.
+bool attn_whole(const pie_pool* p, int32_t batch, int32_t max_blocks, bool step) {
+  return attn_direct(p, batch, max_blocks) && (size_t)max_blocks * (p->block_bytes / p->cfg.n_kv_heads) <= kWholeBytes &&
+         (!step || (int64_t)batch * p->cfg.n_kv_heads <= 4 * (int64_t)p->n_cu);
+}
+
 // How many layers of a step one launch may take: as many as the pool has room for parts of.
 int32_t attn_step_layers(const pie_pool* p, int32_t batch, int32_t max_blocks) {
   const pie_config& c = p->cfg;
+  if (attn_whole(p, batch, max_blocks, true)) return c.n_layers;   // (no parts)
   const int32_t units = direct_max_units(p, batch, max_blocks);
   if (units <= 0) return 0;
   const size_t rows = (size_t)(direct_grid(units, c.n_kv_heads, batch, max_blocks) / c.n_kv_heads) * c.n_q_heads;
@@ -764,15 +778,6 @@ int launch_step_begin(const pie_pool* p, const int32_t* d_table, int32_t max_blo
   return PIE_OK;
 }
 
-// Calls and one-layer steps whose table cannot name more than 256 KB of keys and values a kv head, with no more heads than
-// compute units, are not cut: what a few more passes over blocks cost is less than storing, counting and merging parts, up
-// to there.  us a call, cut and whole: 9 sequences, 12 heads of 64, f16, of up to 128 / 300 / 601 / 800 / 1 000 tokens (256
-// KB): 6.1 / 6.4 / 6.7 / 7.6 / 7.7 and 4.4 / 4.4 / 4.7 / 5.5 / 5.7; 4 sequences, 32 heads over 8, of up to 128 / 256 / 400 /
-// 512 tokens (256 KB): 6.5 / 6.5 / 6.5 / 6.6 and 4.4 / 5.0 / 5.7 / 6.5; one of 700 (358 KB) 6.6 and 8.3.
-static bool attn_whole(const pie_pool* p, int32_t batch, int32_t max_blocks) {
-  return (int64_t)batch * p->cfg.n_kv_heads <= p->n_cu && (size_t)max_blocks * (p->block_bytes / p->cfg.n_kv_heads) <= kWholeBytes;
-}
-
 template <typename W>
 static int launch_whole(const DirectArgs& a, dim3 grid, hipStream_t s, hipEvent_t done, size_t min_lds) {
   return launch_direct_as<W, kWholeWaves, kDirectPlanNone>(a, grid, s, done, min_lds);
@@ -782,13 +787,14 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
                        const int32_t* d_ctx, int32_t batch, void* d_out, bool stage_valid, hipStream_t s,
                        const void* d_k_new, const void* d_v_new, int32_t append, const LayerView* view,
                        const AttnWork* work, hipEvent_t k_start, hipEvent_t k_end, unsigned long long* clock_row,
-                       hipEvent_t done, int32_t plan, bool leave_room, int32_t n_layers, int32_t region, bool alone) {
+                       hipEvent_t done, int32_t plan, bool leave_room, int32_t n_layers, int32_t region) {
   // How many workgroups a compute unit holds, by the LDS they ask for: three, where head_dim 128 in 16 bits leaves registers
   // for four (16 layers as above 3 392 us with four, 3 340 with three; it is 3 300 with two, but 32 layers of eight sequences
   // take 170 then and not 162, and the lengths are not known here).  Two where a gather beside them needs room to start
   // before one ends (step_body says when that pays, with the times).
   const size_t min_lds = leave_room ? (size_t)56 << 10 : p->cfg.head_dim == 128 && p->cfg.dtype != PIE_DTYPE_F32 ? (size_t)41 << 10 : 0;
-  if (plan != kDirectPlanNone && work) return PIE_EINVAL;   // the plan lies in the pool's scratch, by region
+  const bool planned = plan == kDirectPlanReplay || plan == kDirectPlanReplaySplit;
+  if (planned && work) return PIE_EINVAL;         // the plan lies in the pool's scratch, by region
   if (region < 0) region = view ? 0 : layer & 1;
   if (region > 1 || (view && region)) return PIE_EINVAL;
   const pie_config& c = p->cfg;
@@ -800,6 +806,8 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   if (max_units <= 0) return PIE_EINVAL;
   const int32_t places = direct_grid(max_units, H, batch, max_blocks) / H;   // the items there may be, at most max_units / H
   if (n_layers < 1 || (n_layers > 1 && (work || clock_row || n_layers > attn_step_layers(p, batch, max_blocks)))) return PIE_EINVAL;
+  const bool whole = plan == kDirectWhole;
+  if (whole && !attn_whole(p, batch, max_blocks, false)) return PIE_EINVAL;
   DirectArgs a;
   a.kv_layer = view ? view->kv_base : p->d_kv + (size_t)layer * p->d_layer_stride;
   a.table = d_table;
@@ -820,7 +828,7 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   a.new_stride = (size_t)batch * H * c.head_dim * p->elem_bytes;
   a.ws_bytes = places * c.n_q_heads * (c.head_dim + 4) * (int32_t)sizeof(float);
   a.arrive_lines = work ? kArriveWords : (int32_t)direct_pool_words(c);
-  a.plan = plan == kDirectPlanNone ? nullptr : plan_region(p, region);
+  a.plan = planned ? plan_region(p, region) : nullptr;
   a.scale_log2e = p->scale_log2e;
   a.group = group;
   a.n_q_heads = c.n_q_heads;
@@ -849,8 +857,7 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   if (k_start) PIE_HIP(hipEventRecord(k_start, s));
   int rc = PIE_EINVAL;
   const bool hd128 = c.head_dim == 128;
-  const bool whole = alone && plan == kDirectPlanNone && attn_whole(p, batch, max_blocks);
-  const dim3 pairs(H, 1, batch);
+  const dim3 pairs(H, n_layers, batch);
   switch (c.dtype) {
     case PIE_DTYPE_F32:
       if (whole) rc = hd128 ? launch_whole<Wave32<128>>(a, pairs, s, done, min_lds) : launch_whole<Wave32<64>>(a, pairs, s, done, min_lds);

@@ -534,9 +534,11 @@ int pie_elastic_step(pie_elastic_pool* lp, const void* d_q_all, const void* d_k_
     return rc;
   // The layers share the split; every one looks its blocks up through a map of its own.  While all are on the GPU and none
   // has to move, nothing is to be done between them and they share a launch.
-  const bool split_once = direct && lp->n > 1 &&
-                          pie::layers_apart(d_out_all, d_q_all, lp->n * q_stride, d_k_new, d_v_new, lp->n * kv_stride);
-  const bool together = split_once && all_settled(lp->sched) && !(p->layer_compute_us > 0.f);
+  // (short contexts are not split: a step that leaves them whole has its launches store the rows)
+  const bool apart = direct && lp->n > 1 &&
+                     pie::layers_apart(d_out_all, d_q_all, lp->n * q_stride, d_k_new, d_v_new, lp->n * kv_stride);
+  const bool whole = direct && pie::attn_whole(p, batch, max_blocks, true), split_once = apart && !whole;
+  const bool together = apart && all_settled(lp->sched) && !(p->layer_compute_us > 0.f);
   const pie::LayerView first{p->d_kv, lp->d_maps, lp->H, lp->N * lp->C};
   if (split_once) {
     pie::AppendArgs rows;
@@ -555,9 +557,10 @@ int pie_elastic_step(pie_elastic_pool* lp, const void* d_q_all, const void* d_k_
       if ((rc = pie::launch_attn_direct(p, k, (const char*)d_q_all + k * q_stride, d_block_table, max_blocks, d_ctx_lens, batch,
                                         (char*)d_out_all + k * q_stride, false, cs,
                                         d_k_new ? (const char*)d_k_new + k * kv_stride : nullptr,
-                                        d_k_new ? (const char*)d_v_new + k * kv_stride : nullptr, -1, &view, nullptr, nullptr,
+                                        d_k_new ? (const char*)d_v_new + k * kv_stride : nullptr,
+                                        d_k_new && !split_once ? pie::kAppendGpuStrict : -1, &view, nullptr, nullptr,
                                         nullptr, nullptr, k + m == lp->n ? lp->ev_layer[lp->n - 1] : nullptr,
-                                        pie::kDirectPlanReplaySplit, false, m)))
+                                        split_once ? pie::kDirectPlanReplaySplit : pie::kDirectWhole, false, m)))
         return rc;
     }
     for (int32_t k = 0; k < lp->n; ++k) {
@@ -603,8 +606,7 @@ int pie_elastic_step(pie_elastic_pool* lp, const void* d_q_all, const void* d_k_
     if (direct) {
       if ((rc = pie::launch_attn_direct(p, k, q_k, d_block_table, max_blocks, d_ctx_lens, batch, out_k, false, cs, k_k, v_k,
                                         d_k_new && !append_apart ? pie::kAppendGpuStrict : -1, &view, nullptr, nullptr, nullptr, nullptr,
-                                        done, split_once ? pie::kDirectPlanReplaySplit : pie::kDirectPlanNone, false, 1, -1,
-                                        lp->n == 1)))
+                                        done, split_once ? pie::kDirectPlanReplaySplit : whole ? pie::kDirectWhole : pie::kDirectPlanNone)))
         return rc;
     } else {
       if ((rc = pie::launch_attn_resolve(p, d_block_table, d_ctx_lens, batch, max_blocks, true, false, false, false, cs,

@@ -264,15 +264,15 @@ inline int32_t attn_min_units(const pie_pool* p) { return p->n_cu * 17; }   // s
 // which needs no planning before it.  append: kAppend* mode in which the new rows are stored as well, or -1.
 // plan: whether the launch works its split and slots out for itself, or starts from what launch_attn_split left with the
 // same batch, table, context lengths and maps: all of it (kDirectPlanReplay), or the split alone (kDirectPlanReplaySplit:
-// the layer has a map of its own).  leave_room: a gather kernel runs beside it.  n_layers: the launch takes so many layers
-// from `layer` on, at most attn_step_layers.  region: whose map and plan it reads; -1: the layer's.  alone: a call, or a
-// step's only layer, whose contexts need not be cut as those of a step's other layers are.
-constexpr int32_t kDirectPlanNone = 0, kDirectPlanReplay = 1, kDirectPlanReplaySplit = 2;
+// the layer has a map of its own), or leaves contexts whole (kDirectWhole, where attn_whole says so).  leave_room: a gather kernel runs beside it.  n_layers: the launch takes so many layers
+// from `layer` on, at most attn_step_layers.  region: whose map and plan it reads; -1: the layer's.
+constexpr int32_t kDirectPlanNone = 0, kDirectPlanReplay = 1, kDirectPlanReplaySplit = 2, kDirectWhole = 3;
 // How the layers of a step of n_layers run: planned, or by k_attn_direct, whose launches where layers move store the new
 // rows or leave that to k_kv_append.  The same for every kind of step, so that their results are the same bits.
 constexpr int kStepPlanned = 0, kStepDirect = 1, kStepDirectAppendApart = 2;
 int attn_step_path(const pie_pool* p, int32_t n_layers, int32_t batch, int32_t max_blocks);
 bool attn_direct(const pie_pool* p, int32_t batch, int32_t max_blocks);
+bool attn_whole(const pie_pool* p, int32_t batch, int32_t max_blocks, bool step);
 size_t attn_direct_floats(const pie_config& c);
 size_t attn_arrive_lines(const pie_config& c);   // lines of arrival words in a pool
 // The new rows of one or more layers, to be stored into their tail blocks.
@@ -308,8 +308,7 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
                        const void* d_k_new = nullptr, const void* d_v_new = nullptr, int32_t append = -1,
                        const LayerView* view = nullptr, const AttnWork* work = nullptr, hipEvent_t k_start = nullptr,
                        hipEvent_t k_end = nullptr, unsigned long long* clock_row = nullptr, hipEvent_t done = nullptr,
-                       int32_t plan = 0, bool leave_room = false, int32_t n_layers = 1, int32_t region = -1,
-                       bool alone = false);
+                       int32_t plan = 0, bool leave_room = false, int32_t n_layers = 1, int32_t region = -1);
 int launch_stream_probe(const pie_pool* p, int32_t layer, int32_t max_blocks, int32_t batch, hipStream_t s);
 int attn_static_scratch(char** out, std::atomic<uint64_t>** out_launches = nullptr);
 int attn_static_work(const pie_pool* p, int32_t batch, int32_t max_blocks, AttnWork* out);

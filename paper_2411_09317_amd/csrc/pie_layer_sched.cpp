@@ -380,7 +380,8 @@ int pie_layer_step(pie_layer_pool* lp, const void* d_q_all, const void* d_k_new,
   const int path = pie::attn_step_path(p, lp->n_layers, batch, max_blocks);
   const bool direct = path != pie::kStepPlanned, append_apart = d_k_new && path != pie::kStepDirect;
   // (layers move, so each stores its own rows; the split and the slots of both maps are worked out once)
-  if (direct && lp->n_layers > 1 &&
+  const bool whole = direct && pie::attn_whole(p, batch, max_blocks, true), plan_left = direct && lp->n_layers > 1 && !whole;
+  if (plan_left &&
       (rc = pie::launch_step_begin(p, d_block_table, max_blocks, d_ctx_lens, batch, false, d_k_new != nullptr,
                                    d_k_new && !append_apart ? pie::kAppendGpuStrict : -1, 2, cs)))
     return rc;
@@ -428,8 +429,7 @@ int pie_layer_step(pie_layer_pool* lp, const void* d_q_all, const void* d_k_new,
       if ((rc = pie::launch_attn_direct(p, slot, q_k, d_block_table, max_blocks, d_ctx_lens, batch, out_k, false, cs, k_k,
                                         v_k, d_k_new && !append_apart ? pie::kAppendGpuStrict : -1, nullptr, nullptr, nullptr,
                                         nullptr, nullptr, done,
-                                        lp->n_layers == 1 ? pie::kDirectPlanNone : pie::kDirectPlanReplay, false, 1,
-                                        -1, lp->n_layers == 1)))
+                                        plan_left ? pie::kDirectPlanReplay : whole ? pie::kDirectWhole : pie::kDirectPlanNone)))
         return rc;
     } else {
       if ((rc = pie::launch_attn_decode(p, slot, q_k, max_blocks, d_ctx_lens, batch, out_k, cs, nullptr, nullptr,

@@ -856,8 +856,8 @@ static int attn_decode_impl(pie_pool* p, int32_t layer, const void* d_q, const i
   if ((rc = compute_prologue(p, layer, s, &stage_valid))) return rc;
   if (attn_direct(p, batch, max_blocks)) {
     if ((rc = launch_attn_direct(p, layer, d_q, d_block_table, max_blocks, d_ctx_lens, batch, d_out, stage_valid, s,
-                                 nullptr, nullptr, -1, nullptr, work, nullptr, nullptr, nullptr, nullptr, kDirectPlanNone,
-                                 false, 1, -1, true)))
+                                 nullptr, nullptr, -1, nullptr, work, nullptr, nullptr, nullptr, nullptr,
+                                 attn_whole(p, batch, max_blocks, false) ? kDirectWhole : kDirectPlanNone)))
       return rc;
     return compute_epilogue(p, layer, s);
   }
@@ -1041,7 +1041,8 @@ static int step_body(pie_pool* p, const StepJob& j) {
   const bool together = apart && L > 1 && n_prefetch == 0 && !timed && !clocked && !(p->layer_compute_us > 0.f);
   // (by themselves, few layers do better to work the split out each: 8 sequences of 100 to 2 000 tokens, 32 heads over 8, 0.6 %
   // on the host, us a step with a plan and without: 2 layers 66 and 63, 3 layers 100 and 95, 4 layers 114 and 113)
-  const bool planned_once = direct && apart && L > (together ? 1 : 3);
+  const bool whole = direct && attn_whole(p, batch, max_blocks, true);   // (short contexts: nothing to plan)
+  const bool planned_once = direct && !whole && apart && L > (together ? 1 : 3);
   if (append_apart || staged_tails) {            // the appends read the maps sent above
     PIE_HIP(hipEventRecord(p->ev_map, cs));
     p->ev_map_rec = true;
@@ -1062,6 +1063,9 @@ static int step_body(pie_pool* p, const StepJob& j) {
                                 with_new ? &rows : nullptr, L)))
       return rc;
   }
+  if (whole && together && with_new &&
+      (rc = launch_kv_append(p, 0, L, d_k_new, d_v_new, d_block_table, max_blocks, d_ctx_lens, batch, append_mode, cs)))
+    return rc;
   if (with_new) note_stream(p, os);
   if ((append_apart || staged_tails) && os != cs) PIE_HIP(hipStreamWaitEvent(os, p->ev_map, 0));
   if (append_apart) {
@@ -1107,7 +1111,7 @@ static int step_body(pie_pool* p, const StepJob& j) {
       const char* v_l = with_new ? (const char*)d_v_new + l * kv_stride : nullptr;
       if (direct)
         rc = launch_attn_direct(p, l, q_l, d_block_table, max_blocks, d_ctx_lens, batch, out_l, true, cs, k_l, v_l, -1, nullptr,
-                                nullptr, nullptr, nullptr, nullptr, nullptr, kDirectPlanReplay, false, n, 0);
+                                nullptr, nullptr, nullptr, nullptr, nullptr, whole ? kDirectWhole : kDirectPlanReplay, false, n, 0);
       else
         rc = launch_attn_decode(p, l, q_l, max_blocks, d_ctx_lens, batch, out_l, cs, nullptr, nullptr, -1, nullptr, nullptr,
                                 nullptr, nullptr, k_l, v_l, n);
@@ -1147,7 +1151,7 @@ static int step_body(pie_pool* p, const StepJob& j) {
     if (direct)
       rc = launch_attn_direct(p, l, q_l, d_block_table, max_blocks, d_ctx_lens, batch, out_l, true, cs, k_l, v_l,
                               with_new && !planned_once ? append_mode : -1, nullptr, nullptr, k_start, k_end, clock_row(l), done,
-                              planned_once ? kDirectPlanReplay : kDirectPlanNone, leave_room, 1, -1, L == 1);
+                              planned_once ? kDirectPlanReplay : whole ? kDirectWhole : kDirectPlanNone, leave_room);
     else
       rc = launch_attn_decode(p, l, q_l, max_blocks, d_ctx_lens, batch, out_l, cs, k_start, k_end, -1, clock_row(l),
                               nullptr, done, nullptr, k_l, v_l);

@@ -363,7 +363,8 @@ def test_big_steps_without_grouped_queries_give_the_bits_of_the_planned_path():
     (2, 8, 8, 64, I.DTYPE_F32, [1, 300, 64], 19),
     (17, 8, 2, 128, I.DTYPE_BF16, [700, 1, 16, 17, 0, 1000], 64),              # a second line of arrival words
     (33, 4, 1, 64, I.DTYPE_F16, [2100], 140),                                  # a third
-    (5, 64, 8, 128, I.DTYPE_BF16, [1 + i % 16 for i in range(250)], 3),        # scratch for three layers a launch
+    (18, 8, 8, 64, I.DTYPE_F16, [1 + i * 41 % 900 for i in range(70)], 64),    # short: contexts left whole
+    (5, 64, 8, 128, I.DTYPE_BF16, [1 + i % 16 for i in range(250)], 33),       # scratch for three layers a launch
     (9, 16, 16, 64, I.DTYPE_F16, [300 + i * 37 % 600 for i in range(52)], 400),    # planned, all layers at once
     (3, 16, 4, 64, I.DTYPE_F16, [64 + i % 3 for i in range(260)], 9),          # planned: more sequences than the split takes
 ])
@@ -415,14 +416,12 @@ def test_layers_that_share_a_launch_give_the_bits_of_a_launch_each(layers, hq, h
     (12, 12, 64, I.DTYPE_F16, [601, 1, 0, 15, 16, 17, 1040, 128, 129], 65),    # and one block wider
     (16, 2, 128, I.DTYPE_F16, [512, 300], 32),
     (16, 1, 128, I.DTYPE_BF16, [512, 65, 128], 32),
-    (28, 4, 128, I.DTYPE_BF16, [100 + 6 * i for i in range(64)], 32),          # a head for every compute unit
-    (28, 4, 128, I.DTYPE_BF16, [100 + 6 * i for i in range(65)], 32),          # and more
+    (28, 4, 128, I.DTYPE_BF16, [100 + 6 * i for i in range(65)], 32),          # more heads than compute units
     (8, 8, 64, I.DTYPE_F32, [512, 1, 77], 32),
     (2, 2, 128, I.DTYPE_F32, [256, 255, 3], 16),
 ])
 def test_short_contexts_that_are_not_cut(hq, hkv, d, dtype, ctx, width):
-    """Around the table width and the number of heads up to which a workgroup takes a whole context: the call and the
-    one-layer step with new rows against the oracle, the step's stored rows against those of a planned step.  For f16 an
+    """Around the table width up to which a workgroup takes a whole context: the call and the one-layer step with new rows against the oracle, the step's stored rows against those of a planned step.  For f16 an
     infinity among the values stays one, and the dims beside it what they are."""
     ctx = np.asarray(ctx, np.int32)
     w = I.Workload("whole", 1, len(ctx), hq, hkv, d, dtype, value_scale=0.5, seed=47)
