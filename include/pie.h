@@ -196,7 +196,8 @@ int pie_set_swap_path(pie_pool* pool, int32_t path);
  * grid more than about eight and a half (partition, kv head) units per workgroup (small units even out the
  * workgroups' different streaming rates, every unit has a fixed cost).  With 0, calls run as one launch with a split of
  * its own, as fine as it takes to fill the GPU, if they have up to 256 sequences, their table is not so wide that the
- * longest contexts it can name would not fit the split, and they are not fp32 with grouped queries; so do the layers of
+ * longest contexts it can name would not fit the split, and they are not fp32 with grouped queries (contexts are not split at
+ * all under a table that cannot name more than 256 KB of keys and values a kv head); so do the layers of
  * small steps, and with grouped queries those of big steps of eight layers or more (pie_step_attn_kernel). */
 int pie_set_attn_partition(pie_pool* pool, int32_t tokens);
 
@@ -581,7 +582,8 @@ int pie_elastic_capacity(pie_elastic_pool* ep, int32_t* out_visible_blocks, int3
  * min(max_chunks_per_layer, N / (n - m)) chunks (Section 3.1's a / (n - m), in whole chunks).  For a scheduler
  * that must know what fits below a size before it asks for it.  PIE_EINVAL unless 0 <= m < n_layers. */
 int pie_elastic_blocks_for(pie_elastic_pool* ep, int32_t m, int32_t* out_blocks);
-/* One decode step over the logical layers, in order; arguments as pie_layer_step. */
+/* One decode step over the logical layers, in order; arguments as pie_layer_step.  While all layers are on the GPU and none
+ * has to move, they share launches as in pie_step, and the call does not wait for any of them. */
 int pie_elastic_step(pie_elastic_pool* ep, const void* d_q_all, const void* d_k_new, const void* d_v_new,
                      const int32_t* d_block_table, int32_t max_blocks, const int32_t* d_ctx_lens, int32_t batch,
                      void* d_out_all, void* compute_stream, void* swap_in_stream, void* swap_out_stream);

@@ -10,8 +10,8 @@
 // The layers of a step start from a plan that one launch ahead of them works out, and where nothing has to happen between
 // them they share a launch too (n_layers): then the chain of accesses, the tail and the gap behind it, 7 of 11 us a layer of
 // a small step, come once a step and not once a layer.  us a step, a launch a layer before and one for all now: 32 layers of
-// 8 sequences of 128 to 4 096 tokens, 32 heads over 8, 358 and 166 (888 MB, 5.3 TB/s); 16 of 24 of 100 to 1 100, 32 heads, 613
-// and 527; 16 of 256 of 128 to 4 096, 32 over 8, 3 454 and 3 383; 16 growing caches of 48 sequences, 685 and 569.
+// 8 sequences of 128 to 4 096 tokens, 32 heads over 8, 358 and 162 (888 MB, 5.5 TB/s); 16 of 24 of 100 to 1 100, 32 heads, 613
+// and 527; 16 of 256 of 128 to 4 096, 32 over 8, 3 454 and 3 361; 16 growing caches of 48 sequences, 685 and 563.
 //
 // What bounds it: for small calls a chain of dependent accesses, about 7 us from the first workgroup's start (context
 // lengths and split 1.4 us, table and map 0.7, a block 0.9, the part's state stored 1.0 and counted 0.4 to 1.3, the
