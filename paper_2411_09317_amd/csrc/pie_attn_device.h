@@ -281,15 +281,17 @@ __device__ __forceinline__ int32_t clamp_ctx(int32_t ctx, int32_t max_blocks) {
 // One block of one wave, 16-bit caches: scores of its sixteen tokens, online softmax, accumulation of the values.
 // kr, vr: the block's K and V vectors as loaded (vr is masked in place where the block holds rows beyond `limit`);
 // qreg: the B operand of the first product; lane (quad, col) holds S[t_first + 4 quad + r][head col].
-template <typename E, int HD, bool SPLIT>
+// keys_used, values_used: called when kr and vr have been read and may be loaded again.
+template <typename E, int HD, bool SPLIT, typename KeysUsed, typename ValuesUsed>
 __device__ __forceinline__ void mfma_block(uint4 (&kr)[HD / 32], uint4 (&vr)[HD / 32], const uint4 (&qreg)[HD / 32],
                                            int32_t t_first, int32_t limit, int quad, float scale_log2e, float& m, float& l,
-                                           f32x4 (&o)[HD / 16]) {
+                                           f32x4 (&o)[HD / 16], KeysUsed keys_used, ValuesUsed values_used) {
   using MM = Mfma<E>;
   constexpr int NKC = HD / 32, NO = HD / 16;
   f32x4 s = {0.f, 0.f, 0.f, 0.f};             // s[r]: token t_first + 4 quad + r, head col
 #pragma unroll
   for (int kc = 0; kc < NKC; ++kc) s = MM::qk(kr[kc], qreg[kc], s);
+  keys_used();
 #pragma unroll
   for (int r = 0; r < 4; ++r) s[r] *= scale_log2e;
   if (t_first + kBlockTokens > limit) {       // the block holds rows beyond the context
@@ -341,6 +343,13 @@ __device__ __forceinline__ void mfma_block(uint4 (&kr)[HD / 32], uint4 (&vr)[HD 
       o[2 * i + 1] = MM::pv(MM::bounded(v1), p_lo, o[2 * i + 1]);
     }
   }
+  values_used();
+}
+template <typename E, int HD, bool SPLIT>
+__device__ __forceinline__ void mfma_block(uint4 (&kr)[HD / 32], uint4 (&vr)[HD / 32], const uint4 (&qreg)[HD / 32],
+                                           int32_t t_first, int32_t limit, int quad, float scale_log2e, float& m, float& l,
+                                           f32x4 (&o)[HD / 16]) {
+  mfma_block<E, HD, SPLIT>(kr, vr, qreg, t_first, limit, quad, scale_log2e, m, l, o, [] {}, [] {});
 }
 
 // One block of one wave and one query head, fp32 caches.  Lane (quad, row) holds, of the K tile, token `row`'s

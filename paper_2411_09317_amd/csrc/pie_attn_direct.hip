@@ -28,6 +28,11 @@
 
 namespace pie {
 
+// Where the arrival word of a pair in a launch's layer lies: sixteen layers of a pair share a line.
+__device__ __forceinline__ size_t arrive_word(int32_t lines, int32_t layer, size_t pair) {
+  return ((size_t)(layer / kArriveStride) * lines + pair) * kArriveStride + layer % kArriveStride;
+}
+
 struct SplitIn {             // what the split of a call follows from
   const int32_t* ctx;
   uint32_t* err;
@@ -45,6 +50,9 @@ struct SplitArgs : SplitIn { // the plan of a step
   int32_t n_handles, n_gpu_blocks, n_slots, stage_valid;
   int32_t append;            // kAppend*, where each layer's launch stores its rows, or -1
   int32_t places;            // items there may be: a workgroup each; those behind them store the new rows
+  uint32_t* counters;        // of k_attn_direct_wide, to clear: tickets, one a layer of the pool,
+  uint64_t* arrive;          // and the arrival words of the layers of a launch, or NULL
+  int32_t n_counters, arrive_lines, n_layers;
 };
 
 struct DirectArgs : SplitIn {
@@ -70,6 +78,8 @@ struct DirectArgs : SplitIn {
   int32_t group, n_q_heads;
   int32_t n_handles, n_gpu_blocks, n_slots, stage_valid;
   int32_t append;            // kAppend*: store the new rows into the tail blocks this says, or -1
+  int32_t n_layers, places;  // k_attn_direct_wide: layers of the launch, items there may be,
+  uint32_t* counter;         // its ticket counter, cleared ahead of it like the arrival words it uses
 };
 
 // ---- one wave's share of a unit ------------------------------------------------------------------------
@@ -97,6 +107,11 @@ struct Wave16 {              // 16-bit caches: all query heads of a kv head, on 
   }
   __device__ __forceinline__ void block(uint4 (&kr)[NL], uint4 (&vr)[NL], int32_t t_first, int32_t limit, int lane, float scale) {
     mfma_block<E, HD, SPLIT>(kr, vr, q, t_first, limit, lane >> 4, scale, m, l, o);
+  }
+  template <typename KeysUsed, typename ValuesUsed>
+  __device__ __forceinline__ void block(uint4 (&kr)[NL], uint4 (&vr)[NL], int32_t t_first, int32_t limit, int lane, float scale,
+                                        KeysUsed keys_used, ValuesUsed values_used) {
+    mfma_block<E, HD, SPLIT>(kr, vr, q, t_first, limit, lane >> 4, scale, m, l, o, keys_used, values_used);
   }
   __device__ __forceinline__ void to_lds(float* s_m, float* s_l, float* s_acc, int row_floats, int wave, int G, int lane) {
     const int col = lane & 15, quad = lane >> 4;
@@ -172,6 +187,13 @@ __device__ __forceinline__ void put2(__amdgpu_buffer_rsrc_t r, int32_t off, floa
 }
 __device__ __forceinline__ float2 get2(__amdgpu_buffer_rsrc_t r, int32_t off) {
   return bits_as<float2>(__builtin_amdgcn_raw_buffer_load_b64(r, off, 0, kAuxAgent));
+}
+// One more in a word of which the first thread of a wave gets the old value, the others nothing: for the others it lies out of
+// the buffer's range, so there is no branch around it and nobody waits for the answer before it is used (an atomic by one
+// thread is waited for where the branches meet).
+__device__ __forceinline__ uint32_t add_one(void* word, int32_t thread) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(word, 0, 4, 0x00027000);
+  return (uint32_t)__builtin_amdgcn_raw_ptr_buffer_atomic_add_i32(1, r, 4 * thread, 0, 0);
 }
 __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
@@ -320,6 +342,13 @@ __global__ __launch_bounds__(kWaves * 64) void k_step_begin(const SplitArgs a, c
   const int32_t place = blockIdx.x, lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const Item it = split_item(a, place, place == 0, true);
+  if (a.arrive && place == 0)
+    for (int32_t i = threadIdx.x; i < a.n_counters; i += kWaves * 64) a.counters[i] = 0;
+  if (a.arrive && it.b >= 0 && it.np > 1 && it.part == 0)
+    for (int32_t i = threadIdx.x; i < a.n_layers * a.n_kv_heads; i += kWaves * 64) {
+      const int32_t l = i / a.n_kv_heads, g = i - l * a.n_kv_heads;
+      a.arrive[arrive_word(a.arrive_lines, l, (size_t)it.b * a.n_kv_heads + g)] = 0;
+    }
   const int32_t jb = it.tok0 / kBlockTokens + wave + kWaves * lane;
   const bool live = it.b >= 0 && jb * kBlockTokens < it.tok1;
   const int32_t ctx_raw = it.b >= 0 ? a.ctx[it.b] : 0, jt = (ctx_raw - 1) / kBlockTokens;
@@ -333,9 +362,9 @@ __global__ __launch_bounds__(kWaves * 64) void k_step_begin(const SplitArgs a, c
     int32_t tail_slot = -1;
     if (a.map[r] && has_tail)
       tail_slot = append_slot(tail, a.map[r], a.n_handles, a.n_gpu_blocks, a.n_slots, a.append, threadIdx.x == 0, a.err);
-    if (a.map[r] && live)
+    if (live)
       rec[kPlanRec + wave * kDirectMaxQuanta + lane] =
-          resolve_slot(handle, a.map[r], a.n_handles, a.n_gpu_blocks, a.n_slots, a.stage_valid != 0, a.err);
+          a.map[r] ? resolve_slot(handle, a.map[r], a.n_handles, a.n_gpu_blocks, a.n_slots, a.stage_valid != 0, a.err) : handle;
     if (threadIdx.x == 0) {
       *reinterpret_cast<int4*>(rec) = make_int4(it.b, it.tok0, it.tok1, it.np);
       *reinterpret_cast<int4*>(rec + 4) = make_int4(it.first, it.part, tail_slot, ctx_raw);
@@ -659,6 +688,433 @@ void k_attn_direct(const DirectArgs a) {
   }
 }
 
+// ---- layers that share a launch, four kv heads side by side -------------------------------------------------
+// The same parts, states and sums as k_attn_direct's, with the work dealt out otherwise.  There a workgroup's four waves take the
+// four shares of one head's part, and three workgroups a compute unit keep 96 KB in flight that lie 4 KB here and 4 KB there.
+// HBM bounds both, and gives more when less is asked for at a time and what is asked for lies together: reads alone, of 4 KB
+// tiles of blocks of 64 KB, 6.82 TB/s so and 7.24 with four waves a compute unit on four neighbouring heads of one block; of
+// blocks of 256 KB 6.68 and 6.91.  So a workgroup stays on a compute unit and takes units by ticket, the largest parts first, of
+// four heads each: a wave a head, which takes the four shares one after another.  A block's sixteen loads go out together behind
+// the block before (the keys' behind its keys' product, the values' behind its values': 3 352 us and not 3 093 for 16 layers of
+// 256 sequences of 128 to 4 096 tokens, 32 heads over 8).
+//
+// With one wave in flight a SIMD nothing may come between two blocks.  What a unit needs beyond them is asked for a unit ahead;
+// and what is left to do when its blocks have been read - the merge of the shares, and, where the context is cut, the part's
+// stores, the count and the merge of the parts, 5 us in all - is another four waves', out of LDS, one half of which the first
+// four fill while the others work on what the other half holds.  us a step, launches of k_attn_direct, the reading waves doing
+// all of it, and so: the above 3 330, 3 079, 3 075 (21.5 GB, 7.0 TB/s); 8 layers of 120 of 500 to 2 500, 32 over 8, 937, 900,
+// 889; 32 of 8 of 128 to 4 096 162, 180, 162; 16 of 24 of 100 to 1 100, 32 heads, 525, 518, 518.
+struct PartOf { int32_t b, g, layer, np, first, part, ctx_raw; };
+
+// What k_attn_direct's workgroup does when its waves have streamed their shares of a part, by one wave for a kv head: the four
+// states in LDS become one; a lone part's is finished, another's stored, counted and, by the last to arrive, merged with the
+// others'.  The same sums in the same order, so that a step's results are the same bits whichever kernel its layers run in.
+template <typename W>
+struct PartEnd {
+  using E = typename W::E;
+  static constexpr int HD = W::HD;
+  static constexpr int NW = kWaves, NT = 64;
+  static constexpr int ROW = HD + 4;
+  static constexpr int TPH = HD / 4;              // threads per head when states are merged, four dims each
+  static constexpr int PART = (HD + 4) * 4;       // bytes of a head's partial state: accumulator, max, sum, padding
+  const DirectArgs& a;
+  PartOf p;
+  float *s_m, *s_l, *s_acc, *s_w;                 // s_w: 2 NT floats
+  int tid;
+  uint64_t* word;                                 // its pair's arrival word
+  __amdgpu_buffer_rsrc_t ws;                      // the layer's parts
+  size_t row0;                                    // first row among the queries and results
+  float4 qd, kd, vd;                              // the newest token's part is (q . k, 1, v)
+
+  __device__ __forceinline__ PartEnd(const DirectArgs& a_, const PartOf& p_, float* s_state, float* s_weights, int thread)
+      : a(a_), p(p_), s_m(s_state), s_l(s_state + NW * kMaxGroup), s_acc(s_state + 2 * NW * kMaxGroup), s_w(s_weights),
+        tid(thread), word(a_.arrive + arrive_word(a_.arrive_lines, p_.layer, (size_t)p_.b * a_.n_kv_heads + p_.g)),
+        ws(parts_rsrc(a_.ws + (size_t)p_.layer * (a_.ws_bytes / 4), a_.ws_bytes)),
+        row0((size_t)p_.b * a_.n_q_heads + (size_t)p_.g * a_.group) {}
+  __device__ __forceinline__ static void sync() {   // what its threads have left in LDS can be read
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  // thread t has head t / TPH, dims 4 (t % TPH) ..
+  __device__ __forceinline__ int cols() const { return a.group * TPH; }
+  __device__ __forceinline__ bool add_new() const { return a.new_k && p.ctx_raw > 0; }
+  // The newest token's rows are read here, for the thread's first column, so that they have arrived when the last step needs
+  // them.
+  __device__ __forceinline__ void read_q(int c) { qd = load_elem4<E>(a.q + p.layer * a.q_stride, (row0 + c / TPH) * HD + 4 * (c % TPH)); }
+  __device__ __forceinline__ void read_new() {
+    if (!add_new() || tid >= cols()) return;
+    const size_t at = ((size_t)p.b * a.n_kv_heads + p.g) * HD + 4 * (tid % TPH);
+    read_q(tid);
+    kd = load_elem4<E>(a.new_k + p.layer * a.new_stride, at);   // (NT is a multiple of TPH: the same dims in all columns)
+    vd = load_elem4<E>(a.new_v + p.layer * a.new_stride, at);
+  }
+  __device__ __forceinline__ void finish(int c, float M, float L, float4 A) {   // a column
+    const int d0 = 4 * (c % TPH);
+    const size_t row = row0 + c / TPH;
+    if (add_new()) {
+      if (c >= NT) read_q(c);
+      const float dot = fmaf(qd.x, kd.x, qd.y * kd.y) + fmaf(qd.z, kd.z, qd.w * kd.w);
+      const float s_new = head_sum<TPH>(dot) * a.scale_log2e;
+      const float m2 = fmaxf(M, s_new);
+      const float w_old = __builtin_amdgcn_exp2f(M - m2), w_new = __builtin_amdgcn_exp2f(s_new - m2);
+      L = fmaf(L, w_old, w_new);
+      A = make_float4(A.x * w_old, A.y * w_old, A.z * w_old, A.w * w_old);
+      axpy(A, w_new, vd);
+    }
+    const bool some = L > 0.f;
+    char* const out = a.out + p.layer * a.q_stride;
+    store_elem2<E>(out, row * HD + d0, make_float2(some ? A.x / L : 0.f, some ? A.y / L : 0.f));
+    store_elem2<E>(out, row * HD + d0 + 2, make_float2(some ? A.z / L : 0.f, some ? A.w / L : 0.f));
+  }
+  // n states in LDS (the waves', or the merging groups') into one
+  __device__ __forceinline__ void merge_lds(int n, int h, int d0, float& M, float& L, float4& A) const {
+    M = s_m[h];
+    for (int i = 1; i < n; ++i) M = fmaxf(M, s_m[i * kMaxGroup + h]);
+    L = 0.f;
+    A = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int i = 0; i < n; ++i) {
+      const float wt = __builtin_amdgcn_exp2f(s_m[i * kMaxGroup + h] - M);
+      L = fmaf(wt, s_l[i * kMaxGroup + h], L);
+      axpy(A, wt, *reinterpret_cast<const float4*>(&s_acc[((size_t)i * a.group + h) * ROW + d0]));
+    }
+  }
+  // the states into one, which is finished (the newest token's rows have been read) or stored
+  __device__ __forceinline__ void leave() {
+    for (int c = tid; c < cols(); c += NT) {
+      const int h = c / TPH, d0 = 4 * (c % TPH);
+      float M, L;
+      float4 A;
+      merge_lds(NW, h, d0, M, L, A);
+      if (p.np == 1) {
+        finish(c, M, L, A);
+      } else {
+        const int32_t off = (((p.first + p.part) * a.n_kv_heads + p.g) * a.group + h) * PART;
+        put4(ws, off + d0 * 4, A);
+        if (d0 == 0) put2(ws, off + HD * 4, M, L);
+      }
+    }
+  }
+  // One more part stored, the word having been cleared ahead of the launch; the last arrival leaves it zero again.
+  __device__ __forceinline__ uint32_t count() const { return add_one(word, tid); }
+  __device__ __forceinline__ bool is_last(uint32_t counted) const {
+    return __builtin_amdgcn_readfirstlane(counted) == (uint32_t)(p.np - 1);
+  }
+  // NC columns of a thread from c0 on, of the parts [s_begin, s_end), UNR parts' loads in flight for each column: thread t
+  // of a head's TPH reads part t's (M, L) and works out its weight, then every thread sums its four dims over the parts, the
+  // weights fetched from LDS.  sub: whose group's result it is, or -1: the only one's.
+  template <int NC, int UNR>
+  __device__ __forceinline__ void merge_columns(int sub, int32_t s_begin, int32_t s_end, int c0) {
+    const int32_t G = a.group, H = a.n_kv_heads, step = H * G * PART;
+    const int t = c0 % TPH, d0 = 4 * t;
+    int32_t part0[NC];
+    float M[NC], L[NC];
+    float4 A[NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const int c = NC == 1 ? c0 : min(c0 + NT * j, cols() - TPH + t);
+      part0[j] = ((p.first * H + p.g) * G + c / TPH) * PART;
+      M[j] = kNegBig;
+      L[j] = 0.f;
+      A[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    for (int32_t s0 = s_begin; s0 < s_end; s0 += TPH) {
+      const int32_t n = min(s_end - s0, TPH);
+      float2 ml[NC];
+#pragma unroll
+      for (int j = 0; j < NC; ++j) {
+        ml[j] = make_float2(kNegBig, 0.f);
+        if (t < n) ml[j] = get2(ws, part0[j] + (s0 + t) * step + HD * 4);
+      }
+      for (int32_t u0 = 0; u0 < n; u0 += UNR) {
+        float4 ai[NC][UNR];
+#pragma unroll
+        for (int j = 0; j < NC; ++j)
+#pragma unroll
+          for (int u = 0; u < UNR; ++u) ai[j][u] = get4(ws, part0[j] + d0 * 4, (s0 + min(u0 + u, n - 1)) * step);
+        if (u0 == 0) {
+#pragma unroll
+          for (int j = 0; j < NC; ++j) {
+            const float m_new = fmaxf(M[j], head_max<TPH>(ml[j].x));
+            const float corr = __builtin_amdgcn_exp2f(M[j] - m_new);
+            const float wt = t < n ? __builtin_amdgcn_exp2f(ml[j].x - m_new) : 0.f;
+            L[j] = fmaf(L[j], corr, head_sum<TPH>(wt * ml[j].y));
+            A[j] = make_float4(A[j].x * corr, A[j].y * corr, A[j].z * corr, A[j].w * corr);
+            M[j] = m_new;
+            s_w[j * NT + tid] = wt;               // read by this wave only
+          }
+          __builtin_amdgcn_wave_barrier();
+        }
+#pragma unroll
+        for (int j = 0; j < NC; ++j)
+#pragma unroll
+          for (int u = 0; u < UNR; u += 4) {      // (threads beyond n hold weight 0; TPH is a multiple of UNR)
+            const float4 wu = *reinterpret_cast<const float4*>(&s_w[j * NT + (tid & ~(TPH - 1)) + u0 + u]);
+            axpy(A[j], wu.x, ai[j][u]);
+            axpy(A[j], wu.y, ai[j][u + 1]);
+            axpy(A[j], wu.z, ai[j][u + 2]);
+            axpy(A[j], wu.w, ai[j][u + 3]);
+          }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      // A round that is not full reads its last part several times, with weights of zero for all but one.  If that
+      // part holds an infinity, or any other, the sum is made once more part by part.
+      if (!(fmaf(A[j].x, 0.f, fmaf(A[j].y, 0.f, fmaf(A[j].z, 0.f, A[j].w * 0.f))) == 0.f)) {
+        A[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int32_t s = s_begin; s < s_end; ++s)
+          axpy(A[j], __builtin_amdgcn_exp2f(get2(ws, part0[j] + s * step + HD * 4).x - M[j]),
+               get4(ws, part0[j] + d0 * 4, s * step));
+      }
+      const int c = c0 + NT * j, h = c / TPH;
+      if (NC > 1 && c >= cols()) continue;
+      if (sub < 0) {
+        finish(c, M[j], L[j], A[j]);
+      } else {
+        if (d0 == 0) {
+          s_m[sub * kMaxGroup + h] = M[j];
+          s_l[sub * kMaxGroup + h] = L[j];
+        }
+        *reinterpret_cast<float4*>(&s_acc[((size_t)sub * G + h) * ROW + d0]) = A[j];
+      }
+    }
+  }
+  // By the last to arrive: every part is stored; merge them, in order, in as many groups as a workgroup's threads would make.
+  __device__ __forceinline__ void merge() {
+    if (tid == 0) __hip_atomic_store(word, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int32_t np = p.np;
+    const int pitch = (cols() + 63) & ~63;        // threads of a group: whole waves
+    const int nsub = np > 16 ? max(1, NW * 64 / pitch) : 1;
+    auto merge_share = [&](int sub, int from) {
+      const int32_t s_begin = np * sub / nsub, s_end = np * (sub + 1) / nsub;
+      if (np <= 8) {                              // few parts: no more loads than there are, and two columns' at a time
+        for (int c = from; c < cols(); c += 2 * NT) merge_columns<2, 8>(-1, s_begin, s_end, c);
+        return;
+      }
+      for (int c = from; c < cols(); c += NT) merge_columns<1, 16>(nsub > 1 ? sub : -1, s_begin, s_end, c);
+    };
+    for (int sub = 0; sub < nsub; ++sub) merge_share(sub, tid);   // one group's share after another
+    if (nsub > 1) {
+      sync();
+      for (int c = tid; c < cols(); c += NT) {
+        const int d0 = 4 * (c % TPH);
+        float M, L;
+        float4 A;
+        merge_lds(nsub, c / TPH, d0, M, L, A);
+        finish(c, M, L, A);
+      }
+    }
+  }
+};
+
+constexpr int kWideWaves = 2 * kWaves;           // as many read as finish what those have read
+template <typename W, bool SLOTS>
+__global__ __launch_bounds__(kWideWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 8)))
+void k_attn_direct_wide(const DirectArgs a) {
+  constexpr int HD = W::HD, NL = W::NL, EB = W::EB;
+  constexpr int TILE_BYTES = kBlockTokens * HD * EB;
+  constexpr int ROW = HD + 4;
+  using End = PartEnd<W>;
+  extern __shared__ __align__(16) float s_dyn[];
+  __shared__ __align__(16) float s_wts[kWaves * 128];   // weights of parts being merged, of two columns a lane
+  __shared__ uint32_t s_ticket[2];
+  __shared__ int32_t s_part[2][8];                // what the states in either half of s_dyn are of
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int32_t G = a.group, H = a.n_kv_heads, L = a.n_layers;
+  const int head_floats = 2 * kWaves * kMaxGroup + kWaves * G * ROW;
+  int half = 0;
+
+  if (wave >= kWaves) {                           // finishes: head `wave - kWaves` of the four
+    int thread = lane;
+    for (;; half ^= 1) {
+      __syncthreads();                            // the states are there (and those of the part before have been read)
+      asm volatile("" : "+v"(thread));            // (or all addresses are worked out ahead of the loop, and spill)
+      const int32_t x = s_part[half][thread & 7];
+      PartOf p;
+      p.b = __builtin_amdgcn_readlane(x, 0);
+      if (p.b < 0) return;
+      p.g = __builtin_amdgcn_readlane(x, 1) + wave - kWaves;
+      p.layer = __builtin_amdgcn_readlane(x, 2);
+      p.np = __builtin_amdgcn_readlane(x, 3);
+      p.first = __builtin_amdgcn_readlane(x, 4);
+      p.part = __builtin_amdgcn_readlane(x, 5);
+      p.ctx_raw = __builtin_amdgcn_readlane(x, 6);
+      End end(a, p, s_dyn + (half * kWaves + wave - kWaves) * head_floats, s_wts + (wave - kWaves) * 128, thread);
+      if (p.np == 1) end.read_new();
+      end.leave();
+      if (p.np > 1) {
+        wait_stores();
+        if (end.is_last(end.count())) {
+          end.read_new();
+          End::sync();
+          end.merge();
+        }
+      }
+    }
+  }
+
+  struct Unit { int32_t b, tok0, tok1, np, first, part, ctx_raw, layer, g, place; };
+  auto unit_of = [&](uint32_t t) {                // what ticket t stands for: place < 0 beyond the last
+    Unit u = {};
+    const uint32_t hg = H / kWaves, i = t / hg;
+    u.g = (int32_t)(t - i * hg) * kWaves + wave;
+    u.place = (int32_t)(i / (uint32_t)L);
+    u.layer = (int32_t)(i - (uint32_t)u.place * L);
+    u.b = -1;
+    if (u.place >= a.places) u.place = -1;
+    return u;
+  };
+  struct Meta { int32_t rec, slots[kWaves]; };    // the record, a word to a lane, and the slots (handles) of the four shares
+  auto fetch = [&](const Unit& u, Meta& x) {
+    const int32_t* rec = a.plan + (size_t)(u.place < 0 ? 0 : u.place) * kPlanInts;
+    x.rec = rec[lane & (kPlanRec - 1)];
+#pragma unroll
+    for (int s = 0; s < kWaves; ++s) x.slots[s] = rec[kPlanRec + s * kDirectMaxQuanta + lane];
+  };
+  auto n_all = [&](const Unit& u) { return (u.tok1 > 0 ? (u.tok1 + kBlockTokens - 1) / kBlockTokens : 0) - u.tok0 / kBlockTokens; };
+  auto n_blocks = [&](const Unit& u, int s) { return (n_all(u) - s + kWaves - 1) / kWaves; };
+  auto settle = [&](Unit& u, Meta& x) {           // what was fetched has arrived
+    asm volatile("" : "+v"(x.rec), "+v"(x.slots[0]), "+v"(x.slots[1]), "+v"(x.slots[2]), "+v"(x.slots[3]));
+    u.b = u.place < 0 ? -1 : __builtin_amdgcn_readlane(x.rec, 0);
+    u.tok0 = __builtin_amdgcn_readlane(x.rec, 1);
+    u.tok1 = __builtin_amdgcn_readlane(x.rec, 2);
+    u.np = __builtin_amdgcn_readlane(x.rec, 3);
+    u.first = __builtin_amdgcn_readlane(x.rec, 4);
+    u.part = __builtin_amdgcn_readlane(x.rec, 5);
+    u.ctx_raw = __builtin_amdgcn_readlane(x.rec, 7);
+  };
+  // with a map to each layer the plan holds handles
+  auto look_up = [&](const Unit& u, const Meta& x, int32_t (&found)[kWaves]) {
+    if constexpr (!SLOTS) {
+      const int32_t* map = a.map + (size_t)u.layer * a.map_stride;
+#pragma unroll
+      for (int s = 0; s < kWaves; ++s) {
+        const bool live = u.b >= 0 && lane < n_blocks(u, s) && x.slots[s] >= 0 && x.slots[s] < a.n_handles;
+        found[s] = map[live ? x.slots[s] : 0];
+      }
+    }
+  };
+  auto found_out = [&](const Unit& u, Meta& x, const int32_t (&found)[kWaves]) {
+    if constexpr (!SLOTS) {
+#pragma unroll
+      for (int s = 0; s < kWaves; ++s)
+        x.slots[s] = u.b >= 0 && lane < n_blocks(u, s)
+                         ? check_slot(x.slots[s], found[s], a.n_handles, a.n_gpu_blocks, a.n_slots, a.stage_valid != 0, a.err)
+                         : -1;
+    }
+  };
+  auto slots_of = [&](const Meta& x, int s) { return s == 0 ? x.slots[0] : s == 1 ? x.slots[1] : s == 2 ? x.slots[2] : x.slots[3]; };
+  auto tile = [&](const Unit& u, int32_t slot) {
+    slot = slot < 0 ? 0 : slot;                   // flagged blocks are masked when consumed
+    return a.kv_layer + u.layer * a.kv_stride + (size_t)slot * a.block_bytes + (size_t)u.g * TILE_BYTES + (size_t)lane * 16;
+  };
+  W w;
+  uint4 kr[NL], vr[NL], q_next[NL];
+  auto load_tile = [&](const char* p) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NL; ++i) kr[i] = nt_load16(p + (size_t)i * 1024);
+#pragma unroll
+    for (int i = 0; i < NL; ++i) vr[i] = nt_load16(p + a.block_bytes / 2 + (size_t)i * 1024);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // where the first block of a unit lies (anywhere in the caches, if it has none)
+  auto first_tile = [&](const Unit& u, const Meta& x) {
+    const bool some = u.b >= 0 && n_all(u) > 0;
+    Unit v = u;
+    if (u.b < 0) { v.layer = 0; v.g = 0; }
+    return tile(v, some ? __builtin_amdgcn_readlane(x.slots[0], 0) : 0);
+  };
+  // the query rows: lanes beyond the group read the last one's, and are cleared once it has arrived
+  auto load_q = [&](const Unit& u) {
+    const int32_t b = u.b < 0 ? 0 : u.b;
+    const size_t row = (size_t)b * a.n_q_heads + (size_t)(u.b < 0 ? 0 : u.g) * G + min(lane & 15, G - 1);
+    const char* q = a.q + (u.b < 0 ? 0 : u.layer) * a.q_stride + (row * HD + 8 * (lane >> 4)) * 2;
+#pragma unroll
+    for (int kc = 0; kc < NL; ++kc) q_next[kc] = *reinterpret_cast<const uint4*>(q + 64 * kc);
+  };
+  auto settle_q = [&] {
+    const bool mine = (lane & 15) < G;
+#pragma unroll
+    for (int kc = 0; kc < NL; ++kc) {
+      asm volatile("" : "+v"(q_next[kc].x), "+v"(q_next[kc].y), "+v"(q_next[kc].z), "+v"(q_next[kc].w));
+      w.q[kc] = make_uint4(mine ? q_next[kc].x : 0u, mine ? q_next[kc].y : 0u, mine ? q_next[kc].z : 0u, mine ? q_next[kc].w : 0u);
+    }
+  };
+
+  Unit u = unit_of(blockIdx.x), n = unit_of(gridDim.x + blockIdx.x), nn = n;
+  uint32_t t2 = 2 * gridDim.x + blockIdx.x, drawn = 0;
+  Meta mu, mn, mm;
+  int32_t found[kWaves] = {};
+  fetch(u, mu);
+  fetch(n, mn);
+  settle(u, mu);
+  look_up(u, mu, found);
+  found_out(u, mu, found);
+  load_q(u);
+  load_tile(first_tile(u, mu));
+  mm = mn;
+  while (u.b >= 0) {
+    settle_q();
+    settle(n, mn);
+    const int32_t jb0 = u.tok0 / kBlockTokens;
+    float* const state = s_dyn + (half * kWaves + wave) * head_floats;
+    // what the units behind this one need is asked for behind its first block, ahead of its second: then no block waits for it
+    bool ahead = false;
+    auto ask_ahead = [&] {
+      ahead = true;
+      drawn = add_one(a.counter, threadIdx.x);
+      look_up(n, mn, found);
+      load_q(n);
+      nn = unit_of(t2);
+      fetch(nn, mm);
+    };
+    if (n_all(u) <= 0) ask_ahead();
+    const char* next_unit = nullptr;
+#pragma unroll 1
+    for (int s = 0; s < kWaves; ++s) {
+      const int32_t n_it = n_blocks(u, s), slots = slots_of(mu, s);
+      w.reset();
+      for (int32_t it = 0; it < n_it; ++it) {
+        const bool present = __builtin_amdgcn_readlane(slots, it) >= 0;
+        w.block(kr, vr, (jb0 + s + kWaves * it) * kBlockTokens, present ? u.tok1 : 0, lane, a.scale_log2e);
+        if (!ahead) ask_ahead();
+        const char* p;
+        if (it + 1 < n_it) {
+          p = tile(u, __builtin_amdgcn_readlane(slots, it + 1));
+        } else if (s + 1 < kWaves && n_blocks(u, s + 1) > 0) {
+          p = tile(u, __builtin_amdgcn_readlane(slots_of(mu, s + 1), 0));
+        } else {
+          found_out(n, mn, found);
+          p = first_tile(n, mn);
+        }
+        load_tile(p);
+      }
+      w.to_lds(state, state + kWaves * kMaxGroup, state + 2 * kWaves * kMaxGroup, ROW, s, G, lane);
+    }
+    if (n_all(u) <= 0) {
+      found_out(n, mn, found);
+      load_tile(first_tile(n, mn));
+    }
+    if (threadIdx.x == 0) {
+      s_ticket[half] = 3 * gridDim.x + drawn;
+      int32_t* const x = s_part[half];
+      x[0] = u.b; x[1] = u.g; x[2] = u.layer; x[3] = u.np; x[4] = u.first; x[5] = u.part; x[6] = u.ctx_raw;
+    }
+    __syncthreads();                              // the states and the new ticket are there
+    t2 = __builtin_amdgcn_readfirstlane(s_ticket[half]);
+    half ^= 1;
+    u = n;
+    mu = mn;
+    n = nn;
+    mn = mm;
+  }
+  if (threadIdx.x == 0) s_part[half][0] = -1;
+  __syncthreads();
+}
+
 // ---- dispatch --------------------------------------------------------------------------------------------
 
 // Its scratch in a pool: the parts, then the items' records and slot lists of the two staging regions, for as many units
@@ -718,6 +1174,14 @@ int32_t attn_step_layers(const pie_pool* p, int32_t batch, int32_t max_blocks, b
   return units > 0 ? direct_step_layers(c, units, batch, max_blocks) : 0;
 }
 
+// Whether so many layers of a step share a launch of k_attn_direct_wide.
+static bool attn_wide(const pie_pool* p, int32_t batch, int32_t max_blocks, int32_t layers) {
+  const pie_config& c = p->cfg;
+  const int32_t units = direct_max_units(p, batch, max_blocks), H = c.n_kv_heads;
+  return units > 0 && direct_wide(p->n_cu, H, c.n_q_heads / H, c.head_dim, p->elem_bytes, layers, batch,
+                                  direct_grid(units, H, batch, max_blocks) / H, max_blocks);
+}
+
 // A launch in a graph has the same number in every replay, so there the words it uses are cleared ahead of it.
 __global__ __launch_bounds__(256) void k_arrive_clear(uint64_t* __restrict__ words, int32_t n) {
   const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
@@ -732,6 +1196,20 @@ static int launch_direct_as(const DirectArgs& a, dim3 grid, hipStream_t s, hipEv
   else hipLaunchKernelGGL((k_attn_direct<W, NW, PLAN, TWO>), grid, dim3(NW * 64), (uint32_t)lds, s, a);
   PIE_HIP(hipGetLastError());
   return PIE_OK;
+}
+
+template <typename W, bool SLOTS>
+static int launch_wide(const pie_pool* p, const DirectArgs& a, hipStream_t s, hipEvent_t done) {
+  const uint32_t lds = (uint32_t)direct_wide_lds(a.group, W::HD);
+  const dim3 grid(p->n_cu), block(kWideWaves * 64);
+  if (done) hipExtLaunchKernelGGL((k_attn_direct_wide<W, SLOTS>), grid, block, lds, s, nullptr, done, 0, a);
+  else hipLaunchKernelGGL((k_attn_direct_wide<W, SLOTS>), grid, block, lds, s, a);
+  PIE_HIP(hipGetLastError());
+  return PIE_OK;
+}
+template <typename W>
+static int launch_wide(const pie_pool* p, const DirectArgs& a, hipStream_t s, hipEvent_t done, int32_t plan) {
+  return plan == kDirectPlanReplay ? launch_wide<W, true>(p, a, s, done) : launch_wide<W, false>(p, a, s, done);
 }
 
 template <typename W, bool TWO>
@@ -782,6 +1260,15 @@ int launch_step_begin(const pie_pool* p, const int32_t* d_table, int32_t max_blo
   a.stage_valid = stage_valid ? 1 : 0;
   a.append = append;
   a.places = direct_grid(max_units, H, batch, max_blocks) / H;
+  const int32_t most = attn_step_layers(p, batch, max_blocks, false), together = n_layers < most ? n_layers : most;
+  const bool wide = regions < 2 && attn_wide(p, batch, max_blocks, together);
+  if (wide) {
+    a.counters = reinterpret_cast<uint32_t*>(p->d_plan + kPlanHdrInts);
+    a.n_counters = c.n_layers;
+    a.arrive = p->d_arrive;
+    a.arrive_lines = (int32_t)direct_pool_words(c);
+    a.n_layers = together;
+  }
   const int64_t grid = a.places + (rows ? (int64_t)batch * n_layers : 0);
   if (grid > INT32_MAX) return PIE_EINVAL;
   hipLaunchKernelGGL(k_step_begin, dim3((uint32_t)grid), dim3(kWaves * 64), 0, s, a, rows ? *rows : AppendArgs{});
@@ -789,6 +1276,7 @@ int launch_step_begin(const pie_pool* p, const int32_t* d_table, int32_t max_blo
   p->step_plan = StepPlan{};
   for (int r = 0; r < 2; ++r)
     if (a.plan[r]) p->step_plan.add(batch, max_blocks, without_last, r, a.map[r] != nullptr, append);
+  p->step_plan.shared = wide ? together : 0;
   return PIE_OK;
 }
 
@@ -866,6 +1354,10 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   a.stage_valid = stage_valid ? 1 : 0;
   a.append = append;
   const dim3 grid(H, n_layers, places);
+  a.n_layers = n_layers;
+  a.places = places;
+  a.counter = reinterpret_cast<uint32_t*>(p->d_plan + kPlanHdrInts) + layer;   // (a launch a counter: the first layer's)
+  const bool wide = planned && n_layers > 1 && n_layers <= p->step_plan.shared && layer >= 0 && layer < c.n_layers;
   a.clock = clock_row;
   a.clock_wg = nullptr;
   if (clock_row) {                                // (a pair for every workgroup: kDirectMaxUnits <= kClockWgs)
@@ -882,6 +1374,9 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
     hipLaunchKernelGGL(k_arrive_clear, dim3((n + 255) / 256), dim3(256), 0, s, a.arrive, n);
     PIE_HIP(hipGetLastError());
   }
+  if (wide)
+    return c.dtype == PIE_DTYPE_F16 ? launch_wide<Wave16<F16, 128, false>>(p, a, s, done, plan)
+                                    : launch_wide<Wave16<BF16, 128, true>>(p, a, s, done, plan);
   if (k_start) PIE_HIP(hipEventRecord(k_start, s));
   int rc = PIE_EINVAL;
   const bool hd128 = c.head_dim == 128;

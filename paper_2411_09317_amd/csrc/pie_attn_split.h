@@ -103,6 +103,30 @@ inline bool direct_whole(int32_t n_cu, int64_t pairs, int32_t layers, int32_t ma
   if (max_blocks > 6 * kWholeWaves && pairs * (layers > 0 ? layers : 1) * 6 < n_cu) return false;
   return layers == 0 || pairs <= 4 * (int64_t)n_cu;
 }
+// Whether the layers that share a launch are read four kv heads side by side (k_attn_direct_wide), by workgroups that stay and
+// take units of four heads.  With one workgroup a compute unit there have to be several for each, or the last ones to end are
+// waited for.  us a step, k_attn_direct and side by side, units a compute unit in brackets:
+//   32 heads over 8, 16 layers of 256 sequences of 128 to 4 096 tokens, 3 330 and 3 075 (36); 16 of 48 such, growing caches, 562
+//   and 542 (12); 8 of 120 of 500 to 2 500 937 and 889 (12); 8 of 190 of 60 to 300 208.6 and 207.1 (12); 32 of 8 of the first,
+//   cut in four, 161.6 and 161.7 to 164.7 (8); 4 of 2 of 1 500 18.9 and 25.3 (2).
+//   64 over 8, 8 of 60 of 300 to 3 000, 542 and 523 (6); 4 of 3 of 5 000 54.1 and 56.0 (1).  32 heads, 16 of 24 of 100 to 1 100
+//   525 and 518 (12); 10 of 10 of 100 to
+//   4 000 609 and 591 (7); 40 heads, 6 of 12 of 200 to 1 500 235 and 242 (4).
+//   28 over 4, whose blocks are half as large, 8 of 100 of 300 to 3 000, 459 and 470 (6).  64 dims, whose tiles are half as
+//   large, so that four waves have too little in flight: 12 heads, 8 of 60 of 200 to 1 800, 248 and 333.
+//   Under a table that names far more than the contexts have the units are many and small: 16 of 8 of the first under 131 072
+//   tokens 143 and 183.
+constexpr int kWideGroup = 8;                    // query heads of a kv head: the LDS holds the states of no more
+inline bool direct_wide(int32_t n_cu, int32_t n_kv_heads, int32_t group, int32_t head_dim, int32_t elem_bytes, int32_t layers,
+                        int32_t batch, int32_t places, int32_t max_blocks) {
+  if (elem_bytes != 2 || head_dim != 128 || n_kv_heads % kWaves || n_kv_heads < 8 || group > kWideGroup) return false;
+  if (max_blocks > 2 * kDirectMaxQuanta * kWaves) return false;
+  const int64_t units = (int64_t)places * (n_kv_heads / kWaves) * layers;
+  return layers > 1 && units >= (places < 3 * batch ? 6 : 12) * (int64_t)n_cu;
+}
+inline size_t direct_wide_lds(int32_t group, int32_t head_dim) {   // two halves of four heads' four states
+  return (size_t)2 * kWaves * (2 * kWaves * 16 + kWaves * group * (head_dim + 4)) * sizeof(float);
+}
 // Items, partial states and arrival words a pool has room for: as many as its largest batch and widest table can make.
 inline size_t direct_pool_items(const pie_config& c) {
   const size_t most = (size_t)kDirectMaxUnits / c.n_kv_heads + 1;

@@ -54,6 +54,8 @@ constexpr int kArriveWords = 4096;
 constexpr int kArriveStride = 16;
 constexpr int kArriveShift = 16;
 
+constexpr int kPlanHdrInts = 16;      // of the planning state; ticket counters, one a layer, follow
+
 struct Home {
   int32_t where = -1;  // PIE_WHERE_* or -1 = unallocated
   int32_t slot = -1;
@@ -105,6 +107,7 @@ struct StepPlan {
   bool without_last = false;    // the newest tokens are not read from the cache
   uint8_t items = 0, slots = 0;
   int32_t append = -1;          // kAppend* mode the tails' slots are listed for, or -1
+  int32_t shared = 0;           // layers a launch may share whose tickets and arrival words have been cleared for it, or 0
   void add(int32_t b, int32_t blocks, bool no_last, int32_t region, bool with_slots, int32_t tails) {
     if (b != batch || blocks != max_blocks || no_last != without_last || tails != append)
       *this = StepPlan{b, blocks, no_last, 0, 0, tails};

@@ -330,7 +330,6 @@ int launch_kv_append(const pie_pool* p, int32_t layer, int32_t n_layers, const v
 
 constexpr int kMinPartTokens = 256;
 constexpr int kMaxPlanBatch = 4096;   // sequences the planning kernel keeps in LDS
-constexpr int kPlanHdrInts = 16;
 
 // ---- planning: the list of work items ------------------------------------------------------------------
 // items[i] = {sequence | part << 16, context length of the sequence}: item `part` covers the tokens

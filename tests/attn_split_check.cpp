@@ -156,6 +156,18 @@ static void check_rules() {
   REQUIRE(direct_plan_ahead(n_cu, 2 * n_cu + 1, 3) && !direct_plan_ahead(n_cu, 2 * n_cu, 80));
 }
 
+// Four heads side by side: only what the kernel is written for, what its LDS holds, and units numbered in 32 bits.
+static void check_wide() {
+  const int32_t n_cu = pick({64, 256, 304}), H = pick({1, 2, 4, 8, 12, 32, 40, 300}), group = pick({1, 3, 4, 8, 16}), hd = pick({64, 128});
+  const int32_t bytes = pick({2, 4}), layers = ri(0, 100), places = ri(1, 4096), blocks = ri(1, 2000);
+  const int32_t batch = ri(1, 256);
+  if (!direct_wide(n_cu, H, group, hd, bytes, layers, batch, places, blocks)) return;
+  REQUIRE(bytes == 2 && hd == 128 && H % kWaves == 0 && layers > 1 && group <= 8);
+  REQUIRE(direct_wide_lds(group, hd) + 4096 <= (size_t)160 << 10);
+  REQUIRE((int64_t)places * (H / kWaves) * layers + 3 * n_cu <= INT32_MAX);
+  REQUIRE(direct_wide(n_cu, H, group, hd, bytes, layers + 1, batch, places, blocks));
+}
+
 // Contexts are left whole only where a workgroup's waves can list their blocks, never more than 256 KB of them; a few pairs
 // not beyond six passes, whichever way the pairs of a step are divided into layers.
 static void check_whole() {
@@ -176,6 +188,7 @@ int main() {
   REQUIRE(taken > 5000);
   for (int i = 0; i < 60000; ++i) check_planned();
   for (int i = 0; i < 60000; ++i) check_whole();
+  for (int i = 0; i < 60000; ++i) check_wide();
   for (int i = 0; i < 1000; ++i) check_rules();
   printf("split ok (%d calls)\n", taken);
   return 0;
