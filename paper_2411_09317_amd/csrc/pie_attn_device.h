@@ -281,17 +281,15 @@ __device__ __forceinline__ int32_t clamp_ctx(int32_t ctx, int32_t max_blocks) {
 // One block of one wave, 16-bit caches: scores of its sixteen tokens, online softmax, accumulation of the values.
 // kr, vr: the block's K and V vectors as loaded (vr is masked in place where the block holds rows beyond `limit`);
 // qreg: the B operand of the first product; lane (quad, col) holds S[t_first + 4 quad + r][head col].
-// keys_used, values_used: called when kr and vr have been read and may be loaded again.
-template <typename E, int HD, bool SPLIT, typename KeysUsed, typename ValuesUsed>
+template <typename E, int HD, bool SPLIT>
 __device__ __forceinline__ void mfma_block(uint4 (&kr)[HD / 32], uint4 (&vr)[HD / 32], const uint4 (&qreg)[HD / 32],
                                            int32_t t_first, int32_t limit, int quad, float scale_log2e, float& m, float& l,
-                                           f32x4 (&o)[HD / 16], KeysUsed keys_used, ValuesUsed values_used) {
+                                           f32x4 (&o)[HD / 16]) {
   using MM = Mfma<E>;
   constexpr int NKC = HD / 32, NO = HD / 16;
   f32x4 s = {0.f, 0.f, 0.f, 0.f};             // s[r]: token t_first + 4 quad + r, head col
 #pragma unroll
   for (int kc = 0; kc < NKC; ++kc) s = MM::qk(kr[kc], qreg[kc], s);
-  keys_used();
 #pragma unroll
   for (int r = 0; r < 4; ++r) s[r] *= scale_log2e;
   if (t_first + kBlockTokens > limit) {       // the block holds rows beyond the context
@@ -343,14 +341,47 @@ __device__ __forceinline__ void mfma_block(uint4 (&kr)[HD / 32], uint4 (&vr)[HD 
       o[2 * i + 1] = MM::pv(MM::bounded(v1), p_lo, o[2 * i + 1]);
     }
   }
-  values_used();
 }
-template <typename E, int HD, bool SPLIT>
-__device__ __forceinline__ void mfma_block(uint4 (&kr)[HD / 32], uint4 (&vr)[HD / 32], const uint4 (&qreg)[HD / 32],
-                                           int32_t t_first, int32_t limit, int quad, float scale_log2e, float& m, float& l,
-                                           f32x4 (&o)[HD / 16]) {
-  mfma_block<E, HD, SPLIT>(kr, vr, qreg, t_first, limit, quad, scale_log2e, m, l, o, [] {}, [] {});
-}
+
+// A wave's share of a part.
+template <typename E_, int HD_, bool SPLIT>
+struct Wave16 {              // 16-bit caches: all query heads of a kv head, on the matrix cores
+  using E = E_;
+  static constexpr int HD = HD_, NL = HD / 32, EB = 2, kWavesPerEu = HD == 128 ? 3 : 4;
+  uint4 q[NL];
+  float m, l;
+  f32x4 o[HD / 16];
+  __device__ __forceinline__ void load_q(const char* base, size_t row0, int G, int lane, float) {
+    const int col = lane & 15, quad = lane >> 4;
+#pragma unroll
+    for (int kc = 0; kc < NL; ++kc) {
+      q[kc] = make_uint4(0, 0, 0, 0);
+      if (col < G) q[kc] = *reinterpret_cast<const uint4*>(base + ((row0 + col) * HD + 32 * kc + 8 * quad) * 2);
+    }
+  }
+  __device__ __forceinline__ void reset() {
+    m = kNegBig;
+    l = 0.f;
+#pragma unroll
+    for (int n = 0; n < HD / 16; ++n) o[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ __forceinline__ void block(uint4 (&kr)[NL], uint4 (&vr)[NL], int32_t t_first, int32_t limit, int lane, float scale) {
+    mfma_block<E, HD, SPLIT>(kr, vr, q, t_first, limit, lane >> 4, scale, m, l, o);
+  }
+  __device__ __forceinline__ void to_lds(float* s_m, float* s_l, float* s_acc, int row_floats, int wave, int G, int lane) {
+    const int col = lane & 15, quad = lane >> 4;
+    l = quad16_sum(l);
+    if (col < G) {
+      if (quad == 0) {
+        s_m[wave * kMaxGroup + col] = m;
+        s_l[wave * kMaxGroup + col] = l;
+      }
+      float* row = s_acc + ((size_t)wave * G + col) * row_floats + 4 * quad;
+#pragma unroll
+      for (int n = 0; n < HD / 16; ++n) *reinterpret_cast<f32x4*>(row + 16 * n) = o[n];
+    }
+  }
+};
 
 // One block of one wave and one query head, fp32 caches.  Lane (quad, row) holds, of the K tile, token `row`'s
 // 4-dim vectors 4 i + quad; of the V tile, dim 16 n + row of the tokens 4 quad .. 4 quad + 3.  qf is scaled.

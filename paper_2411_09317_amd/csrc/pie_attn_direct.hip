@@ -24,7 +24,7 @@
 
 #include <atomic>
 
-#include "pie_attn_device.h"
+#include "pie_attn_wide.h"
 
 namespace pie {
 
@@ -83,50 +83,6 @@ struct DirectArgs : SplitIn {
 };
 
 // ---- one wave's share of a unit ------------------------------------------------------------------------
-
-template <typename E_, int HD_, bool SPLIT>
-struct Wave16 {              // 16-bit caches: all query heads of a kv head, on the matrix cores
-  using E = E_;
-  static constexpr int HD = HD_, NL = HD / 32, EB = 2, kWavesPerEu = HD == 128 ? 3 : 4;
-  uint4 q[NL];
-  float m, l;
-  f32x4 o[HD / 16];
-  __device__ __forceinline__ void load_q(const char* base, size_t row0, int G, int lane, float) {
-    const int col = lane & 15, quad = lane >> 4;
-#pragma unroll
-    for (int kc = 0; kc < NL; ++kc) {
-      q[kc] = make_uint4(0, 0, 0, 0);
-      if (col < G) q[kc] = *reinterpret_cast<const uint4*>(base + ((row0 + col) * HD + 32 * kc + 8 * quad) * 2);
-    }
-  }
-  __device__ __forceinline__ void reset() {
-    m = kNegBig;
-    l = 0.f;
-#pragma unroll
-    for (int n = 0; n < HD / 16; ++n) o[n] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-  __device__ __forceinline__ void block(uint4 (&kr)[NL], uint4 (&vr)[NL], int32_t t_first, int32_t limit, int lane, float scale) {
-    mfma_block<E, HD, SPLIT>(kr, vr, q, t_first, limit, lane >> 4, scale, m, l, o);
-  }
-  template <typename KeysUsed, typename ValuesUsed>
-  __device__ __forceinline__ void block(uint4 (&kr)[NL], uint4 (&vr)[NL], int32_t t_first, int32_t limit, int lane, float scale,
-                                        KeysUsed keys_used, ValuesUsed values_used) {
-    mfma_block<E, HD, SPLIT>(kr, vr, q, t_first, limit, lane >> 4, scale, m, l, o, keys_used, values_used);
-  }
-  __device__ __forceinline__ void to_lds(float* s_m, float* s_l, float* s_acc, int row_floats, int wave, int G, int lane) {
-    const int col = lane & 15, quad = lane >> 4;
-    l = quad16_sum(l);
-    if (col < G) {
-      if (quad == 0) {
-        s_m[wave * kMaxGroup + col] = m;
-        s_l[wave * kMaxGroup + col] = l;
-      }
-      float* row = s_acc + ((size_t)wave * G + col) * row_floats + 4 * quad;
-#pragma unroll
-      for (int n = 0; n < HD / 16; ++n) *reinterpret_cast<f32x4*>(row + 16 * n) = o[n];
-    }
-  }
-};
 
 template <int HD_>
 struct Wave32 {              // fp32 caches: one query head, on the vector ALU
@@ -187,13 +143,6 @@ __device__ __forceinline__ void put2(__amdgpu_buffer_rsrc_t r, int32_t off, floa
 }
 __device__ __forceinline__ float2 get2(__amdgpu_buffer_rsrc_t r, int32_t off) {
   return bits_as<float2>(__builtin_amdgcn_raw_buffer_load_b64(r, off, 0, kAuxAgent));
-}
-// One more in a word of which the first thread of a wave gets the old value, the others nothing: for the others it lies out of
-// the buffer's range, so there is no branch around it and nobody waits for the answer before it is used (an atomic by one
-// thread is waited for where the branches meet).
-__device__ __forceinline__ uint32_t add_one(void* word, int32_t thread) {
-  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(word, 0, 4, 0x00027000);
-  return (uint32_t)__builtin_amdgcn_raw_ptr_buffer_atomic_add_i32(1, r, 4 * thread, 0, 0);
 }
 __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
@@ -908,40 +857,68 @@ struct PartEnd {
   }
 };
 
-constexpr int kWideWaves = 2 * kWaves;           // as many read as finish what those have read
+// Where k_step_begin has left the parts.  SLOTS: with their slots; else, every layer having a map of its own, with handles.
+template <bool SLOTS>
+struct StepParts {
+  const DirectArgs& a;
+  __device__ __forceinline__ void fetch(const WideUnit& u, int lane, WideMeta& x) const {
+    const int32_t* rec = a.plan + (size_t)(u.place < 0 ? 0 : u.place) * kPlanInts;
+    x.rec = rec[lane & (kPlanRec - 1)];
+#pragma unroll
+    for (int s = 0; s < kWaves; ++s) x.slots[s] = rec[kPlanRec + s * kDirectMaxQuanta + lane];
+  }
+  __device__ __forceinline__ void read(WideUnit& u, const WideMeta& x) const {
+    u.b = __builtin_amdgcn_readlane(x.rec, 0);
+    u.tok0 = __builtin_amdgcn_readlane(x.rec, 1);
+    u.tok1 = __builtin_amdgcn_readlane(x.rec, 2);
+    u.np = __builtin_amdgcn_readlane(x.rec, 3);
+    u.first = __builtin_amdgcn_readlane(x.rec, 4);
+    u.part = __builtin_amdgcn_readlane(x.rec, 5);
+    u.ctx_raw = __builtin_amdgcn_readlane(x.rec, 7);
+  }
+  __device__ __forceinline__ void look_up(const WideUnit& u, const WideMeta& x, int32_t (&found)[kWaves]) const {
+    if constexpr (!SLOTS) {
+      const int32_t* map = a.map + (size_t)u.layer * a.map_stride;
+      const int lane = threadIdx.x & 63;
+#pragma unroll
+      for (int s = 0; s < kWaves; ++s) {
+        const bool live = u.b >= 0 && lane < share_blocks(u, s) && x.slots[s] >= 0 && x.slots[s] < a.n_handles;
+        found[s] = map[live ? x.slots[s] : 0];
+      }
+    }
+  }
+  __device__ __forceinline__ void found_out(const WideUnit& u, WideMeta& x, const int32_t (&found)[kWaves]) const {
+    if constexpr (!SLOTS) {
+      const int lane = threadIdx.x & 63;
+#pragma unroll
+      for (int s = 0; s < kWaves; ++s)
+        x.slots[s] = u.b >= 0 && lane < share_blocks(u, s)
+                         ? check_slot(x.slots[s], found[s], a.n_handles, a.n_gpu_blocks, a.n_slots, a.stage_valid != 0, a.err)
+                         : -1;
+    }
+  }
+};
+
 template <typename W, bool SLOTS>
-__global__ __launch_bounds__(kWideWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 8)))
+__global__ __launch_bounds__((kWideHeads + kFinishers) * 64) __attribute__((amdgpu_waves_per_eu(2, 8)))
 void k_attn_direct_wide(const DirectArgs a) {
-  constexpr int HD = W::HD, NL = W::NL, EB = W::EB;
-  constexpr int TILE_BYTES = kBlockTokens * HD * EB;
-  constexpr int ROW = HD + 4;
   using End = PartEnd<W>;
   extern __shared__ __align__(16) float s_dyn[];
-  __shared__ __align__(16) float s_wts[kWaves * 128];   // weights of parts being merged, of two columns a lane
-  __shared__ uint32_t s_ticket[2];
-  __shared__ int32_t s_part[2][8];                // what the states in either half of s_dyn are of
-  const int lane = threadIdx.x & 63;
+  __shared__ __align__(16) float s_wts[kFinishers * 128];   // weights of parts being merged, of two columns a lane
+  __shared__ WideLds lds;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int32_t G = a.group, H = a.n_kv_heads, L = a.n_layers;
-  const int head_floats = 2 * kWaves * kMaxGroup + kWaves * G * ROW;
-  int half = 0;
-
-  if (wave >= kWaves) {                           // finishes: head `wave - kWaves` of the four
-    int thread = lane;
-    for (;; half ^= 1) {
-      __syncthreads();                            // the states are there (and those of the part before have been read)
-      asm volatile("" : "+v"(thread));            // (or all addresses are worked out ahead of the loop, and spill)
-      const int32_t x = s_part[half][thread & 7];
+  if (wave >= kWideHeads) {                       // finishes, a head
+    const int w = wave - kWideHeads;
+    wide_finish(lds, [&](int half, int32_t x, int thread) {
       PartOf p;
       p.b = __builtin_amdgcn_readlane(x, 0);
-      if (p.b < 0) return;
-      p.g = __builtin_amdgcn_readlane(x, 1) + wave - kWaves;
+      p.g = __builtin_amdgcn_readlane(x, 1) + w;
       p.layer = __builtin_amdgcn_readlane(x, 2);
       p.np = __builtin_amdgcn_readlane(x, 3);
       p.first = __builtin_amdgcn_readlane(x, 4);
       p.part = __builtin_amdgcn_readlane(x, 5);
       p.ctx_raw = __builtin_amdgcn_readlane(x, 6);
-      End end(a, p, s_dyn + (half * kWaves + wave - kWaves) * head_floats, s_wts + (wave - kWaves) * 128, thread);
+      End end(a, p, s_dyn + (half * kWideHeads + w) * wide_head_floats(W::HD, a.group), s_wts + w * 128, thread);
       if (p.np == 1) end.read_new();
       end.leave();
       if (p.np > 1) {
@@ -952,167 +929,12 @@ void k_attn_direct_wide(const DirectArgs a) {
           end.merge();
         }
       }
-    }
+    });
+    return;
   }
-
-  struct Unit { int32_t b, tok0, tok1, np, first, part, ctx_raw, layer, g, place; };
-  auto unit_of = [&](uint32_t t) {                // what ticket t stands for: place < 0 beyond the last
-    Unit u = {};
-    const uint32_t hg = H / kWaves, i = t / hg;
-    u.g = (int32_t)(t - i * hg) * kWaves + wave;
-    u.place = (int32_t)(i / (uint32_t)L);
-    u.layer = (int32_t)(i - (uint32_t)u.place * L);
-    u.b = -1;
-    if (u.place >= a.places) u.place = -1;
-    return u;
-  };
-  struct Meta { int32_t rec, slots[kWaves]; };    // the record, a word to a lane, and the slots (handles) of the four shares
-  auto fetch = [&](const Unit& u, Meta& x) {
-    const int32_t* rec = a.plan + (size_t)(u.place < 0 ? 0 : u.place) * kPlanInts;
-    x.rec = rec[lane & (kPlanRec - 1)];
-#pragma unroll
-    for (int s = 0; s < kWaves; ++s) x.slots[s] = rec[kPlanRec + s * kDirectMaxQuanta + lane];
-  };
-  auto n_all = [&](const Unit& u) { return (u.tok1 > 0 ? (u.tok1 + kBlockTokens - 1) / kBlockTokens : 0) - u.tok0 / kBlockTokens; };
-  auto n_blocks = [&](const Unit& u, int s) { return (n_all(u) - s + kWaves - 1) / kWaves; };
-  auto settle = [&](Unit& u, Meta& x) {           // what was fetched has arrived
-    asm volatile("" : "+v"(x.rec), "+v"(x.slots[0]), "+v"(x.slots[1]), "+v"(x.slots[2]), "+v"(x.slots[3]));
-    u.b = u.place < 0 ? -1 : __builtin_amdgcn_readlane(x.rec, 0);
-    u.tok0 = __builtin_amdgcn_readlane(x.rec, 1);
-    u.tok1 = __builtin_amdgcn_readlane(x.rec, 2);
-    u.np = __builtin_amdgcn_readlane(x.rec, 3);
-    u.first = __builtin_amdgcn_readlane(x.rec, 4);
-    u.part = __builtin_amdgcn_readlane(x.rec, 5);
-    u.ctx_raw = __builtin_amdgcn_readlane(x.rec, 7);
-  };
-  // with a map to each layer the plan holds handles
-  auto look_up = [&](const Unit& u, const Meta& x, int32_t (&found)[kWaves]) {
-    if constexpr (!SLOTS) {
-      const int32_t* map = a.map + (size_t)u.layer * a.map_stride;
-#pragma unroll
-      for (int s = 0; s < kWaves; ++s) {
-        const bool live = u.b >= 0 && lane < n_blocks(u, s) && x.slots[s] >= 0 && x.slots[s] < a.n_handles;
-        found[s] = map[live ? x.slots[s] : 0];
-      }
-    }
-  };
-  auto found_out = [&](const Unit& u, Meta& x, const int32_t (&found)[kWaves]) {
-    if constexpr (!SLOTS) {
-#pragma unroll
-      for (int s = 0; s < kWaves; ++s)
-        x.slots[s] = u.b >= 0 && lane < n_blocks(u, s)
-                         ? check_slot(x.slots[s], found[s], a.n_handles, a.n_gpu_blocks, a.n_slots, a.stage_valid != 0, a.err)
-                         : -1;
-    }
-  };
-  auto slots_of = [&](const Meta& x, int s) { return s == 0 ? x.slots[0] : s == 1 ? x.slots[1] : s == 2 ? x.slots[2] : x.slots[3]; };
-  auto tile = [&](const Unit& u, int32_t slot) {
-    slot = slot < 0 ? 0 : slot;                   // flagged blocks are masked when consumed
-    return a.kv_layer + u.layer * a.kv_stride + (size_t)slot * a.block_bytes + (size_t)u.g * TILE_BYTES + (size_t)lane * 16;
-  };
-  W w;
-  uint4 kr[NL], vr[NL], q_next[NL];
-  auto load_tile = [&](const char* p) {
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < NL; ++i) kr[i] = nt_load16(p + (size_t)i * 1024);
-#pragma unroll
-    for (int i = 0; i < NL; ++i) vr[i] = nt_load16(p + a.block_bytes / 2 + (size_t)i * 1024);
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  // where the first block of a unit lies (anywhere in the caches, if it has none)
-  auto first_tile = [&](const Unit& u, const Meta& x) {
-    const bool some = u.b >= 0 && n_all(u) > 0;
-    Unit v = u;
-    if (u.b < 0) { v.layer = 0; v.g = 0; }
-    return tile(v, some ? __builtin_amdgcn_readlane(x.slots[0], 0) : 0);
-  };
-  // the query rows: lanes beyond the group read the last one's, and are cleared once it has arrived
-  auto load_q = [&](const Unit& u) {
-    const int32_t b = u.b < 0 ? 0 : u.b;
-    const size_t row = (size_t)b * a.n_q_heads + (size_t)(u.b < 0 ? 0 : u.g) * G + min(lane & 15, G - 1);
-    const char* q = a.q + (u.b < 0 ? 0 : u.layer) * a.q_stride + (row * HD + 8 * (lane >> 4)) * 2;
-#pragma unroll
-    for (int kc = 0; kc < NL; ++kc) q_next[kc] = *reinterpret_cast<const uint4*>(q + 64 * kc);
-  };
-  auto settle_q = [&] {
-    const bool mine = (lane & 15) < G;
-#pragma unroll
-    for (int kc = 0; kc < NL; ++kc) {
-      asm volatile("" : "+v"(q_next[kc].x), "+v"(q_next[kc].y), "+v"(q_next[kc].z), "+v"(q_next[kc].w));
-      w.q[kc] = make_uint4(mine ? q_next[kc].x : 0u, mine ? q_next[kc].y : 0u, mine ? q_next[kc].z : 0u, mine ? q_next[kc].w : 0u);
-    }
-  };
-
-  Unit u = unit_of(blockIdx.x), n = unit_of(gridDim.x + blockIdx.x), nn = n;
-  uint32_t t2 = 2 * gridDim.x + blockIdx.x, drawn = 0;
-  Meta mu, mn, mm;
-  int32_t found[kWaves] = {};
-  fetch(u, mu);
-  fetch(n, mn);
-  settle(u, mu);
-  look_up(u, mu, found);
-  found_out(u, mu, found);
-  load_q(u);
-  load_tile(first_tile(u, mu));
-  mm = mn;
-  while (u.b >= 0) {
-    settle_q();
-    settle(n, mn);
-    const int32_t jb0 = u.tok0 / kBlockTokens;
-    float* const state = s_dyn + (half * kWaves + wave) * head_floats;
-    // what the units behind this one need is asked for behind its first block, ahead of its second: then no block waits for it
-    bool ahead = false;
-    auto ask_ahead = [&] {
-      ahead = true;
-      drawn = add_one(a.counter, threadIdx.x);
-      look_up(n, mn, found);
-      load_q(n);
-      nn = unit_of(t2);
-      fetch(nn, mm);
-    };
-    if (n_all(u) <= 0) ask_ahead();
-    const char* next_unit = nullptr;
-#pragma unroll 1
-    for (int s = 0; s < kWaves; ++s) {
-      const int32_t n_it = n_blocks(u, s), slots = slots_of(mu, s);
-      w.reset();
-      for (int32_t it = 0; it < n_it; ++it) {
-        const bool present = __builtin_amdgcn_readlane(slots, it) >= 0;
-        w.block(kr, vr, (jb0 + s + kWaves * it) * kBlockTokens, present ? u.tok1 : 0, lane, a.scale_log2e);
-        if (!ahead) ask_ahead();
-        const char* p;
-        if (it + 1 < n_it) {
-          p = tile(u, __builtin_amdgcn_readlane(slots, it + 1));
-        } else if (s + 1 < kWaves && n_blocks(u, s + 1) > 0) {
-          p = tile(u, __builtin_amdgcn_readlane(slots_of(mu, s + 1), 0));
-        } else {
-          found_out(n, mn, found);
-          p = first_tile(n, mn);
-        }
-        load_tile(p);
-      }
-      w.to_lds(state, state + kWaves * kMaxGroup, state + 2 * kWaves * kMaxGroup, ROW, s, G, lane);
-    }
-    if (n_all(u) <= 0) {
-      found_out(n, mn, found);
-      load_tile(first_tile(n, mn));
-    }
-    if (threadIdx.x == 0) {
-      s_ticket[half] = 3 * gridDim.x + drawn;
-      int32_t* const x = s_part[half];
-      x[0] = u.b; x[1] = u.g; x[2] = u.layer; x[3] = u.np; x[4] = u.first; x[5] = u.part; x[6] = u.ctx_raw;
-    }
-    __syncthreads();                              // the states and the new ticket are there
-    t2 = __builtin_amdgcn_readfirstlane(s_ticket[half]);
-    half ^= 1;
-    u = n;
-    mu = mn;
-    n = nn;
-    mn = mm;
-  }
-  if (threadIdx.x == 0) s_part[half][0] = -1;
-  __syncthreads();
+  wide_read<W, kWideHeads>({a.kv_layer, a.q, a.counter, a.block_bytes, a.kv_stride, a.q_stride, a.scale_log2e, a.n_kv_heads, a.group,
+                a.n_layers, a.places},
+               StepParts<SLOTS>{a}, s_dyn, lds);
 }
 
 // ---- dispatch --------------------------------------------------------------------------------------------
@@ -1200,8 +1022,8 @@ static int launch_direct_as(const DirectArgs& a, dim3 grid, hipStream_t s, hipEv
 
 template <typename W, bool SLOTS>
 static int launch_wide(const pie_pool* p, const DirectArgs& a, hipStream_t s, hipEvent_t done) {
-  const uint32_t lds = (uint32_t)direct_wide_lds(a.group, W::HD);
-  const dim3 grid(p->n_cu), block(kWideWaves * 64);
+  const uint32_t lds = (uint32_t)wide_lds(kWideHeads, a.group, W::HD);
+  const dim3 grid(p->n_cu), block((kWideHeads + kFinishers) * 64);
   if (done) hipExtLaunchKernelGGL((k_attn_direct_wide<W, SLOTS>), grid, block, lds, s, nullptr, done, 0, a);
   else hipLaunchKernelGGL((k_attn_direct_wide<W, SLOTS>), grid, block, lds, s, a);
   PIE_HIP(hipGetLastError());

@@ -116,16 +116,26 @@ inline bool direct_whole(int32_t n_cu, int64_t pairs, int32_t layers, int32_t ma
 //   large, so that four waves have too little in flight: 12 heads, 8 of 60 of 200 to 1 800, 248 and 333.
 //   Under a table that names far more than the contexts have the units are many and small: 16 of 8 of the first under 131 072
 //   tokens 143 and 183.
+constexpr int kWideHeads = 4, kPlannedWideHeads = 8;
 constexpr int kWideGroup = 8;                    // query heads of a kv head: the LDS holds the states of no more
 inline bool direct_wide(int32_t n_cu, int32_t n_kv_heads, int32_t group, int32_t head_dim, int32_t elem_bytes, int32_t layers,
                         int32_t batch, int32_t places, int32_t max_blocks) {
-  if (elem_bytes != 2 || head_dim != 128 || n_kv_heads % kWaves || n_kv_heads < 8 || group > kWideGroup) return false;
+  if (elem_bytes != 2 || head_dim != 128 || n_kv_heads % kWideHeads || n_kv_heads < 8 || group > kWideGroup) return false;
   if (max_blocks > 2 * kDirectMaxQuanta * kWaves) return false;
-  const int64_t units = (int64_t)places * (n_kv_heads / kWaves) * layers;
+  const int64_t units = (int64_t)places * (n_kv_heads / kWideHeads) * layers;
   return layers > 1 && units >= (places < 3 * batch ? 6 : 12) * (int64_t)n_cu;
 }
-inline size_t direct_wide_lds(int32_t group, int32_t head_dim) {   // two halves of four heads' four states
-  return (size_t)2 * kWaves * (2 * kWaves * 16 + kWaves * group * (head_dim + 4)) * sizeof(float);
+// And planned steps: eight heads at a time and three waves a SIMD, of which one finishes.  It takes many units a workgroup to gain.
+// us a step, k_attn_decode_mfma and side by side, 32 heads: 64 sequences of 1 024 to 2 048 tokens, 4 / 8 / 16 / 32 layers
+// 1 044 / 2 106 / 4 134 / 7 930 and 1 055 / 2 080 / 3 979 / 7 690 (four heads at a time 1 060 / 2 102 / 4 001 / 7 732); 30 of 500 to
+// 2 500, 8 / 16 / 32 955 / 2 018 / 3 544 and 982 / 1 965 / 3 434; 40 heads, 16 of 40 of 300 to 1 700 2 313 and 2 244; bf16, 12 of
+// 100 of 100 to 3 000 3 188 and 3 213.  A layer a launch it loses: 12 of the first with host blocks 3 122 and 3 430, one of 260 of
+// 1 000 to 3 000, 32 over 8, 332 and 368.
+inline bool planned_wide(int32_t n_kv_heads, int32_t group, int32_t head_dim, int32_t layers) {
+  return head_dim == 128 && n_kv_heads % kPlannedWideHeads == 0 && group <= kWideGroup / 2 && layers >= 16;
+}
+inline size_t wide_lds(int32_t heads, int32_t group, int32_t head_dim) {   // two halves of the heads' four states
+  return (size_t)2 * heads * (2 * kWaves * 16 + kWaves * group * (head_dim + 4)) * sizeof(float);
 }
 // Items, partial states and arrival words a pool has room for: as many as its largest batch and widest table can make.
 inline size_t direct_pool_items(const pie_config& c) {

@@ -20,7 +20,7 @@
 
 #include <hip/hip_ext.h>
 
-#include "pie_attn_device.h"
+#include "pie_attn_wide.h"
 #include "pie_internal.h"
 
 namespace pie {
@@ -826,6 +826,85 @@ void k_attn_decode_mfma(const AttnArgs a) {
   }
 }
 
+// The same items, states and sums, read eight kv heads side by side (pie_attn_wide.h): a unit is an item for eight heads, of
+// which a wave each takes the four shares that a workgroup's waves take above, and four more waves merge those and store the
+// results, two heads each.  For planned steps of many layers (planned_wide): HBM-bound, the tiles read lie in 32 KB pieces and no
+// merge stands between two units.  32 layers of 64 sequences of 1 024 to 2 048 tokens, 32 heads: 7 930 us in k_attn_decode_mfma,
+// 7 690 here (49.4 GB, 6.6 TB/s without the rows).
+struct PlannedItems {
+  const AttnArgs& a;
+  int32_t part_tokens, bpi, n_items;
+  __device__ __forceinline__ void fetch(const WideUnit& u, int lane, WideMeta& x) const {
+    const int32_t i = u.place >= 0 && u.place < n_items ? u.place : 0;
+    x.rec = reinterpret_cast<const int32_t*>(a.items + i)[lane & 1];
+#pragma unroll
+    for (int s = 0; s < kWaves; ++s) x.slots[s] = a.slots[(size_t)i * bpi + min(s + kWaves * lane, bpi - 1)];
+  }
+  __device__ __forceinline__ void read(WideUnit& u, const WideMeta& x) const {
+    const uint32_t of = (uint32_t)__builtin_amdgcn_readlane(x.rec, 0);
+    const int32_t ctx = __builtin_amdgcn_readlane(x.rec, 1);       // clamped context length of the sequence
+    u.b = u.place < n_items ? (int32_t)(of & 0xffffu) : -1;
+    u.part = (int32_t)(of >> 16);
+    u.tok0 = u.part * part_tokens;
+    u.tok1 = min(ctx, u.tok0 + part_tokens);     // <= tok0 only for an empty sequence
+    u.np = ctx > 0 ? (ctx + part_tokens - 1) / part_tokens : 1;
+    u.first = u.ctx_raw = 0;
+  }
+  __device__ __forceinline__ void look_up(const WideUnit&, const WideMeta&, int32_t (&)[kWaves]) const {}
+  __device__ __forceinline__ void found_out(const WideUnit&, WideMeta&, const int32_t (&)[kWaves]) const {}
+};
+
+template <typename E, int HD, bool SPLIT>
+__global__ __launch_bounds__((kPlannedWideHeads + kFinishers) * 64) __attribute__((amdgpu_waves_per_eu(3, 8)))
+void k_attn_decode_wide(const AttnArgs a) {
+  constexpr int ROW = HD + 4, HW = kPlannedWideHeads;
+  extern __shared__ __align__(16) float s_dyn[];
+  __shared__ WideLds lds;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int32_t n_items = a.hdr[0], part_tokens = a.hdr[1];
+  if (wave < HW) {
+    wide_read<Wave16<E, HD, SPLIT>, HW>({a.kv_layer, a.q, a.counter, a.block_bytes, a.kv_stride, a.q_stride, a.scale_log2e,
+                                     a.n_kv_heads, a.group, a.n_layers, a.max_items},
+                                    PlannedItems{a, part_tokens, part_tokens / kBlockTokens, n_items}, s_dyn, lds);
+    return;
+  }
+  const int32_t G = a.group, n_q_heads = a.n_kv_heads * G;
+  wide_finish(lds, [&](int half, int32_t x, int thread) {
+    const int32_t b = __builtin_amdgcn_readlane(x, 0), g0 = __builtin_amdgcn_readlane(x, 1);
+    const int32_t layer = __builtin_amdgcn_readlane(x, 2), np = __builtin_amdgcn_readlane(x, 3), part = __builtin_amdgcn_readlane(x, 5);
+    for (int hw = wave - HW; hw < HW; hw += kFinishers) {
+    const int32_t g = g0 + hw;
+    const float* const s_m = s_dyn + (half * HW + hw) * wide_head_floats(HD, G);
+    const float* const s_l = s_m + kWaves * kMaxGroup;
+    const float* const s_acc = s_l + kWaves * kMaxGroup;
+    for (int idx = 2 * thread; idx < G * HD; idx += 128) {
+      const int h = idx / HD, dim = idx % HD;
+      float M = s_m[h];
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) M = fmaxf(M, s_m[w * kMaxGroup + h]);
+      float L = 0.f;
+      float2 A = make_float2(0.f, 0.f);
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        const float wt = __builtin_amdgcn_exp2f(s_m[w * kMaxGroup + h] - M);
+        const float2 y = *reinterpret_cast<const float2*>(&s_acc[((size_t)w * G + h) * ROW + dim]);
+        L = fmaf(wt, s_l[w * kMaxGroup + h], L);
+        A.x = fmaf(wt, y.x, A.x);
+        A.y = fmaf(wt, y.y, A.y);
+      }
+      const size_t orow = (size_t)b * n_q_heads + g * G + h;
+      if (np == 1 && !a.new_k) {                 // the only partition of its sequence: this is the result
+        store_elem2<E>(a.out + layer * a.q_stride, orow * HD + dim, make_float2(L > 0.f ? A.x / L : 0.f, L > 0.f ? A.y / L : 0.f));
+      } else {
+        float* w = a.ws + layer * a.ws_stride + (orow * a.n_parts + part) * (HD + 2);
+        if (dim == 0) *reinterpret_cast<float2*>(w) = make_float2(M, L);
+        *reinterpret_cast<float2*>(w + 2 + dim) = A;
+      }
+    }
+    }
+  });
+}
+
 // Calibration: reads exactly the K and V tiles the decode kernel reads for the planned items, in the same
 // order and with the same loads (units by ticket, wave w takes blocks w, w + kWaves, ..., two blocks in
 // flight), and does nothing with them but fold them into a word nobody looks at.  Its rate is what this
@@ -1359,6 +1438,16 @@ static int launch_mfma(const pie_pool* p, const AttnArgs& a, int32_t layer_row, 
   // (Chosen by the units on the device, with both loops in the kernel: 24.6, 37.9, 48.0, but 1 000 of 20 to 300, which have
   // one, 166.6 and not 161.4.)
   const bool wide_table = a.n_layers == 1 && direct_too_wide(p->n_cu, a.n_kv_heads, a.group, batch, a.max_blocks);
+  if constexpr (!VALU && HD == 128)              // (more than one layer: neither events, nor the clock, nor a map of its own)
+    if (p->attn_partition <= 0 && !a.clock && planned_wide(a.n_kv_heads, a.group, HD, a.n_layers)) {
+      hipLaunchKernelGGL((k_attn_decode_wide<E, HD, SPLIT>), dim3(p->n_cu), dim3((kPlannedWideHeads + kFinishers) * 64),
+                         (uint32_t)wide_lds(kPlannedWideHeads, a.group, HD), s, a);
+      PIE_HIP(hipGetLastError());
+      if (a.n_parts > 1 || a.new_k) launch_reduce<E, HD>(a, batch, n_q_heads, s, done);
+      else if (done) PIE_HIP(hipEventRecord(done, s));
+      PIE_HIP(hipGetLastError());
+      return PIE_OK;
+    }
   if constexpr (!VALU)
     if (p->attn_partition <= 0 && !wide_table)
       return launch_mfma_as<E, HD, SPLIT, false, false>(p, a, layer_row, batch, n_q_heads, s, e0, e1, done);

@@ -161,9 +161,11 @@ static void check_wide() {
   const int32_t n_cu = pick({64, 256, 304}), H = pick({1, 2, 4, 8, 12, 32, 40, 300}), group = pick({1, 3, 4, 8, 16}), hd = pick({64, 128});
   const int32_t bytes = pick({2, 4}), layers = ri(0, 100), places = ri(1, 4096), blocks = ri(1, 2000);
   const int32_t batch = ri(1, 256);
+  if (planned_wide(H, group, hd, layers))
+    REQUIRE(hd == 128 && H % kPlannedWideHeads == 0 && layers > 1 && wide_lds(kPlannedWideHeads, group, hd) + 4096 <= (size_t)160 << 10);
   if (!direct_wide(n_cu, H, group, hd, bytes, layers, batch, places, blocks)) return;
   REQUIRE(bytes == 2 && hd == 128 && H % kWaves == 0 && layers > 1 && group <= 8);
-  REQUIRE(direct_wide_lds(group, hd) + 4096 <= (size_t)160 << 10);
+  REQUIRE(wide_lds(kWideHeads, group, hd) + 4096 <= (size_t)160 << 10);
   REQUIRE((int64_t)places * (H / kWaves) * layers + 3 * n_cu <= INT32_MAX);
   REQUIRE(direct_wide(n_cu, H, group, hd, bytes, layers + 1, batch, places, blocks));
 }
