@@ -191,7 +191,8 @@ struct Item {
 };
 // The item size the planning kernel would have chosen, as asked for by pie_get_attn_partition_sync, worked out by one wave
 // whose lane i has the lengths of the sequences i, i + 64, ...
-__device__ __forceinline__ void note_item_size(const SplitIn& a, const int32_t (&c4)[kDirectLaneSeqs]) {
+template <int SEQS>
+__device__ __forceinline__ void note_item_size(const SplitIn& a, const int32_t (&c4)[SEQS]) {
   const int lane = threadIdx.x & 63;
   int32_t size = auto_part(0);
   if (a.min_units > 0) {
@@ -199,7 +200,7 @@ __device__ __forceinline__ void note_item_size(const SplitIn& a, const int32_t (
     for (int t = 1; t < kAutoParts; ++t) {
       int32_t n = 0;
 #pragma unroll
-      for (int i = 0; i < kDirectLaneSeqs; ++i)
+      for (int i = 0; i < SEQS; ++i)
         if (64 * i + lane < a.batch) n += c4[i] > 0 ? (c4[i] + auto_part(t) - 1) / auto_part(t) : 1;
       if ((long long)wave_sum(n) * a.n_kv_heads > a.min_units) size = auto_part(t);
     }
@@ -208,12 +209,13 @@ __device__ __forceinline__ void note_item_size(const SplitIn& a, const int32_t (
 }
 
 // The split, by one wave: lane i has the sequences i, i + 64, ...  lead: the one workgroup that reports errors and the size.
+template <int SEQS>
 __device__ __forceinline__ Item split_item(const SplitIn& a, int32_t place, bool lead, bool ranked) {
   const int lane = threadIdx.x & 63;
-  int32_t c4[kDirectLaneSeqs], q4[kDirectLaneSeqs], n4[kDirectLaneSeqs], k4[kDirectLaneSeqs], end4[kDirectLaneSeqs];
+  int32_t c4[SEQS], q4[SEQS], n4[SEQS], k4[SEQS], end4[SEQS];
   int32_t total = 0;
 #pragma unroll
-  for (int i = 0; i < kDirectLaneSeqs; ++i) {
+  for (int i = 0; i < SEQS; ++i) {
     c4[i] = q4[i] = 0;
     if (64 * i < a.batch) {
       const int32_t b = 64 * i + lane;
@@ -231,14 +233,14 @@ __device__ __forceinline__ Item split_item(const SplitIn& a, int32_t place, bool
   auto items_of = [&](int32_t k) {
     int32_t n = 0;
 #pragma unroll
-    for (int i = 0; i < kDirectLaneSeqs; ++i)
+    for (int i = 0; i < SEQS; ++i)
       if (64 * i < a.batch) n += div_up(q4[i], k, FastRcp());   // (0 beyond the batch)
     return wave_sum(n);
   };
   const int32_t k = quanta_per_part(total, a.max_items, items_of);
   int32_t n_items = 0;
 #pragma unroll
-  for (int i = 0; i < kDirectLaneSeqs; ++i) {
+  for (int i = 0; i < SEQS; ++i) {
     n4[i] = k4[i] = end4[i] = 0;
     if (64 * i < a.batch) {
       if (q4[i] > 0) {
@@ -254,11 +256,11 @@ __device__ __forceinline__ Item split_item(const SplitIn& a, int32_t place, bool
   // one unit a workgroup: the launch has at least as many workgroups as the split can make units
   int32_t b = 0;                                  // sequences whose items all come before this one
 #pragma unroll
-    for (int i = 0; i < kDirectLaneSeqs; ++i)
+    for (int i = 0; i < SEQS; ++i)
       if (64 * i < a.batch) b += __popcll(__builtin_amdgcn_ballot_w64(64 * i + lane < a.batch && end4[i] <= item));
   int32_t ctx_b = 0, kq = 1, end = 1, np = 1, at = place;
 #pragma unroll
-    for (int i = 0; i < kDirectLaneSeqs; ++i)
+    for (int i = 0; i < SEQS; ++i)
       if (b >> 6 == i) {
         ctx_b = __builtin_amdgcn_readlane(c4[i], b & 63);
         kq = __builtin_amdgcn_readlane(k4[i], b & 63);
@@ -274,7 +276,7 @@ __device__ __forceinline__ Item split_item(const SplitIn& a, int32_t place, bool
   if (ranked && b >= 0) {
     int32_t before = 0;
 #pragma unroll
-    for (int i = 0; i < kDirectLaneSeqs; ++i)
+    for (int i = 0; i < SEQS; ++i)
       if (64 * i < a.batch) before += k4[i] > kq || (k4[i] == kq && 64 * i + lane < b) ? n4[i] : 0;
     at = wave_sum(before) + part;
   }
@@ -290,7 +292,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_step_begin(const SplitArgs a, c
   }
   const int32_t place = blockIdx.x, lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const Item it = split_item(a, place, place == 0, true);
+  const Item it = split_item<kDirectLaneSeqs>(a, place, place == 0, true);
   if (a.arrive && place == 0)
     for (int32_t i = threadIdx.x; i < a.n_counters; i += kWaves * 64) a.counters[i] = 0;
   if (a.arrive && it.b >= 0 && it.np > 1 && it.part == 0)
@@ -321,7 +323,12 @@ __global__ __launch_bounds__(kWaves * 64) void k_step_begin(const SplitArgs a, c
   }
 }
 
-template <typename W, int NW, int PLAN, bool TWO>
+// SEQS: sequences to a lane in the split.  A small call runs its code once, so every instruction of it is a wait: with one to a
+// lane, for up to 64 sequences, the split is a quarter as long.  us a call, four and one: one sequence of 700 tokens, 32 heads over
+// 8, 6.48 and 6.24; 8 of 100 to 1 000 7.67 and 7.42; 30 of 100 to 1 000 16.2 and 15.8; 64 of 200 to 1 800, 12 heads of 64, 37.9
+// and 37.1; one of 32 749, 64 over 8, 24.5 and 24.2.  (To look the whole of a small table up beside the lengths, and not behind the
+// split, saves two accesses and costs more than those in code: 6.48 and 7.29.)
+template <typename W, int NW, int PLAN, bool TWO, int SEQS>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW > kWaves ? NW / 4 : W::kWavesPerEu, 8)))
 void k_attn_direct(const DirectArgs a) {
   using E = typename W::E;
@@ -379,7 +386,7 @@ void k_attn_direct(const DirectArgs a) {
     first = place;
     part = 0;
   } else {
-    const Item it = split_item(a, place, lead, LEAVES);
+    const Item it = split_item<SEQS>(a, place, lead, LEAVES);
     b = it.b; tok0 = it.tok0; tok1 = it.tok1; np = it.np; first = it.first; part = it.part; at = it.at;
     ctx_raw = b >= 0 ? a.ctx[b] : 0;
   }
@@ -1010,12 +1017,12 @@ __global__ __launch_bounds__(256) void k_arrive_clear(uint64_t* __restrict__ wor
   if (i < n) words[i] = 0;
 }
 
-template <typename W, int NW, int PLAN, bool TWO>
+template <typename W, int NW, int PLAN, bool TWO, int SEQS = kDirectLaneSeqs>
 static int launch_direct_as(const DirectArgs& a, dim3 grid, hipStream_t s, hipEvent_t done, size_t min_lds) {
   size_t lds = ((size_t)NW * 2 * kMaxGroup + (size_t)NW * a.group * (W::HD + 4)) * sizeof(float);
   if (lds < min_lds) lds = min_lds;
-  if (done) hipExtLaunchKernelGGL((k_attn_direct<W, NW, PLAN, TWO>), grid, dim3(NW * 64), (uint32_t)lds, s, nullptr, done, 0, a);
-  else hipLaunchKernelGGL((k_attn_direct<W, NW, PLAN, TWO>), grid, dim3(NW * 64), (uint32_t)lds, s, a);
+  if (done) hipExtLaunchKernelGGL((k_attn_direct<W, NW, PLAN, TWO, SEQS>), grid, dim3(NW * 64), (uint32_t)lds, s, nullptr, done, 0, a);
+  else hipLaunchKernelGGL((k_attn_direct<W, NW, PLAN, TWO, SEQS>), grid, dim3(NW * 64), (uint32_t)lds, s, a);
   PIE_HIP(hipGetLastError());
   return PIE_OK;
 }
@@ -1040,7 +1047,9 @@ static int launch_cut(const DirectArgs& a, dim3 grid, hipStream_t s, hipEvent_t 
     case kDirectPlanReplay: return launch_direct_as<W, kWaves, kDirectPlanReplay, TWO>(a, grid, s, done, min_lds);
     case kDirectPlanReplaySplit: return launch_direct_as<W, kWaves, kDirectPlanReplaySplit, TWO>(a, grid, s, done, min_lds);
     case kDirectPlanWrite: return launch_direct_as<W, kWaves, kDirectPlanWrite, TWO>(a, grid, s, done, min_lds);
-    default: return launch_direct_as<W, kWaves, kDirectPlanNone, TWO>(a, grid, s, done, min_lds);
+    default:
+      return a.batch <= 64 ? launch_direct_as<W, kWaves, kDirectPlanNone, TWO, 1>(a, grid, s, done, min_lds)
+                           : launch_direct_as<W, kWaves, kDirectPlanNone, TWO>(a, grid, s, done, min_lds);
   }
 }
 
