@@ -310,7 +310,8 @@ int pie_step(pie_pool* pool, const void* d_q_all, const void* d_k_new, const voi
 
 /* The name of the kernel that runs a layer's attention in a step of n_layers layers over `batch` sequences under a
  * table of `max_blocks` columns, with the pool's present settings: "k_attn_direct" (a launch a layer, or one for several),
- * "k_attn_decode_mfma" or "k_attn_decode_f32" (planned once a step, with a reduction behind each layer).  The same
+ * "k_attn_decode_mfma" or "k_attn_decode_f32" (planned once a step, with a reduction behind each layer).  (Where layers
+ * share a launch the first two stand for their forms that read several heads side by side too, to the same bits.)  The same
  * for pie_step, pie_layer_step and pie_elastic_step.  A static string, NULL for arguments no step takes.  For
  * measurements that name what they measured. */
 const char* pie_step_attn_kernel(pie_pool* pool, int32_t n_layers, int32_t batch, int32_t max_blocks);
