@@ -1188,7 +1188,11 @@ int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const 
   a.n_layers = n_layers;
   a.places = places;
   a.counter = reinterpret_cast<uint32_t*>(p->d_plan + kPlanHdrInts) + layer;   // (a launch a counter: the first layer's)
-  const bool wide = planned && n_layers > 1 && n_layers <= p->step_plan.shared && layer >= 0 && layer < c.n_layers;
+  // (By the launch's own layers: a step's last one may have too few.  us with both side by side and with the last in k_attn_direct:
+  // 24 layers of 39 sequences of up to 1 024 tokens, 32 heads over 8, 20 and 4, 204.9 and 198.2; 16 of 38 of 542, 64 over 8, 10 and
+  // 6, 285 and 279; growing caches, 10 of 60 of 122 to 3 912, 64 over 8, 8 and 2, 585 and 575.)
+  const bool wide = planned && n_layers > 1 && n_layers <= p->step_plan.shared && layer >= 0 && layer < c.n_layers &&
+                    attn_wide(p, batch, max_blocks, n_layers);
   a.clock = clock_row;
   a.clock_wg = nullptr;
   if (clock_row) {                                // (a pair for every workgroup: kDirectMaxUnits <= kClockWgs)

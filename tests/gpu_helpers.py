@@ -1,5 +1,7 @@
 """Plumbing for the GPU parity tests: put a synthetic case into a library pool
 and into the oracle's pool model with identical placement."""
+import re
+
 import numpy as np
 import torch
 
@@ -73,6 +75,17 @@ def rowwise_rel_err(got: np.ndarray, ref: np.ndarray) -> float:
     den = np.abs(ref).max(axis=-1)
     den = np.where(den == 0, 1.0, den)
     return float((num / den).max())
+
+
+def kernels_of(call):
+    """The attention kernels that `call` launches on the GPU, in the order they ran: names without template arguments."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as p:
+        call()
+        torch.cuda.synchronize()
+    ran = sorted((e.time_range.start, e.name) for e in p.events() if e.device_type == torch.autograd.DeviceType.CUDA)
+    return [m.group(1) for _, name in ran if (m := re.search(r"pie::(k_attn\w+)", name))]
 
 
 def copy_engine_us(nbytes: int, pieces: int = 1, both_directions: bool = True, reps: int = 3) -> float:
