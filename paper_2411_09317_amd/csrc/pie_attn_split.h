@@ -105,13 +105,15 @@ inline bool direct_whole(int32_t n_cu, int64_t pairs, int32_t layers, int32_t ma
 }
 // Whether the layers that share a launch are read four kv heads side by side (k_attn_direct_wide), by workgroups that stay and
 // take units of four heads.  With one workgroup a compute unit there have to be several for each, or the last ones to end are
-// waited for.  us a step, k_attn_direct and side by side, units a compute unit in brackets:
-//   32 heads over 8, 16 layers of 256 sequences of 128 to 4 096 tokens, 3 330 and 3 075 (36); 16 of 48 such, growing caches, 562
-//   and 542 (12); 8 of 120 of 500 to 2 500 937 and 889 (12); 8 of 190 of 60 to 300 208.6 and 207.1 (12); 32 of 8 of the first,
-//   cut in four, 161.6 and 161.7 to 164.7 (8); 4 of 2 of 1 500 18.9 and 25.3 (2).
-//   64 over 8, 8 of 60 of 300 to 3 000, 542 and 523 (6); 4 of 3 of 5 000 54.1 and 56.0 (1).  32 heads, 16 of 24 of 100 to 1 100
-//   525 and 518 (12); 10 of 10 of 100 to
-//   4 000 609 and 591 (7); 40 heads, 6 of 12 of 200 to 1 500 235 and 242 (4).
+// waited for: nine.  us a launch in k_attn_direct over us side by side, both in turn on one pool, 195 steps drawn over batches of
+// 1 to 256, 16 to 8 192 tokens and 2 to 24 layers, by units a compute unit: 3 to 6 0.87 to 1.10, 0.97 in the mean; 6 to 9 0.94 to
+// 1.07, 1.00; 9 to 12 1.00 to 1.28, 1.05; 12 and more 0.99 to 1.36, 1.08.  us a step, units in brackets:
+//   32 heads over 8, 16 layers of 256 sequences of 128 to 4 096 tokens, 3 414 and 3 153 (36); 16 of 48 such, growing caches, 573
+//   and 556 (12); 13 of 30 of 249 to 7 996 694 and 659 (9.8); 8 of 45 of 144 to 723, 64 over 8, 134 and 143 (6); 32 heads over 8,
+//   32 of 8 of the first 162.2 and 163.2 (8).
+//   32 heads, 16 of 24 of 100 to 1 100 525 and 518 (12); 14 of 9 of 50 to 1 620 224.4 and 221.6 (10.5); 9 of 11 of 255 to 1 276 227
+//   and 231 (6.8); 40 heads, 10 of 9 of 413 154 and 161 (7.4); 24 over 12, 3 of 192 of 62 to 313 140 and 146 (6.8).  Many more and
+//   short: 40 heads, 12 of 44 of 6 to 33 138 and 105 (20.6).
 //   28 over 4, whose blocks are half as large, 8 of 100 of 300 to 3 000, 459 and 470 (6).  64 dims, whose tiles are half as
 //   large, so that four waves have too little in flight: 12 heads, 8 of 60 of 200 to 1 800, 248 and 333.
 //   Under a table that names far more than the contexts have the units are many and small: 16 of 8 of the first under 131 072
@@ -119,11 +121,10 @@ inline bool direct_whole(int32_t n_cu, int64_t pairs, int32_t layers, int32_t ma
 constexpr int kWideHeads = 4, kPlannedWideHeads = 8;
 constexpr int kWideGroup = 8;                    // query heads of a kv head: the LDS holds the states of no more
 inline bool direct_wide(int32_t n_cu, int32_t n_kv_heads, int32_t group, int32_t head_dim, int32_t elem_bytes, int32_t layers,
-                        int32_t batch, int32_t places, int32_t max_blocks) {
+                        int32_t places, int32_t max_blocks) {
   if (elem_bytes != 2 || head_dim != 128 || n_kv_heads % kWideHeads || n_kv_heads < 8 || group > kWideGroup) return false;
   if (max_blocks > 2 * kDirectMaxQuanta * kWaves) return false;
-  const int64_t units = (int64_t)places * (n_kv_heads / kWideHeads) * layers;
-  return layers > 1 && units >= (places < 3 * batch ? 6 : 12) * (int64_t)n_cu;
+  return layers > 1 && (int64_t)places * (n_kv_heads / kWideHeads) * layers >= 9 * (int64_t)n_cu;
 }
 // And planned steps: eight heads at a time and three waves a SIMD, of which one finishes.  It takes many units a workgroup to gain.
 // us a step, k_attn_decode_mfma and side by side, 32 heads: 64 sequences of 1 024 to 2 048 tokens, 4 / 8 / 16 / 32 layers

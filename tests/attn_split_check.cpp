@@ -160,14 +160,27 @@ static void check_rules() {
 static void check_wide() {
   const int32_t n_cu = pick({64, 256, 304}), H = pick({1, 2, 4, 8, 12, 32, 40, 300}), group = pick({1, 3, 4, 8, 16}), hd = pick({64, 128});
   const int32_t bytes = pick({2, 4}), layers = ri(0, 100), places = ri(1, 4096), blocks = ri(1, 2000);
-  const int32_t batch = ri(1, 256);
   if (planned_wide(H, group, hd, layers))
     REQUIRE(hd == 128 && H % kPlannedWideHeads == 0 && layers > 1 && wide_lds(kPlannedWideHeads, group, hd) + 4096 <= (size_t)160 << 10);
-  if (!direct_wide(n_cu, H, group, hd, bytes, layers, batch, places, blocks)) return;
+  if (!direct_wide(n_cu, H, group, hd, bytes, layers, places, blocks)) return;
   REQUIRE(bytes == 2 && hd == 128 && H % kWaves == 0 && layers > 1 && group <= 8);
   REQUIRE(wide_lds(kWideHeads, group, hd) + 4096 <= (size_t)160 << 10);
   REQUIRE((int64_t)places * (H / kWaves) * layers + 3 * n_cu <= INT32_MAX);
-  REQUIRE(direct_wide(n_cu, H, group, hd, bytes, layers + 1, batch, places, blocks));
+  REQUIRE(direct_wide(n_cu, H, group, hd, bytes, layers + 1, places, blocks));
+}
+
+// Which launches are read so, of 256 compute units: those that measured faster, down to nine units a compute unit.
+static void check_wide_shapes() {
+  struct Shape { int32_t H, group, batch, blocks, layers; bool wide; };
+  for (const Shape& s : {Shape{8, 4, 256, 256, 16, true}, Shape{8, 4, 48, 256, 16, true}, Shape{32, 1, 24, 69, 16, true},
+                         Shape{8, 4, 30, 500, 13, true}, Shape{16, 2, 12, 445, 12, true}, Shape{40, 1, 44, 3, 12, true},
+                         Shape{8, 4, 8, 316, 32, false}, Shape{8, 8, 45, 46, 8, false}, Shape{12, 2, 192, 20, 3, false},
+                         Shape{40, 1, 9, 46, 10, false}, Shape{32, 1, 11, 80, 9, false}, Shape{8, 4, 39, 64, 4, false}}) {
+    const int32_t units = direct_units(256, s.H, s.group, s.batch, s.blocks);
+    REQUIRE(units > 0);
+    const int32_t places = direct_grid(units, s.H, s.batch, s.blocks) / s.H;
+    REQUIRE(direct_wide(256, s.H, s.group, 128, 2, s.layers, places, s.blocks) == s.wide);
+  }
 }
 
 // Contexts are left whole only where a workgroup's waves can list their blocks, never more than 256 KB of them; a few pairs
@@ -191,6 +204,7 @@ int main() {
   for (int i = 0; i < 60000; ++i) check_planned();
   for (int i = 0; i < 60000; ++i) check_whole();
   for (int i = 0; i < 60000; ++i) check_wide();
+  check_wide_shapes();
   for (int i = 0; i < 1000; ++i) check_rules();
   printf("split ok (%d calls)\n", taken);
   return 0;
