@@ -286,10 +286,10 @@ def roofline_of(w, dw, streams, steps, warmup):
     assert dw.pool.check_errors() == 0
     k_ms = float(np.mean(prof["kernel"]))
     achieved = dw.kv_bytes_per_layer / (k_ms * 1e-3) / 1e9
-    kernel = dw.pool.step_attn_kernel(w.batch, dw.table.shape[1])
+    step_kernel, kernel = step_kernels(dw)
     traffic, source = traffic_from_profile(f"attn_decode_{w.name}_pmc.txt", kernel)
     res = {"tokens_per_s": w.batch / s, "ms_per_step": s * 1e3, "layers": w.n_layers,
-           "attn_partition_tokens": dw.pool.attn_partition(),
+           "attn_partition_tokens": dw.pool.attn_partition(), "step": step_rate(w, dw, step_kernel, s * 1e3),
            "roofline": {"bound": "hbm", "kernel": kernel, "achieved": achieved, "peak": HBM_PEAK_GBS,
                         "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": source,
                         "kernel_ms": k_ms, "algorithmic_bytes_per_launch": dw.kv_bytes_per_layer,
@@ -466,8 +466,27 @@ def layer_fifo_leg(w, dw, m, n_steps, t_other_us, base_step_ms):
     return res
 
 
-def traffic_from_profile(name, kernel):
-    """HBM bytes per launch measured with rocprofv3 counters, as a committed summary states them: (bytes, where
+def step_kernels(dw):
+    """The kernels of a step over the workload: in the timed steps, whose layers share launches, and in monitored ones, which
+    give the times of the layers (a launch each)."""
+    names = []
+    for timing in (False, True):
+        dw.pool.set_timing(timing)
+        names.append(dw.pool.step_attn_kernel(dw.w.batch, dw.table.shape[1]))
+    dw.pool.set_timing(False)
+    return names
+
+
+def step_rate(w, dw, kernel, ms_per_step):
+    """What the timed steps' kernel reads: keys and values of all layers, over the time of the whole step."""
+    traffic, source = traffic_from_profile(f"attn_step_{w.name}_pmc.txt", kernel, "traffic_bytes_per_layer")
+    achieved = w.n_layers * dw.kv_bytes_per_layer / (ms_per_step * 1e-3) / 1e9
+    return {"kernel": kernel, "achieved_over_whole_step": achieved, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
+            "algorithmic_bytes_per_layer": dw.kv_bytes_per_layer, "traffic_per_layer": traffic, "traffic_source": source}
+
+
+def traffic_from_profile(name, kernel, key="traffic_bytes_per_launch"):
+    """HBM bytes per launch (or by another key) measured with rocprofv3 counters, as a committed summary states them: (bytes, where
     that number comes from).  It is a figure from an earlier, separate profiler run of the same command (counters
     cannot be collected inside this run), so the line names the file and its date beside it.  None where the file is
     about another kernel than the one that ran here."""
@@ -475,7 +494,7 @@ def traffic_from_profile(name, kernel):
     if not os.path.exists(path) or f": {kernel} " not in open(path).readline():
         return None, None
     for line in open(path):
-        if line.startswith("traffic_bytes_per_launch"):
+        if line.startswith(key):
             stamp = time.strftime("%Y-%m-%d", time.gmtime(os.path.getmtime(path)))
             return float(line.split("=")[1].split()[0]), (f"profiles/{name} (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, separate "
                                                           f"earlier runs, file dated {stamp}; not measured in this run)")
@@ -836,8 +855,6 @@ def main():
     dw.pool.set_swap_path(args.swap_path)
     if args.attn_vector_alu:
         dw.pool.set_attn_vector_alu(True)
-    kernel = dw.pool.step_attn_kernel(w.batch, dw.table.shape[1])
-    traffic, traffic_source = traffic_from_profile(f"attn_decode_{w.name}_pmc.txt", kernel)
     if args.swap_wgs:
         dw.pool.set_swap_workgroups(args.swap_wgs)
     streams = (torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.Stream())
@@ -849,6 +866,8 @@ def main():
         args.t_other_us = w.layer_weight_bytes / (dw.kv_bytes_per_layer / probe_ms) * 1e3
     if args.t_other_us:
         dw.pool.set_layer_compute_us(args.t_other_us)
+    step_kernel, kernel = step_kernels(dw)
+    traffic, traffic_source = traffic_from_profile(f"attn_decode_{w.name}_pmc.txt", kernel)
 
     if args.calib_copy_mib:
         n = args.calib_copy_mib * (1 << 20) // 4
@@ -888,7 +907,8 @@ def main():
                    "metric_parts": {"decode tokens/s": "value (0 % host-resident), swap.tokens_per_s, "
                                                        "swap_below_knee.tokens_per_s, swap_kernel.*.tokens_per_s, "
                                                        "cfg4.fixed_fraction[].tokens_per_s, cfg5.*.tokens_per_s",
-                                    "HBM GB/s": "roofline.achieved, cfg4.roofline.achieved, cfg5.roofline.achieved",
+                                    "HBM GB/s": "roofline.achieved, cfg4.roofline.achieved, cfg5.roofline.achieved "
+                                                "(a layer's launch); step.achieved_over_whole_step and the like",
                                     "X% host-resident": "swap.host_fraction, swap_below_knee.host_fraction, "
                                                         "cfg4.fixed_fraction[].host_fraction, "
                                                         "cfg5.overflow_on_host.host_fraction",
@@ -896,6 +916,7 @@ def main():
                                                                    "slowdown) and inflation_e2e (step time, waits "
                                                                    "included) in swap, swap_below_knee, swap_kernel.*, "
                                                                    "cfg4.fixed_fraction[], cfg5.overflow_on_host"}},
+        "step": step_rate(w, dw, step_kernel, ms_per_step),
         "roofline": {"bound": "hbm", "kernel": kernel, "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": traffic, "traffic_source": traffic_source,

@@ -308,12 +308,14 @@ int pie_step(pie_pool* pool, const void* d_q_all, const void* d_k_new, const voi
              int32_t n_prefetch, const int32_t* h_prefetch, int32_t n_dirty, const int32_t* h_dirty,
              void* d_out_all, void* compute_stream, void* swap_in_stream, void* swap_out_stream);
 
-/* The name of the kernel that runs a layer's attention in a step of n_layers layers over `batch` sequences under a
- * table of `max_blocks` columns, with the pool's present settings: "k_attn_direct" (a launch a layer, or one for several),
- * "k_attn_decode_mfma" or "k_attn_decode_f32" (planned once a step, with a reduction behind each layer).  (Where layers
- * share a launch the first two stand for their forms that read several heads side by side too, to the same bits.)  The same
- * for pie_step, pie_layer_step and pie_elastic_step.  A static string, NULL for arguments no step takes.  For
- * measurements that name what they measured. */
+/* The name of the kernel that runs the attention of the first layers of a step of n_layers layers over `batch` sequences
+ * under a table of `max_blocks` columns, with the pool's present settings: "k_attn_direct" (a launch a layer, or one for
+ * several), "k_attn_decode_mfma" or "k_attn_decode_f32" (planned once a step, with a reduction behind each launch), or, where
+ * layers share launches and are read several heads side by side, "k_attn_direct_wide" or "k_attn_decode_wide" - of a step with
+ * all its blocks on the GPU and results that lie apart from its inputs; one with host blocks, timing or a stand-in has a launch a
+ * layer, of the first three.  (A step's last launch, which may have fewer layers, may be one of those too.)  The same for pie_step,
+ * pie_layer_step and pie_elastic_step, whose moving layers and planned ones keep a launch each.  A static string, NULL for
+ * arguments no step takes.  For measurements that name what they measured. */
 const char* pie_step_attn_kernel(pie_pool* pool, int32_t n_layers, int32_t batch, int32_t max_blocks);
 
 /* Host-homed handles among h_block_table[b][j], j < ceil(ctx/T), without repeats, in ascending order of their

@@ -1004,7 +1004,7 @@ int32_t attn_step_layers(const pie_pool* p, int32_t batch, int32_t max_blocks, b
 }
 
 // Whether so many layers of a step share a launch of k_attn_direct_wide.
-static bool attn_wide(const pie_pool* p, int32_t batch, int32_t max_blocks, int32_t layers) {
+bool attn_wide(const pie_pool* p, int32_t batch, int32_t max_blocks, int32_t layers) {
   const pie_config& c = p->cfg;
   const int32_t units = direct_max_units(p, batch, max_blocks), H = c.n_kv_heads;
   return units > 0 && direct_wide(p->n_cu, H, c.n_q_heads / H, c.head_dim, p->elem_bytes, layers,

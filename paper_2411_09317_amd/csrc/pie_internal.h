@@ -284,6 +284,7 @@ int launch_attn_decode(const pie_pool* p, int32_t layer, const void* d_q, int32_
                        hipEvent_t done = nullptr, const AttnWork* work = nullptr, const void* d_k_new = nullptr,
                        const void* d_v_new = nullptr, int32_t n_layers = 1);
 int32_t attn_planned_layers(const pie_pool* p, int32_t batch, int32_t max_blocks);
+bool attn_planned_wide(const pie_pool* p, int32_t batch, int32_t layers);   // whether a launch of so many is of k_attn_decode_wide
 inline int32_t attn_min_units(const pie_pool* p) { return p->n_cu * 17; }   // see k_attn_plan
 // The one-launch attention path (pie_attn_direct.hip): whether it takes a call, and the launch,
 // which needs no planning before it.  append: kAppend* mode in which the new rows are stored as well, or -1.
@@ -329,6 +330,7 @@ inline bool clear_of(const void* out, size_t out_bytes, const void* in, size_t i
   return !in || o + out_bytes <= i || i + in_bytes <= o;
 }
 int32_t attn_step_layers(const pie_pool* p, int32_t batch, int32_t max_blocks, bool whole);
+bool attn_wide(const pie_pool* p, int32_t batch, int32_t max_blocks, int32_t layers);   // ... of k_attn_direct_wide
 int launch_attn_direct(const pie_pool* p, int32_t layer, const void* d_q, const int32_t* d_table, int32_t max_blocks,
                        const int32_t* d_ctx, int32_t batch, void* d_out, bool stage_valid, hipStream_t s,
                        const void* d_k_new = nullptr, const void* d_v_new = nullptr, int32_t append = -1,

@@ -1378,6 +1378,13 @@ int launch_attn_resolve(const pie_pool* p, const int32_t* d_table, const int32_t
   return PIE_OK;
 }
 
+bool attn_planned_wide(const pie_pool* p, int32_t batch, int32_t layers) {
+  const pie_config& c = p->cfg;
+  (void)batch;
+  if (c.dtype == PIE_DTYPE_F32 || p->attn_partition > 0 || (p->attn_valu && c.n_q_heads == c.n_kv_heads)) return false;
+  return planned_wide(c.n_kv_heads, c.n_q_heads / c.n_kv_heads, c.head_dim, layers);
+}
+
 // done: an event that is to complete with this kernel (it rides on the kernel's own completion signal), or NULL
 template <typename E, int HD>
 static void launch_reduce(const AttnArgs& a, int32_t batch, int32_t n_q_heads, hipStream_t s, hipEvent_t done) {
@@ -1439,7 +1446,7 @@ static int launch_mfma(const pie_pool* p, const AttnArgs& a, int32_t layer_row, 
   // one, 166.6 and not 161.4.)
   const bool wide_table = a.n_layers == 1 && direct_too_wide(p->n_cu, a.n_kv_heads, a.group, batch, a.max_blocks);
   if constexpr (!VALU && HD == 128)              // (more than one layer: neither events, nor the clock, nor a map of its own)
-    if (p->attn_partition <= 0 && !a.clock && planned_wide(a.n_kv_heads, a.group, HD, a.n_layers)) {
+    if (attn_planned_wide(p, batch, a.n_layers)) {
       hipLaunchKernelGGL((k_attn_decode_wide<E, HD, SPLIT>), dim3(p->n_cu), dim3((kPlannedWideHeads + kFinishers) * 64),
                          (uint32_t)wide_lds(kPlannedWideHeads, a.group, HD), s, a);
       PIE_HIP(hipGetLastError());

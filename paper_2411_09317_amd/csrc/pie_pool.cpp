@@ -485,6 +485,7 @@ int pie_pool_init(const pie_config* cfg, void* d_base, size_t d_bytes, void* h_p
     p->map_dirty_flag[r].assign(p->n_handles, 0);
   }
   p->h_kv = (char*)h_pinned_base;
+  p->ws_floats = l.ws_floats;
   // tuning hooks for experiments; the defaults are what the benchmarks use
   if (const char* e = std::getenv("PIE_ATTN_PART")) { const int v = std::atoi(e); if (v >= 0) p->attn_partition = v; }
   if (const char* e = std::getenv("PIE_DMA_STREAM_ORDER")) p->dma_stream_order = std::atoi(e) != 0;
@@ -495,7 +496,6 @@ int pie_pool_init(const pie_config* cfg, void* d_base, size_t d_bytes, void* h_p
     p->d_map[0] = (int32_t*)(base + l.off_map0);
     p->d_map[1] = (int32_t*)(base + l.off_map1);
     p->d_ws = (float*)(base + l.off_ws);
-    p->ws_floats = l.ws_floats;
     p->d_plan = (int32_t*)(base + l.off_plan);
     p->d_err = (uint32_t*)(base + l.off_err);
     p->d_clock = (unsigned long long*)(base + l.off_clock);
@@ -931,7 +931,13 @@ int pie_attn_stream_probe_sync(pie_pool* p, int32_t layer, const int32_t* d_bloc
 const char* pie_step_attn_kernel(pie_pool* p, int32_t n_layers, int32_t batch, int32_t max_blocks) {
   if (!p || n_layers < 1 || batch < 1 || max_blocks < 1) return nullptr;
   if (batch > p->cfg.max_batch || max_blocks > p->cfg.max_blocks_per_seq || submit_drain(p)) return nullptr;
-  if (attn_step_path(p, n_layers, batch, max_blocks) != kStepPlanned) return "k_attn_direct";
+  const bool direct = attn_step_path(p, n_layers, batch, max_blocks) != kStepPlanned;
+  const bool whole = direct && attn_whole(p, batch, max_blocks, n_layers);
+  const bool together = n_layers > 1 && p->timing == PIE_TIMING_OFF && !(p->layer_compute_us > 0.f);
+  const int32_t most = direct ? attn_step_layers(p, batch, max_blocks, whole) : attn_planned_layers(p, batch, max_blocks);
+  const int32_t n = together ? std::min(most, n_layers) : 1;
+  if (direct) return !whole && attn_wide(p, batch, max_blocks, n) ? "k_attn_direct_wide" : "k_attn_direct";
+  if (attn_planned_wide(p, batch, n)) return "k_attn_decode_wide";
   return p->cfg.dtype == PIE_DTYPE_F32 ? "k_attn_decode_f32" : "k_attn_decode_mfma";
 }
 

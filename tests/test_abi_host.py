@@ -62,6 +62,28 @@ def test_the_kernel_of_a_steps_layers_by_shape_and_settings():
     p.close()
 
 
+def test_the_kernel_of_layers_that_share_launches():
+    """Steps that read several heads side by side say so - as long as their layers share launches."""
+    def kernels(layers, hq, hkv, dtype, batch, width, blocks):
+        p = B.Pool(layers, hq, hkv, 128, 16, dtype, blocks, 0, 0, max_batch=batch, max_blocks_per_seq=width, device=None)
+        first = p.step_attn_kernel(batch, width)
+        p.set_layer_compute_us(1.0)
+        apart = p.step_attn_kernel(batch, width)
+        p.set_layer_compute_us(0.0)
+        assert p.step_attn_kernel(batch, width) == first
+        p.close()
+        return first, apart
+    F16, BF16 = I.DTYPE_F16, I.DTYPE_BF16
+    assert kernels(16, 32, 8, BF16, 256, 256, 25000) == ("k_attn_direct_wide", "k_attn_direct")
+    assert kernels(24, 32, 8, BF16, 39, 64, 600) == ("k_attn_direct_wide", "k_attn_direct")
+    assert kernels(4, 32, 8, BF16, 39, 64, 600) == ("k_attn_direct", "k_attn_direct")              # too few layers
+    assert kernels(16, 32, 8, BF16, 30, 2048, 600) == ("k_attn_direct", "k_attn_direct")           # too wide a table
+    assert kernels(18, 8, 8, F16, 70, 16, 600) == ("k_attn_direct", "k_attn_direct")               # contexts left whole
+    assert kernels(32, 32, 32, F16, 64, 128, 6244) == ("k_attn_decode_wide", "k_attn_decode_mfma")
+    assert kernels(2, 32, 32, F16, 64, 128, 6244) == ("k_attn_decode_mfma", "k_attn_decode_mfma")
+    assert kernels(8, 8, 8, I.DTYPE_F32, 8, 16, 100) == ("k_attn_direct", "k_attn_direct")
+
+
 def host_pool(n_gpu=40, n_stage=16, n_host=24, **kw):
     args = dict(n_layers=3, n_q_heads=4, n_kv_heads=2, head_dim=64, block_tokens=16, dtype=I.DTYPE_F16)
     args.update(kw)
