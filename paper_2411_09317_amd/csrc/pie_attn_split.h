@@ -126,14 +126,18 @@ inline bool direct_wide(int32_t n_cu, int32_t n_kv_heads, int32_t group, int32_t
   if (max_blocks > 2 * kDirectMaxQuanta * kWaves) return false;
   return layers > 1 && (int64_t)places * (n_kv_heads / kWideHeads) * layers >= 9 * (int64_t)n_cu;
 }
-// And planned steps: eight heads at a time and three waves a SIMD, of which one finishes.  It takes many units a workgroup to gain.
-// us a step, k_attn_decode_mfma and side by side, 32 heads: 64 sequences of 1 024 to 2 048 tokens, 4 / 8 / 16 / 32 layers
-// 1 044 / 2 106 / 4 134 / 7 930 and 1 055 / 2 080 / 3 979 / 7 690 (four heads at a time 1 060 / 2 102 / 4 001 / 7 732); 30 of 500 to
-// 2 500, 8 / 16 / 32 955 / 2 018 / 3 544 and 982 / 1 965 / 3 434; 40 heads, 16 of 40 of 300 to 1 700 2 313 and 2 244; bf16, 12 of
-// 100 of 100 to 3 000 3 188 and 3 213.  A layer a launch it loses: 12 of the first with host blocks 3 122 and 3 430, one of 260 of
-// 1 000 to 3 000, 32 over 8, 332 and 368.
-inline bool planned_wide(int32_t n_kv_heads, int32_t group, int32_t head_dim, int32_t layers) {
-  return head_dim == 128 && n_kv_heads % kPlannedWideHeads == 0 && group <= kWideGroup / 2 && layers >= 16;
+// And planned steps: eight heads at a time and three waves a SIMD, of which one finishes.  It takes many units a workgroup to gain
+// here too, and those a launch has follow from its layers and from the items, of which the host knows that every sequence makes
+// one.  us a step in k_attn_decode_mfma over us side by side, both in turn on one pool (64 sequences of 1 024 to 2 048 tokens, 32
+// heads; 26 to 256 of them over other lengths, 8, 16 and 40 heads; 300 over 50 to 700, 32 heads over 8; one rule for f16, bf16
+// and grouped queries, which differ by no more than 0.01): launches of 2 layers 0.94 to 0.99, of 3 0.96 to 1.00, 4 and 5 0.98 to
+// 1.02, 6 and 8 1.00 to 1.03, 10 to 28 1.00 to 1.05.  The first, 4 / 8 / 16 / 24 layers, 1 048 / 2 116 / 4 147 / 6 042 us and
+// 1 046 / 2 080 / 4 052 / 5 864; 12 of 300 of 50 to 700, 32 over 8, bf16, 1 100 and 1 059; 12 of 100 of 100 to 3 000 in
+// launches of 2, bf16, 4 540 and 4 657.  Below four units a compute unit by that count, where tables are far wider than contexts, nothing is known.
+// A layer a launch it loses: 12 of the first with host blocks 3 122 and 3 430, one of 260 of 1 000 to 3 000, 32 over 8, 332 and 368.
+inline bool planned_wide(int32_t n_cu, int32_t n_kv_heads, int32_t group, int32_t head_dim, int32_t layers, int32_t batch) {
+  if (head_dim != 128 || n_kv_heads % kPlannedWideHeads || group > kWideGroup / 2) return false;
+  return layers >= 6 && (int64_t)batch * (n_kv_heads / kPlannedWideHeads) * layers >= 4 * (int64_t)n_cu;
 }
 inline size_t wide_lds(int32_t heads, int32_t group, int32_t head_dim) {   // two halves of the heads' four states
   return (size_t)2 * heads * (2 * kWaves * 16 + kWaves * group * (head_dim + 4)) * sizeof(float);

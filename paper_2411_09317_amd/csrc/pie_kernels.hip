@@ -828,7 +828,7 @@ void k_attn_decode_mfma(const AttnArgs a) {
 
 // The same items, states and sums, read eight kv heads side by side (pie_attn_wide.h): a unit is an item for eight heads, of
 // which a wave each takes the four shares that a workgroup's waves take above, and four more waves merge those and store the
-// results, two heads each.  For planned steps of many layers (planned_wide): HBM-bound, the tiles read lie in 32 KB pieces and no
+// results, two heads each.  For launches of six layers and more (planned_wide): HBM-bound, the tiles read lie in 32 KB pieces and no
 // merge stands between two units.  32 layers of 64 sequences of 1 024 to 2 048 tokens, 32 heads: 7 930 us in k_attn_decode_mfma,
 // 7 690 here (49.4 GB, 6.6 TB/s without the rows).
 struct PlannedItems {
@@ -1380,9 +1380,8 @@ int launch_attn_resolve(const pie_pool* p, const int32_t* d_table, const int32_t
 
 bool attn_planned_wide(const pie_pool* p, int32_t batch, int32_t layers) {
   const pie_config& c = p->cfg;
-  (void)batch;
   if (c.dtype == PIE_DTYPE_F32 || p->attn_partition > 0 || (p->attn_valu && c.n_q_heads == c.n_kv_heads)) return false;
-  return planned_wide(c.n_kv_heads, c.n_q_heads / c.n_kv_heads, c.head_dim, layers);
+  return planned_wide(p->n_cu, c.n_kv_heads, c.n_q_heads / c.n_kv_heads, c.head_dim, layers, batch);
 }
 
 // done: an event that is to complete with this kernel (it rides on the kernel's own completion signal), or NULL

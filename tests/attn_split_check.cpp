@@ -159,9 +159,11 @@ static void check_rules() {
 // Four heads side by side: only what the kernel is written for, what its LDS holds, and units numbered in 32 bits.
 static void check_wide() {
   const int32_t n_cu = pick({64, 256, 304}), H = pick({1, 2, 4, 8, 12, 32, 40, 300}), group = pick({1, 3, 4, 8, 16}), hd = pick({64, 128});
-  const int32_t bytes = pick({2, 4}), layers = ri(0, 100), places = ri(1, 4096), blocks = ri(1, 2000);
-  if (planned_wide(H, group, hd, layers))
+  const int32_t bytes = pick({2, 4}), layers = ri(0, 100), places = ri(1, 4096), blocks = ri(1, 2000), batch = ri(1, 4096);
+  if (planned_wide(n_cu, H, group, hd, layers, batch)) {
     REQUIRE(hd == 128 && H % kPlannedWideHeads == 0 && layers > 1 && wide_lds(kPlannedWideHeads, group, hd) + 4096 <= (size_t)160 << 10);
+    REQUIRE(planned_wide(n_cu, H, group, hd, layers + 1, batch));
+  }
   if (!direct_wide(n_cu, H, group, hd, bytes, layers, places, blocks)) return;
   REQUIRE(bytes == 2 && hd == 128 && H % kWaves == 0 && layers > 1 && group <= 8);
   REQUIRE(wide_lds(kWideHeads, group, hd) + 4096 <= (size_t)160 << 10);
@@ -181,6 +183,10 @@ static void check_wide_shapes() {
     const int32_t places = direct_grid(units, s.H, s.batch, s.blocks) / s.H;
     REQUIRE(direct_wide(256, s.H, s.group, 128, 2, s.layers, places, s.blocks) == s.wide);
   }
+  // planned ones, from six layers on and, a unit a sequence, four units a compute unit
+  REQUIRE(planned_wide(256, 32, 1, 128, 16, 64) && planned_wide(256, 32, 1, 128, 6, 64) && planned_wide(256, 8, 4, 128, 12, 300));
+  REQUIRE(planned_wide(256, 32, 1, 128, 9, 30) && !planned_wide(256, 32, 1, 128, 8, 30) && !planned_wide(256, 32, 1, 128, 5, 300));
+  REQUIRE(!planned_wide(256, 8, 4, 128, 16, 40) && !planned_wide(256, 8, 8, 128, 16, 300) && !planned_wide(256, 32, 1, 64, 16, 64));
 }
 
 // Contexts are left whole only where a workgroup's waves can list their blocks, never more than 256 KB of them; a few pairs
