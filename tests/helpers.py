@@ -74,3 +74,25 @@ def dense_f64(case, layer):
     V = [numfmt.to_f64(v[layer], case.w.dtype) for v in case.v_dense]
     q = numfmt.to_f64(case.q[layer], case.w.dtype)
     return q, K, V
+
+
+# Steps whose layers share launches and are read several heads side by side: (layers, query heads, kv heads, type, context
+# lengths, columns of the table, the attention kernels of its launches, the batches its pool is made for), with 128 dims, on 256
+# compute units.
+_SHORT = [1 + i * 37 % 700 for i in range(30)] + [0, 16, 17, 64, 65, 63, 1024, 1, 0]
+_MANY = [0, 1, 512, 0, 17, 16] + [1 + i * 29 % 300 for i in range(256)]
+SIDE_BY_SIDE = [
+    (24, 32, 8, I.DTYPE_BF16, _SHORT, 64, ["k_attn_direct_wide", "k_attn_direct"], 1),              # scratch for twenty layers a launch
+    (24, 64, 8, I.DTYPE_BF16, [1030 - i * 11 for i in range(40)] + [1, 16, 65, 0, 1056, 64], 66,    # the largest group
+     ["k_attn_direct_wide", "k_attn_direct"], 1),
+    (49, 8, 8, I.DTYPE_F16, [2100, 1900, 33], 140, ["k_attn_direct_wide"], 1),                        # eleven parts
+    (49, 8, 8, I.DTYPE_F16, [2100], 140, ["k_attn_direct_wide"], 1),                                  # seventeen: four groups of
+    (49, 16, 8, I.DTYPE_BF16, [2097], 140, ["k_attn_direct_wide"], 1),                                # threads merge them, with two
+    (49, 32, 8, I.DTYPE_F16, [2240], 140, ["k_attn_direct_wide"], 1),                                 # heads a group too; two, with four
+    (9, 24, 12, I.DTYPE_BF16, [3 + i * 61 % 900 for i in range(80)], 64, ["k_attn_direct_wide"], 1),      # three times four heads
+    (12, 8, 8, I.DTYPE_F16, [8192, 8191] + [200 + 16 * i for i in range(38)], 512, ["k_attn_direct_wide"], 1),   # the widest table
+    (12, 32, 8, I.DTYPE_BF16, _MANY, 32, ["k_attn_decode_wide", "k_attn_decode_mfma"], 1),           # planned; the largest group there
+    (12, 16, 8, I.DTYPE_F16, _MANY[:-2] + [1024, 1009], 64, ["k_attn_decode_wide", "k_attn_decode_mfma"], 1),
+    (12, 16, 16, I.DTYPE_F16, [300 + i * 37 % 600 for i in range(57)] + [0, 1, 1024], 400, ["k_attn_decode_wide"], 10),   # many parts
+    (9, 40, 40, I.DTYPE_BF16, [100 + i * 173 % 2900 for i in range(29)] + [6400], 400, ["k_attn_decode_wide"], 10),
+]

@@ -7,6 +7,7 @@ import re
 import numpy as np
 import pytest
 
+import helpers as H
 from oracle.controller_sim import AdaptiveExpansion, linear_timing
 from oracle.pool_model import PoolError, PoolModel
 from paper_2411_09317_amd import binding as B
@@ -80,8 +81,18 @@ def test_the_kernel_of_layers_that_share_launches():
     assert kernels(16, 32, 8, BF16, 30, 2048, 600) == ("k_attn_direct", "k_attn_direct")           # too wide a table
     assert kernels(18, 8, 8, F16, 70, 16, 600) == ("k_attn_direct", "k_attn_direct")               # contexts left whole
     assert kernels(32, 32, 32, F16, 64, 128, 6244) == ("k_attn_decode_wide", "k_attn_decode_mfma")
+    assert kernels(30, 32, 32, F16, 64, 128, 5000)[0] == "k_attn_decode_wide"                       # 15 layers a launch
     assert kernels(2, 32, 32, F16, 64, 128, 6244) == ("k_attn_decode_mfma", "k_attn_decode_mfma")
     assert kernels(8, 8, 8, I.DTYPE_F32, 8, 16, 100) == ("k_attn_direct", "k_attn_direct")
+
+
+@pytest.mark.parametrize("layers,hq,hkv,dtype,ctx,width,ran,room", H.SIDE_BY_SIDE)
+def test_steps_that_are_compared_side_by_side_are_read_so(layers, hq, hkv, dtype, ctx, width, ran, room):
+    """What the GPU tests of those kernels run is more than the rules call for, and not their other forms against themselves."""
+    blocks = int(I.blocks_needed(np.asarray(ctx, np.int32), 16).sum())
+    p = B.Pool(layers, hq, hkv, 128, 16, dtype, blocks, 0, 0, max_batch=room * len(ctx), max_blocks_per_seq=width, device=None)
+    assert p.step_attn_kernel(len(ctx), width) == ran[0] and ran[0].endswith("_wide")
+    p.close()
 
 
 def host_pool(n_gpu=40, n_stage=16, n_host=24, **kw):
