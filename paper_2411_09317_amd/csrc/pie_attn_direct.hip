@@ -170,6 +170,72 @@ __device__ __forceinline__ float head_sum(float x) {
   return x;
 }
 
+// ---- states into one ---------------------------------------------------------------------------------------
+// What k_attn_direct's workgroups and k_attn_direct_wide's finishing waves sum, a column (four dims of a head) to a thread, in
+// one order: a step's results are the same bits whichever its layers run in.
+
+// n states in LDS (the waves', or the merging groups'): head h, dims d0 ..  (By reference: given the pointers themselves the compiler
+// orders k_attn_direct's tail otherwise, 6.23 us and not 6.21 for one sequence of 700 tokens.)
+template <int ROW>
+__device__ __forceinline__ void merge_states(const float* const& s_m, const float* const& s_l, const float* const& s_acc, const int& G,
+                                             int n, int h, int d0, float& M, float& L, float4& A) {
+  M = s_m[h];
+  for (int i = 1; i < n; ++i) M = fmaxf(M, s_m[i * kMaxGroup + h]);
+  L = 0.f;
+  A = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int i = 0; i < n; ++i) {
+    const float wt = __builtin_amdgcn_exp2f(s_m[i * kMaxGroup + h] - M);
+    L = fmaf(wt, s_l[i * kMaxGroup + h], L);
+    axpy(A, wt, *reinterpret_cast<const float4*>(&s_acc[((size_t)i * G + h) * ROW + d0]));
+  }
+}
+
+// The newest token's part, (q . k, 1, v), to the others'.
+template <int TPH>
+__device__ __forceinline__ void add_newest(float4 q, float4 k, float4 v, float scale_log2e, float M, float& L, float4& A) {
+  const float dot = fmaf(q.x, k.x, q.y * k.y) + fmaf(q.z, k.z, q.w * k.w);
+  const float s_new = head_sum<TPH>(dot) * scale_log2e;
+  const float m2 = fmaxf(M, s_new);
+  const float w_old = __builtin_amdgcn_exp2f(M - m2), w_new = __builtin_amdgcn_exp2f(s_new - m2);
+  L = fmaf(L, w_old, w_new);
+  A = make_float4(A.x * w_old, A.y * w_old, A.z * w_old, A.w * w_old);
+  axpy(A, w_new, v);
+}
+
+// A head's threads take TPH stored parts at a time: thread i has part i's (M, L), if there is one, and works out its weight ...
+template <int TPH>
+__device__ __forceinline__ float weigh_parts(float2 ml, bool live, float& M, float& L, float4& A) {
+  const float m_new = fmaxf(M, head_max<TPH>(ml.x));
+  const float corr = __builtin_amdgcn_exp2f(M - m_new);
+  const float wt = live ? __builtin_amdgcn_exp2f(ml.x - m_new) : 0.f;
+  L = fmaf(L, corr, head_sum<TPH>(wt * ml.y));
+  A = make_float4(A.x * corr, A.y * corr, A.z * corr, A.w * corr);
+  M = m_new;
+  return wt;
+}
+// ... then every thread sums its four dims over them (those beyond the last weigh 0).
+template <int UNR>
+__device__ __forceinline__ void sum_parts(const float* weights, const float4 (&ai)[UNR], float4& A) {
+#pragma unroll
+  for (int u = 0; u < UNR; u += 4) {
+    const float4 wu = *reinterpret_cast<const float4*>(&weights[u]);
+    axpy(A, wu.x, ai[u]);
+    axpy(A, wu.y, ai[u + 1]);
+    axpy(A, wu.z, ai[u + 2]);
+    axpy(A, wu.w, ai[u + 3]);
+  }
+}
+// A round that is not full reads its last part several times, with weights of zero for all but one.  If that part holds an
+// infinity, or any other, the sum is made once more part by part.
+__device__ __forceinline__ void sum_again_if_infinite(__amdgpu_buffer_rsrc_t parts, int32_t part0, int32_t step, int ml_off, int d0,
+                                                      int32_t s_begin, int32_t s_end, float M, float4& A) {
+  if (!(fmaf(A.x, 0.f, fmaf(A.y, 0.f, fmaf(A.z, 0.f, A.w * 0.f))) == 0.f)) {
+    A = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int32_t s = s_begin; s < s_end; ++s)
+      axpy(A, __builtin_amdgcn_exp2f(get2(parts, part0 + s * step + ml_off).x - M), get4(parts, part0 + d0 * 4, s * step));
+  }
+}
+
 struct FastRcp {
   __device__ __forceinline__ float operator()(float y) const { return __builtin_amdgcn_rcpf(y); }
 };
@@ -498,36 +564,18 @@ void k_attn_direct(const DirectArgs a) {
       const size_t row = row0 + c / TPH;
       if (add_new) {
         if (c >= NT) read_new(c);
-        const float dot = fmaf(qd.x, kd.x, qd.y * kd.y) + fmaf(qd.z, kd.z, qd.w * kd.w);
-        const float s_new = head_sum<TPH>(dot) * a.scale_log2e;
-        const float m2 = fmaxf(M, s_new);
-        const float w_old = __builtin_amdgcn_exp2f(M - m2), w_new = __builtin_amdgcn_exp2f(s_new - m2);
-        L = fmaf(L, w_old, w_new);
-        A = make_float4(A.x * w_old, A.y * w_old, A.z * w_old, A.w * w_old);
-        axpy(A, w_new, vd);
+        add_newest<TPH>(qd, kd, vd, a.scale_log2e, M, L, A);
       }
       const bool some = L > 0.f;
       store_elem2<E>(out, row * HD + d0, make_float2(some ? A.x / L : 0.f, some ? A.y / L : 0.f));
       store_elem2<E>(out, row * HD + d0 + 2, make_float2(some ? A.z / L : 0.f, some ? A.w / L : 0.f));
-    };
-    // n states in LDS (the waves', or the merging groups') into one
-    auto merge_lds = [&](int n, int h, int d0, float& M, float& L, float4& A) {
-      M = s_m[h];
-      for (int i = 1; i < n; ++i) M = fmaxf(M, s_m[i * kMaxGroup + h]);
-      L = 0.f;
-      A = make_float4(0.f, 0.f, 0.f, 0.f);
-      for (int i = 0; i < n; ++i) {
-        const float wt = __builtin_amdgcn_exp2f(s_m[i * kMaxGroup + h] - M);
-        L = fmaf(wt, s_l[i * kMaxGroup + h], L);
-        axpy(A, wt, *reinterpret_cast<const float4*>(&s_acc[((size_t)i * G + h) * ROW + d0]));
-      }
     };
     const __amdgpu_buffer_rsrc_t parts = parts_rsrc(a.ws + (size_t)layer * (a.ws_bytes / 4), a.ws_bytes);
     for (int c = tid; c < cols; c += NT) {
       const int h = c / TPH, d0 = 4 * (c % TPH);
       float M, L;
       float4 A;
-      merge_lds(NW, h, d0, M, L, A);
+      merge_states<ROW>(s_m, s_l, s_acc, G, NW, h, d0, M, L, A);
       if (WHOLE || np == 1) {
         finish(c, M, L, A);
       } else {
@@ -547,9 +595,8 @@ void k_attn_direct(const DirectArgs a) {
       __syncthreads();
       if (s_last) {                               // every part is stored: merge them, in order
         if (tid == 0) __hip_atomic_store(word, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // A head's threads take TPH parts at a time: thread i reads part i's (M, L) and works out its weight, then
-        // every thread sums its four dims over the parts, sixteen loads in flight, the weights fetched from LDS.
-        // With few heads and many parts, groups of threads take a share of the parts each and meet in LDS.
+        // TPH parts at a time, sixteen loads in flight, the weights fetched from LDS.  With few heads and many parts, groups of
+        // threads take a share of the parts each and meet in LDS.
         const int pitch = (cols + 63) & ~63;      // threads of a group: whole waves
         const int nsub = np > 16 ? max(1, NT / pitch) : 1;
         const int sub = nsub > 1 ? wave * 64 / pitch : 0;
@@ -570,32 +617,13 @@ void k_attn_direct(const DirectArgs a) {
 #pragma unroll
               for (int u = 0; u < UNR; ++u) ai[u] = get4(parts, part0 + d0 * 4, (s0 + min(u0 + u, n - 1)) * step);
               if (u0 == 0) {
-                const float m_new = fmaxf(M, head_max<TPH>(ml.x));
-                const float corr = __builtin_amdgcn_exp2f(M - m_new);
-                const float wt = t < n ? __builtin_amdgcn_exp2f(ml.x - m_new) : 0.f;
-                L = fmaf(L, corr, head_sum<TPH>(wt * ml.y));
-                A = make_float4(A.x * corr, A.y * corr, A.z * corr, A.w * corr);
-                M = m_new;
-                s_w[tid] = wt;                    // read by this wave only
+                s_w[tid] = weigh_parts<TPH>(ml, t < n, M, L, A);   // read by this wave only
                 __builtin_amdgcn_wave_barrier();
               }
-#pragma unroll
-              for (int u = 0; u < UNR; u += 4) {  // (threads beyond n hold weight 0; TPH is a multiple of UNR)
-                const float4 wu = *reinterpret_cast<const float4*>(&s_w[(tid & ~(TPH - 1)) + u0 + u]);
-                axpy(A, wu.x, ai[u]);
-                axpy(A, wu.y, ai[u + 1]);
-                axpy(A, wu.z, ai[u + 2]);
-                axpy(A, wu.w, ai[u + 3]);
-              }
+              sum_parts<UNR>(&s_w[(tid & ~(TPH - 1)) + u0], ai, A);   // (TPH is a multiple of UNR)
             }
           }
-          // A round that is not full reads its last part several times, with weights of zero for all but one.  If that
-          // part holds an infinity, or any other, the sum is made once more part by part.
-          if (!(fmaf(A.x, 0.f, fmaf(A.y, 0.f, fmaf(A.z, 0.f, A.w * 0.f))) == 0.f)) {
-            A = make_float4(0.f, 0.f, 0.f, 0.f);
-            for (int32_t s = np * sub / nsub; s < s_end; ++s)
-              axpy(A, __builtin_amdgcn_exp2f(get2(parts, part0 + s * step + HD * 4).x - M), get4(parts, part0 + d0 * 4, s * step));
-          }
+          sum_again_if_infinite(parts, part0, step, HD * 4, d0, np * sub / nsub, s_end, M, A);
           if (nsub == 1) {
             finish(c, M, L, A);
           } else {
@@ -612,7 +640,7 @@ void k_attn_direct(const DirectArgs a) {
             const int h = tid / TPH, d0 = 4 * (tid % TPH);
             float M, L;
             float4 A;
-            merge_lds(nsub, h, d0, M, L, A);
+            merge_states<ROW>(s_m, s_l, s_acc, G, nsub, h, d0, M, L, A);
             finish(tid, M, L, A);
           }
         }
@@ -664,7 +692,7 @@ struct PartOf { int32_t b, g, layer, np, first, part, ctx_raw; };
 
 // What k_attn_direct's workgroup does when its waves have streamed their shares of a part, by one wave for a kv head: the four
 // states in LDS become one; a lone part's is finished, another's stored, counted and, by the last to arrive, merged with the
-// others'.  The same sums in the same order, so that a step's results are the same bits whichever kernel its layers run in.
+// others'.
 template <typename W>
 struct PartEnd {
   using E = typename W::E;
@@ -710,30 +738,15 @@ struct PartEnd {
     const size_t row = row0 + c / TPH;
     if (add_new()) {
       if (c >= NT) read_q(c);
-      const float dot = fmaf(qd.x, kd.x, qd.y * kd.y) + fmaf(qd.z, kd.z, qd.w * kd.w);
-      const float s_new = head_sum<TPH>(dot) * a.scale_log2e;
-      const float m2 = fmaxf(M, s_new);
-      const float w_old = __builtin_amdgcn_exp2f(M - m2), w_new = __builtin_amdgcn_exp2f(s_new - m2);
-      L = fmaf(L, w_old, w_new);
-      A = make_float4(A.x * w_old, A.y * w_old, A.z * w_old, A.w * w_old);
-      axpy(A, w_new, vd);
+      add_newest<TPH>(qd, kd, vd, a.scale_log2e, M, L, A);
     }
     const bool some = L > 0.f;
     char* const out = a.out + p.layer * a.q_stride;
     store_elem2<E>(out, row * HD + d0, make_float2(some ? A.x / L : 0.f, some ? A.y / L : 0.f));
     store_elem2<E>(out, row * HD + d0 + 2, make_float2(some ? A.z / L : 0.f, some ? A.w / L : 0.f));
   }
-  // n states in LDS (the waves', or the merging groups') into one
   __device__ __forceinline__ void merge_lds(int n, int h, int d0, float& M, float& L, float4& A) const {
-    M = s_m[h];
-    for (int i = 1; i < n; ++i) M = fmaxf(M, s_m[i * kMaxGroup + h]);
-    L = 0.f;
-    A = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int i = 0; i < n; ++i) {
-      const float wt = __builtin_amdgcn_exp2f(s_m[i * kMaxGroup + h] - M);
-      L = fmaf(wt, s_l[i * kMaxGroup + h], L);
-      axpy(A, wt, *reinterpret_cast<const float4*>(&s_acc[((size_t)i * a.group + h) * ROW + d0]));
-    }
+    merge_states<ROW>(s_m, s_l, s_acc, a.group, n, h, d0, M, L, A);
   }
   // the states into one, which is finished (the newest token's rows have been read) or stored
   __device__ __forceinline__ void leave() {
@@ -756,9 +769,8 @@ struct PartEnd {
   __device__ __forceinline__ bool is_last(uint32_t counted) const {
     return __builtin_amdgcn_readfirstlane(counted) == (uint32_t)(p.np - 1);
   }
-  // NC columns of a thread from c0 on, of the parts [s_begin, s_end), UNR parts' loads in flight for each column: thread t
-  // of a head's TPH reads part t's (M, L) and works out its weight, then every thread sums its four dims over the parts, the
-  // weights fetched from LDS.  sub: whose group's result it is, or -1: the only one's.
+  // NC columns of a thread from c0 on, of the parts [s_begin, s_end), UNR parts' loads in flight for each column, the weights
+  // fetched from LDS.  sub: whose group's result it is, or -1: the only one's.
   template <int NC, int UNR>
   __device__ __forceinline__ void merge_columns(int sub, int32_t s_begin, int32_t s_end, int c0) {
     const int32_t G = a.group, H = a.n_kv_heads, step = H * G * PART;
@@ -790,39 +802,16 @@ struct PartEnd {
           for (int u = 0; u < UNR; ++u) ai[j][u] = get4(ws, part0[j] + d0 * 4, (s0 + min(u0 + u, n - 1)) * step);
         if (u0 == 0) {
 #pragma unroll
-          for (int j = 0; j < NC; ++j) {
-            const float m_new = fmaxf(M[j], head_max<TPH>(ml[j].x));
-            const float corr = __builtin_amdgcn_exp2f(M[j] - m_new);
-            const float wt = t < n ? __builtin_amdgcn_exp2f(ml[j].x - m_new) : 0.f;
-            L[j] = fmaf(L[j], corr, head_sum<TPH>(wt * ml[j].y));
-            A[j] = make_float4(A[j].x * corr, A[j].y * corr, A[j].z * corr, A[j].w * corr);
-            M[j] = m_new;
-            s_w[j * NT + tid] = wt;               // read by this wave only
-          }
+          for (int j = 0; j < NC; ++j) s_w[j * NT + tid] = weigh_parts<TPH>(ml[j], t < n, M[j], L[j], A[j]);   // read by this wave only
           __builtin_amdgcn_wave_barrier();
         }
 #pragma unroll
-        for (int j = 0; j < NC; ++j)
-#pragma unroll
-          for (int u = 0; u < UNR; u += 4) {      // (threads beyond n hold weight 0; TPH is a multiple of UNR)
-            const float4 wu = *reinterpret_cast<const float4*>(&s_w[j * NT + (tid & ~(TPH - 1)) + u0 + u]);
-            axpy(A[j], wu.x, ai[j][u]);
-            axpy(A[j], wu.y, ai[j][u + 1]);
-            axpy(A[j], wu.z, ai[j][u + 2]);
-            axpy(A[j], wu.w, ai[j][u + 3]);
-          }
+        for (int j = 0; j < NC; ++j) sum_parts<UNR>(&s_w[j * NT + (tid & ~(TPH - 1)) + u0], ai[j], A[j]);   // (TPH is a multiple of UNR)
       }
     }
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      // A round that is not full reads its last part several times, with weights of zero for all but one.  If that
-      // part holds an infinity, or any other, the sum is made once more part by part.
-      if (!(fmaf(A[j].x, 0.f, fmaf(A[j].y, 0.f, fmaf(A[j].z, 0.f, A[j].w * 0.f))) == 0.f)) {
-        A[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int32_t s = s_begin; s < s_end; ++s)
-          axpy(A[j], __builtin_amdgcn_exp2f(get2(ws, part0[j] + s * step + HD * 4).x - M[j]),
-               get4(ws, part0[j] + d0 * 4, s * step));
-      }
+      sum_again_if_infinite(ws, part0[j], step, HD * 4, d0, s_begin, s_end, M[j], A[j]);
       const int c = c0 + NT * j, h = c / TPH;
       if (NC > 1 && c >= cols()) continue;
       if (sub < 0) {
