@@ -139,8 +139,12 @@ inline bool planned_wide(int32_t n_cu, int32_t n_kv_heads, int32_t group, int32_
   if (head_dim != 128 || n_kv_heads % kPlannedWideHeads || group > kWideGroup / 2) return false;
   return layers >= 6 && (int64_t)batch * (n_kv_heads / kPlannedWideHeads) * layers >= 4 * (int64_t)n_cu;
 }
-inline size_t wide_lds(int32_t heads, int32_t group, int32_t head_dim) {   // two halves of the heads' four states
-  return (size_t)2 * heads * (2 * kWaves * 16 + kWaves * group * (head_dim + 4)) * sizeof(float);
+// The LDS of such a workgroup: two halves of the heads' four states, and no less than leaves a compute unit room for one alone (with
+// one query head a kv head 21 KB hold the states; two workgroups beside each other would leave another compute unit idle).
+inline size_t wide_lds(int32_t heads, int32_t group, int32_t head_dim) {
+  const size_t states = (size_t)2 * heads * (2 * kWaves * 16 + kWaves * group * (head_dim + 4)) * sizeof(float);
+  const size_t alone = (size_t)81 << 10;
+  return states > alone ? states : alone;
 }
 // Items, partial states and arrival words a pool has room for: as many as its largest batch and widest table can make.
 inline size_t direct_pool_items(const pie_config& c) {

@@ -167,6 +167,7 @@ static void check_wide() {
   if (!direct_wide(n_cu, H, group, hd, bytes, layers, places, blocks)) return;
   REQUIRE(bytes == 2 && hd == 128 && H % kWaves == 0 && layers > 1 && group <= 8);
   REQUIRE(wide_lds(kWideHeads, group, hd) + 4096 <= (size_t)160 << 10);
+  for (const int32_t heads : {kWideHeads, kPlannedWideHeads}) REQUIRE(2 * wide_lds(heads, group, hd) > (size_t)160 << 10);   // one a compute unit
   REQUIRE((int64_t)places * (H / kWaves) * layers + 3 * n_cu <= INT32_MAX);
   REQUIRE(direct_wide(n_cu, H, group, hd, bytes, layers + 1, places, blocks));
 }
