@@ -9,10 +9,10 @@
 //
 // The layers of a step start from a plan, and where nothing has to happen between them they share a launch too (n_layers),
 // behind one that works the plan out: then the chain of accesses, the tail and the gap behind it, 7 of 11 us a layer of a
-// small step, come once a step and not once a layer.  us a step, a launch a layer before and one for all now: 32 layers of 8
-// sequences of 128 to 4 096 tokens, 32 heads over 8, 358 and 162 (888 MB, 5.5 TB/s); 16 of 24 of 100 to 1 100, 32 heads, 613
-// and 526; 16 growing caches of 48 sequences, 685 and 561; 16 of 256 of 128 to 4 096, 32 over 8, no different (3 457 to 3 493
-// and 3 361 to 3 517, by the placement of the pool).
+// small step, come once a step and not once a layer.  us a step, a launch a layer before and one of k_attn_direct for all: 32
+// layers of 8 sequences of 128 to 4 096 tokens, 32 heads over 8, 358 and 162 (888 MB, 5.5 TB/s); 16 of 24 of 100 to 1 100, 32
+// heads, 613 and 525; 16 growing caches of 48 sequences, 685 and 573.  The last two have units enough to be read four heads side
+// by side (k_attn_direct_wide, below), 518 and 556.
 //
 // What bounds it: for small calls a chain of dependent accesses, about 7 us from the first workgroup's start (context
 // lengths and split 1.4 us, table and map 0.7, a block 0.9, the part's state stored 1.0 and counted 0.4 to 1.3, the
@@ -678,7 +678,7 @@ void k_attn_direct(const DirectArgs a) {
 // HBM bounds both, and gives more when less is asked for at a time and what is asked for lies together: reads alone, of 4 KB
 // tiles of blocks of 64 KB, 6.82 TB/s so and 7.24 with four waves a compute unit on four neighbouring heads of one block; of
 // blocks of 256 KB 6.68 and 6.91.  So a workgroup stays on a compute unit and takes units by ticket, the largest parts first, of
-// four heads each: a wave a head, which takes the four shares one after another.  A block's sixteen loads go out together behind
+// four heads each: a wave a head, which takes the four shares one after another.  A block's eight loads go out together behind
 // the block before (the keys' behind its keys' product, the values' behind its values': 3 352 us and not 3 093 for 16 layers of
 // 256 sequences of 128 to 4 096 tokens, 32 heads over 8).
 //
