@@ -133,7 +133,8 @@ inline bool direct_wide(int32_t n_cu, int32_t n_kv_heads, int32_t group, int32_t
 // and grouped queries, which differ by no more than 0.01): launches of 2 layers 0.94 to 0.99, of 3 0.96 to 1.00, 4 and 5 0.98 to
 // 1.02, 6 and 8 1.00 to 1.03, 10 to 28 1.00 to 1.05.  The first, 4 / 8 / 16 / 24 layers, 1 048 / 2 116 / 4 147 / 6 042 us and
 // 1 046 / 2 080 / 4 052 / 5 864; 12 of 300 of 50 to 700, 32 over 8, bf16, 1 100 and 1 059; 12 of 100 of 100 to 3 000 in
-// launches of 2, bf16, 4 540 and 4 657.  Below four units a compute unit by that count, where tables are far wider than contexts, nothing is known.
+// launches of 2, bf16, 4 540 and 4 657.  Many and short gain most: 10 of 116 of 13 to 66, 40 heads, 631 and 364.  Below four units a
+// compute unit by that count, where tables are far wider than contexts, nothing is known.
 // A layer a launch it loses: 12 of the first with host blocks 3 122 and 3 430, one of 260 of 1 000 to 3 000, 32 over 8, 332 and 368.
 inline bool planned_wide(int32_t n_cu, int32_t n_kv_heads, int32_t group, int32_t head_dim, int32_t layers, int32_t batch) {
   if (head_dim != 128 || n_kv_heads % kPlannedWideHeads || group > kWideGroup / 2) return false;
